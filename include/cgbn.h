@@ -46,6 +46,8 @@
  *     set the "cooperative" knob first: their single-launch kernels wait for sibling
  *     workgroups, and two such grids dispatched together could each end up half resident and
  *     starve the other until the bounded waits give up (error word set, NaN statistics).
+ *     (Calls that take the column-slab kernels are exempt: no wait of theirs needs its siblings
+ *     resident, see the knob "last_forward_slab" for which calls those are.)
  *     A workspace must never be shared by calls that can overlap.
  *   - Results are bitwise reproducible run to run (fixed summation order, no
  *     floating-point atomics) and depend on K only through rounding.
@@ -174,7 +176,7 @@ cgbn_status cgbn_backward_relu(const void* dy, const void* y, const void* x,
 
 /* ---- The same path one step at a time, one sweep over the tensor per call.
  * cgbn_forward and cgbn_backward run these kernels back to back where a shape
- * does not qualify for their single-launch kernels (and always when the
+ * qualifies neither for the single-launch NCHW kernels nor for the column-slab kernels (and always when the
  * "fused" knob is 0).  Meant for tests and measurement. ---- */
 
 /* Algorithm 1 steps 1-3: s[k*C + c] = sum over shard k of x. */
@@ -270,14 +272,16 @@ const char* cgbn_status_string(cgbn_status status);
  *                      bfloat16; for float 64 KiB where the sweep reads one tensor, 32 KiB where it reads more)
  *   "reverse"          0/1: alternate the sweep direction between consecutive sweeps
  *   "nt_store"         0/1: non-temporal stores for y and dx
- *   "fused"            0/1: register-resident single-launch forward/backward (NCHW)
+ *   "fused"            0/1: register-resident forward/backward in one launch (the NCHW kernels and the
+ *                      column-slab kernels; 0: separate sweeps)
  *   "one_sweep_stats"  0/1 (default 1): where cgbn_forward runs as separate sweeps, steps 1-10 come from ONE sweep
  *                      over x: each row partial is the sum about a per-channel pivot and M2, the squared
  *                      deviations from the row's own mean (formed chunk by chunk in registers, never as a
  *                      difference of large sums); the combine step turns them into Algorithm 1's sums about the
  *                      pooled mean by the pairwise update.  3 tensor sweeps instead of 4, same results up to
  *                      rounding.  0: one sweep for the sums, a second for the squared deviations (what the
- *                      step-by-step entry points below always do)
+ *                      step-by-step entry points below always do); channels-last forwards then run as
+ *                      separate sweeps whatever their shape
  *   "cooperative"      0/1 (default 0): launch the single-launch kernels cooperatively, so that the runtime
  *                      guarantees the whole grid is resident; needed only if such calls can overlap on
  *                      different streams; costs about 15 us per launch
@@ -296,7 +300,8 @@ const char* cgbn_status_string(cgbn_status status);
  * cgbn_get_tuning returns -1 for an unknown key. */
 cgbn_status cgbn_set_tuning(const char* key, long long value);
 /* also readable: "last_forward_fused", "last_backward_fused" (1 if the last
- * cgbn_forward / cgbn_backward took the single-launch path) */
+ * cgbn_forward / cgbn_backward took the single-launch NCHW kernels), "last_forward_slab",
+ * "last_backward_slab" (1 if it took the column-slab kernels) */
 long long cgbn_get_tuning(const char* key);
 
 /* One number of the launch plan the library would use for this problem under the current
@@ -312,7 +317,12 @@ long long cgbn_get_tuning(const char* key);
  * Single-launch kernels, prefix "fwd_" or "bwd_": "ok" (the shape qualifies), "LB" (bytes per
  * access), "LPPC" (register slots per small plane; 0: large planes), "LPP" (slots a plane fills),
  * "IPU" (images per unit), "U" (units per channel), "tp" / "TL" (tiles per large plane, tile
- * elements), "rows", "rps", "G", "big" (0, or which LDS variant), "total_units". */
+ * elements), "rows", "rps", "G", "big" (0, or which LDS variant), "total_units".
+ * Column-slab kernels, prefix "sfwd_" or "sbwd_": "ok" (the shape takes them), "vecs" (16-byte
+ * vectors per row of the matrix), "R" (its rows), "cpc" (columns per channel), "cols" (vectors per
+ * slab), "slabs", "nch" (channels per slab, rounded up to a power of two), "rpp" (rows per pass),
+ * "tpc" (threads that add one channel's partial sums), "U" (units per slab), "rpu" (rows per unit),
+ * "P" (vectors per thread of the kernel variant). */
 long long cgbn_plan_get(int N, int C, int H, int W, cgbn_layout layout, cgbn_dtype dtype, int K,
                         const char* key);
 

@@ -2,8 +2,8 @@
 
 The host code and the multi-sweep kernels are one translation unit; the NCHW
 single-launch kernels are instantiated in ten more (element type x direction
-x activation), compiled side by side, then everything is linked into one
-shared library."""
+x activation), the column-slab kernels in four (element type x direction),
+compiled side by side, then everything is linked into one shared library."""
 
 from __future__ import annotations
 
@@ -41,6 +41,8 @@ def _units(obj_dir):
                 units.append((obj, os.path.join(CSRC, "cgbn_fused_inst.hip"),
                               [f"-DCGBN_INST_T={t}", f"-DCGBN_INST_F32={int(t == 'float')}", f"-DCGBN_INST_FWD={fwd}",
                                f"-DCGBN_INST_ACT={act}"]))
+            obj = os.path.join(OBJ, f"slab_{tname}_{'fwd' if fwd else 'bwd'}.o")
+            units.append((obj, os.path.join(CSRC, "cgbn_slab_inst.hip"), [f"-DCGBN_INST_T={t}", f"-DCGBN_INST_FWD={fwd}"]))
     return units
 
 

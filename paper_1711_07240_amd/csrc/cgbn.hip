@@ -5,6 +5,7 @@
 #include "cgbn_kernels.h"
 #include "cgbn_fused.h"
 #include "cgbn_fused_list.h"
+#include "cgbn_slab.h"
 
 #include <atomic>
 #include <cmath>
@@ -51,6 +52,23 @@ CGBN_FUSED_BIG_SMALL(CGBN_DECL_F2)
 CGBN_FUSED_BIG_SMALL(CGBN_DECL_B2)
 #undef CGBN_DECL_F2
 #undef CGBN_DECL_B2
+// ... and the column-slab kernels in cgbn_slab_inst.hip
+#define CGBN_DECL_SF(P_, SOLO_)                                                          \
+    extern template __global__ void slab_forward<float, 0, P_, SOLO_>(SlabArgs);         \
+    extern template __global__ void slab_forward<float, 1, P_, SOLO_>(SlabArgs);         \
+    extern template __global__ void slab_forward<float, 2, P_, SOLO_>(SlabArgs);         \
+    extern template __global__ void slab_forward<bf16_t, 0, P_, SOLO_>(SlabArgs);        \
+    extern template __global__ void slab_forward<bf16_t, 1, P_, SOLO_>(SlabArgs);        \
+    extern template __global__ void slab_forward<bf16_t, 2, P_, SOLO_>(SlabArgs);
+#define CGBN_DECL_SB(P_, SOLO_)                                                          \
+    extern template __global__ void slab_backward<float, 0, P_, SOLO_>(SlabArgs);        \
+    extern template __global__ void slab_backward<float, 1, P_, SOLO_>(SlabArgs);        \
+    extern template __global__ void slab_backward<bf16_t, 0, P_, SOLO_>(SlabArgs);       \
+    extern template __global__ void slab_backward<bf16_t, 1, P_, SOLO_>(SlabArgs);
+CGBN_SLAB_FORWARD_P(CGBN_DECL_SF)
+CGBN_SLAB_BACKWARD_P(CGBN_DECL_SB)
+#undef CGBN_DECL_SF
+#undef CGBN_DECL_SB
 #undef CGBN_DECL_FX
 #undef CGBN_DECL_BX
 #undef CGBN_DECL_F
@@ -119,6 +137,7 @@ Tuning tuning_now()
     std::lock_guard<std::mutex> hold(g_tune_lock);
     return g_tune;
 }
+std::atomic<long long> g_last_forward_slab{0}, g_last_backward_slab{0};
 std::atomic<long long> g_last_forward_fused{0}, g_last_backward_fused{0};   // which path the last call took
 #ifdef CGBN_TRACE
 unsigned long long* g_trace = nullptr;
@@ -133,6 +152,14 @@ struct FusedPlan {
     int tp, TL, LPP, IPU, U, rows, rps, G;
     int big;              // 1 (large planes) / 2 (small planes): the variant that stages few rows and keeps more unit data in LDS
     long long total_units;
+};
+
+// Geometry of the column-slab path for one direction (see cgbn_slab.h).
+struct SlabPlan {
+    int ok;
+    int cols, vecs, pow2, rpp, cpc, nch, tpc, slabs, U, rpu;
+    int P;                // vectors per thread of the kernel variant
+    long long R, row_bytes, total_units;
 };
 
 struct Plan {
@@ -154,6 +181,7 @@ struct Plan {
     int rows, rps, G;
     long long grid;       // workgroups of one sweep
     FusedPlan ff, fb;     // register-resident path, forward and backward
+    SlabPlan sf, sb;      // column-slab path
     // workspace layout (byte offsets)
     size_t off_part0, off_part1, off_sh0, off_sh1, off_mlo, off_sync, bytes;
 };
@@ -165,7 +193,7 @@ void make_fused_plan(const Tuning& T, int N, int C, long long HW, int K, int lay
 {
     std::memset(f, 0, sizeof(*f));
     if (K > kFusedMaxShards) return;
-    if (layout != CGBN_NCHW) return;                   // channels-last shapes take the multi-sweep kernels
+    if (layout != CGBN_NCHW) return;                   // channels-last shapes: see make_slab_plan
     int LB = 0;
     for (int lb = 16; lb >= 4; lb >>= 1)
         if (HW % (lb / eb) == 0) { LB = lb; break; }
@@ -279,6 +307,115 @@ void make_fused_plan(const Tuning& T, int N, int C, long long HW, int K, int lay
     f->ok = 1;
 }
 
+
+int ceil_pow2(int v)
+{
+    int p = 1;
+    while (p < v) p <<= 1;
+    return p;
+}
+
+// The smallest built variant that takes `need` vectors per thread (0: none does), and the largest there is.
+int slab_variant(bool forward, bool solo, long long need)
+{
+    int best = 0;
+#define CGBN_SLAB_BEST(P_, SOLO_) if (SOLO_ == solo && need <= P_ && (best == 0 || P_ < best)) best = P_;
+    if (forward) { CGBN_SLAB_FORWARD_P(CGBN_SLAB_BEST) } else { CGBN_SLAB_BACKWARD_P(CGBN_SLAB_BEST) }
+#undef CGBN_SLAB_BEST
+    return best;
+}
+int slab_most(bool forward, bool solo)
+{
+    int most = 0;
+#define CGBN_SLAB_MOST(P_, SOLO_) if (SOLO_ == solo && P_ > most) most = P_;
+    if (forward) { CGBN_SLAB_FORWARD_P(CGBN_SLAB_MOST) } else { CGBN_SLAB_BACKWARD_P(CGBN_SLAB_MOST) }
+#undef CGBN_SLAB_MOST
+    return most;
+}
+
+// The matrix (vecs, R, row_bytes, cpc) is given: cuts it into slabs of `cols` vectors and `nch` channels with U units each.
+// `row_pairs`: (channel, unit) pairs the workspace has room for.
+bool cut_slabs(SlabPlan* s, int C, int cols, int nch, long long U, long long row_pairs, int cus, bool forward)
+{
+    s->cols = cols;
+    s->nch = nch;
+    s->pow2 = cols <= kWave && (cols & (cols - 1)) == 0;
+    s->rpp = kSlabThreads / cols;
+    s->tpc = nch * kWave <= kSlabThreads ? kWave : kSlabThreads / nch;
+    s->slabs = (s->vecs + cols - 1) / cols;
+    s->rpu = (int)((s->R + U - 1) / U);
+    s->U = (int)((s->R + s->rpu - 1) / s->rpu);       // (no empty unit)
+    s->P = slab_variant(forward, s->U == 1, ((long long)s->rpu + s->rpp - 1) / s->rpp);
+    s->total_units = (long long)s->slabs * s->U;
+    s->ok = 0;
+    if (!s->P || nch > kSlabMaxChannels || s->slabs > C || s->total_units > 0x3fffffffLL) return false;
+    if ((long long)s->rpp * s->row_bytes + (long long)cols * 16 > 0x7fffffffLL) return false;   // 32-bit lane offsets
+    if (s->U > 1) {
+        if (s->U > cus || s->U > 0xffff) return false;                              // a slab's units are resident together
+        if (forward && (long long)s->U * nch > kSlabMaxRows) return false;          // kept in LDS
+        if ((long long)s->slabs * nch * s->U > row_pairs) return false;
+        if ((long long)s->slabs * ((s->U + 31) / 32) > C) return false;             // bitmap words
+    }
+    s->ok = 1;
+    return true;
+}
+
+// Several units per slab: U so that the launch is shortest.  A round of resident units costs the passes of a unit plus a
+// part that every hand-over costs, about that of 10 passes (6 us, against 0.6 us per pass of 512 x 16 bytes on every
+// compute unit) and one more per 1024 (channel, unit) pairs that every unit fetches; rounds are whole.  Slabs that do not
+// end on line boundaries share lines with their neighbours, so they must all be in flight together: one round
+// (measured, fp32 268800 x 136 in four rounds 170 us, the sweeps 101).
+bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_pairs, int cus, bool forward)
+{
+    const int rpp = kSlabThreads / cols;
+    const long long cap = (long long)rpp * slab_most(forward, false);
+    const long long slabs = (s->vecs + cols - 1) / cols;
+    const bool lines = s->row_bytes % 128 == 0 && cols % 8 == 0;
+    const long long least = (s->R + cap - 1) / cap < 2 ? 2 : (s->R + cap - 1) / cap;
+    long long most = cus < s->R ? cus : s->R;
+    if (forward && most > kSlabMaxRows / nch) most = kSlabMaxRows / nch;
+    if (most > row_pairs / (slabs * nch)) most = row_pairs / (slabs * nch);
+    long long best = 0, best_cost = 0;
+    for (int k = 0; k < 8; ++k) {
+        // the fewest units and a few more; as many as fill the compute units once, or half of them, ...
+        const long long U = k < 4 ? least + k : cus / slabs < most ? (cus / slabs) >> (k - 4) : most >> (k - 4);
+        if (U < least || U > most) continue;
+        const long long grid = cus / U * U, units = slabs * U;
+        const long long rounds = (units + grid - 1) / grid;
+        if (rounds > 1 && !lines) continue;
+        const long long rows = (s->R + U - 1) / U, passes = (rows + rpp - 1) / rpp;
+        const long long cost = rounds * (passes * 1024 + 10 * 1024 + U * nch);
+        if (best == 0 || cost < best_cost) { best = U; best_cost = cost; }
+    }
+    return best >= 2 && cut_slabs(s, C, cols, nch, best, row_pairs, cus, forward);
+}
+
+// Which calls take the column-slab kernels, and how they are cut.  Channels-last, C a multiple of a 16-byte vector:
+//   - up to 3072 pixels one workgroup per slab of 2 vectors (forward 5120 while the tensor is at most 6 MB): one launch, nothing
+//     to hand over.  More pixels per workgroup than that are slower than several units.  Measured, forward / backward
+//     us, sweeps -> one unit -> several: bf16 2100 x 512 22 / 30 -> 9.6 / 11.7 -> 13.8 / 13.2; 3200 x 1024 26 / 32 -> 13.9 /
+//     20.9 -> 16.1 / 16.2; 8400 x 512 27 / 32 -> 23 / 32 -> 17.9 / 17.7.
+//   - beyond, units of 128-byte columns wherever a slab's units are resident together.  Measured, sweeps -> units: bf16
+//     67200 x 256 39 / 49 -> 25 / 30, 16800 x 2048 67 / 94 -> 34 / 57, 268800 x 512 182 / 285 -> 155 / 264; fp32 67200 x 512
+//     95 / 139 -> 66 / 100, 67200 x 1024 170 / 260 -> 172 / 260, 268800 x 1024 607 / 976 -> 517 / 920.  Narrower columns lose (half a
+//     line per request), wider ones make a slab's rows more than the hand-over bears.
+void make_slab_plan(int N, int C, long long HW, int layout, int eb, long long row_pairs, int cus, bool forward, SlabPlan* s)
+{
+    std::memset(s, 0, sizeof(*s));
+    const int vec = 16 / eb;
+    if (layout != CGBN_NHWC || C % vec != 0) return;
+    s->vecs = C / vec;
+    s->R = (long long)N * HW;
+    s->row_bytes = (long long)C * eb;
+    s->cpc = 1;
+    if (s->R <= 3072 || (forward && s->R <= 5120 && s->R * s->row_bytes <= 6000000)) {
+        const int cols = s->vecs < 2 ? s->vecs : 2;
+        if (cut_slabs(s, C, cols, cols * vec, 1, row_pairs, cus, forward)) return;
+    }
+    // about 8 vectors, as even as the row allows
+    const int slabs = s->vecs < 12 ? 1 : (s->vecs + 4) / 8, cols = (s->vecs + slabs - 1) / slabs;
+    cut_slabs_in_units(s, C, cols, ceil_pow2(cols * vec), row_pairs, cus, forward);
+}
 
 // compute units of the current device (256 if there is none to ask)
 int compute_units()
@@ -431,6 +568,17 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
     // the sync area comes first, so that the error word has the same offset in every workspace
     size_t sync = align256(((size_t)kSyncHeader + 4 * (size_t)C) * sizeof(unsigned));
     size_t part = align256((size_t)C * max_rows * sizeof(float));
+    // The column-slab path keeps its rows where the other paths keep theirs (part0 and part1 are adjacent) and makes that
+    // room larger only up to half a MiB, so that it changes no limit.
+    const long long row_pairs = part > (256u << 10) ? (long long)(part / sizeof(float)) : (256 << 10) / (long long)sizeof(float);
+    const int cus = compute_units();
+    make_slab_plan(N, C, HW, layout, p->eb, row_pairs, cus, true, &p->sf);
+    make_slab_plan(N, C, HW, layout, p->eb, row_pairs, cus, false, &p->sb);
+    for (const SlabPlan* s : {&p->sf, &p->sb})
+        if (s->ok && s->U > 1) {
+            const size_t need = align256((size_t)s->slabs * s->nch * s->U * sizeof(float));
+            if (need > part) part = need;
+        }
     size_t sh = align256((size_t)K * C * sizeof(double));
     p->off_sync = 0;
     p->off_part0 = sync;
@@ -585,7 +733,7 @@ cgbn_status launch_combine(int mode, const Plan& p, char* ws, float* out0, float
 // ---- register-resident path ------------------------------------------------
 
 // workgroups of `kernel` that are resident at once on the current device (cached per kernel and device)
-template <typename KernelT> int resident_groups(KernelT kernel)
+template <typename KernelT> int resident_groups(KernelT kernel, int threads = kThreads)
 {
     static std::mutex lock;
     static std::map<std::pair<const void*, int>, int> cache;
@@ -595,7 +743,7 @@ template <typename KernelT> int resident_groups(KernelT kernel)
     std::lock_guard<std::mutex> hold(lock);
     auto it = cache.find(key);
     if (it != cache.end()) return it->second;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kThreads, 0) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
     cache[key] = per_cu * cus;
     return per_cu * cus;
@@ -752,6 +900,59 @@ FusedArgs fused_args(const Plan& p, const FusedPlan& f, char* ws)
     A.trace = g_trace;
 #endif
     return A;
+}
+
+SlabArgs slab_args(const Plan& p, const SlabPlan& s, char* ws)
+{
+    SlabArgs A;
+    std::memset(&A, 0, sizeof(A));
+    A.rows = reinterpret_cast<unsigned*>(ws + p.off_part0);
+    A.sync = reinterpret_cast<unsigned*>(ws + p.off_sync);
+    A.R = s.R; A.row_bytes = s.row_bytes;
+    A.M = p.M; A.inv_M_f64 = 1.0 / p.M; A.inv_M = (float)(1.0 / p.M);
+    A.vecs = s.vecs; A.cols = s.cols; A.ncols = s.cols * (16 / p.eb); A.pow2 = s.pow2; A.rpp = s.rpp;
+    A.cpc = s.cpc; A.nch = s.nch; A.tpc = s.tpc; A.rch = A.ncols / s.cpc;
+    while ((1 << A.nsh) < s.nch) ++A.nsh;
+    A.C = p.C; A.slabs = s.slabs; A.U = s.U; A.rpu = s.rpu; A.total_units = (int)s.total_units;
+    A.pivot_stride = p.layout == CGBN_NCHW ? p.HW : 1;
+    A.nt = (int)p.t.nt_store && s.U > 1;
+    A.spin_limit = (unsigned)p.t.spin_limit;
+    A.bitmap_words = (unsigned)((s.U + 31) / 32);
+    A.cpc_magic = (unsigned)(((1ULL << 32) + s.cpc - 1) / s.cpc);     // (not used for one column per channel)
+    return A;
+}
+
+template <typename KernelT>
+cgbn_status launch_slab_kernel(KernelT kernel, const Plan& p, const SlabPlan& s, const SlabArgs& A, hipStream_t st)
+{
+    long long groups = s.total_units;
+    if (s.U > 1) {
+        const long long resident = resident_groups(kernel, kSlabThreads);
+        if (resident < 1) return CGBN_ERR_HIP;
+        if (groups > resident) groups = resident;
+        if (p.t.fused_groups > 0 && p.t.fused_groups < groups) groups = p.t.fused_groups > s.U ? p.t.fused_groups : s.U;
+        // whole slabs only: the units of a straddling slab would wait a round for their siblings
+        if (groups > s.U && groups < s.total_units) groups = groups / s.U * s.U;
+        const long long words = 2LL * s.slabs * s.nch * s.U;
+        long long want = (words + kThreads - 1) / kThreads;
+        const unsigned init_groups = (unsigned)(want < 1 ? 1 : (want > 2048 ? 2048 : want));
+        hipLaunchKernelGGL(fused_init, dim3(init_groups), dim3(kThreads), 0, st, A.sync, kSyncHeader + 4 * p.C, A.rows, words);
+    }
+    hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3(kSlabThreads), 0, st, A);
+    return launched();
+}
+
+template <typename T, bool FWD, int ACT>
+cgbn_status launch_slab_t(const Plan& p, const SlabPlan& s, const SlabArgs& A, hipStream_t st)
+{
+#define CGBN_SLAB_CASE(P_, SOLO_)                                                                               \
+    if (s.P == P_ && (s.U == 1) == SOLO_) {                                                                     \
+        if constexpr (FWD) return launch_slab_kernel(slab_forward<T, ACT, P_, SOLO_>, p, s, A, st);             \
+        else return launch_slab_kernel(slab_backward<T, ACT, P_, SOLO_>, p, s, A, st);                          \
+    }
+    if constexpr (FWD) { CGBN_SLAB_FORWARD_P(CGBN_SLAB_CASE) } else { CGBN_SLAB_BACKWARD_P(CGBN_SLAB_CASE) }
+#undef CGBN_SLAB_CASE
+    return CGBN_ERR_HIP;              // (no such variant: the plan takes its sizes from the same list)
 }
 
 bool eps_ok(float eps) { return std::isfinite(eps) && eps > 0.f; }
@@ -983,6 +1184,17 @@ cgbn_status forward_impl(const Tuning& T, const void* x, const void* shortcut, b
     }
     g_last_forward_fused = 0;
 
+    g_last_forward_slab = p.t.fused && p.t.one_sweep_stats && p.sf.ok;
+    if (g_last_forward_slab) {
+        SlabArgs F = slab_args(p, p.sf, ws);
+        F.x = x; F.dy = shortcut; F.out = y; F.gamma = gamma; F.beta = beta; F.eps = (double)eps;
+        F.mean = mean; F.mean_lo = mean_lo; F.invstd = invstd;
+        const bool f32 = p.dtype == CGBN_F32;
+        if (relu && shortcut) return f32 ? launch_slab_t<float, true, 2>(p, p.sf, F, st) : launch_slab_t<bf16_t, true, 2>(p, p.sf, F, st);
+        if (relu) return f32 ? launch_slab_t<float, true, 1>(p, p.sf, F, st) : launch_slab_t<bf16_t, true, 1>(p, p.sf, F, st);
+        return f32 ? launch_slab_t<float, true, 0>(p, p.sf, F, st) : launch_slab_t<bf16_t, true, 0>(p, p.sf, F, st);
+    }
+
     SweepArgs A = sweep_args(p);
     A.x = x; A.part0 = part0;
     if (p.t.one_sweep_stats) {
@@ -1046,6 +1258,17 @@ cgbn_status backward_impl(const Tuning& T, const void* dy, const void* y, const 
         if (taken || st_ != CGBN_OK) return st_;
     }
     g_last_backward_fused = 0;
+
+    g_last_backward_slab = p.t.fused && p.sb.ok;
+    if (g_last_backward_slab) {
+        SlabArgs F = slab_args(p, p.sb, ws);
+        F.x = x; F.dy = dy; F.aux = y; F.out = dx; F.out2 = dshortcut; F.gamma = gamma;
+        F.mean = const_cast<float*>(mean); F.mean_lo = const_cast<float*>(mean_lo); F.invstd = const_cast<float*>(invstd);
+        F.dgamma = dgamma; F.dbeta = dbeta;
+        const bool f32 = p.dtype == CGBN_F32;
+        if (relu) return f32 ? launch_slab_t<float, false, 1>(p, p.sb, F, st) : launch_slab_t<bf16_t, false, 1>(p, p.sb, F, st);
+        return f32 ? launch_slab_t<float, false, 0>(p, p.sb, F, st) : launch_slab_t<bf16_t, false, 0>(p, p.sb, F, st);
+    }
 
     SweepArgs A = sweep_args(p);
     A.x = x; A.dy = dy; A.mean = mean; A.mean_lo = mean_lo; A.invstd = invstd;
@@ -1244,6 +1467,23 @@ long long cgbn_plan_get(int N, int C, int H, int W, cgbn_layout layout, cgbn_dty
         if (!std::strcmp(k, "total_units")) return f.total_units;
         return -1;
     }
+    if (!std::strncmp(key, "sfwd_", 5) || !std::strncmp(key, "sbwd_", 5)) {
+        const SlabPlan& s = key[1] == 'b' ? p.sb : p.sf;
+        const char* k = key + 5;
+        if (!std::strcmp(k, "ok")) return s.ok;
+        if (!std::strcmp(k, "cols")) return s.cols;
+        if (!std::strcmp(k, "vecs")) return s.vecs;
+        if (!std::strcmp(k, "cpc")) return s.cpc;
+        if (!std::strcmp(k, "nch")) return s.nch;
+        if (!std::strcmp(k, "rpp")) return s.rpp;
+        if (!std::strcmp(k, "tpc")) return s.tpc;
+        if (!std::strcmp(k, "slabs")) return s.slabs;
+        if (!std::strcmp(k, "U")) return s.U;
+        if (!std::strcmp(k, "rpu")) return s.rpu;
+        if (!std::strcmp(k, "P")) return s.P;
+        if (!std::strcmp(k, "R")) return s.R;
+        return -1;
+    }
     if (!std::strcmp(key, "wave_mode")) return p.wave_mode;
     if (!std::strcmp(key, "tiny")) return p.tiny;
     if (!std::strcmp(key, "tg")) return p.tg;
@@ -1275,6 +1515,8 @@ long long cgbn_get_tuning(const char* key)
 {
     if (key && !std::strcmp(key, "last_forward_fused")) return g_last_forward_fused.load();
     if (key && !std::strcmp(key, "last_backward_fused")) return g_last_backward_fused.load();
+    if (key && !std::strcmp(key, "last_forward_slab")) return g_last_forward_slab.load();
+    if (key && !std::strcmp(key, "last_backward_slab")) return g_last_backward_slab.load();
     long long* slot = tuning_slot(key);
     if (!slot) return -1;
     std::lock_guard<std::mutex> hold(g_tune_lock);

@@ -1,0 +1,85 @@
+"""Host-side planning of the column-slab kernels without a GPU: for thousands of seeded shapes the numbers the kernels
+index by cover the matrix exactly, fit the registers, the LDS and the workspace, and change no limit."""
+
+import numpy as np
+import pytest
+
+from paper_1711_07240_amd import cgbn as L
+
+THREADS = 512
+VARIANTS = {("sfwd", True): (4, 8, 12, 20), ("sfwd", False): (6, 12, 20, 28, 36),
+            ("sbwd", True): (4, 8, 12, 20), ("sbwd", False): (6, 10, 14, 18)}
+MAX_PAIRS, MAX_CHANNELS = 12288, 128
+STATIC_SCRATCH = 16 << 20
+
+
+def _check(shape):
+    N, C, H, W, layout, dtype, K = shape
+    vec = 4 if dtype == "f32" else 8
+    taken = 0
+    for d in ("sfwd", "sbwd"):
+        g = lambda k: L.cgbn_plan_get(*shape, f"{d}_{k}")
+        if not g("ok"):
+            continue
+        taken += 1
+        cols, vecs, cpc, nch, rpp, tpc, slabs, U, rpu, P, R = (g(k) for k in (
+            "cols", "vecs", "cpc", "nch", "rpp", "tpc", "slabs", "U", "rpu", "P", "R"))
+        if layout == "NHWC":
+            assert cpc == 1 and R == N * H * W and vecs * vec == C
+        else:
+            assert cpc == H * W and R == N and vecs * vec == C * H * W
+        # slabs cover the vectors, units cover the rows, none of them empty
+        assert 1 <= cols <= THREADS and (slabs - 1) * cols < vecs <= slabs * cols
+        assert (U - 1) * rpu < R <= U * rpu
+        # a slab is whole channels; the padded channel count is a power of two the threads divide into
+        assert cols * vec % cpc == 0 and cols * vec // cpc <= nch <= MAX_CHANNELS and nch & (nch - 1) == 0
+        assert tpc & (tpc - 1) == 0 and 1 <= tpc <= 64 and tpc * nch <= THREADS
+        # registers: a kernel variant with room for the unit's passes
+        assert rpp == THREADS // cols and rpu <= rpp * P and P in VARIANTS[d, U == 1]
+        assert rpp * (C * (H * W if layout == "NCHW" else 1)) * (16 // vec) + cols * 16 < 2 ** 31
+        if U > 1:
+            assert U <= 256                                     # (the compute units of the planning host's default)
+            assert d == "sbwd" or U * nch <= MAX_PAIRS
+            assert slabs * nch * U * 8 <= 2 * L.cgbn_plan_get(*shape, "part_bytes")
+            assert slabs * -(-U // 32) <= C and slabs <= C      # counters and bitmaps inside the sync area
+            if slabs * U > 256:                                 # several rounds: slabs end on lines
+                assert cols % 8 == 0 and vecs * 16 % 128 == 0
+    # the rows add at most half a MiB to what the other kernels need
+    rows = max(L.cgbn_plan_get(*shape, "rows"), *(L.cgbn_plan_get(*shape, f"{d}_rows") for d in ("fwd", "bwd")))
+    assert L.cgbn_plan_get(*shape, "part_bytes") <= max(-(-C * rows * 4 // 256) * 256, 256 << 10)
+    return taken
+
+
+def _shapes(count, seed, layout):
+    r = np.random.default_rng(seed)
+    for _ in range(count):
+        dtype = "f32" if r.random() < 0.5 else "bf16"
+        N = int(np.exp(r.uniform(0, np.log(512))))
+        C = int(np.exp(r.uniform(np.log(4), np.log(4096))))
+        C = max(8, C // 8 * 8) if r.random() < 0.9 else C
+        H, W = int(np.exp(r.uniform(0, np.log(260)))), int(np.exp(r.uniform(0, np.log(400))))
+        if N * C * H * W <= 2 ** 33:
+            K = int(r.choice([k for k in range(1, N + 1) if N % k == 0]))
+            yield (N, C, H, W, layout, dtype, K)
+
+
+@pytest.mark.parametrize("layout", ["NHWC", "NCHW"])
+@pytest.mark.parametrize("seed", [1, 2])
+def test_random_shapes(seed, layout):
+    taken = 0
+    for shape in _shapes(1200, seed, layout):
+        try:
+            taken += _check(shape)
+        except AssertionError as e:
+            raise AssertionError(f"{shape}: {e}") from e
+    if layout == "NHWC":
+        assert taken > 1200
+
+
+def test_detector_layers():
+    one = (2, 512, 25, 42, "NHWC", "bf16", 2)
+    assert L.cgbn_plan_get(*one, "sfwd_U") == 1 and L.cgbn_plan_get(*one, "sbwd_U") == 1 and _check(one) == 2
+    many = (16, 256, 50, 84, "NHWC", "bf16", 8)
+    assert L.cgbn_plan_get(*many, "sfwd_U") > 1 and _check(many) == 2
+    odd = (16, 250, 50, 84, "NHWC", "bf16", 8)                  # channels that are no whole vectors
+    assert L.cgbn_plan_get(*odd, "sfwd_ok") == 0 and L.cgbn_plan_get(*odd, "sbwd_ok") == 0
