@@ -156,7 +156,8 @@ struct FusedPlan {
 
 // Geometry of the column-slab path for one direction (see cgbn_slab.h).
 struct SlabPlan {
-    int ok;
+    int ok;               // the shape can take the path, and it is faster than separate sweeps
+    int first;            // ... and faster than the single-launch NCHW kernels, where the shape can take those too
     int cols, vecs, pow2, rpp, cpc, nch, tpc, slabs, U, rpu;
     int P;                // vectors per thread of the kernel variant
     long long R, row_bytes, total_units;
@@ -370,7 +371,7 @@ bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_pai
     const int rpp = kSlabThreads / cols;
     const long long cap = (long long)rpp * slab_most(forward, false);
     const long long slabs = (s->vecs + cols - 1) / cols;
-    const bool lines = s->row_bytes % 128 == 0 && cols % 8 == 0;
+    const bool lines = cols >= 48 || (s->row_bytes % 128 == 0 && cols % 8 == 0);     // (a wide slab shares little)
     const long long least = (s->R + cap - 1) / cap < 2 ? 2 : (s->R + cap - 1) / cap;
     long long most = cus < s->R ? cus : s->R;
     if (forward && most > kSlabMaxRows / nch) most = kSlabMaxRows / nch;
@@ -399,22 +400,53 @@ bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_pai
 //     67200 x 256 39 / 49 -> 25 / 30, 16800 x 2048 67 / 94 -> 34 / 57, 268800 x 512 182 / 285 -> 155 / 264; fp32 67200 x 512
 //     95 / 139 -> 66 / 100, 67200 x 1024 170 / 260 -> 172 / 260, 268800 x 1024 607 / 976 -> 517 / 920.  Narrower columns lose (half a
 //     line per request), wider ones make a slab's rows more than the hand-over bears.
-void make_slab_plan(int N, int C, long long HW, int layout, int eb, long long row_pairs, int cus, bool forward, SlabPlan* s)
+//
+// NCHW, planes of at most 512 values, C a multiple of a 16-byte vector's elements (a slab starts and ends on 16 bytes):
+//   - images that fit one workgroup: instead of the sweeps always.  Instead of the single-launch kernels where a channel is
+//     several of their units, and where a thread holds few vectors and there are 1024 channels, or 128 and 24 images: those
+//     kernels move one plane per wavefront at a time and leave most of its lanes idle.  Measured, them -> here, forward / backward us: fp32 256 x 1024 planes of 4x4 100 /
+//     135 -> 12 / 14, bf16 16 x 2048 of 8x8 19 / 17 -> 8.3 / 8.0; with few channels and images they stay ahead: fp32 8 x 256
+//     of 16x20 6.3 / 5.6 against 6.4 / 6.4, bf16 16 x 256 of 20x20 7.6 / 7.4 against 11.5 / 12.
+//   - several units per slab from 6 MB on (below, the hand-over costs what a launch less saves), and there before the
+//     single-launch kernels while planes are at most 1 KiB and the tensor 200 MB (backward: 512 bytes, float 800, 100 MB): bf16 256 x 1024 of 7x7 31 / 37 -> 23 /
+//     26, of 12x12 110 / 125 -> 49 / 60; fp32 100 x 1024 of 16x20 75 / 97 against 86 / 124.
+void make_slab_plan(int N, int C, long long HW, int layout, int eb, long long row_pairs, int cus, const FusedPlan& f, bool forward,
+                    SlabPlan* s)
 {
     std::memset(s, 0, sizeof(*s));
     const int vec = 16 / eb;
-    if (layout != CGBN_NHWC || C % vec != 0) return;
-    s->vecs = C / vec;
-    s->R = (long long)N * HW;
-    s->row_bytes = (long long)C * eb;
-    s->cpc = 1;
-    if (s->R <= 3072 || (forward && s->R <= 5120 && s->R * s->row_bytes <= 6000000)) {
-        const int cols = s->vecs < 2 ? s->vecs : 2;
-        if (cut_slabs(s, C, cols, cols * vec, 1, row_pairs, cus, forward)) return;
+    if (C % vec != 0 || (layout == CGBN_NCHW && HW > kSlabThreads)) return;
+    if (layout == CGBN_NHWC) {
+        s->vecs = C / vec;
+        s->R = (long long)N * HW;
+        s->row_bytes = (long long)C * eb;
+        s->cpc = 1;
+        if (s->R <= 3072 || (forward && s->R <= 5120 && s->R * s->row_bytes <= 6000000)) {
+            const int cols = s->vecs < 2 ? s->vecs : 2;
+            if (cut_slabs(s, C, cols, cols * vec, 1, row_pairs, cus, forward)) return;
+        }
+        // about 8 vectors, as even as the row allows
+        const int slabs = s->vecs < 12 ? 1 : (s->vecs + 4) / 8, cols = (s->vecs + slabs - 1) / slabs;
+        cut_slabs_in_units(s, C, cols, ceil_pow2(cols * vec), row_pairs, cus, forward);
+        return;
     }
-    // about 8 vectors, as even as the row allows
-    const int slabs = s->vecs < 12 ? 1 : (s->vecs + 4) / 8, cols = (s->vecs + slabs - 1) / slabs;
-    cut_slabs_in_units(s, C, cols, ceil_pow2(cols * vec), row_pairs, cus, forward);
+    const long long row_vecs = (long long)C * HW / vec;
+    if (row_vecs > 0x7fffffffLL) return;
+    s->vecs = (int)row_vecs;
+    s->R = N;
+    s->row_bytes = (long long)C * HW * eb;
+    s->cpc = (int)HW;
+    int nch = vec;                                     // channels per slab: at least 8 vectors, if there are that many
+    while (nch * 2 <= kSlabMaxChannels && nch < C && (long long)nch / vec * HW < 8) nch *= 2;
+    const int cols = (int)(nch / vec * HW), rpp = kSlabThreads / cols;
+    if (N <= rpp * slab_most(forward, true) && cut_slabs(s, C, cols, nch, 1, row_pairs, cus, forward)) {
+        s->first = !f.ok || f.U > 1 || (C >= 1024 && s->P <= (forward ? 12 : 8)) ||
+                   (N >= 24 && C >= 128 && s->P <= (forward ? 8 : 4));
+        return;
+    }
+    if (N * s->row_bytes < 6000000) return;
+    if (cut_slabs_in_units(s, C, cols, nch, row_pairs, cus, forward))
+        s->first = !f.ok || (f.U > 1 && (forward ? HW * eb <= 1024 && N * s->row_bytes <= 200000000 : HW * eb <= (eb == 2 ? 512 : 800) && N * s->row_bytes <= 100000000));
 }
 
 // compute units of the current device (256 if there is none to ask)
@@ -572,8 +604,8 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
     // room larger only up to half a MiB, so that it changes no limit.
     const long long row_pairs = part > (256u << 10) ? (long long)(part / sizeof(float)) : (256 << 10) / (long long)sizeof(float);
     const int cus = compute_units();
-    make_slab_plan(N, C, HW, layout, p->eb, row_pairs, cus, true, &p->sf);
-    make_slab_plan(N, C, HW, layout, p->eb, row_pairs, cus, false, &p->sb);
+    make_slab_plan(N, C, HW, layout, p->eb, row_pairs, cus, p->ff, true, &p->sf);
+    make_slab_plan(N, C, HW, layout, p->eb, row_pairs, cus, p->fb, false, &p->sb);
     for (const SlabPlan* s : {&p->sf, &p->sb})
         if (s->ok && s->U > 1) {
             const size_t need = align256((size_t)s->slabs * s->nch * s->U * sizeof(float));
@@ -1165,7 +1197,8 @@ cgbn_status forward_impl(const Tuning& T, const void* x, const void* shortcut, b
     float* mlo = reinterpret_cast<float*>(ws + p.off_mlo);
     const int rev = (int)p.t.reverse;
 
-    if (p.t.fused && p.ff.ok) {
+    const bool slab = p.t.fused && p.t.one_sweep_stats && p.sf.ok;
+    if (p.t.fused && p.ff.ok && !(slab && p.sf.first)) {
         FusedArgs F = fused_args(p, p.ff, ws);
         F.x = x; F.out = y; F.gamma = gamma; F.beta = beta; F.eps = (double)eps; F.aux = shortcut;
         F.mean = mean; F.mean_lo = mlo; F.mean_lo_user = mean_lo; F.invstd = invstd;
@@ -1180,12 +1213,13 @@ cgbn_status forward_impl(const Tuning& T, const void* x, const void* shortcut, b
                                : (f32 ? launch_fused_t<float, true, 0>(p.t, p.ff, F, sync_words, st, &taken, moved)
                                       : launch_fused_t<bf16_t, true, 0>(p.t, p.ff, F, sync_words, st, &taken, moved));
         g_last_forward_fused = taken;
+        if (taken) g_last_forward_slab = 0;
         if (taken || st_ != CGBN_OK) return st_;
     }
     g_last_forward_fused = 0;
 
-    g_last_forward_slab = p.t.fused && p.t.one_sweep_stats && p.sf.ok;
-    if (g_last_forward_slab) {
+    g_last_forward_slab = slab;
+    if (slab) {
         SlabArgs F = slab_args(p, p.sf, ws);
         F.x = x; F.dy = shortcut; F.out = y; F.gamma = gamma; F.beta = beta; F.eps = (double)eps;
         F.mean = mean; F.mean_lo = mean_lo; F.invstd = invstd;
@@ -1241,7 +1275,8 @@ cgbn_status backward_impl(const Tuning& T, const void* dy, const void* y, const 
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int rev = (int)p.t.reverse;
 
-    if (p.t.fused && p.fb.ok) {
+    const bool slab = p.t.fused && p.sb.ok;
+    if (p.t.fused && p.fb.ok && !(slab && p.sb.first)) {
         FusedArgs F = fused_args(p, p.fb, ws);
         F.x = x; F.dy = dy; F.out = dx; F.gamma = gamma; F.aux = y; F.out2 = dshortcut;
         F.mean = const_cast<float*>(mean); F.mean_lo = const_cast<float*>(mean_lo);
@@ -1255,12 +1290,13 @@ cgbn_status backward_impl(const Tuning& T, const void* dy, const void* y, const 
                                : (f32 ? launch_fused_t<float, false, 0>(p.t, p.fb, F, sync_words, st, &taken, moved)
                                       : launch_fused_t<bf16_t, false, 0>(p.t, p.fb, F, sync_words, st, &taken, moved));
         g_last_backward_fused = taken;
+        if (taken) g_last_backward_slab = 0;
         if (taken || st_ != CGBN_OK) return st_;
     }
     g_last_backward_fused = 0;
 
-    g_last_backward_slab = p.t.fused && p.sb.ok;
-    if (g_last_backward_slab) {
+    g_last_backward_slab = slab;
+    if (slab) {
         SlabArgs F = slab_args(p, p.sb, ws);
         F.x = x; F.dy = dy; F.aux = y; F.out = dx; F.out2 = dshortcut; F.gamma = gamma;
         F.mean = const_cast<float*>(mean); F.mean_lo = const_cast<float*>(mean_lo); F.invstd = const_cast<float*>(invstd);
@@ -1471,6 +1507,7 @@ long long cgbn_plan_get(int N, int C, int H, int W, cgbn_layout layout, cgbn_dty
         const SlabPlan& s = key[1] == 'b' ? p.sb : p.sf;
         const char* k = key + 5;
         if (!std::strcmp(k, "ok")) return s.ok;
+        if (!std::strcmp(k, "first")) return s.first;
         if (!std::strcmp(k, "cols")) return s.cols;
         if (!std::strcmp(k, "vecs")) return s.vecs;
         if (!std::strcmp(k, "cpc")) return s.cpc;

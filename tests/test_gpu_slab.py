@@ -35,6 +35,16 @@ SHAPES = [
     ("ragged-last-slab-many-units", (2, 136, 110, 101, 1, "NHWC", "bf16"), "several"),
     ("full-lines-f32", (16, 64, 23, 29, 8, "NHWC", "f32"), "several"),
     ("longest-units", (1, 512, 100, 170, 1, "NHWC", "bf16"), "several"),
+    ("planes-of-one", (64, 24, 1, 1, 8, "NCHW", "bf16"), 1),
+    ("planes-of-two-vectors-of-channels", (40, 1024, 2, 1, 4, "NCHW", "f32"), 1),
+    ("planes-of-9-doubled-slab", (30, 24, 3, 3, 3, "NCHW", "f32"), 1),
+    ("planes-of-49-ragged-slab", (37, 40, 7, 7, 37, "NCHW", "bf16"), 1),
+    ("planes-of-64-power-of-two", (27, 128, 8, 8, 3, "NCHW", "bf16"), 1),
+    ("planes-of-273-one-row-a-pass", (16, 24, 13, 21, 8, "NCHW", "bf16"), 1),
+    ("planes-of-512", (3, 1024, 16, 32, 3, "NCHW", "f32"), 1),
+    ("planes-of-49-several-units", (300, 256, 7, 7, 5, "NCHW", "bf16"), "several"),
+    ("planes-of-225-several-units", (60, 256, 15, 15, 4, "NCHW", "bf16"), "several"),
+    ("planes-of-144-float-several-units", (100, 128, 12, 12, 4, "NCHW", "f32"), "several"),
     ("8x8-planes-channels-last-k1", (64, 128, 8, 13, 64, "NHWC", "bf16"), "several"),
 ]
 
@@ -135,7 +145,7 @@ def test_relu_against_the_oracle(name, shape, units, with_shortcut):
         assert np.array_equal(G.to_host_f64(dz, wl.dtype), dzr)
 
 
-MOVED_ON = [s for s in SHAPES if s[2] == "several"][:6]
+MOVED_ON = [s for s in SHAPES if s[2] == "several"][:6] + [s for s in SHAPES if s[0] == "planes-of-49-several-units"]
 
 
 @pytest.mark.parametrize("name,shape,units", MOVED_ON, ids=[s[0] for s in MOVED_ON])
