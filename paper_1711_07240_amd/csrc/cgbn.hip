@@ -397,8 +397,8 @@ bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_pai
 //     us, sweeps -> one unit -> several: bf16 2100 x 512 22 / 30 -> 9.6 / 11.7 -> 13.8 / 13.2; 3200 x 1024 26 / 32 -> 13.9 /
 //     20.9 -> 16.1 / 16.2; 8400 x 512 27 / 32 -> 23 / 32 -> 17.9 / 17.7.
 //   - beyond, units of 128-byte columns wherever a slab's units are resident together.  Measured, sweeps -> units: bf16
-//     67200 x 256 39 / 49 -> 25 / 30, 16800 x 2048 67 / 94 -> 34 / 57, 268800 x 512 182 / 285 -> 155 / 264; fp32 67200 x 512
-//     95 / 139 -> 66 / 100, 67200 x 1024 170 / 260 -> 172 / 260, 268800 x 1024 607 / 976 -> 517 / 920.  Narrower columns lose (half a
+//     67200 x 256 38 / 49 -> 26 / 31, 16800 x 2048 67 / 94 -> 34 / 57, 268800 x 512 181 / 288 -> 159 / 253; fp32 67200 x 512
+//     95 / 139 -> 66 / 100, 67200 x 1024 168 / 255 -> 144 / 222, 268800 x 1024 599 / 974 -> 568 / 908.  Narrower columns lose (half a
 //     line per request), wider ones make a slab's rows more than the hand-over bears.
 //
 // NCHW, planes of at most 512 values, C a multiple of a 16-byte vector's elements (a slab starts and ends on 16 bytes):
@@ -955,7 +955,7 @@ SlabArgs slab_args(const Plan& p, const SlabPlan& s, char* ws)
 }
 
 template <typename KernelT>
-cgbn_status launch_slab_kernel(KernelT kernel, const Plan& p, const SlabPlan& s, const SlabArgs& A, hipStream_t st)
+cgbn_status launch_slab_kernel(KernelT kernel, const Plan& p, const SlabPlan& s, SlabArgs A, hipStream_t st)
 {
     long long groups = s.total_units;
     if (s.U > 1) {
@@ -965,6 +965,7 @@ cgbn_status launch_slab_kernel(KernelT kernel, const Plan& p, const SlabPlan& s,
         if (p.t.fused_groups > 0 && p.t.fused_groups < groups) groups = p.t.fused_groups > s.U ? p.t.fused_groups : s.U;
         // whole slabs only: the units of a straddling slab would wait a round for their siblings
         if (groups > s.U && groups < s.total_units) groups = groups / s.U * s.U;
+        A.inflight = (int)(groups / s.U < s.slabs ? groups / s.U : s.slabs);
         const long long words = 2LL * s.slabs * s.nch * s.U;
         long long want = (words + kThreads - 1) / kThreads;
         const unsigned init_groups = (unsigned)(want < 1 ? 1 : (want > 2048 ? 2048 : want));

@@ -63,6 +63,7 @@ struct SlabArgs {
     int cpc, nch, nsh, tpc;   // columns per channel, rch rounded up to a power of two 2^nsh, threads that add one channel's partial sums
     int C, slabs, U, rpu; // rpu: rows per unit
     int total_units;
+    int inflight;         // slabs whose units the grid holds at once
     long long pivot_stride;   // elements between the first values of consecutive channels
     int nt;
     unsigned spin_limit;
@@ -198,7 +199,7 @@ __device__ __forceinline__ void slab_gather(const SlabArgs& A, LDS& L, int slab,
     const int t = threadIdx.x, pairs = A.U * A.nch;
     const unsigned long long* src = reinterpret_cast<const unsigned long long*>(A.rows) + (size_t)slab * pairs;
     const unsigned long long t0 = wall_clock64();
-    constexpr int B = 4;                                  // fetches in flight per lane
+    constexpr int B = 8;                                  // fetches in flight per lane
     for (int i = t; i < pairs; i += B * kSlabThreads) {
         unsigned long long v[B];
         for (;;) {
@@ -272,6 +273,17 @@ __device__ __forceinline__ int slab_of_block(int b, int G)
 }
 
 __device__ __forceinline__ void slab_forget(u32x4& v) { asm volatile("" : "+v"(v)); }    // (see forget)
+
+// Several units: the order in which the slabs are taken.  Those in flight together are spread evenly over the row, and a
+// round moves on by one slab: neighbouring columns at a long row stride would crowd the memory channels (measured,
+// the loads and stores alone, 67200 rows of 4096 bytes: eight neighbouring slabs in flight 154 us, eight spread 114; rows
+// of 1024 bytes 115 either way).  Bijective for any number of slabs.
+__device__ __forceinline__ int slab_of_turn(const SlabArgs& A, int turn)
+{
+    const int q = A.slabs / A.inflight, rem = A.slabs - q * A.inflight;
+    const int k = turn / A.inflight, j = turn - k * A.inflight;
+    return j * q + min(j, rem) + k;
+}
 
 template <bool NT> __device__ __forceinline__ void slab_load(const char* p, u32x4& d)
 {
@@ -375,7 +387,8 @@ __global__ __launch_bounds__(kSlabThreads, P * (ACT == 2 ? 2 : 1) <= 4 ? 4 : 2) 
     if (SOLO && blockIdx.x == 0 && t == 0) A.sync[1] = 0u;
 
     for (int unit = SOLO ? slab_of_block(blockIdx.x, gridDim.x) : (int)blockIdx.x; unit < A.total_units; unit += gridDim.x) {
-        const int slab = SOLO ? unit : unit / A.U, u = SOLO ? 0 : unit - slab * A.U;
+        const int turn = SOLO ? unit : unit / A.U, u = SOLO ? 0 : unit - turn * A.U;
+        const int slab = SOLO ? unit : slab_of_turn(A, turn);
         const int c0 = slab * A.rch;
         const bool live = r < A.rpp && slab * A.cols + col < A.vecs;
         const SlabGeom g = slab_geometry(A, slab, u);
@@ -613,7 +626,8 @@ __global__ __launch_bounds__(kSlabThreads, P * (ACT != 0 ? 3 : 2) <= 8 ? 4 : 2) 
     if (SOLO && blockIdx.x == 0 && t == 0) A.sync[1] = 0u;
 
     for (int unit = SOLO ? slab_of_block(blockIdx.x, gridDim.x) : (int)blockIdx.x; unit < A.total_units; unit += gridDim.x) {
-        const int slab = SOLO ? unit : unit / A.U, u = SOLO ? 0 : unit - slab * A.U;
+        const int turn = SOLO ? unit : unit / A.U, u = SOLO ? 0 : unit - turn * A.U;
+        const int slab = SOLO ? unit : slab_of_turn(A, turn);
         const int c0 = slab * A.rch;
         const bool live = r < A.rpp && slab * A.cols + col < A.vecs;
         const SlabGeom g = slab_geometry(A, slab, u);

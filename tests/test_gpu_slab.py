@@ -197,15 +197,17 @@ def test_units_that_stop_waiting_relu(act):
     assert all(torch.equal(a, b) for a, b in zip(want, got)) and _error_word(p) == 0
 
 
-def test_several_rounds_of_units():
-    """A small persistent grid: a workgroup walks units of many slabs."""
+@pytest.mark.parametrize("groups", [4, 23, 48])
+def test_several_rounds_of_units(groups):
+    """A small persistent grid: a workgroup walks units of many slabs, whose order is spread over the row (whole rounds
+    and a ragged last one)."""
     wl, d, p = _problem((2, 512, 60, 50, 2, "NHWC", "f32"))
     p.forward()
     p.backward()
     _ran_here()
     torch.cuda.synchronize()
     want = _outputs(p)
-    with _Knobs(fused_groups=48):
+    with _Knobs(fused_groups=groups):
         p.forward()
         p.backward()
         torch.cuda.synchronize()
