@@ -353,8 +353,8 @@ bool cut_slabs(SlabPlan* s, int C, int cols, int nch, long long U, long long row
     if ((long long)s->rpp * s->row_bytes + (long long)cols * 16 > 0x7fffffffLL) return false;   // 32-bit lane offsets
     if (s->U > 1) {
         if (s->U > cus || s->U > 0xffff) return false;                              // a slab's units are resident together
-        if (forward && (long long)s->U * nch > kSlabMaxRows) return false;          // kept in LDS
-        if ((long long)s->slabs * nch * s->U > row_pairs) return false;
+        if (s->U > kSlabRowsPerLane * kWave) return false;
+        if ((long long)s->slabs * nch * (s->U + 2) > row_pairs) return false;
         if ((long long)s->slabs * ((s->U + 31) / 32) > C) return false;             // bitmap words
     }
     s->ok = 1;
@@ -363,7 +363,8 @@ bool cut_slabs(SlabPlan* s, int C, int cols, int nch, long long U, long long row
 
 // Several units per slab: U so that the launch is shortest.  A round of resident units costs the passes of a unit plus a
 // part that every hand-over costs, about that of 10 passes (6 us, against 0.6 us per pass of 512 x 16 bytes on every
-// compute unit) and one more per 1024 (channel, unit) pairs that every unit fetches; rounds are whole.  Slabs that do not
+// compute unit); rounds are whole.  (Two units of half the size per compute unit instead of one: fp32 67200 x 1024 forward /
+// backward 163 / 259 us against 142 / 224.)  Slabs that do not
 // end on line boundaries share lines with their neighbours, so they must all be in flight together: one round
 // (measured, fp32 268800 x 136 in four rounds 170 us, the sweeps 101).
 bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_pairs, int cus, bool forward)
@@ -374,8 +375,8 @@ bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_pai
     const bool lines = cols >= 48 || (s->row_bytes % 128 == 0 && cols % 8 == 0);     // (a wide slab shares little)
     const long long least = (s->R + cap - 1) / cap < 2 ? 2 : (s->R + cap - 1) / cap;
     long long most = cus < s->R ? cus : s->R;
-    if (forward && most > kSlabMaxRows / nch) most = kSlabMaxRows / nch;
-    if (most > row_pairs / (slabs * nch)) most = row_pairs / (slabs * nch);
+    if (most > kSlabRowsPerLane * kWave) most = kSlabRowsPerLane * kWave;
+    if (most > row_pairs / (slabs * nch) - 2) most = row_pairs / (slabs * nch) - 2;
     long long best = 0, best_cost = 0;
     for (int k = 0; k < 8; ++k) {
         // the fewest units and a few more; as many as fill the compute units once, or half of them, ...
@@ -385,7 +386,7 @@ bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_pai
         const long long rounds = (units + grid - 1) / grid;
         if (rounds > 1 && !lines) continue;
         const long long rows = (s->R + U - 1) / U, passes = (rows + rpp - 1) / rpp;
-        const long long cost = rounds * (passes * 1024 + 10 * 1024 + U * nch);
+        const long long cost = rounds * (passes + 10);
         if (best == 0 || cost < best_cost) { best = U; best_cost = cost; }
     }
     return best >= 2 && cut_slabs(s, C, cols, nch, best, row_pairs, cus, forward);
@@ -608,7 +609,7 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
     make_slab_plan(N, C, HW, layout, p->eb, row_pairs, cus, p->fb, false, &p->sb);
     for (const SlabPlan* s : {&p->sf, &p->sb})
         if (s->ok && s->U > 1) {
-            const size_t need = align256((size_t)s->slabs * s->nch * s->U * sizeof(float));
+            const size_t need = align256((size_t)s->slabs * s->nch * (s->U + 2) * sizeof(float));
             if (need > part) part = need;
         }
     size_t sh = align256((size_t)K * C * sizeof(double));
@@ -946,6 +947,7 @@ SlabArgs slab_args(const Plan& p, const SlabPlan& s, char* ws)
     A.cpc = s.cpc; A.nch = s.nch; A.tpc = s.tpc; A.rch = A.ncols / s.cpc;
     while ((1 << A.nsh) < s.nch) ++A.nsh;
     A.C = p.C; A.slabs = s.slabs; A.U = s.U; A.rpu = s.rpu; A.total_units = (int)s.total_units;
+    A.G = s.U < kWave ? ceil_pow2(s.U) : kWave;
     A.pivot_stride = p.layout == CGBN_NCHW ? p.HW : 1;
     A.nt = (int)p.t.nt_store && s.U > 1;
     A.spin_limit = (unsigned)p.t.spin_limit;
@@ -966,7 +968,11 @@ cgbn_status launch_slab_kernel(KernelT kernel, const Plan& p, const SlabPlan& s,
         // whole slabs only: the units of a straddling slab would wait a round for their siblings
         if (groups > s.U && groups < s.total_units) groups = groups / s.U * s.U;
         A.inflight = (int)(groups / s.U < s.slabs ? groups / s.U : s.slabs);
-        const long long words = 2LL * s.slabs * s.nch * s.U;
+        if (groups < s.total_units) {
+            const int polling = ((A.rch + s.U - 1) / s.U * A.G + kWave - 1) / kWave;      // wavefronts with channels to add up
+            A.prefetch = polling < kSlabWaves ? polling : 0;
+        }
+        const long long words = 2LL * s.slabs * s.nch * (s.U + 2);
         long long want = (words + kThreads - 1) / kThreads;
         const unsigned init_groups = (unsigned)(want < 1 ? 1 : (want > 2048 ? 2048 : want));
         hipLaunchKernelGGL(fused_init, dim3(init_groups), dim3(kThreads), 0, st, A.sync, kSyncHeader + 4 * p.C, A.rows, words);

@@ -13,8 +13,8 @@
 //
 // U > 1: a unit publishes, per channel, s = sum(x - p) and q = sum(x - a)^2 about its own centre (backward: sum dy and
 // sum dy * xhat) as one 8-byte store, and counts itself in on the slab's counter; the unit that completes the count
-// raises the slab's flag; every unit then fetches the slab's rows and reduces them itself in double precision and in
-// a fixed order (the same in every unit), as the NCHW single-launch kernels do.  Unlike those, no wait here needs its
+// learns so from it; the units share out the slab's channels, add up their rows in double precision and in a fixed order
+// and publish the results, which every unit then fetches.  Unlike in the NCHW single-launch kernels, no wait here needs its
 // siblings to be resident: a unit whose wait runs out marks itself in the slab's bitmap (unless the count completed
 // meanwhile) and its workgroup moves on; the unit that completes the count finds the marks in the value its own
 // arrival returned and, once it has the statistics, reads the marked units' values again and writes their results.
@@ -27,7 +27,7 @@ namespace cgbn {
 
 constexpr int kSlabThreads = 512;
 constexpr int kSlabWaves = kSlabThreads / kWave;
-constexpr int kSlabMaxRows = 12288;        // forward: (channel, unit) pairs of one slab kept in LDS while they are reduced
+constexpr int kSlabRowsPerLane = 4;        // rows of a channel that one lane adds up: at most 4 x 64 units per slab
 constexpr int kSlabMaxChannels = 128;      // channels of one slab
 constexpr unsigned kSlabWaitTicks = 30000; // 100 MHz ticks (300 us) a unit waits for its siblings before it moves on ...
 constexpr unsigned kSlabWaitTicksLater = 3000;   // ... once some unit of the launch has done so
@@ -49,7 +49,7 @@ struct SlabArgs {
     float* invstd;
     float* dgamma;
     float* dbeta;
-    unsigned* rows;       // [slab][unit][channel] pairs of floats
+    unsigned* rows;       // per slab: [unit][channel] pairs of floats, then [channel][2] pairs of results
     unsigned* sync;
     long long R;          // rows of the matrix
     long long row_bytes;
@@ -63,23 +63,23 @@ struct SlabArgs {
     int cpc, nch, nsh, tpc;   // columns per channel, rch rounded up to a power of two 2^nsh, threads that add one channel's partial sums
     int C, slabs, U, rpu; // rpu: rows per unit
     int total_units;
+    int G;                // lanes that add up one channel's rows
     int inflight;         // slabs whose units the grid holds at once
     long long pivot_stride;   // elements between the first values of consecutive channels
     int nt;
     unsigned spin_limit;
+    int prefetch;         // several rounds: the wavefronts from this one on fetch the next unit's first passes into LDS during the hand-over
     unsigned bitmap_words;    // per slab
     unsigned cpc_magic;       // 2^32 / cpc, rounded up: i / cpc is the high word of i * cpc_magic for the small i here
 };
 
-// LDS of a workgroup; SOLO needs no staging for other units' rows
-template <bool SOLO, bool STAGE> struct SlabLds {
+// LDS of a workgroup
+struct SlabLds {
     float part[2][kSlabThreads * 8];                     // [row lane or wavefront][column]
-    float rows[2][STAGE ? kSlabMaxRows : 1];             // forward: the thread's own pairs between the two passes over them
-    double dsum[SOLO ? 1 : 2][SOLO ? 1 : kSlabThreads];
-    double mean[SOLO ? 1 : kSlabMaxChannels];
     float piv[kSlabMaxChannels], ctr[kSlabMaxChannels];  // forward: pivot and the unit's centre
+    float res[3][kSlabMaxChannels];                      // several units: the channels' results (forward mean, its rest, 1/sqrt; backward dbeta, dgamma)
     float k0[kSlabMaxChannels], k1[kSlabMaxChannels], k2[kSlabMaxChannels], k3[kSlabMaxChannels];   // write-out constants
-    int skip, last, fix, redo;        // this unit moves on (2: rows are missing for good); it completed the count; there are units for it to finish
+    int skip, last, fix, wait, redo;  // this unit moves on (2: results are missing for good); it completed the count; there are units for it to finish; the count is complete, the results are not there yet
 };
 
 // Sums a thread's column values over the slab: the row lanes of a wavefront by shuffles (power-of-two column counts),
@@ -87,7 +87,7 @@ template <bool SOLO, bool STAGE> struct SlabLds {
 template <int VEC, int Q, class LDS>
 __device__ __forceinline__ void slab_sum(const SlabArgs& A, LDS& L, float (&v)[Q][VEC], int col, int r, double (&out)[Q])
 {
-    const int t = threadIdx.x, lane = t & (kWave - 1), w = t >> 6;
+    const int t = (int)fresh(threadIdx.x), lane = t & (kWave - 1), w = t >> 6;
     if (A.pow2) {
         for (int off = A.cols; off < kWave; off <<= 1)
 #pragma unroll
@@ -132,39 +132,139 @@ __device__ __forceinline__ unsigned slab_bits(float v)      // NaN in canonical 
     return v != v ? 0x7fc00000u : __float_as_uint(v);
 }
 
-// After a unit's rows are on their way: counts it in and waits for the slab.  Returns false if the unit moves on
-// (its bitmap bit is set).  L.fix: units that moved on before this one completed the count.
-template <class LDS>
-__device__ __forceinline__ bool slab_hand_over(const SlabArgs& A, LDS& L, int slab, int u)
+// A slab's memory: [unit][channel] rows, then the channels' results (two pairs each), all 8-byte pairs that hold the
+// sentinel until they are written.
+__device__ __forceinline__ unsigned long long* slab_rows(const SlabArgs& A, int slab)
 {
+    return reinterpret_cast<unsigned long long*>(A.rows) + (size_t)slab * (A.U + 2) * A.nch;
+}
+__device__ __forceinline__ void slab_put(unsigned long long* p, float lo, float hi)
+{
+    __hip_atomic_store(p, ((unsigned long long)slab_bits(hi) << 32) | slab_bits(lo), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool slab_missing(unsigned long long v)
+{
+    return (unsigned)v == kRowSentinel || (unsigned)(v >> 32) == kRowSentinel;
+}
+
+// Polls with `fetch` (false: something is missing) until a wavefront has everything, `polls` or the time runs out.
+template <class F> __device__ __forceinline__ bool slab_poll(const SlabArgs& A, bool patient, F fetch)
+{
+    const unsigned long long t0 = wall_clock64();
+    unsigned long long limit = patient ? kSlabBackstopTicks : kSlabWaitTicks;
+    for (unsigned polls = 0; patient || polls < A.spin_limit; ++polls) {
+        if (__ballot(!fetch()) == 0ull) return true;
+        if ((polls & 31u) == 31u) {
+            if (!patient && ld_agent(A.sync + kSlabMovedOn) != 0u) limit = kSlabWaitTicksLater;
+            if (wall_clock64() - t0 > limit) return false;
+        }
+        __builtin_amdgcn_s_sleep(1);
+    }
+    return false;
+}
+
+// One channel's rows added up by the `G` lanes of a group (lane `gl`), double precision, fixed order; the group's first
+// lane writes the results.  False: rows are missing.  (Lanes without a channel take part in the polls.)
+template <bool FWD> __device__ __forceinline__ bool slab_reduce(const SlabArgs& A, SlabLds& L, int slab, int c, bool patient)
+{
+    const int gl = (int)fresh(threadIdx.x) & (A.G - 1);
+    const bool duty = c < A.rch;
+    unsigned long long* row = slab_rows(A, slab) + (duty ? c : 0);
+    unsigned long long v[kSlabRowsPerLane];
+    if (!slab_poll(A, patient, [&] {
+            bool there = true;
+#pragma unroll
+            for (int j = 0; j < kSlabRowsPerLane; ++j) {
+                v[j] = 0ull;
+                if (duty && gl + j * A.G < A.U) v[j] = __hip_atomic_load(row + (size_t)(gl + j * A.G) * A.nch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+#pragma unroll
+            for (int j = 0; j < kSlabRowsPerLane; ++j) there &= !slab_missing(v[j]);
+            return there;
+        }))
+        return false;
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+    for (int j = 0; j < kSlabRowsPerLane; ++j) {
+        s0 += (double)__uint_as_float((unsigned)v[j]);
+        if (!FWD) s1 += (double)__uint_as_float((unsigned)(v[j] >> 32));
+    }
+    for (int off = A.G >> 1; off >= 1; off >>= 1) {
+        s0 += __shfl_xor(s0, off);
+        if (!FWD) s1 += __shfl_xor(s1, off);
+    }
+    unsigned long long* result = slab_rows(A, slab) + (size_t)A.U * A.nch + 2 * (duty ? c : 0);
+    if (FWD) {
+        const float p = L.piv[duty ? c : 0];
+        const double mean = (double)p + s0 * A.inv_M_f64;
+#pragma unroll
+        for (int j = 0; j < kSlabRowsPerLane; ++j) {
+            const int k = gl + j * A.G;
+            if (k < A.U) {
+                const double n = (double)(k + 1 < A.U ? A.rpu : (int)(A.R - (long long)k * A.rpu)) * (double)A.cpc;
+                s1 += row_sqdev(__uint_as_float((unsigned)v[j]), __uint_as_float((unsigned)(v[j] >> 32)), n, p, mean);
+            }
+        }
+        for (int off = A.G >> 1; off >= 1; off >>= 1) s1 += __shfl_xor(s1, off);
+        if (duty && gl == 0) {
+            const float hi = (float)mean;
+            slab_put(result, hi, (float)(mean - (double)hi));
+            slab_put(result + 1, (float)rsqrt_f64(s1 * A.inv_M_f64 + A.eps), 0.f);
+        }
+    } else if (duty && gl == 0) {
+        slab_put(result, (float)s0, (float)s1);
+    }
+    return true;
+}
+
+// The slab's results into L.res (one wavefront).  False: some are missing.
+template <bool FWD> __device__ __forceinline__ bool slab_results(const SlabArgs& A, SlabLds& L, int slab, bool patient)
+{
+    const unsigned long long* result = slab_rows(A, slab) + (size_t)A.U * A.nch;
+    return slab_poll(A, patient, [&] {
+        bool there = true;
+        for (int c = (int)fresh(threadIdx.x) & (kWave - 1); c < A.rch; c += kWave) {
+            const unsigned long long v = __hip_atomic_load(result + 2 * c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned long long w = FWD ? __hip_atomic_load(result + 2 * c + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+            there &= !slab_missing(v) && !slab_missing(w);
+            L.res[0][c] = __uint_as_float((unsigned)v);
+            L.res[1][c] = __uint_as_float((unsigned)(v >> 32));
+            if (FWD) L.res[2][c] = __uint_as_float((unsigned)w);
+        }
+        return there;
+    });
+}
+
+// After a unit's rows are on their way: counts it in, adds up the channels that are this unit's to add up (u, u + U, ...)
+// and waits for the others'.  Every row crosses the chip once and every unit fetches one result per channel; were each unit
+// to add up all rows itself, that would be U times as much (7680 pairs of a slab of 268800 x 64 bf16: 4 us a unit).
+// Returns false if the unit moves on (its bitmap bit is set).  L.fix: units that moved on before this one completed the
+// count; the channels they owe are added up here too.
+// `meanwhile()`: run by the wavefronts that fetch ahead once the rows are out.
+template <bool FWD, class F> __device__ __forceinline__ bool slab_hand_over(const SlabArgs& A, SlabLds& L, int slab, int u, F meanwhile)
+{
+    const int t = (int)fresh(threadIdx.x);          // (what is formed from it stays here: see fresh)
     unsigned* cnt = A.sync + kSyncHeader + slab;
     unsigned* bitmap = A.sync + kSyncHeader + A.C + (size_t)slab * A.bitmap_words;
     __syncthreads();                  // every wavefront has issued its row stores
-    if (threadIdx.x < kWave) {
-        const int lane = threadIdx.x;
-        unsigned old = 0;
-        if (lane == 0) old = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const unsigned long long t0 = wall_clock64();
-        unsigned long long limit = kSlabWaitTicks;
-        bool up = false;
-        const unsigned* rep = A.rows + (size_t)slab * A.U * A.nch * 2;
-        for (unsigned polls = 0; polls < A.spin_limit; ++polls) {
-            bool miss = false;
-            for (int k = lane; k < A.U; k += kWave) miss |= ld_agent(rep + (size_t)k * A.nch * 2) == kRowSentinel;
-            if (__ballot(miss) == 0ull) { up = true; break; }
-            if ((polls & 31u) == 31u) {
-                if (ld_agent(A.sync + kSlabMovedOn) != 0u) limit = kSlabWaitTicksLater;
-                if (wall_clock64() - t0 > limit) break;
-            }
-            __builtin_amdgcn_s_sleep(2);
-        }
-        if (lane == 0) {
-            L.skip = L.last = L.fix = 0;
+    unsigned old;                     // (of the first thread; given a value for the others it would be waited for here)
+    if (t == 0) old = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_readfirstlane(t) >= A.prefetch * kWave) meanwhile();
+    const int mine = u + t / A.G * A.U;
+    // (whole wavefronts: the first group of each has the lowest channel)
+    const bool any = __builtin_amdgcn_readfirstlane(mine) < A.rch;
+    const bool done = !any || slab_reduce<FWD>(A, L, slab, mine, false);
+    if (t < kWave) {
+        const bool up = slab_results<FWD>(A, L, slab, false);
+        if (t == 0) {
+            L.skip = L.last = L.fix = L.wait = 0;
             if ((old & 0xffffu) == (unsigned)(A.U - 1)) {
                 L.last = 1;
+                L.wait = !up;
                 const int moved = (int)(old >> 16);
                 if (moved > 0) {
                     // (their workgroups are about to set their bits: they have seen the count)
+                    const unsigned long long t0 = wall_clock64();
                     for (;;) {
                         int have = 0;
                         for (unsigned i = 0; i < A.bitmap_words; ++i) have += __popc(ld_agent(bitmap + i));
@@ -181,64 +281,30 @@ __device__ __forceinline__ bool slab_hand_over(const SlabArgs& A, LDS& L, int sl
                     L.skip = 1;
                     atomicOr(bitmap + (u >> 5), 1u << (u & 31));
                     __hip_atomic_store(A.sync + kSlabMovedOn, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                } else {
+                    L.wait = 1;
                 }
             }
         }
     }
     __syncthreads();
-    return L.skip == 0;
-}
-
-// Adds up the slab's rows, double precision, fixed order.  Thread t fetches the pairs t, t + 512, ...: all of channel
-// t % nch (nch divides 512), units t / nch, t / nch + 512 / nch, ...; `f(k, unit, first, second)` takes each in (k: the thread's k-th
-// pair).  Rows still in flight are fetched again: all of them have been issued.  The bound is a backstop; when it is
-// hit, L.skip = 2 makes the caller poison the statistics.
-template <class LDS, class F>
-__device__ __forceinline__ void slab_gather(const SlabArgs& A, LDS& L, int slab, F f)
-{
-    const int t = threadIdx.x, pairs = A.U * A.nch;
-    const unsigned long long* src = reinterpret_cast<const unsigned long long*>(A.rows) + (size_t)slab * pairs;
-    const unsigned long long t0 = wall_clock64();
-    constexpr int B = 8;                                  // fetches in flight per lane
-    for (int i = t; i < pairs; i += B * kSlabThreads) {
-        unsigned long long v[B];
-        for (;;) {
-            bool missing = false;
-#pragma unroll
-            for (int b = 0; b < B; ++b) {
-                const int j = i + b * kSlabThreads;
-                v[b] = __hip_atomic_load(src + (j < pairs ? j : i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-#pragma unroll
-            for (int b = 0; b < B; ++b) missing |= ((unsigned)v[b] == kRowSentinel) | ((unsigned)(v[b] >> 32) == kRowSentinel);
-            if (!missing) break;
-            if (wall_clock64() - t0 > kSlabBackstopTicks) {
-                atomicExch(A.sync + 1, 1u);
-                L.skip = 2;
-                break;
-            }
+    if (L.fix | L.wait) {
+        // Every unit has counted itself in, so every row has been issued.  The backstop, if it is ever hit, makes the
+        // caller poison the statistics.
+        bool sound = true;
+        if (L.fix) {
+            for (int c = t / A.G; __builtin_amdgcn_readfirstlane(c) < A.rch; c += kSlabThreads / A.G) sound &= slab_reduce<FWD>(A, L, slab, c, true);
+        } else if (!done) {
+            sound = slab_reduce<FWD>(A, L, slab, mine, true);
         }
-#pragma unroll
-        for (int b = 0; b < B; ++b) {
-            const int j = i + b * kSlabThreads;
-            if (j < pairs) f(j / kSlabThreads, j >> A.nsh, __uint_as_float((unsigned)v[b]), __uint_as_float((unsigned)(v[b] >> 32)));
+        if (t < kWave) sound &= slab_results<FWD>(A, L, slab, true);
+        if (!sound) {
+            atomicExch(A.sync + 1, 1u);
+            L.skip = 2;
         }
+        __syncthreads();
     }
-}
-
-// The threads' values of a channel added in a fixed order (lane by lane through LDS, then a tree); all of the channel's
-// `tpc` threads (channel t / tpc) get the sum.
-template <class LDS> __device__ __forceinline__ double slab_channel_total(const SlabArgs& A, LDS& L, double v, int slot)
-{
-    const int t = threadIdx.x;
-    L.dsum[slot][t] = v;
-    __syncthreads();
-    const int ch = t / A.tpc, sub = t & (A.tpc - 1);
-    double acc = 0.0;
-    if (ch < A.nch)
-        for (int i = sub; i < kSlabThreads / A.nch; i += A.tpc) acc += L.dsum[slot][i * A.nch + ch];
-    for (int off = 1; off < A.tpc; off <<= 1) acc += __shfl_xor(acc, off);
-    return acc;
+    return L.skip != 1;
 }
 
 // the next unit after `u` that moved on, -1 if there is none (the completing unit is never marked)
@@ -362,6 +428,39 @@ __device__ __forceinline__ SlabPass slab_pass(const SlabArgs& A, int n, bool liv
     return p;
 }
 
+// Prefetch (several rounds of units).  While the statistics complete, no load or store of the launch is in flight; the
+// register file has no room for the next unit, the LDS has room for 2/5 of it.  Every wavefront but those that poll (their
+// polls would queue behind their loads; always the first) fetches its part of the next unit's first passes straight into LDS.
+// Measured, without -> with, us: fp32 67200 x 1024 forward 141 -> 129, backward 224 -> 204, fp32 268800 x 512 304 -> 276 and
+// 454 -> 440, bf16 268800 x 512 151 -> 146 and 247 -> 239.
+constexpr int kSlabAhead = kSlabWaves - 1;         // wavefronts that fetch ahead
+struct SlabAhead {
+    SlabPass ps;
+    const char* base[2];
+    __device__ __forceinline__ SlabAhead(const SlabArgs& A, int unit, const char* b0, const char* b1)
+    {
+        const int t = (int)fresh(threadIdx.x), col = t % A.cols, r = t / A.cols;
+        const int turn = unit / A.U, slab = slab_of_turn(A, turn);
+        const SlabGeom g = slab_geometry(A, slab, unit - turn * A.U);
+        ps = slab_pass(A, g.n, r < A.rpp && slab * A.cols + col < A.vecs, r, col);
+        base[0] = b0 + g.base;
+        base[1] = b1 + g.base;
+    }
+    template <int PRE, int TENSORS> __device__ __forceinline__ void fetch(u32x4* ext)
+    {
+        const int w = __builtin_amdgcn_readfirstlane((int)(fresh(threadIdx.x) >> 6)) - 1;
+#pragma unroll
+        for (int i = 0; i < PRE; ++i)
+#pragma unroll
+            for (int q = 0; q < TENSORS; ++q) {
+                __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(base[q] + ps.lane(i)),
+                                                 (void __attribute__((address_space(3)))*)(ext + ((q * PRE + i) * kSlabAhead + w) * kWave), 16, 0, 0);
+                base[q] += ps.advance(i);
+            }
+    }
+};
+__device__ __forceinline__ const u32x4& slab_fetched(const u32x4* ext, int slot, int t) { return ext[slot * kSlabAhead * kWave + t - kWave]; }
+
 // ---------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------
@@ -373,20 +472,23 @@ __device__ __forceinline__ SlabPass slab_pass(const SlabArgs& A, int n, bool liv
 // precision.  That loses (a - p)^2 / variance times the accuracy of D, so a unit in which some channel's pivot lies more
 // than 8 standard deviations from its mean makes a second pass over its registers, about a, for q.
 template <typename T, int ACT, int P, bool SOLO>
-__global__ __launch_bounds__(kSlabThreads, P * (ACT == 2 ? 2 : 1) <= 4 ? 4 : 2) void slab_forward(SlabArgs A)
+__global__ __launch_bounds__(kSlabThreads, P * (ACT == 2 ? 2 : 1) <= (SOLO ? 4 : 18) ? 4 : 2) void slab_forward(SlabArgs A)
 {
     constexpr int VEC = 16 / (int)sizeof(T);
     constexpr bool EARLY = ACT == 2 && P <= 20;
-    __shared__ SlabLds<SOLO, !SOLO> L;
-    const int t = threadIdx.x;
-    const int col = t % A.cols, r = t / A.cols;
-    const int ch = t / A.tpc, sub = t & (A.tpc - 1);      // the channel this thread helps to add up
+    constexpr int PRE = !SOLO && P >= 28 ? 16 : 0;
+    __shared__ SlabLds L;
+    __shared__ u32x4 ext[PRE ? PRE * kSlabAhead * kWave : 1];
+    int fetched = 0;                  // (uniform over a wavefront)
     const char* xb = static_cast<const char*>(A.x);
     const char* rb = static_cast<const char*>(A.dy);
     char* yb = static_cast<char*>(A.out);
-    if (SOLO && blockIdx.x == 0 && t == 0) A.sync[1] = 0u;
-
+    if (SOLO && blockIdx.x == 0 && threadIdx.x == 0) A.sync[1] = 0u;
     for (int unit = SOLO ? slab_of_block(blockIdx.x, gridDim.x) : (int)blockIdx.x; unit < A.total_units; unit += gridDim.x) {
+        // (formed anew for every unit: carried round the loop, what depends on them would cost registers)
+        const int t = (int)fresh(threadIdx.x);
+        const int col = t % A.cols, r = t / A.cols;
+        const int ch = t / A.tpc, sub = t & (A.tpc - 1);  // the channel this thread helps to add up
         const int turn = SOLO ? unit : unit / A.U, u = SOLO ? 0 : unit - turn * A.U;
         const int slab = SOLO ? unit : slab_of_turn(A, turn);
         const int c0 = slab * A.rch;
@@ -415,8 +517,21 @@ __global__ __launch_bounds__(kSlabThreads, P * (ACT == 2 ? 2 : 1) <= 4 ? 4 : 2) 
         {
             const char* xu = xb + g.base;
             const char* ru = rb + g.base;
-            unroll_planes<P>([&](auto i_) __attribute__((always_inline)) {
-                constexpr int i = decltype(i_)::value;
+            if (PRE != 0 && __builtin_amdgcn_readfirstlane(fetched) != 0) {
+                unroll_planes<PRE>([&](auto i_) __attribute__((always_inline)) {
+                    constexpr int i = decltype(i_)::value;
+                    d[i] = slab_fetched(ext, i, t);
+                    xu += ps.advance(i);
+                });
+            } else {
+                unroll_planes<PRE>([&](auto i_) __attribute__((always_inline)) {
+                    constexpr int i = decltype(i_)::value;
+                    slab_load<!SOLO>(xu + ps.lane(i), d[i]);
+                    xu += ps.advance(i);
+                });
+            }
+            unroll_planes<P - PRE>([&](auto i_) __attribute__((always_inline)) {
+                constexpr int i = PRE + decltype(i_)::value;
                 slab_load<!SOLO>(xu + ps.lane(i), d[i]);
                 xu += ps.advance(i);
             });
@@ -484,46 +599,36 @@ __global__ __launch_bounds__(kSlabThreads, P * (ACT == 2 ? 2 : 1) <= 4 ? 4 : 2) 
             q = sq[0];
         }
         // ---- steps 4-5 and 9-10
-        double mean, dev;
+        double mean = 0.0, dev = 0.0;
         bool ok = true, mine = true;
         if (SOLO) {
             mean = (double)pv + tot[0] * A.inv_M_f64;
             const double dd = (double)ctr - mean;
             dev = q + dd * (2.0 * (tot[0] - n_row * ((double)ctr - (double)pv)) + n_row * dd);
         } else {
-            if (ch < A.nch && sub == 0)
-                __hip_atomic_store(reinterpret_cast<unsigned long long*>(A.rows) + ((size_t)slab * A.U + u) * A.nch + ch,
-                                   ((unsigned long long)slab_bits((float)q) << 32) | slab_bits(sf),
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            mine = slab_hand_over(A, L, slab, u);
-            if (mine) {
-                double acc = 0.0;
-                slab_gather(A, L, slab, [&](int k, int, float sk, float qk) {
-                    acc += (double)sk;
-                    L.rows[0][k * kSlabThreads + t] = sk;
-                    L.rows[1][k * kSlabThreads + t] = qk;
-                });
-                acc = slab_channel_total(A, L, acc, 0);
-                mean = (double)pv + acc * A.inv_M_f64;
-                if (ch < A.nch && sub == 0) L.mean[ch] = mean;
-                __syncthreads();
-                ok = L.skip != 2;
-                const int gc = t & (A.nch - 1);           // the channel of the pairs this thread fetched
-                const float p = L.piv[gc];
-                const double m = L.mean[gc];
-                acc = 0.0;
-                for (int j = t; j < A.U * A.nch; j += kSlabThreads) {
-                    const int k = j >> A.nsh;
-                    const double n = (double)(k + 1 < A.U ? A.rpu : (int)(A.R - (long long)k * A.rpu)) * (double)A.cpc;
-                    acc += row_sqdev(L.rows[0][j], L.rows[1][j], n, p, m);
-                }
-                dev = slab_channel_total(A, L, acc, 1);
-            }
+            if (ch < A.nch && sub == 0) slab_put(slab_rows(A, slab) + (size_t)u * A.nch + ch, sf, (float)q);
+            fetched = 0;
+            mine = slab_hand_over<true>(A, L, slab, u, [&] {
+                if constexpr (PRE != 0)
+                    if (A.prefetch != 0 && unit + (int)gridDim.x < A.total_units) {
+                        SlabAhead(A, unit + (int)gridDim.x, xb, xb).template fetch<PRE, 1>(ext);
+                        fetched = 1;
+                    }
+            });
+            ok = L.skip != 2;
         }
         if (mine) {
             if (ch < A.nch && sub == 0) {
-                float hi = (float)mean, lo = (float)(mean - (double)hi);
-                float is = (float)rsqrt_f64(dev * A.inv_M_f64 + A.eps);
+                float hi, lo, is;
+                if (SOLO) {
+                    hi = (float)mean;
+                    lo = (float)(mean - (double)hi);
+                    is = (float)rsqrt_f64(dev * A.inv_M_f64 + A.eps);
+                } else {
+                    hi = L.res[0][ch];
+                    lo = L.res[1][ch];
+                    is = L.res[2][ch];
+                }
                 if (!ok) hi = is = __uint_as_float(0x7fc00000u);
                 const float gs = gm * is;
                 L.k0[ch] = hi;
@@ -599,7 +704,10 @@ __global__ __launch_bounds__(kSlabThreads, P * (ACT == 2 ? 2 : 1) <= 4 ? 4 : 2) 
                 }
             }
         }
-        if (!SOLO) __syncthreads();       // the hand-over's verdicts have been read by everyone
+        if (!SOLO) {
+            if (PRE != 0 && !mine) wait_vector_memory();      // what was fetched ahead has landed (else before the write-out)
+            __syncthreads();              // the hand-over's verdicts have been read by everyone
+        }
     }
 }
 
@@ -610,22 +718,25 @@ __global__ __launch_bounds__(kSlabThreads, P * (ACT == 2 ? 2 : 1) <= 4 ? 4 : 2) 
 // output's vectors are loaded beside the other two where the registers allow (P <= 10), else through the storage x takes
 // afterwards.
 template <typename T, int ACT, int P, bool SOLO>
-__global__ __launch_bounds__(kSlabThreads, P * (ACT != 0 ? 3 : 2) <= 8 ? 4 : 2) void slab_backward(SlabArgs A)
+__global__ __launch_bounds__(kSlabThreads, SOLO ? (P * (ACT != 0 ? 3 : 2) <= 8 ? 4 : 2) : (P <= 9 ? 4 : 2)) void slab_backward(SlabArgs A)
 {
     constexpr int VEC = 16 / (int)sizeof(T);
-    constexpr bool THREE = ACT != 0 && P <= 10;
-    __shared__ SlabLds<SOLO, false> L;
-    const int t = threadIdx.x;
-    const int col = t % A.cols, r = t / A.cols;
-    const int ch = t / A.tpc, sub = t & (A.tpc - 1);
+    constexpr bool THREE = ACT != 0 && P <= (SOLO ? 10 : 6);
+    constexpr int PRE = !SOLO && P >= 14 ? 8 : 0;
+    __shared__ SlabLds L;
+    __shared__ u32x4 ext[PRE ? 2 * PRE * kSlabAhead * kWave : 1];
+    int fetched = 0;                  // (uniform over a wavefront)
     const char* xb = static_cast<const char*>(A.x);
     const char* gb = static_cast<const char*>(A.dy);
     const char* ab = static_cast<const char*>(A.aux);
     char* ob = static_cast<char*>(A.out);
     char* zb = static_cast<char*>(A.out2);
-    if (SOLO && blockIdx.x == 0 && t == 0) A.sync[1] = 0u;
-
+    if (SOLO && blockIdx.x == 0 && threadIdx.x == 0) A.sync[1] = 0u;
     for (int unit = SOLO ? slab_of_block(blockIdx.x, gridDim.x) : (int)blockIdx.x; unit < A.total_units; unit += gridDim.x) {
+        // (formed anew for every unit: carried round the loop, what depends on them would cost registers)
+        const int t = (int)fresh(threadIdx.x);
+        const int col = t % A.cols, r = t / A.cols;
+        const int ch = t / A.tpc, sub = t & (A.tpc - 1);  // the channel this thread helps to add up
         const int turn = SOLO ? unit : unit / A.U, u = SOLO ? 0 : unit - turn * A.U;
         const int slab = SOLO ? unit : slab_of_turn(A, turn);
         const int c0 = slab * A.rch;
@@ -651,19 +762,37 @@ __global__ __launch_bounds__(kSlabThreads, P * (ACT != 0 ? 3 : 2) <= 8 ? 4 : 2) 
             const char* gu = gb + g.base;
             const char* xu = xb + g.base;
             const char* yu = ab + g.base;
-            unroll_planes<P>([&](auto i_) __attribute__((always_inline)) {
+            auto load = [&](auto i_, u32x4& dg, u32x4& dx) __attribute__((always_inline)) {
                 constexpr int i = decltype(i_)::value;
-                slab_load<!SOLO>(gu + ps.lane(i), gd[i]);
+                slab_load<!SOLO>(gu + ps.lane(i), dg);
                 gu += ps.advance(i);
                 if constexpr (ACT == 0 || THREE) {
-                    slab_load<!SOLO>(xu + ps.lane(i), xd[i]);
+                    slab_load<!SOLO>(xu + ps.lane(i), dx);
                     xu += ps.advance(i);
                 }
                 if constexpr (ACT != 0) {
                     if constexpr (THREE) slab_load<!SOLO>(yu + ps.lane(i), yd[i]);
-                    else slab_load<!SOLO>(yu + ps.lane(i), xd[i]);
+                    else slab_load<!SOLO>(yu + ps.lane(i), dx);
                     yu += ps.advance(i);
                 }
+            };
+            if (PRE != 0 && __builtin_amdgcn_readfirstlane(fetched) != 0) {
+                unroll_planes<PRE>([&](auto i_) __attribute__((always_inline)) {
+                    constexpr int i = decltype(i_)::value;
+                    gd[i] = slab_fetched(ext, i, t);
+                    xd[i] = slab_fetched(ext, PRE + i, t);
+                    gu += ps.advance(i);
+                    if constexpr (ACT == 0) xu += ps.advance(i);
+                    else yu += ps.advance(i);
+                });
+            } else {
+                unroll_planes<PRE>([&](auto i_) __attribute__((always_inline)) {
+                    load(i_, gd[decltype(i_)::value], xd[decltype(i_)::value]);
+                });
+            }
+            unroll_planes<P - PRE>([&](auto i_) __attribute__((always_inline)) {
+                constexpr int i = PRE + decltype(i_)::value;
+                load(std::integral_constant<int, i>{}, gd[i], xd[i]);
             });
             if constexpr (ACT != 0 && !THREE) {           // mask; x over the stored output's storage
                 SlabPass again = ps;                      // (lane offsets formed anew: kept, they would cost a register each)
@@ -697,7 +826,7 @@ __global__ __launch_bounds__(kSlabThreads, P * (ACT != 0 ? 3 : 2) <= 8 ? 4 : 2) 
         });
         double tot[2];
         slab_sum<VEC, 2>(A, L, a, col, r, tot);
-        double db, dg;
+        double db = 0.0, dg = 0.0;
         bool ok = true, mine = true;
         if (SOLO) {
             db = tot[0];
@@ -705,25 +834,21 @@ __global__ __launch_bounds__(kSlabThreads, P * (ACT != 0 ? 3 : 2) <= 8 ? 4 : 2) 
         } else {
             if (ch < A.nch && sub == 0) {
                 const float ta = (float)tot[0], tb = (float)((tot[1] - (double)lv * tot[0]) * (double)is);
-                __hip_atomic_store(reinterpret_cast<unsigned long long*>(A.rows) + ((size_t)slab * A.U + u) * A.nch + ch,
-                                   ((unsigned long long)slab_bits(tb) << 32) | slab_bits(ta), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
+                slab_put(slab_rows(A, slab) + (size_t)u * A.nch + ch, ta, tb);
             }
-            mine = slab_hand_over(A, L, slab, u);
-            if (mine) {
-                double s0 = 0.0, s1 = 0.0;
-                slab_gather(A, L, slab, [&](int, int, float ak, float bk) {
-                    s0 += (double)ak;
-                    s1 += (double)bk;
-                });
-                db = slab_channel_total(A, L, s0, 0);
-                dg = slab_channel_total(A, L, s1, 1);
-                ok = L.skip != 2;
-            }
+            fetched = 0;
+            mine = slab_hand_over<false>(A, L, slab, u, [&] {
+                if constexpr (PRE != 0)
+                    if (A.prefetch != 0 && unit + (int)gridDim.x < A.total_units) {
+                        SlabAhead(A, unit + (int)gridDim.x, gb, ACT == 0 ? xb : ab).template fetch<PRE, 2>(ext);
+                        fetched = 1;
+                    }
+            });
+            ok = L.skip != 2;
         }
         if (mine) {
             if (ch < A.nch && sub == 0) {
-                float dbf = (float)db, dgf = (float)dg;
+                float dbf = SOLO ? (float)db : L.res[0][ch], dgf = SOLO ? (float)dg : L.res[1][ch];
                 if (!ok) dbf = dgf = __uint_as_float(0x7fc00000u);
                 // dx = gsc * dy + k0 - k2 * (x - mu), see nchw_fused_backward.  SOLO, where a channel may have a handful of
                 // values: gsc * (dy - c1) + (k0 - k2 * (x - mu)), so that what cancels is dy and its mean, as stored
@@ -788,12 +913,15 @@ __global__ __launch_bounds__(kSlabThreads, P * (ACT != 0 ? 3 : 2) <= 8 ? 4 : 2) 
                 }
             }
         }
-        if (!SOLO) __syncthreads();
+        if (!SOLO) {
+            if (PRE != 0 && !mine) wait_vector_memory();
+            __syncthreads();
+        }
     }
 }
 
 // X(vectors per thread (and tensor), one unit per slab)
-#define CGBN_SLAB_FORWARD_P(X) X(4, true) X(8, true) X(12, true) X(20, true) X(6, false) X(12, false) X(20, false) X(28, false) X(36, false)
-#define CGBN_SLAB_BACKWARD_P(X) X(4, true) X(8, true) X(12, true) X(20, true) X(6, false) X(10, false) X(14, false) X(18, false)
+#define CGBN_SLAB_FORWARD_P(X) X(4, true) X(8, true) X(12, true) X(20, true) X(6, false) X(12, false) X(18, false) X(28, false) X(36, false)
+#define CGBN_SLAB_BACKWARD_P(X) X(4, true) X(8, true) X(12, true) X(20, true) X(6, false) X(9, false) X(14, false) X(18, false)
 
 }  // namespace cgbn

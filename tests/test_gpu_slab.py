@@ -215,6 +215,40 @@ def test_several_rounds_of_units(groups):
     G.check_against_oracle(p.results(), _reference(wl, d), wl.dtype, "rounds")
 
 
+@pytest.mark.parametrize("shape", [(5, 128, 127, 126, 5, "NHWC", "f32"), (3, 192, 171, 200, 1, "NHWC", "bf16")], ids=["f32", "bf16"])
+@pytest.mark.parametrize("slabs", [1, 2, 3])
+def test_units_fetched_ahead(shape, slabs):
+    """Long units in several rounds (one, two, three slabs in flight): a unit's first passes come out of LDS, where they were
+    fetched while the one before waited.  The same bits as with the largest grid, also where every unit moves on."""
+    wl, d, p = _problem(shape)
+    n, c, h, w, k, layout, dtype = shape
+    get = lambda key: L.cgbn_plan_get(n, c, h, w, layout, dtype, k, key)
+    assert get("sfwd_P") >= 28 and get("sbwd_P") >= 14
+    dz = torch.empty_like(p.x)
+
+    def step():
+        for t in (p.y, p.dx, dz):
+            t.zero_()
+        p.forward()
+        p.backward()
+        _ran_here()
+        out = _outputs(p)
+        L.cgbn_backward_relu(p.dy, p.y, p.x, p.mean, p.invstd, p.gamma, p.dx, dz, p.dgamma, p.dbeta, *p.shape_args, wl.layout,
+                             wl.K, wl.dtype, p.mean_lo, p.ws)
+        torch.cuda.synchronize()
+        assert _error_word(p) == 0
+        return out + [p.dx.clone(), dz.clone(), p.dgamma.clone(), p.dbeta.clone()]
+
+    want = step()
+    if slabs == 1:
+        p.forward()
+        p.backward()
+        G.check_against_oracle(p.results(), _reference(wl, d), dtype, "long units")
+    for spin in (None, 0):
+        with _Knobs(fused_groups=slabs * max(get("sfwd_U"), get("sbwd_U")), **({} if spin is None else {"spin_limit": spin})):
+            assert all(torch.equal(a, b) for a, b in zip(want, step()))
+
+
 @pytest.mark.parametrize("shape", [(2, 16, 30, 40, 2, "NHWC", "f32"), (4, 64, 40, 50, 4, "NHWC", "f32"),
                                    (4, 64, 40, 50, 4, "NHWC", "bf16")], ids=["one-unit", "several-f32", "several-bf16"])
 @pytest.mark.parametrize("sigmas", [6.0, 12.0, 5000.0])
