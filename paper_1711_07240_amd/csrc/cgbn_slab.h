@@ -68,6 +68,7 @@ struct SlabArgs {
     long long pivot_stride;   // elements between the first values of consecutive channels
     int nt;
     unsigned spin_limit;
+    unsigned stagger;     // start-up stagger: 100 MHz ticks per slab in flight
     int prefetch;         // several rounds: the wavefronts from this one on fetch the next unit's first passes into LDS during the hand-over
     unsigned bitmap_words;    // per slab
     unsigned cpc_magic;       // 2^32 / cpc, rounded up: i / cpc is the high word of i * cpc_magic for the small i here
@@ -428,6 +429,17 @@ __device__ __forceinline__ SlabPass slab_pass(const SlabArgs& A, int n, bool liv
     return p;
 }
 
+// Start-up stagger: where few slabs are in flight and there are several rounds, slab j of the first round starts j steps
+// later, so that some slabs read while others wait or write.  Measured, without -> with, us: two in flight (6 us a step),
+// backward of 134400 x 512 bf16 119 -> 106, forward of 268800 x 512 bf16 147 -> 140, fp32 276 -> 271; four (2.5 us),
+// backward of 67200 x 1024 fp32 204 -> 193, of 67200 x 2048 bf16 224 -> 210, forward of 134400 x 512 bf16 73.5 -> 69.6.  With
+// more in flight they drift apart by themselves (eight, forward of 67200 x 1024 fp32: 129 -> 142 at 2.5 us).
+__device__ __forceinline__ void slab_stagger(const SlabArgs& A)
+{
+    const unsigned long long wait = (unsigned long long)A.stagger * (blockIdx.x / A.U), t0 = wall_clock64();
+    while (wall_clock64() - t0 < wait) __builtin_amdgcn_s_sleep(4);
+}
+
 // Prefetch (several rounds of units).  While the statistics complete, no load or store of the launch is in flight; the
 // register file has no room for the next unit, the LDS has room for 2/5 of it.  Every wavefront but those that poll (their
 // polls would queue behind their loads; always the first) fetches its part of the next unit's first passes straight into LDS.
@@ -484,6 +496,8 @@ __global__ __launch_bounds__(kSlabThreads, P * (ACT == 2 ? 2 : 1) <= (SOLO ? 4 :
     const char* rb = static_cast<const char*>(A.dy);
     char* yb = static_cast<char*>(A.out);
     if (SOLO && blockIdx.x == 0 && threadIdx.x == 0) A.sync[1] = 0u;
+    if (!SOLO) slab_stagger(A);
+
     for (int unit = SOLO ? slab_of_block(blockIdx.x, gridDim.x) : (int)blockIdx.x; unit < A.total_units; unit += gridDim.x) {
         // (formed anew for every unit: carried round the loop, what depends on them would cost registers)
         const int t = (int)fresh(threadIdx.x);
@@ -732,6 +746,8 @@ __global__ __launch_bounds__(kSlabThreads, SOLO ? (P * (ACT != 0 ? 3 : 2) <= 8 ?
     char* ob = static_cast<char*>(A.out);
     char* zb = static_cast<char*>(A.out2);
     if (SOLO && blockIdx.x == 0 && threadIdx.x == 0) A.sync[1] = 0u;
+    if (!SOLO) slab_stagger(A);
+
     for (int unit = SOLO ? slab_of_block(blockIdx.x, gridDim.x) : (int)blockIdx.x; unit < A.total_units; unit += gridDim.x) {
         // (formed anew for every unit: carried round the loop, what depends on them would cost registers)
         const int t = (int)fresh(threadIdx.x);
