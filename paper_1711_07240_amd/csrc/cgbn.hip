@@ -394,7 +394,9 @@ bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_pai
 
 // Which calls take the column-slab kernels, and how they are cut.  Channels-last, C a multiple of a 16-byte vector:
 //   - up to 3072 pixels one workgroup per slab of 2 vectors (forward 5120 while the tensor is at most 6 MB): one launch, nothing
-//     to hand over.  More pixels per workgroup than that are slower than several units.  Measured, forward / backward
+//     to hand over.  Backward: slabs of one vector while that gives every compute unit at most one workgroup, since fewer bytes
+//     per compute unit then count for more than the half lines (measured, 2 vectors -> 1, with ReLU: bf16 2100 x 512 12.8 ->
+//     11.1, 2100 x 2048 20.2 -> 16.9; beyond, fp32 2100 x 2048 20.5 -> 24.0; forward 11.0 -> 12.3).  More pixels per workgroup than that are slower than several units.  Measured, forward / backward
 //     us, sweeps -> one unit -> several: bf16 2100 x 512 22 / 30 -> 9.6 / 11.7 -> 13.8 / 13.2; 3200 x 1024 26 / 32 -> 13.9 /
 //     20.9 -> 16.1 / 16.2; 8400 x 512 27 / 32 -> 23 / 32 -> 17.9 / 17.7.
 //   - beyond, units of 128-byte columns wherever a slab's units are resident together.  Measured, sweeps -> units: bf16
@@ -423,7 +425,7 @@ void make_slab_plan(int N, int C, long long HW, int layout, int eb, long long ro
         s->row_bytes = (long long)C * eb;
         s->cpc = 1;
         if (s->R <= 3072 || (forward && s->R <= 5120 && s->R * s->row_bytes <= 6000000)) {
-            const int cols = s->vecs < 2 ? s->vecs : 2;
+            const int cols = s->vecs < 2 || (!forward && s->vecs <= cus) ? 1 : 2;
             if (cut_slabs(s, C, cols, cols * vec, 1, row_pairs, cus, forward)) return;
         }
         // about 8 vectors, as even as the row allows

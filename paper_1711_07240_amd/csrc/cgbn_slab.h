@@ -937,7 +937,7 @@ __global__ __launch_bounds__(kSlabThreads, SOLO ? (P * (ACT != 0 ? 3 : 2) <= 8 ?
 }
 
 // X(vectors per thread (and tensor), one unit per slab)
-#define CGBN_SLAB_FORWARD_P(X) X(4, true) X(8, true) X(12, true) X(20, true) X(6, false) X(12, false) X(18, false) X(28, false) X(36, false)
-#define CGBN_SLAB_BACKWARD_P(X) X(4, true) X(8, true) X(12, true) X(20, true) X(6, false) X(9, false) X(14, false) X(18, false)
+#define CGBN_SLAB_FORWARD_P(X) X(4, true) X(8, true) X(10, true) X(12, true) X(20, true) X(6, false) X(12, false) X(18, false) X(28, false) X(36, false)
+#define CGBN_SLAB_BACKWARD_P(X) X(4, true) X(6, true) X(8, true) X(10, true) X(12, true) X(20, true) X(6, false) X(9, false) X(14, false) X(18, false)
 
 }  // namespace cgbn

@@ -26,6 +26,8 @@ SHAPES = [
     ("4-passes-exactly", (4, 16, 16, 16, 2, "NHWC", "bf16"), 1),
     ("5-passes-ragged-slab", (5, 40, 15, 14, 5, "NHWC", "bf16"), 1),
     ("12-passes-exactly", (3, 24, 32, 32, 3, "NHWC", "f32"), 1),
+    ("10-passes-exactly", (2, 16, 40, 32, 2, "NHWC", "bf16"), 1),
+    ("slabs-of-two-vectors-ragged", (2, 1028, 20, 33, 2, "NHWC", "f32"), 1),
     ("most-rows-one-unit-forward", (2, 16, 40, 64, 1, "NHWC", "f32"), 1),
     ("first-rows-of-several-units", (1, 64, 53, 97, 1, "NHWC", "bf16"), "several"),
     ("narrow-c16", (7, 16, 45, 31, 7, "NHWC", "bf16"), "several"),

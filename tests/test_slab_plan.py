@@ -7,8 +7,8 @@ import pytest
 from paper_1711_07240_amd import cgbn as L
 
 THREADS = 512
-VARIANTS = {("sfwd", True): (4, 8, 12, 20), ("sfwd", False): (6, 12, 18, 28, 36),
-            ("sbwd", True): (4, 8, 12, 20), ("sbwd", False): (6, 9, 14, 18)}
+VARIANTS = {("sfwd", True): (4, 8, 10, 12, 20), ("sfwd", False): (6, 12, 18, 28, 36),
+            ("sbwd", True): (4, 6, 8, 10, 12, 20), ("sbwd", False): (6, 9, 14, 18)}
 MAX_CHANNELS = 128
 STATIC_SCRATCH = 16 << 20
 
