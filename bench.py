@@ -165,7 +165,9 @@ def measure_workload(layer, torch, steps, warmup):
     wall_ms = (time.perf_counter() - t0) * 1e3 / steps
     fwd_in, bwd_in = time_step_halves(torch, layer, steps)
     per_step = [f + b for f, b in zip(fwd_in, bwd_in)]
-    fused_f, fused_b = (layer.cgbn.cgbn_get_tuning("last_forward_fused"), layer.cgbn.cgbn_get_tuning("last_backward_fused"))
+    # one launch that reads every value once: the NCHW single-launch kernels or the column-slab kernels
+    fused_f, fused_b = (layer.cgbn.cgbn_get_tuning(f"last_{d}_fused") or layer.cgbn.cgbn_get_tuning(f"last_{d}_slab")
+                        for d in ("forward", "backward"))
     # bytes the step moves by design: 5 tensors when both directions run as one launch each; as separate sweeps
     # the forward moves 3 (statistics from one sweep over x, the default) or 4, the backward 5
     one_sweep = layer.cgbn.cgbn_get_tuning("one_sweep_stats")
@@ -346,8 +348,8 @@ def main():
         bms = statistics.median(time_calls(torch, bw, 3, max(10, args.steps // 2)))
         moved_f, moved_b = (3 if sc is not None else 2), (5 if dsc is not None else 4)
         relu[name] = dict(fwd_ms=fms, bwd_ms=bms, fwd_moved_GBps=moved_f * Sb / fms / 1e6, bwd_moved_GBps=moved_b * Sb / bms / 1e6,
-                          single_launch=dict(forward=cgbn.cgbn_get_tuning("last_forward_fused"),
-                                             backward=cgbn.cgbn_get_tuning("last_backward_fused")))
+                          single_launch={d: cgbn.cgbn_get_tuning(f"last_{d}_fused") or cgbn.cgbn_get_tuning(f"last_{d}_slab")
+                                         for d in ("forward", "backward")})
     del dz
 
     # What this machine's memory system gives a plain streaming copy (the library's copy kernel, 1 GiB read + 1 GiB

@@ -400,8 +400,8 @@ bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_pai
 //     us, sweeps -> one unit -> several: bf16 2100 x 512 22 / 30 -> 9.6 / 11.7 -> 13.8 / 13.2; 3200 x 1024 26 / 32 -> 13.9 /
 //     20.9 -> 16.1 / 16.2; 8400 x 512 27 / 32 -> 23 / 32 -> 17.9 / 17.7.
 //   - beyond, units of 128-byte columns wherever a slab's units are resident together.  Measured, sweeps -> units: bf16
-//     67200 x 256 38 / 49 -> 26 / 31, 16800 x 2048 67 / 94 -> 34 / 57, 268800 x 512 181 / 288 -> 159 / 253; fp32 67200 x 512
-//     95 / 139 -> 66 / 100, 67200 x 1024 168 / 255 -> 144 / 222, 268800 x 1024 599 / 974 -> 568 / 908.  Narrower columns lose (half a
+//     67200 x 256 38 / 49 -> 26 / 30, 16800 x 2048 67 / 94 -> 34 / 52, 268800 x 512 181 / 288 -> 140 / 239; fp32 67200 x 1024
+//     168 / 255 -> 129 / 193, 268800 x 1024 599 / 974 -> at most 568 / 908.  Narrower columns lose (half a
 //     line per request), wider ones make a slab's rows more than the hand-over bears.
 //
 // NCHW, planes of at most 512 values, C a multiple of a 16-byte vector's elements (a slab starts and ends on 16 bytes):
