@@ -11,7 +11,7 @@
 // step are one sum inside the workgroup: no row is published, nothing is waited for, one launch and no prepared
 // workspace.
 //
-// U > 1: a unit publishes, per channel, s = sum(x - p) and q = sum(x - a)^2 about its own centre (backward: sum dy and
+// U > 1: a unit publishes, per channel, s = sum(x - p) and q, the squared deviations from its own mean (backward: sum dy and
 // sum dy * xhat) as one 8-byte store, and counts itself in on the slab's counter; the unit that completes the count
 // learns so from it; the units share out the slab's channels, add up their rows in double precision and in a fixed order
 // and publish the results, which every unit then fetches.  Unlike in the NCHW single-launch kernels, no wait here needs its
@@ -77,24 +77,72 @@ struct SlabArgs {
 // LDS of a workgroup
 struct SlabLds {
     float part[2][kSlabThreads * 8];                     // [row lane or wavefront][column]
-    float piv[kSlabMaxChannels], ctr[kSlabMaxChannels];  // forward: pivot and the unit's centre
+    float piv[kSlabMaxChannels], ctr[kSlabMaxChannels];  // forward: pivot, and how far the unit's mean lies from it
     float res[3][kSlabMaxChannels];                      // several units: the channels' results (forward mean, its rest, 1/sqrt; backward dbeta, dgamma)
     float k0[kSlabMaxChannels], k1[kSlabMaxChannels], k2[kSlabMaxChannels], k3[kSlabMaxChannels];   // write-out constants
-    int skip, last, fix, wait, redo;  // this unit moves on (2: results are missing for good); it completed the count; there are units for it to finish; the count is complete, the results are not there yet
+    int skip, last, fix, wait;  // this unit moves on (2: results are missing for good); it completed the count; there are units for it to finish; the count is complete, the results are not there yet
 };
 
-// Sums a thread's column values over the slab: the row lanes of a wavefront by shuffles (power-of-two column counts),
+// v plus the value of lane ^ OFF, by vector instructions: __shfl_xor goes through the LDS, which the eight wavefronts of a
+// workgroup share, and the forward sums twice (measured, through the LDS -> this, us, bf16: forward of 16 x 256 planes of
+// 13x21 12.7 -> 12.1, of 3136 x 256 channels-last 12.0 -> 11.5; backward of 2100 x 512 10.1 -> 9.6, of 268800 x 512 240 -> 230).
+template <int OFF> __device__ __forceinline__ void lane_pair(unsigned v, unsigned& a, unsigned& b)
+{
+    if constexpr (OFF == 32 || OFF == 16) {            // (a, b): the values of the lower and the upper lane of the pair
+        const auto t = OFF == 32 ? __builtin_amdgcn_permlane32_swap(v, v, false, false) : __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        a = t[0];
+        b = t[1];
+    } else {
+        int o = (int)v;
+        if constexpr (OFF == 1) o = __builtin_amdgcn_update_dpp(o, (int)v, 0xB1, 0xf, 0xf, false);        // quad_perm [1,0,3,2]
+        else if constexpr (OFF == 2) o = __builtin_amdgcn_update_dpp(o, (int)v, 0x4E, 0xf, 0xf, false);   // quad_perm [2,3,0,1]
+        else if constexpr (OFF == 4) {
+            o = __builtin_amdgcn_update_dpp(o, (int)v, 0x104, 0xf, 0x5, false);                           // row_shl:4 into banks 0 and 2
+            o = __builtin_amdgcn_update_dpp(o, (int)v, 0x114, 0xf, 0xA, false);                           // row_shr:4 into banks 1 and 3
+        } else o = __builtin_amdgcn_update_dpp(o, (int)v, 0x128, 0xf, 0xf, false);                        // row_ror:8
+        a = v;
+        b = (unsigned)o;
+    }
+}
+template <int OFF> __device__ __forceinline__ float lane_add(float v)
+{
+    unsigned a, b;
+    lane_pair<OFF>(__float_as_uint(v), a, b);
+    return __uint_as_float(a) + __uint_as_float(b);
+}
+template <int OFF> __device__ __forceinline__ double lane_add(double v)
+{
+    const unsigned long long w = (unsigned long long)__double_as_longlong(v);
+    unsigned al, bl, ah, bh;
+    lane_pair<OFF>((unsigned)w, al, bl);
+    lane_pair<OFF>((unsigned)(w >> 32), ah, bh);
+    return __longlong_as_double((long long)(((unsigned long long)ah << 32) | al)) + __longlong_as_double((long long)(((unsigned long long)bh << 32) | bl));
+}
+// Sums over the lanes that differ in the bits from `lowest` up to, not including, `end` (powers of two, uniform): f(off) adds one of them.
+template <class F> __device__ __forceinline__ void lanes_add(int lowest, int end, F f)
+{
+    asm volatile("" : "+s"(lowest), "+s"(end));       // (or the compiler keeps every comparison of every call in registers)
+    if (lowest <= 1 && end > 1) f(std::integral_constant<int, 1>{});
+    if (lowest <= 2 && end > 2) f(std::integral_constant<int, 2>{});
+    if (lowest <= 4 && end > 4) f(std::integral_constant<int, 4>{});
+    if (lowest <= 8 && end > 8) f(std::integral_constant<int, 8>{});
+    if (lowest <= 16 && end > 16) f(std::integral_constant<int, 16>{});
+    if (lowest <= 32 && end > 32) f(std::integral_constant<int, 32>{});
+}
+
+// Sums a thread's column values over the slab: the row lanes of a wavefront first (power-of-two column counts),
 // then through LDS; the first of a channel's `tpc` threads (t % tpc == 0, channel t / tpc) gets the channel's sums.
 template <int VEC, int Q, class LDS>
 __device__ __forceinline__ void slab_sum(const SlabArgs& A, LDS& L, float (&v)[Q][VEC], int col, int r, double (&out)[Q])
 {
     const int t = (int)fresh(threadIdx.x), lane = t & (kWave - 1), w = t >> 6;
     if (A.pow2) {
-        for (int off = A.cols; off < kWave; off <<= 1)
+        lanes_add(A.cols, kWave, [&](auto off) __attribute__((always_inline)) {
 #pragma unroll
             for (int q = 0; q < Q; ++q)
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) v[q][e] += __shfl_xor(v[q][e], off);
+                for (int e = 0; e < VEC; ++e) v[q][e] = lane_add<decltype(off)::value>(v[q][e]);
+        });
         if (lane < A.cols)
 #pragma unroll
             for (int q = 0; q < Q; ++q)
@@ -111,7 +159,8 @@ __device__ __forceinline__ void slab_sum(const SlabArgs& A, LDS& L, float (&v)[Q
     const int ch = t / A.tpc, sub = t & (A.tpc - 1);
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-        double acc = 0.0;
+        double& acc = out[q];
+        acc = 0.0;
         if (ch * A.cpc < A.ncols) {               // (channels beyond the slab's columns hold zeros)
             if (A.cpc == 1) {
                 for (int i = sub; i < lanes; i += A.tpc) acc += (double)L.part[q][i * A.ncols + ch];
@@ -123,9 +172,11 @@ __device__ __forceinline__ void slab_sum(const SlabArgs& A, LDS& L, float (&v)[Q
                 }
             }
         }
-        for (int off = 1; off < A.tpc; off <<= 1) acc += __shfl_xor(acc, off);
-        out[q] = acc;
     }
+    lanes_add(1, A.tpc, [&](auto off) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) out[q] = lane_add<decltype(off)::value>(out[q]);
+    });
 }
 
 __device__ __forceinline__ unsigned slab_bits(float v)      // NaN in canonical form: never the sentinel
@@ -164,6 +215,13 @@ template <class F> __device__ __forceinline__ bool slab_poll(const SlabArgs& A, 
     return false;
 }
 
+// 1 / n to about 1e-14 (a Newton step from the hardware's float reciprocal)
+__device__ __forceinline__ double slab_reciprocal(double n)
+{
+    const double r = (double)__builtin_amdgcn_rcpf((float)n);
+    return r * (2.0 - n * r);
+}
+
 // One channel's rows added up by the `G` lanes of a group (lane `gl`), double precision, fixed order; the group's first
 // lane writes the results.  False: rows are missing.  (Lanes without a channel take part in the polls.)
 template <bool FWD> __device__ __forceinline__ bool slab_reduce(const SlabArgs& A, SlabLds& L, int slab, int c, bool patient)
@@ -190,23 +248,25 @@ template <bool FWD> __device__ __forceinline__ bool slab_reduce(const SlabArgs& 
         s0 += (double)__uint_as_float((unsigned)v[j]);
         if (!FWD) s1 += (double)__uint_as_float((unsigned)(v[j] >> 32));
     }
-    for (int off = A.G >> 1; off >= 1; off >>= 1) {
-        s0 += __shfl_xor(s0, off);
-        if (!FWD) s1 += __shfl_xor(s1, off);
-    }
+    lanes_add(1, A.G, [&](auto off) __attribute__((always_inline)) {
+        s0 = lane_add<decltype(off)::value>(s0);
+        if (!FWD) s1 = lane_add<decltype(off)::value>(s1);
+    });
     unsigned long long* result = slab_rows(A, slab) + (size_t)A.U * A.nch + 2 * (duty ? c : 0);
     if (FWD) {
-        const float p = L.piv[duty ? c : 0];
-        const double mean = (double)p + s0 * A.inv_M_f64;
+        // steps 6-8 about the pooled mean: every unit's squared deviations from its own mean and n times the distance between
+        // the two means squared; nothing is subtracted from anything but means
+        const double off = s0 * A.inv_M_f64, mean = (double)L.piv[duty ? c : 0] + off;
 #pragma unroll
         for (int j = 0; j < kSlabRowsPerLane; ++j) {
             const int k = gl + j * A.G;
             if (k < A.U) {
                 const double n = (double)(k + 1 < A.U ? A.rpu : (int)(A.R - (long long)k * A.rpu)) * (double)A.cpc;
-                s1 += row_sqdev(__uint_as_float((unsigned)v[j]), __uint_as_float((unsigned)(v[j] >> 32)), n, p, mean);
+                const double d = (double)__uint_as_float((unsigned)v[j]) * slab_reciprocal(n) - off;
+                s1 += (double)__uint_as_float((unsigned)(v[j] >> 32)) + n * (d * d);
             }
         }
-        for (int off = A.G >> 1; off >= 1; off >>= 1) s1 += __shfl_xor(s1, off);
+        lanes_add(1, A.G, [&](auto off) __attribute__((always_inline)) { s1 = lane_add<decltype(off)::value>(s1); });
         if (duty && gl == 0) {
             const float hi = (float)mean;
             slab_put(result, hi, (float)(mean - (double)hi));
@@ -479,10 +539,15 @@ __device__ __forceinline__ const u32x4& slab_fetched(const u32x4* ext, int slot,
 // P: vectors per thread.  ACT as in the NCHW kernels; the shortcut (ACT == 2) is fetched with x where the
 // registers allow (P <= 20), else while the unit is written out.
 //
-// Statistics.  One pass, under the loads: per column sum(x - p) and D = sum (x - p)^2 about the channel's pivot p, its
-// first stored value.  With a the unit's own centre, q = sum (x - a)^2 = D - 2 (a - p) sum(x - p) + n (a - p)^2 in double
-// precision.  That loses (a - p)^2 / variance times the accuracy of D, so a unit in which some channel's pivot lies more
-// than 8 standard deviations from its mean makes a second pass over its registers, about a, for q.
+// Statistics.  One pass, under the loads: per column of a thread the sum S of x - f about the thread's first value f, and the
+// squared deviations from the thread's own mean, one value at a time (the weights are constants of the unrolled loop):
+//     M2 <- M2 + (x - f - S / i)^2 * i / (i + 1),      S <- S + (x - f).
+// The unit's mean follows from the sums S + n (f - p) about the channel's pivot p, its first stored value; its squared
+// deviations are the sum of M2 + n ((f - p) + S / n - mean)^2 over the threads.  Every term is positive and nothing is a difference
+// of large sums, so it does not matter where the pivot lies.  (A sum of (x - p)^2 with the difference taken off at the
+// end loses (mean - p)^2 / variance times the accuracy of a float sum: relative error of 1/sqrt, the worst of many
+// channels, pivot 4 standard deviations off 8.8e-7, here 6.1e-8; a few activations among zeros, the
+// first of them the pivot, 6.3e-6 and 7.8e-8.)
 template <typename T, int ACT, int P, bool SOLO>
 __global__ __launch_bounds__(kSlabThreads, P * (ACT == 2 ? 2 : 1) <= (SOLO ? 4 : 18) ? 4 : 2) void slab_forward(SlabArgs A)
 {
@@ -557,70 +622,58 @@ __global__ __launch_bounds__(kSlabThreads, P * (ACT == 2 ? 2 : 1) <= (SOLO ? 4 :
                 });
             }
         }
-        // ---- sums about the pivots
-        float a[2][VEC];
+        // ---- the thread's sums and squared deviations
+        float first[VEC], a[VEC], m2[VEC];
+        slab_unpack<T>(d[0], first);
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) a[0][e] = a[1][e] = 0.f;
-        unroll_planes<P>([&](auto i_) __attribute__((always_inline)) {
-            constexpr int i = decltype(i_)::value;
+        for (int e = 0; e < VEC; ++e) {
+            if (ps.nr == 0) first[e] = piv[e];            // (what was loaded is no value of this channel)
+            a[e] = m2[e] = 0.f;
+        }
+        unroll_planes<P - 1>([&](auto i_) __attribute__((always_inline)) {
+            constexpr int i = decltype(i_)::value + 1;
             if (i < ps.nr) {
                 float f[VEC];
                 slab_unpack<T>(d[i], f);
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) {
-                    const float dv = f[e] - piv[e];
-                    a[0][e] += dv;
-                    a[1][e] += dv * dv;
+                    const float dv = f[e] - first[e];
+                    const float dd = dv - a[e] * (1.0f / (float)i);
+                    m2[e] += dd * (dd * ((float)i / (float)(i + 1)));
+                    a[e] += dv;
                 }
             }
         });
-        if (t == 0) L.redo = 0;
-        double tot[2];
-        slab_sum<VEC, 2>(A, L, a, col, r, tot);
+        // ---- the unit's
         const double n_row = (double)g.n * (double)A.cpc;
-        const float sf = (float)tot[0];
-        const float ctr = row_centre(pv, sf, (float)n_row);
-        double q;
-        {
-            const double off = (double)ctr - (double)pv, mm = tot[0] * tot[0] / n_row;
-            q = tot[1] - off * (2.0 * tot[0] - n_row * off);
-            if (ch < A.nch && sub == 0) {
-                L.piv[ch] = pv;
-                L.ctr[ch] = ctr;
-                if (mm > 64.0 * (tot[1] - mm)) L.redo = 1;
-            }
+        const float cnt = (float)ps.nr, inv_cnt = ps.nr > 0 ? __builtin_amdgcn_rcpf(cnt) : 0.f;
+        float b[1][VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            const float off = first[e] - piv[e];
+            b[0][e] = a[e] + cnt * off;
+            a[e] = a[e] * inv_cnt + off;
+        }
+        double tot[1], q[1];
+        slab_sum<VEC, 1>(A, L, b, col, r, tot);
+        if (ch < A.nch && sub == 0) {
+            L.piv[ch] = pv;
+            L.ctr[ch] = (float)(tot[0] * slab_reciprocal(n_row));
         }
         __syncthreads();
-        if (L.redo) {
-            float b[1][VEC];
+        {
             const SlabChannels<VEC> c2(A, (int)fresh((unsigned)col));
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) { piv[e] = L.ctr[c2[e]]; b[0][e] = 0.f; }
-            unroll_planes<P>([&](auto i_) __attribute__((always_inline)) {
-                constexpr int i = decltype(i_)::value;
-                if (i < ps.nr) {
-                    float f[VEC];
-                    slab_unpack<T>(d[i], f);
-#pragma unroll
-                    for (int e = 0; e < VEC; ++e) {
-                        const float dv = f[e] - piv[e];
-                        b[0][e] += dv * dv;
-                    }
-                }
-            });
-            double sq[1];
-            slab_sum<VEC, 1>(A, L, b, col, r, sq);
-            q = sq[0];
+            for (int e = 0; e < VEC; ++e) {
+                const float dd = a[e] - L.ctr[c2[e]];
+                b[0][e] = m2[e] + cnt * (dd * dd);
+            }
         }
+        slab_sum<VEC, 1>(A, L, b, col, r, q);
         // ---- steps 4-5 and 9-10
-        double mean = 0.0, dev = 0.0;
         bool ok = true, mine = true;
-        if (SOLO) {
-            mean = (double)pv + tot[0] * A.inv_M_f64;
-            const double dd = (double)ctr - mean;
-            dev = q + dd * (2.0 * (tot[0] - n_row * ((double)ctr - (double)pv)) + n_row * dd);
-        } else {
-            if (ch < A.nch && sub == 0) slab_put(slab_rows(A, slab) + (size_t)u * A.nch + ch, sf, (float)q);
+        if (!SOLO) {
+            if (ch < A.nch && sub == 0) slab_put(slab_rows(A, slab) + (size_t)u * A.nch + ch, (float)tot[0], (float)q[0]);
             fetched = 0;
             mine = slab_hand_over<true>(A, L, slab, u, [&] {
                 if constexpr (PRE != 0)
@@ -635,9 +688,10 @@ __global__ __launch_bounds__(kSlabThreads, P * (ACT == 2 ? 2 : 1) <= (SOLO ? 4 :
             if (ch < A.nch && sub == 0) {
                 float hi, lo, is;
                 if (SOLO) {
+                    const double mean = (double)pv + tot[0] * A.inv_M_f64;
                     hi = (float)mean;
                     lo = (float)(mean - (double)hi);
-                    is = (float)rsqrt_f64(dev * A.inv_M_f64 + A.eps);
+                    is = (float)rsqrt_f64(q[0] * A.inv_M_f64 + A.eps);
                 } else {
                     hi = L.res[0][ch];
                     lo = L.res[1][ch];

@@ -271,6 +271,42 @@ def test_first_value_far_from_the_mean(shape, sigmas):
     assert np.max(np.abs(got["invstd"] / ref["invstd"] - 1)) <= 1e-6
 
 
+# one unit; several short and long ones; float and bf16; a plane's value per column and two units per slab
+STATISTICS = [(2, 256, 25, 42, 2, "NHWC", "f32"), (2, 1024, 25, 42, 2, "NHWC", "bf16"), (4, 64, 40, 50, 4, "NHWC", "f32"),
+              (1, 512, 100, 170, 1, "NHWC", "bf16"), (2, 128, 100, 168, 2, "NHWC", "f32"), (300, 256, 7, 7, 5, "NCHW", "bf16"),
+              (37, 512, 7, 7, 37, "NCHW", "f32")]
+
+
+def _skew(kind, layout):
+    """Where a channel's first value lies: how many standard deviations off, or an activation among mostly zeros."""
+    def change(x):
+        v = x if layout == "NHWC" else x.transpose(0, 2, 3, 1)              # (a view: written through)
+        if kind == "sparse":
+            np.maximum(v - v.mean((0, 1, 2)) - 1.5 * v.std((0, 1, 2)), 0, out=v)
+            v[0, 0, 0, :] = 4 * v.std((0, 1, 2))
+        else:
+            v[0, 0, 0, :] = v.mean((0, 1, 2)) + kind * v.std((0, 1, 2))
+    return change
+
+
+@pytest.mark.parametrize("kind", [0.0, 2.0, 4.0, 6.0, 7.9, 30.0, "sparse"])
+@pytest.mark.parametrize("shape", STATISTICS, ids=lambda s: "x".join(map(str, s)))
+def test_variance_keeps_its_accuracy_wherever_the_first_value_lies(shape, kind):
+    """invstd of every channel to one unit in the last place, 2^-23 relative: half of one for the stored float; the sums of
+    squared deviations are sums of positive terms, and a thread's 4 to 36 roundings (2^-25 of its sum on average each)
+    count half in the root and average out over the hundreds of threads of a channel."""
+    print(f"[case] variance {shape} {kind}", flush=True)
+    wl, d, p = _problem(shape, change=_skew(kind, shape[5]))
+    p.forward()
+    torch.cuda.synchronize()
+    assert L.cgbn_get_tuning("last_forward_slab") == 1
+    x = G.widen(d["x"], wl.dtype)
+    var = x.var((0, 1, 2) if wl.layout == "NHWC" else (0, 2, 3))
+    err = np.abs(p.invstd.cpu().numpy().astype(np.float64) * np.sqrt(var + wl.eps) - 1)
+    print(f"[error] {err.max():.2e}", flush=True)
+    assert err.max() <= 2.0 ** -23
+
+
 def test_offset_data_keeps_its_accuracy():
     """Normal(100, 0.01) in float32: |mean| is 10^4 standard deviations."""
     wl, d, p = _problem((4, 64, 40, 50, 4, "NHWC", "f32"), base=synth.WORKLOADS["cfg4b"])
