@@ -158,7 +158,7 @@ struct FusedPlan {
 struct SlabPlan {
     int ok;               // the shape can take the path, and it is faster than separate sweeps
     int first;            // ... and faster than the single-launch NCHW kernels, where the shape can take those too
-    int cols, vecs, pow2, rpp, cpc, nch, tpc, slabs, U, rpu;
+    int cols, vecs, rpp, cpc, nch, tpc, slabs, U, rpu;
     int P;                // vectors per thread of the kernel variant
     long long R, row_bytes, total_units;
 };
@@ -334,13 +334,15 @@ int slab_most(bool forward, bool solo)
     return most;
 }
 
+// 8-byte words of a plan's rows and results
+long long slab_row_words(const SlabPlan& s) { return (long long)s.slabs * s.nch * 2 * (s.U + 1); }
+
 // The matrix (vecs, R, row_bytes, cpc) is given: cuts it into slabs of `cols` vectors and `nch` channels with U units each.
-// `row_pairs`: (channel, unit) pairs the workspace has room for.
-bool cut_slabs(SlabPlan* s, int C, int cols, int nch, long long U, long long row_pairs, int cus, bool forward)
+// `row_words`: 8-byte words the workspace has room for (a channel's row is two a unit, its results two more).
+bool cut_slabs(SlabPlan* s, int C, int cols, int nch, long long U, long long row_words, int cus, bool forward)
 {
     s->cols = cols;
     s->nch = nch;
-    s->pow2 = cols <= kWave && (cols & (cols - 1)) == 0;
     s->rpp = kSlabThreads / cols;
     s->tpc = nch * kWave <= kSlabThreads ? kWave : kSlabThreads / nch;
     s->slabs = (s->vecs + cols - 1) / cols;
@@ -349,12 +351,13 @@ bool cut_slabs(SlabPlan* s, int C, int cols, int nch, long long U, long long row
     s->P = slab_variant(forward, s->U == 1, ((long long)s->rpu + s->rpp - 1) / s->rpp);
     s->total_units = (long long)s->slabs * s->U;
     s->ok = 0;
+    if (s->cpc == 1 && cols > kSlabMaxPixelCols) return false;
     if (!s->P || nch > kSlabMaxChannels || s->slabs > C || s->total_units > 0x3fffffffLL) return false;
     if ((long long)s->rpp * s->row_bytes + (long long)cols * 16 > 0x7fffffffLL) return false;   // 32-bit lane offsets
     if (s->U > 1) {
         if (s->U > cus || s->U > 0xffff) return false;                              // a slab's units are resident together
         if (s->U > kSlabRowsPerLane * kWave) return false;
-        if ((long long)s->slabs * nch * (s->U + 2) > row_pairs) return false;
+        if (slab_row_words(*s) > row_words) return false;
         if ((long long)s->slabs * ((s->U + 31) / 32) > C) return false;             // bitmap words
     }
     s->ok = 1;
@@ -367,7 +370,7 @@ bool cut_slabs(SlabPlan* s, int C, int cols, int nch, long long U, long long row
 // backward 163 / 259 us against 142 / 224.)  Slabs that do not
 // end on line boundaries share lines with their neighbours, so they must all be in flight together: one round
 // (measured, fp32 268800 x 136 in four rounds 170 us, the sweeps 101).
-bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_pairs, int cus, bool forward)
+bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_words, int cus, bool forward)
 {
     const int rpp = kSlabThreads / cols;
     const long long cap = (long long)rpp * slab_most(forward, false);
@@ -376,7 +379,7 @@ bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_pai
     const long long least = (s->R + cap - 1) / cap < 2 ? 2 : (s->R + cap - 1) / cap;
     long long most = cus < s->R ? cus : s->R;
     if (most > kSlabRowsPerLane * kWave) most = kSlabRowsPerLane * kWave;
-    if (most > row_pairs / (slabs * nch) - 2) most = row_pairs / (slabs * nch) - 2;
+    if (most > row_words / (2 * slabs * nch) - 1) most = row_words / (2 * slabs * nch) - 1;
     long long best = 0, best_cost = 0;
     for (int k = 0; k < 8; ++k) {
         // the fewest units and a few more; as many as fill the compute units once, or half of them, ...
@@ -389,7 +392,7 @@ bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_pai
         const long long cost = rounds * (passes + 10);
         if (best == 0 || cost < best_cost) { best = U; best_cost = cost; }
     }
-    return best >= 2 && cut_slabs(s, C, cols, nch, best, row_pairs, cus, forward);
+    return best >= 2 && cut_slabs(s, C, cols, nch, best, row_words, cus, forward);
 }
 
 // Which calls take the column-slab kernels, and how they are cut.  Channels-last, C a multiple of a 16-byte vector:
@@ -413,7 +416,7 @@ bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_pai
 //   - several units per slab from 6 MB on (below, the hand-over costs what a launch less saves), and there before the
 //     single-launch kernels while planes are at most 1 KiB and the tensor 200 MB (backward: 512 bytes, float 800, 100 MB): bf16 256 x 1024 of 7x7 31 / 37 -> 23 /
 //     26, of 12x12 110 / 125 -> 49 / 60; fp32 100 x 1024 of 16x20 75 / 97 against 86 / 124.
-void make_slab_plan(int N, int C, long long HW, int layout, int eb, long long row_pairs, int cus, const FusedPlan& f, bool forward,
+void make_slab_plan(int N, int C, long long HW, int layout, int eb, long long row_words, int cus, const FusedPlan& f, bool forward,
                     SlabPlan* s)
 {
     std::memset(s, 0, sizeof(*s));
@@ -426,11 +429,11 @@ void make_slab_plan(int N, int C, long long HW, int layout, int eb, long long ro
         s->cpc = 1;
         if (s->R <= 3072 || (forward && s->R <= 5120 && s->R * s->row_bytes <= 6000000)) {
             const int cols = s->vecs < 2 || (!forward && s->vecs <= cus) ? 1 : 2;
-            if (cut_slabs(s, C, cols, cols * vec, 1, row_pairs, cus, forward)) return;
+            if (cut_slabs(s, C, cols, cols * vec, 1, row_words, cus, forward)) return;
         }
         // about 8 vectors, as even as the row allows
         const int slabs = s->vecs < 12 ? 1 : (s->vecs + 4) / 8, cols = (s->vecs + slabs - 1) / slabs;
-        cut_slabs_in_units(s, C, cols, ceil_pow2(cols * vec), row_pairs, cus, forward);
+        cut_slabs_in_units(s, C, cols, ceil_pow2(cols * vec), row_words, cus, forward);
         return;
     }
     const long long row_vecs = (long long)C * HW / vec;
@@ -442,13 +445,13 @@ void make_slab_plan(int N, int C, long long HW, int layout, int eb, long long ro
     int nch = vec;                                     // channels per slab: at least 8 vectors, if there are that many
     while (nch * 2 <= kSlabMaxChannels && nch < C && (long long)nch / vec * HW < 8) nch *= 2;
     const int cols = (int)(nch / vec * HW), rpp = kSlabThreads / cols;
-    if (N <= rpp * slab_most(forward, true) && cut_slabs(s, C, cols, nch, 1, row_pairs, cus, forward)) {
+    if (N <= rpp * slab_most(forward, true) && cut_slabs(s, C, cols, nch, 1, row_words, cus, forward)) {
         s->first = !f.ok || f.U > 1 || (C >= 1024 && s->P <= (forward ? 12 : 8)) ||
                    (N >= 24 && C >= 128 && s->P <= (forward ? 8 : 4));
         return;
     }
     if (N * s->row_bytes < 6000000) return;
-    if (cut_slabs_in_units(s, C, cols, nch, row_pairs, cus, forward))
+    if (cut_slabs_in_units(s, C, cols, nch, row_words, cus, forward))
         s->first = !f.ok || (f.U > 1 && (forward ? HW * eb <= 1024 && N * s->row_bytes <= 200000000 : HW * eb <= (eb == 2 ? 512 : 800) && N * s->row_bytes <= 100000000));
 }
 
@@ -603,25 +606,29 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
     // the sync area comes first, so that the error word has the same offset in every workspace
     size_t sync = align256(((size_t)kSyncHeader + 4 * (size_t)C) * sizeof(unsigned));
     size_t part = align256((size_t)C * max_rows * sizeof(float));
-    // The column-slab path keeps its rows where the other paths keep theirs (part0 and part1 are adjacent) and makes that
-    // room larger only up to half a MiB, so that it changes no limit.
-    const long long row_pairs = part > (256u << 10) ? (long long)(part / sizeof(float)) : (256 << 10) / (long long)sizeof(float);
+    size_t sh = align256((size_t)K * C * sizeof(double));
+    // The column-slab path keeps its rows where the other paths keep theirs and the shard sums (the four arrays are adjacent)
+    // and makes that room larger only up to a MiB, or twice the rows of the others while the workspace still fits the static
+    // scratch, so that it changes no limit.
+    const size_t mlo = align256((size_t)C * sizeof(float)), others = 2 * part + 2 * sh;
+    size_t room = others > (1u << 20) ? others : (1u << 20);
+    if (sync + others + 2 * part + mlo <= (size_t)CGBN_STATIC_SCRATCH_BYTES && others + 2 * part > room) room = others + 2 * part;
+    const long long row_words = (long long)(room / sizeof(double));
     const int cus = compute_units();
-    make_slab_plan(N, C, HW, layout, p->eb, row_pairs, cus, p->ff, true, &p->sf);
-    make_slab_plan(N, C, HW, layout, p->eb, row_pairs, cus, p->fb, false, &p->sb);
+    make_slab_plan(N, C, HW, layout, p->eb, row_words, cus, p->ff, true, &p->sf);
+    make_slab_plan(N, C, HW, layout, p->eb, row_words, cus, p->fb, false, &p->sb);
     for (const SlabPlan* s : {&p->sf, &p->sb})
         if (s->ok && s->U > 1) {
-            const size_t need = align256((size_t)s->slabs * s->nch * (s->U + 2) * sizeof(float));
-            if (need > part) part = need;
+            const size_t need = (size_t)slab_row_words(*s) * sizeof(double);
+            if (need > 2 * part + 2 * sh) part = align256((need - 2 * sh + 1) / 2);
         }
-    size_t sh = align256((size_t)K * C * sizeof(double));
     p->off_sync = 0;
     p->off_part0 = sync;
     p->off_part1 = sync + part;
     p->off_sh0 = sync + 2 * part;
     p->off_sh1 = sync + 2 * part + sh;
     p->off_mlo = sync + 2 * part + 2 * sh;
-    p->bytes = p->off_mlo + align256((size_t)C * sizeof(float));
+    p->bytes = p->off_mlo + mlo;
     return CGBN_OK;
 }
 
@@ -941,11 +948,11 @@ SlabArgs slab_args(const Plan& p, const SlabPlan& s, char* ws)
 {
     SlabArgs A;
     std::memset(&A, 0, sizeof(A));
-    A.rows = reinterpret_cast<unsigned*>(ws + p.off_part0);
+    A.rows = reinterpret_cast<unsigned long long*>(ws + p.off_part0);
     A.sync = reinterpret_cast<unsigned*>(ws + p.off_sync);
     A.R = s.R; A.row_bytes = s.row_bytes;
     A.M = p.M; A.inv_M_f64 = 1.0 / p.M; A.inv_M = (float)(1.0 / p.M);
-    A.vecs = s.vecs; A.cols = s.cols; A.ncols = s.cols * (16 / p.eb); A.pow2 = s.pow2; A.rpp = s.rpp;
+    A.vecs = s.vecs; A.cols = s.cols; A.ncols = s.cols * (16 / p.eb); A.rpp = s.rpp;
     A.cpc = s.cpc; A.nch = s.nch; A.tpc = s.tpc; A.rch = A.ncols / s.cpc;
     while ((1 << A.nsh) < s.nch) ++A.nsh;
     A.C = p.C; A.slabs = s.slabs; A.U = s.U; A.rpu = s.rpu; A.total_units = (int)s.total_units;
@@ -975,10 +982,11 @@ cgbn_status launch_slab_kernel(KernelT kernel, const Plan& p, const SlabPlan& s,
             A.prefetch = polling < kSlabWaves ? polling : 0;
             A.stagger = A.inflight == 2 ? 600u : (A.inflight == 3 || A.inflight == 4 ? 250u : 0u);      // see slab_stagger
         }
-        const long long words = 2LL * s.slabs * s.nch * (s.U + 2);
+        const long long words = 2 * slab_row_words(s);
         long long want = (words + kThreads - 1) / kThreads;
         const unsigned init_groups = (unsigned)(want < 1 ? 1 : (want > 2048 ? 2048 : want));
-        hipLaunchKernelGGL(fused_init, dim3(init_groups), dim3(kThreads), 0, st, A.sync, kSyncHeader + 4 * p.C, A.rows, words);
+        hipLaunchKernelGGL(fused_init, dim3(init_groups), dim3(kThreads), 0, st, A.sync, kSyncHeader + 4 * p.C,
+                           reinterpret_cast<unsigned*>(A.rows), words);
     }
     hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3(kSlabThreads), 0, st, A);
     return launched();

@@ -12,7 +12,8 @@
 // workspace.
 //
 // U > 1: a unit publishes, per channel, s = sum(x - p) and q, the squared deviations from its own mean (backward: sum dy and
-// sum dy * xhat) as one 8-byte store, and counts itself in on the slab's counter; the unit that completes the count
+// sum dy * xhat) as two doubles (with a handful of units there are few roundings to average: as floats, two units of 6272 values
+// each left the mean 1e-7 standard deviations off, now 3e-10), and counts itself in on the slab's counter; the unit that completes the count
 // learns so from it; the units share out the slab's channels, add up their rows in double precision and in a fixed order
 // and publish the results, which every unit then fetches.  Unlike in the NCHW single-launch kernels, no wait here needs its
 // siblings to be resident: a unit whose wait runs out marks itself in the slab's bitmap (unless the count completed
@@ -29,6 +30,8 @@ constexpr int kSlabThreads = 512;
 constexpr int kSlabWaves = kSlabThreads / kWave;
 constexpr int kSlabRowsPerLane = 4;        // rows of a channel that one lane adds up: at most 4 x 64 units per slab
 constexpr int kSlabMaxChannels = 128;      // channels of one slab
+constexpr int kSlabMaxPixelCols = 16;      // vector columns of a slab whose channels are one column each
+constexpr int kSlabPartWords = 8 * (kSlabThreads + 8 * kSlabMaxPixelCols + 8);
 constexpr unsigned kSlabWaitTicks = 30000; // 100 MHz ticks (300 us) a unit waits for its siblings before it moves on ...
 constexpr unsigned kSlabWaitTicksLater = 3000;   // ... once some unit of the launch has done so
 constexpr unsigned long long kSlabBackstopTicks = 100000000ull;     // a second: waits that end within microseconds in a sound launch
@@ -49,7 +52,7 @@ struct SlabArgs {
     float* invstd;
     float* dgamma;
     float* dbeta;
-    unsigned* rows;       // per slab: [unit][channel] pairs of floats, then [channel][2] pairs of results
+    unsigned long long* rows; // per slab: [unit][channel][2] doubles, then [channel][2] pairs of floats, the results
     unsigned* sync;
     long long R;          // rows of the matrix
     long long row_bytes;
@@ -57,7 +60,6 @@ struct SlabArgs {
     float inv_M;
     int vecs;             // 16-byte vectors per row
     int cols, ncols;      // vector columns of a slab, its element columns
-    int pow2;             // cols is a power of two <= 64: row lanes are folded inside the wavefronts first
     int rpp;              // rows per pass
     int rch;                  // channels per slab
     int cpc, nch, nsh, tpc;   // columns per channel, rch rounded up to a power of two 2^nsh, threads that add one channel's partial sums
@@ -76,16 +78,15 @@ struct SlabArgs {
 
 // LDS of a workgroup
 struct SlabLds {
-    float part[2][kSlabThreads * 8];                     // [row lane or wavefront][column]
+    float part[2][kSlabPartWords];                       // see slab_sum
     float piv[kSlabMaxChannels], ctr[kSlabMaxChannels];  // forward: pivot, and how far the unit's mean lies from it
     float res[3][kSlabMaxChannels];                      // several units: the channels' results (forward mean, its rest, 1/sqrt; backward dbeta, dgamma)
     float k0[kSlabMaxChannels], k1[kSlabMaxChannels], k2[kSlabMaxChannels], k3[kSlabMaxChannels];   // write-out constants
     int skip, last, fix, wait;  // this unit moves on (2: results are missing for good); it completed the count; there are units for it to finish; the count is complete, the results are not there yet
 };
 
-// v plus the value of lane ^ OFF, by vector instructions: __shfl_xor goes through the LDS, which the eight wavefronts of a
-// workgroup share, and the forward sums twice (measured, through the LDS -> this, us, bf16: forward of 16 x 256 planes of
-// 13x21 12.7 -> 12.1, of 3136 x 256 channels-last 12.0 -> 11.5; backward of 2100 x 512 10.1 -> 9.6, of 268800 x 512 240 -> 230).
+// v plus the value of lane ^ OFF, by vector instructions (__shfl_xor goes through the LDS, which the eight wavefronts of a
+// workgroup share).
 template <int OFF> __device__ __forceinline__ void lane_pair(unsigned v, unsigned& a, unsigned& b)
 {
     if constexpr (OFF == 32 || OFF == 16) {            // (a, b): the values of the lower and the upper lane of the pair
@@ -104,12 +105,6 @@ template <int OFF> __device__ __forceinline__ void lane_pair(unsigned v, unsigne
         b = (unsigned)o;
     }
 }
-template <int OFF> __device__ __forceinline__ float lane_add(float v)
-{
-    unsigned a, b;
-    lane_pair<OFF>(__float_as_uint(v), a, b);
-    return __uint_as_float(a) + __uint_as_float(b);
-}
 template <int OFF> __device__ __forceinline__ double lane_add(double v)
 {
     const unsigned long long w = (unsigned long long)__double_as_longlong(v);
@@ -118,44 +113,43 @@ template <int OFF> __device__ __forceinline__ double lane_add(double v)
     lane_pair<OFF>((unsigned)(w >> 32), ah, bh);
     return __longlong_as_double((long long)(((unsigned long long)ah << 32) | al)) + __longlong_as_double((long long)(((unsigned long long)bh << 32) | bl));
 }
-// Sums over the lanes that differ in the bits from `lowest` up to, not including, `end` (powers of two, uniform): f(off) adds one of them.
-template <class F> __device__ __forceinline__ void lanes_add(int lowest, int end, F f)
+// Sums over groups of `lanes` lanes (a power of two up to 64, uniform): f(off) adds the lanes that differ in one bit.
+template <class F> __device__ __forceinline__ void lanes_add(int lanes, F f)
 {
-    asm volatile("" : "+s"(lowest), "+s"(end));       // (or the compiler keeps every comparison of every call in registers)
-    if (lowest <= 1 && end > 1) f(std::integral_constant<int, 1>{});
-    if (lowest <= 2 && end > 2) f(std::integral_constant<int, 2>{});
-    if (lowest <= 4 && end > 4) f(std::integral_constant<int, 4>{});
-    if (lowest <= 8 && end > 8) f(std::integral_constant<int, 8>{});
-    if (lowest <= 16 && end > 16) f(std::integral_constant<int, 16>{});
-    if (lowest <= 32 && end > 32) f(std::integral_constant<int, 32>{});
+    asm volatile("" : "+s"(lanes));                   // (or the compiler keeps every comparison of every call in registers)
+    if (lanes > 1) f(std::integral_constant<int, 1>{});
+    if (lanes > 2) f(std::integral_constant<int, 2>{});
+    if (lanes > 4) f(std::integral_constant<int, 4>{});
+    if (lanes > 8) f(std::integral_constant<int, 8>{});
+    if (lanes > 16) f(std::integral_constant<int, 16>{});
+    if (lanes > 32) f(std::integral_constant<int, 32>{});
 }
 
-// Sums a thread's column values over the slab: the row lanes of a wavefront first (power-of-two column counts),
-// then through LDS; the first of a channel's `tpc` threads (t % tpc == 0, channel t / tpc) gets the channel's sums.
+// Sums a thread's column values over the slab, in double precision: every thread leaves its values in LDS, and each channel's
+// `tpc` threads add them up; the first of them (t % tpc == 0, channel t / tpc) gets the channel's sums.  One column a channel:
+// the values of a column lie side by side, columns 8 words further on than they need be, so that neither the stores (lanes that
+// differ in column and row) nor the loads (in channel and row) meet in a bank.  (Folding the row lanes of a wavefront first, in
+// float, left the mean of 2100 x 2048 bf16 1.1e-7 standard deviations off, now 7e-10, and took longer:
+// backward of 2100 x 512 9.6 us, now 8.9; forward 9.4, now 8.7.)
 template <int VEC, int Q, class LDS>
 __device__ __forceinline__ void slab_sum(const SlabArgs& A, LDS& L, float (&v)[Q][VEC], int col, int r, double (&out)[Q])
 {
-    const int t = (int)fresh(threadIdx.x), lane = t & (kWave - 1), w = t >> 6;
-    if (A.pow2) {
-        lanes_add(A.cols, kWave, [&](auto off) __attribute__((always_inline)) {
+    const int t = (int)fresh(threadIdx.x);
+    const int rs = A.rpp + 8, es = A.cols * rs + 8;       // one column a channel: words between columns, between a thread's values
+    if (r < A.rpp) {
+        if (A.cpc == 1) {
 #pragma unroll
             for (int q = 0; q < Q; ++q)
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) v[q][e] = lane_add<decltype(off)::value>(v[q][e]);
-        });
-        if (lane < A.cols)
+                for (int e = 0; e < VEC; ++e) L.part[q][e * es + col * rs + r] = v[q][e];
+        } else {
 #pragma unroll
             for (int q = 0; q < Q; ++q)
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) L.part[q][w * A.ncols + col * VEC + e] = v[q][e];
-    } else if (r < A.rpp) {
-#pragma unroll
-        for (int q = 0; q < Q; ++q)
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) L.part[q][r * A.ncols + col * VEC + e] = v[q][e];
+                for (int e = 0; e < VEC; ++e) L.part[q][r * A.ncols + col * VEC + e] = v[q][e];
+        }
     }
     __syncthreads();
-    const int lanes = A.pow2 ? kSlabWaves : A.rpp;
     const int ch = t / A.tpc, sub = t & (A.tpc - 1);
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
@@ -163,17 +157,18 @@ __device__ __forceinline__ void slab_sum(const SlabArgs& A, LDS& L, float (&v)[Q
         acc = 0.0;
         if (ch * A.cpc < A.ncols) {               // (channels beyond the slab's columns hold zeros)
             if (A.cpc == 1) {
-                for (int i = sub; i < lanes; i += A.tpc) acc += (double)L.part[q][i * A.ncols + ch];
+                const float* p = L.part[q] + (ch % VEC) * es + (ch / VEC) * rs;
+                for (int i = sub; i < A.rpp; i += A.tpc) acc += (double)p[i];
             } else {
                 // the channel's cpc columns of every row lane, dealt to its threads
-                for (int k = sub; k < lanes * A.cpc; k += A.tpc) {
+                for (int k = sub; k < A.rpp * A.cpc; k += A.tpc) {
                     const int i = (int)__umulhi((unsigned)k, A.cpc_magic), j = k - i * A.cpc;
                     acc += (double)L.part[q][i * A.ncols + ch * A.cpc + j];
                 }
             }
         }
     }
-    lanes_add(1, A.tpc, [&](auto off) __attribute__((always_inline)) {
+    lanes_add(A.tpc, [&](auto off) __attribute__((always_inline)) {
 #pragma unroll
         for (int q = 0; q < Q; ++q) out[q] = lane_add<decltype(off)::value>(out[q]);
     });
@@ -184,11 +179,18 @@ __device__ __forceinline__ unsigned slab_bits(float v)      // NaN in canonical 
     return v != v ? 0x7fc00000u : __float_as_uint(v);
 }
 
-// A slab's memory: [unit][channel] rows, then the channels' results (two pairs each), all 8-byte pairs that hold the
-// sentinel until they are written.
+// A slab's memory: [unit][channel][2] rows of doubles, then the channels' results (two pairs of floats each), all 8-byte words that
+// hold the sentinel until they are written.
 __device__ __forceinline__ unsigned long long* slab_rows(const SlabArgs& A, int slab)
 {
-    return reinterpret_cast<unsigned long long*>(A.rows) + (size_t)slab * (A.U + 2) * A.nch;
+    return A.rows + (size_t)slab * (A.U + 1) * A.nch * 2;
+}
+__device__ __forceinline__ void slab_put_row(const SlabArgs& A, int slab, int u, int c, double a, double b)
+{
+    unsigned long long* p = slab_rows(A, slab) + ((size_t)u * A.nch + c) * 2;
+    // (NaN in canonical form, as in slab_bits)
+    __hip_atomic_store(p, a != a ? 0x7ff8000000000000ull : (unsigned long long)__double_as_longlong(a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p + 1, b != b ? 0x7ff8000000000000ull : (unsigned long long)__double_as_longlong(b), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void slab_put(unsigned long long* p, float lo, float hi)
 {
@@ -228,31 +230,35 @@ template <bool FWD> __device__ __forceinline__ bool slab_reduce(const SlabArgs& 
 {
     const int gl = (int)fresh(threadIdx.x) & (A.G - 1);
     const bool duty = c < A.rch;
-    unsigned long long* row = slab_rows(A, slab) + (duty ? c : 0);
-    unsigned long long v[kSlabRowsPerLane];
+    unsigned long long* row = slab_rows(A, slab) + 2 * (duty ? c : 0);
+    unsigned long long v[kSlabRowsPerLane], w[kSlabRowsPerLane];
     if (!slab_poll(A, patient, [&] {
             bool there = true;
 #pragma unroll
             for (int j = 0; j < kSlabRowsPerLane; ++j) {
-                v[j] = 0ull;
-                if (duty && gl + j * A.G < A.U) v[j] = __hip_atomic_load(row + (size_t)(gl + j * A.G) * A.nch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                v[j] = w[j] = 0ull;
+                if (duty && gl + j * A.G < A.U) {
+                    unsigned long long* p = row + (size_t)(gl + j * A.G) * A.nch * 2;
+                    v[j] = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    w[j] = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
             }
 #pragma unroll
-            for (int j = 0; j < kSlabRowsPerLane; ++j) there &= !slab_missing(v[j]);
+            for (int j = 0; j < kSlabRowsPerLane; ++j) there &= v[j] != ~0ull && w[j] != ~0ull;       // (two words of kRowSentinel)
             return there;
         }))
         return false;
     double s0 = 0.0, s1 = 0.0;
 #pragma unroll
     for (int j = 0; j < kSlabRowsPerLane; ++j) {
-        s0 += (double)__uint_as_float((unsigned)v[j]);
-        if (!FWD) s1 += (double)__uint_as_float((unsigned)(v[j] >> 32));
+        s0 += __longlong_as_double((long long)v[j]);
+        if (!FWD) s1 += __longlong_as_double((long long)w[j]);
     }
-    lanes_add(1, A.G, [&](auto off) __attribute__((always_inline)) {
+    lanes_add(A.G, [&](auto off) __attribute__((always_inline)) {
         s0 = lane_add<decltype(off)::value>(s0);
         if (!FWD) s1 = lane_add<decltype(off)::value>(s1);
     });
-    unsigned long long* result = slab_rows(A, slab) + (size_t)A.U * A.nch + 2 * (duty ? c : 0);
+    unsigned long long* result = slab_rows(A, slab) + ((size_t)A.U * A.nch + (duty ? c : 0)) * 2;
     if (FWD) {
         // steps 6-8 about the pooled mean: every unit's squared deviations from its own mean and n times the distance between
         // the two means squared; nothing is subtracted from anything but means
@@ -262,11 +268,11 @@ template <bool FWD> __device__ __forceinline__ bool slab_reduce(const SlabArgs& 
             const int k = gl + j * A.G;
             if (k < A.U) {
                 const double n = (double)(k + 1 < A.U ? A.rpu : (int)(A.R - (long long)k * A.rpu)) * (double)A.cpc;
-                const double d = (double)__uint_as_float((unsigned)v[j]) * slab_reciprocal(n) - off;
-                s1 += (double)__uint_as_float((unsigned)(v[j] >> 32)) + n * (d * d);
+                const double d = __longlong_as_double((long long)v[j]) * slab_reciprocal(n) - off;
+                s1 += __longlong_as_double((long long)w[j]) + n * (d * d);
             }
         }
-        lanes_add(1, A.G, [&](auto off) __attribute__((always_inline)) { s1 = lane_add<decltype(off)::value>(s1); });
+        lanes_add(A.G, [&](auto off) __attribute__((always_inline)) { s1 = lane_add<decltype(off)::value>(s1); });
         if (duty && gl == 0) {
             const float hi = (float)mean;
             slab_put(result, hi, (float)(mean - (double)hi));
@@ -281,7 +287,7 @@ template <bool FWD> __device__ __forceinline__ bool slab_reduce(const SlabArgs& 
 // The slab's results into L.res (one wavefront).  False: some are missing.
 template <bool FWD> __device__ __forceinline__ bool slab_results(const SlabArgs& A, SlabLds& L, int slab, bool patient)
 {
-    const unsigned long long* result = slab_rows(A, slab) + (size_t)A.U * A.nch;
+    const unsigned long long* result = slab_rows(A, slab) + (size_t)A.U * A.nch * 2;
     return slab_poll(A, patient, [&] {
         bool there = true;
         for (int c = (int)fresh(threadIdx.x) & (kWave - 1); c < A.rch; c += kWave) {
@@ -673,7 +679,7 @@ __global__ __launch_bounds__(kSlabThreads, P * (ACT == 2 ? 2 : 1) <= (SOLO ? 4 :
         // ---- steps 4-5 and 9-10
         bool ok = true, mine = true;
         if (!SOLO) {
-            if (ch < A.nch && sub == 0) slab_put(slab_rows(A, slab) + (size_t)u * A.nch + ch, (float)tot[0], (float)q[0]);
+            if (ch < A.nch && sub == 0) slab_put_row(A, slab, u, ch, tot[0], q[0]);
             fetched = 0;
             mine = slab_hand_over<true>(A, L, slab, u, [&] {
                 if constexpr (PRE != 0)
@@ -902,10 +908,7 @@ __global__ __launch_bounds__(kSlabThreads, SOLO ? (P * (ACT != 0 ? 3 : 2) <= 8 ?
             db = tot[0];
             dg = (tot[1] - (double)lv * tot[0]) * (double)is;
         } else {
-            if (ch < A.nch && sub == 0) {
-                const float ta = (float)tot[0], tb = (float)((tot[1] - (double)lv * tot[0]) * (double)is);
-                slab_put(slab_rows(A, slab) + (size_t)u * A.nch + ch, ta, tb);
-            }
+            if (ch < A.nch && sub == 0) slab_put_row(A, slab, u, ch, tot[0], (tot[1] - (double)lv * tot[0]) * (double)is);
             fetched = 0;
             mine = slab_hand_over<false>(A, L, slab, u, [&] {
                 if constexpr (PRE != 0)

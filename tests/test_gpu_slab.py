@@ -307,6 +307,25 @@ def test_variance_keeps_its_accuracy_wherever_the_first_value_lies(shape, kind):
     assert err.max() <= 2.0 ** -23
 
 
+@pytest.mark.parametrize("kind", [1.0, 4.0, 30.0])
+@pytest.mark.parametrize("shape", STATISTICS + [(256, 1024, 7, 7, 8, "NCHW", "bf16")], ids=lambda s: "x".join(map(str, s)))
+def test_mean_keeps_its_accuracy(shape, kind):
+    """mean + mean_lo in standard deviations, the first value (the pivot of all sums) `kind` of them off.  The only float
+    sums are a thread's: of its n <= 36 values about its own first one (a rounding error of about 2^-25 sqrt(n) times a standard
+    deviation per value), taken to the pivot by one more rounding (2^-25 kind per value); over the at least 256 threads
+    of a channel they average out to an eighth at the worst of 1024 channels (4 of 16 standard errors)."""
+    print(f"[case] mean {shape} {kind}", flush=True)
+    wl, d, p = _problem(shape, change=_skew(kind, shape[5]))
+    p.forward()
+    torch.cuda.synchronize()
+    assert L.cgbn_get_tuning("last_forward_slab") == 1
+    axes = (0, 1, 2) if wl.layout == "NHWC" else (0, 2, 3)
+    x = G.widen(d["x"], wl.dtype)
+    err = np.abs(p.mean.cpu().numpy().astype(np.float64) + p.mean_lo.cpu().numpy() - x.mean(axes)) / x.std(axes)
+    print(f"[mean error] {err.max():.2e}", flush=True)
+    assert err.max() <= 2.0 ** -25 * (6 + kind) / 4
+
+
 def test_offset_data_keeps_its_accuracy():
     """Normal(100, 0.01) in float32: |mean| is 10^4 standard deviations."""
     wl, d, p = _problem((4, 64, 40, 50, 4, "NHWC", "f32"), base=synth.WORKLOADS["cfg4b"])

@@ -39,13 +39,17 @@ def _check(shape):
         assert rpp * (C * (H * W if layout == "NCHW" else 1)) * (16 // vec) + cols * 16 < 2 ** 31
         if U > 1:
             assert U <= 256                                     # (the compute units of the planning host's default)
-            assert slabs * nch * (U + 2) * 8 <= 2 * L.cgbn_plan_get(*shape, "part_bytes")
+            # rows of two doubles a unit and channel, two pairs of results: in the rows and shard sums of the other kernels
+            assert slabs * nch * (U + 1) * 16 <= 2 * sum(L.cgbn_plan_get(*shape, k) for k in ("part_bytes", "shard_bytes"))
             assert slabs * -(-U // 32) <= C and slabs <= C      # counters and bitmaps inside the sync area
             if slabs * U > 256:                                 # several rounds: slabs end on lines, or are many lines wide
                 assert cols >= 48 or (cols % 8 == 0 and vecs * 16 % 128 == 0)
-    # the rows add at most half a MiB to what the other kernels need
+    # the rows need at most a MiB, or as much again as the other kernels' rows while everything fits the static scratch
     rows = max(L.cgbn_plan_get(*shape, "rows"), *(L.cgbn_plan_get(*shape, f"{d}_rows") for d in ("fwd", "bwd")))
-    assert L.cgbn_plan_get(*shape, "part_bytes") <= max(-(-C * rows * 4 // 256) * 256, 256 << 10)
+    part, own = L.cgbn_plan_get(*shape, "part_bytes"), -(-C * rows * 4 // 256) * 256
+    assert part <= max(2 * own, 512 << 10)
+    if part > max(own, 512 << 10):
+        assert L.cgbn_workspace_bytes(*shape) <= STATIC_SCRATCH
     return taken
 
 
