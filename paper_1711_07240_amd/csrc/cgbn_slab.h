@@ -924,10 +924,12 @@ __global__ __launch_bounds__(kSlabThreads, SOLO ? (P * (ACT != 0 ? 3 : 2) <= 8 ?
                 float dbf = SOLO ? (float)db : L.res[0][ch], dgf = SOLO ? (float)dg : L.res[1][ch];
                 if (!ok) dbf = dgf = __uint_as_float(0x7fc00000u);
                 // dx = gsc * dy + k0 - k2 * (x - mu), see nchw_fused_backward.  SOLO, where a channel may have a handful of
-                // values: gsc * (dy - c1) + (k0 - k2 * (x - mu)), so that what cancels is dy and its mean, as stored
-                const float gs = gm * is, c1 = dbf * A.inv_M, c2 = dgf * A.inv_M, kk = gs * is * c2;
-                L.k0[ch] = SOLO ? kk * lv : kk * lv - gs * c1;
-                if (SOLO) L.k3[ch] = c1;
+                // values: gsc * (dy - c1) + (k0 - k2 * (x - mu)), so that what cancels is dy and its mean, as stored.  k0 is
+                // rounded once: where dy has a mean that is large beside its spread, that rounding is dx's error.
+                const float gs = gm * is, kk = gs * is * (dgf * A.inv_M);
+                const double c1 = (SOLO ? db : (double)dbf) * A.inv_M_f64;
+                L.k0[ch] = (float)((double)kk * (double)lv - (double)gs * (SOLO ? c1 - (double)(float)c1 : c1));
+                if (SOLO) L.k3[ch] = (float)c1;
                 L.k1[ch] = gs;
                 L.k2[ch] = -kk;
                 if ((SOLO || L.last) && ch < A.rch && c0 + ch < A.C) {

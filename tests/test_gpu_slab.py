@@ -335,6 +335,28 @@ def test_offset_data_keeps_its_accuracy():
     G.check_against_oracle(p.results(), _reference(wl, d), wl.dtype, "offset")
 
 
+@pytest.mark.parametrize("shape", [(4, 256, 40, 50, 4, "NHWC", "f32"), (2, 256, 100, 150, 2, "NHWC", "f32"), (1, 512, 29, 51, 1, "NHWC", "f32"),
+                                   (300, 256, 7, 7, 5, "NCHW", "f32")], ids=lambda s: "x".join(map(str, s)))
+def test_gradients_with_a_mean(shape):
+    """dy = 1 + noise: dx is what is left of dy when its mean has been taken off.  What a channel's constants leave of the mean, in
+    units of it, root mean square over the channels: two roundings to float (dbeta and the constant), each uniform within
+    2^-24 at the most."""
+    print(f"[case] offset gradients {shape}", flush=True)
+    wl, d, p = _problem(shape)
+    axes = (0, 1, 2) if wl.layout == "NHWC" else (0, 2, 3)
+    factor = np.random.default_rng(3).uniform(0.5, 1.5, wl.C).astype(np.float32)
+    factor = factor if wl.layout == "NHWC" else factor[:, None, None]
+    d["dy"] = ((1 + 1e-2 * d["dy"]) * factor).astype(np.float32)
+    p.dy = G.to_dev(d["dy"])
+    p.forward()
+    p.backward()
+    _ran_here()
+    got, ref = p.results(), _reference(wl, d)
+    left = (got["dx"] - ref["dx"]).mean(axes) / (d["gamma"] * ref["invstd"] * d["dy"].astype(np.float64).mean(axes))
+    print(f"[left] {G.rms(left):.2e}", flush=True)
+    assert G.rms(left) <= np.sqrt(2 / 3) * 2.0 ** -24
+
+
 @pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
 @pytest.mark.parametrize("shape", [(2, 32, 30, 40, 2, "NHWC", "bf16"), (4, 64, 40, 50, 4, "NHWC", "f32")], ids=["one", "several"])
 def test_a_bad_value_stays_in_its_channel(shape, bad):
