@@ -554,8 +554,13 @@ __device__ __forceinline__ const u32x4& slab_fetched(const u32x4* ext, int slot,
 // end loses (mean - p)^2 / variance times the accuracy of a float sum: relative error of 1/sqrt, the worst of many
 // channels, pivot 4 standard deviations off 8.8e-7, here 6.1e-8; a few activations among zeros, the
 // first of them the pivot, 6.3e-6 and 7.8e-8.)
+//
+// Launch bounds.  The plan counts one workgroup per compute unit where there are several units, which leaves a wavefront
+// 256 registers; only variants that need no more than 128 anyway are held to them.  (P = 18 held to 128 kept 20 to 60
+// bytes a lane in memory: forward of 256 x 1024 planes of 7x7 bf16 24.3 us, not held 21.7; of 67200 x 256 channels-last 26.8 and 24.6;
+// backward, P = 9, of 26980 x 296 26.8 and 24.5.)
 template <typename T, int ACT, int P, bool SOLO>
-__global__ __launch_bounds__(kSlabThreads, P * (ACT == 2 ? 2 : 1) <= (SOLO ? 4 : 18) ? 4 : 2) void slab_forward(SlabArgs A)
+__global__ __launch_bounds__(kSlabThreads, P * (ACT == 2 ? 2 : 1) <= (SOLO ? 4 : 12) ? 4 : 2) void slab_forward(SlabArgs A)
 {
     constexpr int VEC = 16 / (int)sizeof(T);
     constexpr bool EARLY = ACT == 2 && P <= 20;
@@ -792,7 +797,7 @@ __global__ __launch_bounds__(kSlabThreads, P * (ACT == 2 ? 2 : 1) <= (SOLO ? 4 :
 // output's vectors are loaded beside the other two where the registers allow (P <= 10), else through the storage x takes
 // afterwards.
 template <typename T, int ACT, int P, bool SOLO>
-__global__ __launch_bounds__(kSlabThreads, SOLO ? (P * (ACT != 0 ? 3 : 2) <= 8 ? 4 : 2) : (P <= 9 ? 4 : 2)) void slab_backward(SlabArgs A)
+__global__ __launch_bounds__(kSlabThreads, P * (ACT != 0 ? 3 : 2) <= (SOLO ? 8 : 12) ? 4 : 2) void slab_backward(SlabArgs A)
 {
     constexpr int VEC = 16 / (int)sizeof(T);
     constexpr bool THREE = ACT != 0 && P <= (SOLO ? 10 : 6);
