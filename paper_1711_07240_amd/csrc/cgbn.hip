@@ -364,12 +364,19 @@ bool cut_slabs(SlabPlan* s, int C, int cols, int nch, long long U, long long row
     return true;
 }
 
-// Several units per slab: U so that the launch is shortest.  A round of resident units costs the passes of a unit plus a
-// part that every hand-over costs, about that of 10 passes (6 us, against 0.6 us per pass of 512 x 16 bytes on every
-// compute unit); rounds are whole.  (Two units of half the size per compute unit instead of one: fp32 67200 x 1024 forward /
-// backward 163 / 259 us against 142 / 224.)  Slabs that do not
-// end on line boundaries share lines with their neighbours, so they must all be in flight together: one round
-// (measured, fp32 268800 x 136 in four rounds 170 us, the sweeps 101).
+// Several units per slab: U so that the launch is shortest.  Rounds are whole; a round of several costs the passes of a unit plus a part that
+// every hand-over costs, about that of 10 passes (6 us, against 0.6 us per pass of 512 x 16 bytes on every compute unit).  In one
+// round what counts beside the passes, made and (forward) built into the variant, is what each unit adds to the hand-over: its
+// row, its count, its fetches.  The weights are fitted to 137 calls of 0.5 to 70 MB, each with 5 to 25 numbers of units; what they pick
+// is 1 to 2 % slower than the best in the mean.  Measured, forward / backward us: bf16 8400 x 64 with 255 units of half a pass
+// 16.5 / 15.0, 132 of one 14.1 / 13.1, 64 of three 13.1 / 12.4, 12 of eleven 14.5 / 14.8; 8400 x 256 with 64 of three 16.6 / 15.7, 24 of six
+// 15.1 / 14.8.  (Two units of half the size per compute unit instead of one: fp32 67200 x 1024 forward / backward 163 / 259 us
+// against 142 / 224.)
+//   One round: the fewest units of as many passes, so that the last pass is as full as it gets, in whole eights: units are
+// dealt to the 8 XCDs in turn, and the same rows of neighbouring slabs then meet in one L2.  Where slabs do not end on line
+// boundaries they share those lines: fp32 22400 x 264, 31 units 23.8 / 28.7, 32 units 21.5 / 24.5; 70200 x 112, 63 units 27.7 / 36.3, 64
+// units 24.3 / 29.7 (rows of whole lines: no difference).  Such slabs must also all be in flight together (measured, fp32
+// 268800 x 136 in four rounds 170 us, the sweeps 101).
 bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_words, int cus, bool forward)
 {
     const int rpp = kSlabThreads / cols;
@@ -380,16 +387,27 @@ bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_wor
     long long most = cus < s->R ? cus : s->R;
     if (most > kSlabRowsPerLane * kWave) most = kSlabRowsPerLane * kWave;
     if (most > row_words / (2 * slabs * nch) - 1) most = row_words / (2 * slabs * nch) - 1;
+    const long long top = cus / slabs < most ? cus / slabs : most;
     long long best = 0, best_cost = 0;
-    for (int k = 0; k < 8; ++k) {
-        // the fewest units and a few more; as many as fill the compute units once, or half of them, ...
-        const long long U = k < 4 ? least + k : cus / slabs < most ? (cus / slabs) >> (k - 4) : most >> (k - 4);
+    for (int k = 0; k < 12; ++k) {
+        // the fewest units and a few more; as many as fill the compute units once, or 3/4, 1/2, 3/8, ... of them
+        long long U = k < 4 ? least + k : (k & 1 ? top * 3 >> (k / 2) : top >> (k / 2 - 2));
         if (U < least || U > most) continue;
-        const long long grid = cus / U * U, units = slabs * U;
-        const long long rounds = (units + grid - 1) / grid;
-        if (rounds > 1 && !lines) continue;
-        const long long rows = (s->R + U - 1) / U, passes = (rows + rpp - 1) / rpp;
-        const long long cost = rounds * (passes + 10);
+        long long cost;
+        if (slabs * U > cus / U * U) {
+            if (!lines) continue;
+            const long long grid = cus / U * U, passes = ((s->R + U - 1) / U + rpp - 1) / rpp;
+            cost = (slabs * U + grid - 1) / grid * (passes * 60 + 600);
+        } else {
+            if (!lines && U >= 16 && U / 8 * 8 >= least) U = U / 8 * 8;
+            const long long passes = ((s->R + U - 1) / U + rpp - 1) / rpp;
+            const long long fewest = (s->R + passes * rpp - 1) / (passes * rpp), eights = (fewest + 7) / 8 * 8;
+            if (fewest < 8) U = fewest;
+            else if (eights <= U) U = eights;
+            if (U < least) continue;
+            cost = 255 + (forward ? slab_variant(true, false, passes) * 10 + passes * 10 + U * 75 / 100 : passes * 40 + U / 4) + slabs * U * 60 / 100;
+            if (!lines && slabs > 1 && U % 8 != 0) cost = cost * 5 / 4;
+        }
         if (best == 0 || cost < best_cost) { best = U; best_cost = cost; }
     }
     return best >= 2 && cut_slabs(s, C, cols, nch, best, row_words, cus, forward);

@@ -44,6 +44,9 @@ def _check(shape):
             assert slabs * -(-U // 32) <= C and slabs <= C      # counters and bitmaps inside the sync area
             if slabs * U > 256:                                 # several rounds: slabs end on lines, or are many lines wide
                 assert cols >= 48 or (cols % 8 == 0 and vecs * 16 % 128 == 0)
+            else:                                               # one round: no more units than their passes need, in whole eights
+                fewest = -(-R // (-(-rpu // rpp) * rpp))
+                assert U <= (fewest if fewest < 8 else -(-fewest // 8) * 8)
     # the rows need at most a MiB, or as much again as the other kernels' rows while everything fits the static scratch
     rows = max(L.cgbn_plan_get(*shape, "rows"), *(L.cgbn_plan_get(*shape, f"{d}_rows") for d in ("fwd", "bwd")))
     part, own = L.cgbn_plan_get(*shape, "part_bytes"), -(-C * rows * 4 // 256) * 256
@@ -84,5 +87,8 @@ def test_detector_layers():
     assert L.cgbn_plan_get(*one, "sfwd_U") == 1 and L.cgbn_plan_get(*one, "sbwd_U") == 1 and _check(one) == 2
     many = (16, 256, 50, 84, "NHWC", "bf16", 8)
     assert L.cgbn_plan_get(*many, "sfwd_U") > 1 and _check(many) == 2
+    small = (35, 16, 14, 16, "NHWC", "f32", 35)                 # 62 full passes: every further unit only costs
+    for d in ("sfwd", "sbwd"):
+        assert 1 < L.cgbn_plan_get(*small, f"{d}_U") <= 64
     odd = (16, 250, 50, 84, "NHWC", "bf16", 8)                  # channels that are no whole vectors
     assert L.cgbn_plan_get(*odd, "sfwd_ok") == 0 and L.cgbn_plan_get(*odd, "sbwd_ok") == 0
