@@ -318,7 +318,7 @@ long long cgbn_get_tuning(const char* key);
  * access), "LPPC" (register slots per small plane; 0: large planes), "LPP" (slots a plane fills),
  * "IPU" (images per unit), "U" (units per channel), "tp" / "TL" (tiles per large plane, tile
  * elements), "rows", "rps", "G", "big" (0, or which LDS variant), "total_units".
- * Column-slab kernels, prefix "sfwd_" or "sbwd_": "ok" (the shape takes them instead of
+ * Column-slab kernels, prefix "sfwd_" or "sbwd_" ("sfwds_": the forward with a shortcut, "sbwdm_": the masked backward): "ok" (the shape takes them instead of
  * sweeps), "first" (... also before the single-launch NCHW kernels), "vecs" (16-byte vectors per row of the matrix), "R" (its rows), "cpc" (columns per channel), "cols" (vectors per
  * slab), "slabs", "nch" (channels per slab, rounded up to a power of two), "rpp" (rows per pass),
  * "tpc" (threads that add one channel's partial sums), "U" (units per slab), "rpu" (rows per unit),

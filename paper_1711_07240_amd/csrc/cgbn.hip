@@ -183,6 +183,7 @@ struct Plan {
     long long grid;       // workgroups of one sweep
     FusedPlan ff, fb;     // register-resident path, forward and backward
     SlabPlan sf, sb;      // column-slab path
+    SlabPlan sfs, sbm;    // ... of a forward with a shortcut, of a masked backward
     // workspace layout (byte offsets)
     size_t off_part0, off_part1, off_sh0, off_sh1, off_mlo, off_sync, bytes;
 };
@@ -366,7 +367,7 @@ bool cut_slabs(SlabPlan* s, int C, int cols, int nch, long long U, long long row
 
 // Several units per slab: U so that the launch is shortest.  Rounds are whole; a round of several costs the passes of a unit plus a part that
 // every hand-over costs, about that of 10 passes (6 us, against 0.6 us per pass of 512 x 16 bytes on every compute unit).  In one
-// round what counts beside the passes, made and (forward) built into the variant, is what each unit adds to the hand-over: its
+// round what counts beside the passes, made and (forward that reads x alone) built into the variant, is what each unit adds to the hand-over: its
 // row, its count, its fetches.  The weights are fitted to 137 calls of 0.5 to 70 MB, each with 5 to 25 numbers of units; what they pick
 // is 1 to 2 % slower than the best in the mean.  Measured, forward / backward us: bf16 8400 x 64 with 255 units of half a pass
 // 16.5 / 15.0, 132 of one 14.1 / 13.1, 64 of three 13.1 / 12.4, 12 of eleven 14.5 / 14.8; 8400 x 256 with 64 of three 16.6 / 15.7, 24 of six
@@ -377,7 +378,7 @@ bool cut_slabs(SlabPlan* s, int C, int cols, int nch, long long U, long long row
 // boundaries they share those lines: fp32 22400 x 264, 31 units 23.8 / 28.7, 32 units 21.5 / 24.5; 70200 x 112, 63 units 27.7 / 36.3, 64
 // units 24.3 / 29.7 (rows of whole lines: no difference).  Such slabs must also all be in flight together (measured, fp32
 // 268800 x 136 in four rounds 170 us, the sweeps 101).
-bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_words, int cus, bool forward)
+bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_words, int cus, bool forward, bool second)
 {
     const int rpp = kSlabThreads / cols;
     const long long cap = (long long)rpp * slab_most(forward, false);
@@ -405,7 +406,7 @@ bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_wor
             if (fewest < 8) U = fewest;
             else if (eights <= U) U = eights;
             if (U < least) continue;
-            cost = 255 + (forward ? slab_variant(true, false, passes) * 10 + passes * 10 + U * 75 / 100 : passes * 40 + U / 4) + slabs * U * 60 / 100;
+            cost = 255 + (forward && !second ? slab_variant(true, false, passes) * 10 + passes * 10 + U * 75 / 100 : passes * 40 + U / 4) + slabs * U * 60 / 100;
             if (!lines && slabs > 1 && U % 8 != 0) cost = cost * 5 / 4;
         }
         if (best == 0 || cost < best_cost) { best = U; best_cost = cost; }
@@ -413,29 +414,46 @@ bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_wor
     return best >= 2 && cut_slabs(s, C, cols, nch, best, row_words, cus, forward);
 }
 
-// Which calls take the column-slab kernels, and how they are cut.  Channels-last, C a multiple of a 16-byte vector:
-//   - up to 3072 pixels one workgroup per slab of 2 vectors (forward 5120 while the tensor is at most 6 MB): one launch, nothing
-//     to hand over.  Backward: slabs of one vector while that gives every compute unit at most one workgroup, since fewer bytes
-//     per compute unit then count for more than the half lines (measured, 2 vectors -> 1, with ReLU: bf16 2100 x 512 12.8 ->
-//     11.1, 2100 x 2048 20.2 -> 16.9; beyond, fp32 2100 x 2048 20.5 -> 24.0; forward 11.0 -> 12.3).  More pixels per workgroup than that are slower than several units.  Measured, forward / backward
-//     us, sweeps -> one unit -> several: bf16 2100 x 512 22 / 30 -> 9.6 / 11.7 -> 13.8 / 13.2; 3200 x 1024 26 / 32 -> 13.9 /
-//     20.9 -> 16.1 / 16.2; 8400 x 512 27 / 32 -> 23 / 32 -> 17.9 / 17.7.
+// channels-last: up to how many pixels a slab is one workgroup (rows of at most 64 bytes: a workgroup shares its lines with few others)
+long long few_pixels(bool forward, bool second, long long row_bytes)
+{
+    if (row_bytes <= 64 || (forward && !second)) return 3072;
+    if (forward) return 2560;
+    if (!second) return 2688;
+    return row_bytes < 1024 ? 1536 : row_bytes <= 4096 ? 2112 : 1280;
+}
+
+// Which calls take the column-slab kernels, and how they are cut.  `second`: the forward adds a shortcut, the backward is
+// masked by the stored output: a tensor more.  Channels-last, C a multiple of a 16-byte vector:
+//   - few pixels: one workgroup per slab, one launch, nothing to hand over.  Slabs of 2 vectors, backward of one while that
+//     gives every compute unit at most one workgroup, since fewer bytes per compute unit then count for more than the half
+//     lines (measured, 2 vectors -> 1, with ReLU: bf16 2100 x 512 12.8 -> 11.1, 2100 x 2048 20.2 -> 16.9; beyond, fp32 2100 x 2048 20.5 ->
+//     24.0; forward 11.0 -> 12.3).  How few: where several units become faster.  Measured over 16 to 2048 channels of both types,
+//     us, one unit / several, e.g. 256 channels fp32: forward of 3000 8.5 / 11.8, of 4200 11.7 / 12.6, of 5000 16.1 / 13.3; with shortcut of
+//     2100 9.8 / 13.0, of 2600 13.8 / 13.3; backward of 2600 10.9 / 12.7, of 3000 12.5 / 12.7 (128 channels 13.0 / 11.8); masked of 1500
+//     10.0 / 13.1, of 2100 14.6 / 14.4 (128 channels 14.7 / 12.4, 1024 bf16 17.3 / 17.3, 2048 fp32 34.8 / 23.5).
 //   - beyond, units of 128-byte columns wherever a slab's units are resident together.  Measured, sweeps -> units: bf16
-//     67200 x 256 38 / 49 -> 26 / 30, 16800 x 2048 67 / 94 -> 34 / 52, 268800 x 512 181 / 288 -> 140 / 239; fp32 67200 x 1024
-//     168 / 255 -> 129 / 193, 268800 x 1024 599 / 974 -> at most 568 / 908.  Narrower columns lose (half a
+//     67200 x 256 38 / 49 -> 25 / 30, 16800 x 2048 67 / 94 -> 34 / 52, 268800 x 512 170 / 274 -> 135 / 233; fp32 67200 x 1024
+//     154 / 247 -> 126 / 188, 268800 x 1024 599 / 974 -> at most 568 / 908.  Narrower columns lose (half a
 //     line per request), wider ones make a slab's rows more than the hand-over bears.
+//   - a shortcut that does not fit the registers beside x (P > 20) is fetched batch by batch during the write-out, each batch behind the
+//     stores of the one before.  That is slower than the sweeps for float in several rounds (304290 x 192 172 us, so 275; 67200 x 1024
+//     201, 209), for float slabs that share lines unless their units are in whole eights (224400 x 80 67, 80), and for bf16 in
+//     rounds that are not well filled (45560 x 832 5 %); it is faster where rows of more than 4 KiB crowd the sweeps (164724 x 1376 fp32
+//     269, 198).
 //
 // NCHW, planes of at most 512 values, C a multiple of a 16-byte vector's elements (a slab starts and ends on 16 bytes):
 //   - images that fit one workgroup: instead of the sweeps always.  Instead of the single-launch kernels where a channel is
 //     several of their units, and where a thread holds few vectors and there are 1024 channels, or 128 and 24 images: those
 //     kernels move one plane per wavefront at a time and leave most of its lanes idle.  Measured, them -> here, forward / backward us: fp32 256 x 1024 planes of 4x4 100 /
 //     135 -> 12 / 14, bf16 16 x 2048 of 8x8 19 / 17 -> 8.3 / 8.0; with few channels and images they stay ahead: fp32 8 x 256
-//     of 16x20 6.3 / 5.6 against 6.4 / 6.4, bf16 16 x 256 of 20x20 7.6 / 7.4 against 11.5 / 12.
+//     of 16x20 6.3 / 5.6 against 6.4 / 6.4, bf16 16 x 256 of 20x20 7.6 / 7.4 against 11.5 / 12.  Not with a second tensor, more than
+//     16 passes and few slabs: bf16 20 x 24 of 13x21 with shortcut 12.6 against 14.8, 20 x 48 of 15x23 masked 13.8 against 16.5.
 //   - several units per slab from 6 MB on (below, the hand-over costs what a launch less saves), and there before the
 //     single-launch kernels while planes are at most 1 KiB and the tensor 200 MB (backward: 512 bytes, float 800, 100 MB): bf16 256 x 1024 of 7x7 31 / 37 -> 23 /
 //     26, of 12x12 110 / 125 -> 49 / 60; fp32 100 x 1024 of 16x20 75 / 97 against 86 / 124.
 void make_slab_plan(int N, int C, long long HW, int layout, int eb, long long row_words, int cus, const FusedPlan& f, bool forward,
-                    SlabPlan* s)
+                    bool second, SlabPlan* s)
 {
     std::memset(s, 0, sizeof(*s));
     const int vec = 16 / eb;
@@ -445,13 +463,19 @@ void make_slab_plan(int N, int C, long long HW, int layout, int eb, long long ro
         s->R = (long long)N * HW;
         s->row_bytes = (long long)C * eb;
         s->cpc = 1;
-        if (s->R <= 3072 || (forward && s->R <= 5120 && s->R * s->row_bytes <= 6000000)) {
+        if (s->R <= few_pixels(forward, second, s->row_bytes) || (forward && !second && s->R <= 5120 && s->R * s->row_bytes <= 6000000)) {
             const int cols = s->vecs < 2 || (!forward && s->vecs <= cus) ? 1 : 2;
             if (cut_slabs(s, C, cols, cols * vec, 1, row_words, cus, forward)) return;
         }
         // about 8 vectors, as even as the row allows
         const int slabs = s->vecs < 12 ? 1 : (s->vecs + 4) / 8, cols = (s->vecs + slabs - 1) / slabs;
-        cut_slabs_in_units(s, C, cols, ceil_pow2(cols * vec), row_words, cus, forward);
+        if (cut_slabs_in_units(s, C, cols, ceil_pow2(cols * vec), row_words, cus, forward, second) && forward && second && s->P > 20 &&
+            s->row_bytes <= 4096) {
+            const int inflight = cus / s->U, rounds = (s->slabs + inflight - 1) / inflight;
+            if (eb == 4 ? rounds > 1 || !(s->U % 8 == 0 || (s->row_bytes % 128 == 0 && cols == 8))
+                        : rounds > 1 && s->total_units * 3 < 2LL * rounds * cus)
+                s->ok = 0;
+        }
         return;
     }
     const long long row_vecs = (long long)C * HW / vec;
@@ -464,27 +488,26 @@ void make_slab_plan(int N, int C, long long HW, int layout, int eb, long long ro
     while (nch * 2 <= kSlabMaxChannels && nch < C && (long long)nch / vec * HW < 8) nch *= 2;
     const int cols = (int)(nch / vec * HW), rpp = kSlabThreads / cols;
     if (N <= rpp * slab_most(forward, true) && cut_slabs(s, C, cols, nch, 1, row_words, cus, forward)) {
+        if (second && N > 16 * rpp && s->slabs < 16) s->ok = 0;
         s->first = !f.ok || f.U > 1 || (C >= 1024 && s->P <= (forward ? 12 : 8)) ||
                    (N >= 24 && C >= 128 && s->P <= (forward ? 8 : 4));
         return;
     }
     if (N * s->row_bytes < 6000000) return;
-    if (cut_slabs_in_units(s, C, cols, nch, row_words, cus, forward))
+    if (cut_slabs_in_units(s, C, cols, nch, row_words, cus, forward, second))
         s->first = !f.ok || (f.U > 1 && (forward ? HW * eb <= 1024 && N * s->row_bytes <= 200000000 : HW * eb <= (eb == 2 ? 512 : 800) && N * s->row_bytes <= 100000000));
 }
 
 // compute units of the current device (256 if there is none to ask)
 int compute_units()
 {
-    static std::mutex lock;
-    static std::map<int, int> cache;
+    static std::atomic<int> known[kMaxDevices];
     int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 256;
-    std::lock_guard<std::mutex> hold(lock);
-    auto it = cache.find(dev);
-    if (it != cache.end()) return it->second;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 256;
+    cus = known[dev].load(std::memory_order_relaxed);
+    if (cus > 0) return cus;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
-    cache[dev] = cus;
+    known[dev].store(cus, std::memory_order_relaxed);
     return cus;
 }
 
@@ -632,10 +655,16 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
     size_t room = others > (1u << 20) ? others : (1u << 20);
     if (sync + others + 2 * part + mlo <= (size_t)CGBN_STATIC_SCRATCH_BYTES && others + 2 * part > room) room = others + 2 * part;
     const long long row_words = (long long)(room / sizeof(double));
-    const int cus = compute_units();
-    make_slab_plan(N, C, HW, layout, p->eb, row_words, cus, p->ff, true, &p->sf);
-    make_slab_plan(N, C, HW, layout, p->eb, row_words, cus, p->fb, false, &p->sb);
-    for (const SlabPlan* s : {&p->sf, &p->sb})
+    const int cus = C % (16 / p->eb) == 0 && (layout == CGBN_NHWC || HW <= kSlabThreads) ? compute_units() : 0;    // (else no slab plan needs it)
+    for (const bool forward : {true, false}) {
+        SlabPlan &one = forward ? p->sf : p->sb, &two = forward ? p->sfs : p->sbm;
+        make_slab_plan(N, C, HW, layout, p->eb, row_words, cus, forward ? p->ff : p->fb, forward, false, &one);
+        two = one;
+        // (what a second tensor changes: see there)
+        if (one.ok && (one.U == 1 ? layout == CGBN_NCHW || one.R > few_pixels(forward, true, one.row_bytes) : forward))
+            make_slab_plan(N, C, HW, layout, p->eb, row_words, cus, forward ? p->ff : p->fb, forward, true, &two);
+    }
+    for (const SlabPlan* s : {&p->sf, &p->sfs, &p->sb, &p->sbm})
         if (s->ok && s->U > 1) {
             const size_t need = (size_t)slab_row_words(*s) * sizeof(double);
             if (need > 2 * part + 2 * sh) part = align256((need - 2 * sh + 1) / 2);
@@ -1233,8 +1262,9 @@ cgbn_status forward_impl(const Tuning& T, const void* x, const void* shortcut, b
     float* mlo = reinterpret_cast<float*>(ws + p.off_mlo);
     const int rev = (int)p.t.reverse;
 
-    const bool slab = p.t.fused && p.t.one_sweep_stats && p.sf.ok;
-    if (p.t.fused && p.ff.ok && !(slab && p.sf.first)) {
+    const SlabPlan& sp = shortcut ? p.sfs : p.sf;
+    const bool slab = p.t.fused && p.t.one_sweep_stats && sp.ok;
+    if (p.t.fused && p.ff.ok && !(slab && sp.first)) {
         FusedArgs F = fused_args(p, p.ff, ws);
         F.x = x; F.out = y; F.gamma = gamma; F.beta = beta; F.eps = (double)eps; F.aux = shortcut;
         F.mean = mean; F.mean_lo = mlo; F.mean_lo_user = mean_lo; F.invstd = invstd;
@@ -1256,13 +1286,13 @@ cgbn_status forward_impl(const Tuning& T, const void* x, const void* shortcut, b
 
     g_last_forward_slab = slab;
     if (slab) {
-        SlabArgs F = slab_args(p, p.sf, ws);
+        SlabArgs F = slab_args(p, sp, ws);
         F.x = x; F.dy = shortcut; F.out = y; F.gamma = gamma; F.beta = beta; F.eps = (double)eps;
         F.mean = mean; F.mean_lo = mean_lo; F.invstd = invstd;
         const bool f32 = p.dtype == CGBN_F32;
-        if (relu && shortcut) return f32 ? launch_slab_t<float, true, 2>(p, p.sf, F, st) : launch_slab_t<bf16_t, true, 2>(p, p.sf, F, st);
-        if (relu) return f32 ? launch_slab_t<float, true, 1>(p, p.sf, F, st) : launch_slab_t<bf16_t, true, 1>(p, p.sf, F, st);
-        return f32 ? launch_slab_t<float, true, 0>(p, p.sf, F, st) : launch_slab_t<bf16_t, true, 0>(p, p.sf, F, st);
+        if (relu && shortcut) return f32 ? launch_slab_t<float, true, 2>(p, sp, F, st) : launch_slab_t<bf16_t, true, 2>(p, sp, F, st);
+        if (relu) return f32 ? launch_slab_t<float, true, 1>(p, sp, F, st) : launch_slab_t<bf16_t, true, 1>(p, sp, F, st);
+        return f32 ? launch_slab_t<float, true, 0>(p, sp, F, st) : launch_slab_t<bf16_t, true, 0>(p, sp, F, st);
     }
 
     SweepArgs A = sweep_args(p);
@@ -1311,8 +1341,9 @@ cgbn_status backward_impl(const Tuning& T, const void* dy, const void* y, const 
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int rev = (int)p.t.reverse;
 
-    const bool slab = p.t.fused && p.sb.ok;
-    if (p.t.fused && p.fb.ok && !(slab && p.sb.first)) {
+    const SlabPlan& sp = relu ? p.sbm : p.sb;
+    const bool slab = p.t.fused && sp.ok;
+    if (p.t.fused && p.fb.ok && !(slab && sp.first)) {
         FusedArgs F = fused_args(p, p.fb, ws);
         F.x = x; F.dy = dy; F.out = dx; F.gamma = gamma; F.aux = y; F.out2 = dshortcut;
         F.mean = const_cast<float*>(mean); F.mean_lo = const_cast<float*>(mean_lo);
@@ -1333,13 +1364,13 @@ cgbn_status backward_impl(const Tuning& T, const void* dy, const void* y, const 
 
     g_last_backward_slab = slab;
     if (slab) {
-        SlabArgs F = slab_args(p, p.sb, ws);
+        SlabArgs F = slab_args(p, sp, ws);
         F.x = x; F.dy = dy; F.aux = y; F.out = dx; F.out2 = dshortcut; F.gamma = gamma;
         F.mean = const_cast<float*>(mean); F.mean_lo = const_cast<float*>(mean_lo); F.invstd = const_cast<float*>(invstd);
         F.dgamma = dgamma; F.dbeta = dbeta;
         const bool f32 = p.dtype == CGBN_F32;
-        if (relu) return f32 ? launch_slab_t<float, false, 1>(p, p.sb, F, st) : launch_slab_t<bf16_t, false, 1>(p, p.sb, F, st);
-        return f32 ? launch_slab_t<float, false, 0>(p, p.sb, F, st) : launch_slab_t<bf16_t, false, 0>(p, p.sb, F, st);
+        if (relu) return f32 ? launch_slab_t<float, false, 1>(p, sp, F, st) : launch_slab_t<bf16_t, false, 1>(p, sp, F, st);
+        return f32 ? launch_slab_t<float, false, 0>(p, sp, F, st) : launch_slab_t<bf16_t, false, 0>(p, sp, F, st);
     }
 
     SweepArgs A = sweep_args(p);
@@ -1539,9 +1570,10 @@ long long cgbn_plan_get(int N, int C, int H, int W, cgbn_layout layout, cgbn_dty
         if (!std::strcmp(k, "total_units")) return f.total_units;
         return -1;
     }
-    if (!std::strncmp(key, "sfwd_", 5) || !std::strncmp(key, "sbwd_", 5)) {
-        const SlabPlan& s = key[1] == 'b' ? p.sb : p.sf;
-        const char* k = key + 5;
+    if (!std::strncmp(key, "sfwd_", 5) || !std::strncmp(key, "sbwd_", 5) || !std::strncmp(key, "sfwds_", 6) || !std::strncmp(key, "sbwdm_", 6)) {
+        const bool second = key[4] != '_';
+        const SlabPlan& s = key[1] == 'b' ? (second ? p.sbm : p.sb) : (second ? p.sfs : p.sf);
+        const char* k = key + (second ? 6 : 5);
         if (!std::strcmp(k, "ok")) return s.ok;
         if (!std::strcmp(k, "first")) return s.first;
         if (!std::strcmp(k, "cols")) return s.cols;

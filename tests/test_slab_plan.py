@@ -17,7 +17,7 @@ def _check(shape):
     N, C, H, W, layout, dtype, K = shape
     vec = 4 if dtype == "f32" else 8
     taken = 0
-    for d in ("sfwd", "sbwd"):
+    for d in ("sfwd", "sfwds", "sbwd", "sbwdm"):
         g = lambda k: L.cgbn_plan_get(*shape, f"{d}_{k}")
         if not g("ok"):
             continue
@@ -35,7 +35,7 @@ def _check(shape):
         assert cols * vec % cpc == 0 and cols * vec // cpc <= nch <= MAX_CHANNELS and nch & (nch - 1) == 0
         assert tpc & (tpc - 1) == 0 and 1 <= tpc <= 64 and tpc * nch <= THREADS
         # registers: a kernel variant with room for the unit's passes
-        assert rpp == THREADS // cols and rpu <= rpp * P and P in VARIANTS[d, U == 1]
+        assert rpp == THREADS // cols and rpu <= rpp * P and P in VARIANTS[d[:4], U == 1]
         assert rpp * (C * (H * W if layout == "NCHW" else 1)) * (16 // vec) + cols * 16 < 2 ** 31
         if U > 1:
             assert U <= 256                                     # (the compute units of the planning host's default)
@@ -84,11 +84,16 @@ def test_random_shapes(seed, layout):
 
 def test_detector_layers():
     one = (2, 512, 25, 42, "NHWC", "bf16", 2)
-    assert L.cgbn_plan_get(*one, "sfwd_U") == 1 and L.cgbn_plan_get(*one, "sbwd_U") == 1 and _check(one) == 2
+    assert L.cgbn_plan_get(*one, "sfwd_U") == 1 and L.cgbn_plan_get(*one, "sbwd_U") == 1 and _check(one) == 4
     many = (16, 256, 50, 84, "NHWC", "bf16", 8)
-    assert L.cgbn_plan_get(*many, "sfwd_U") > 1 and _check(many) == 2
+    assert L.cgbn_plan_get(*many, "sfwd_U") > 1 and _check(many) == 4
     small = (35, 16, 14, 16, "NHWC", "f32", 35)                 # 62 full passes: every further unit only costs
     for d in ("sfwd", "sbwd"):
         assert 1 < L.cgbn_plan_get(*small, f"{d}_U") <= 64
+    # a second tensor: float shortcuts in several rounds go to the sweeps, masked backwards of this many pixels to several units
+    large = (10, 192, 161, 189, "NHWC", "f32", 2)
+    assert L.cgbn_plan_get(*large, "sfwd_ok") == 1 and L.cgbn_plan_get(*large, "sfwds_ok") == 0
+    head = (28, 32, 9, 12, "NHWC", "f32", 4)
+    assert L.cgbn_plan_get(*head, "sfwd_U") == 1 and L.cgbn_plan_get(*head, "sbwdm_U") > 1
     odd = (16, 250, 50, 84, "NHWC", "bf16", 8)                  # channels that are no whole vectors
     assert L.cgbn_plan_get(*odd, "sfwd_ok") == 0 and L.cgbn_plan_get(*odd, "sbwd_ok") == 0
