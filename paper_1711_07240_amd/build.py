@@ -2,7 +2,8 @@
 
 The host code and the multi-sweep kernels are one translation unit; the NCHW
 single-launch kernels are instantiated in ten more (element type x direction
-x activation), the column-slab kernels in four (element type x direction),
+x activation), the column-slab kernels in eight (element type x direction x
+register limit),
 compiled side by side, then everything is linked into one shared library."""
 
 from __future__ import annotations
@@ -29,7 +30,8 @@ FLAGS = [
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
 
-# the column-slab kernels keep their unit in registers: one whose registers spill is a build error
+# the column-slab kernels keep their unit in registers: one whose registers spill is a build error (but for those held to half the
+# registers on purpose)
 NO_SCRATCH = ["-Xarch_device", "-Wframe-larger-than=0", "-Xarch_device", "-Werror=frame-larger-than"]
 
 
@@ -44,8 +46,10 @@ def _units(obj_dir):
                 units.append((obj, os.path.join(CSRC, "cgbn_fused_inst.hip"),
                               [f"-DCGBN_INST_T={t}", f"-DCGBN_INST_F32={int(t == 'float')}", f"-DCGBN_INST_FWD={fwd}",
                                f"-DCGBN_INST_ACT={act}"]))
-            obj = os.path.join(OBJ, f"slab_{tname}_{'fwd' if fwd else 'bwd'}.o")
-            units.append((obj, os.path.join(CSRC, "cgbn_slab_inst.hip"), [f"-DCGBN_INST_T={t}", f"-DCGBN_INST_FWD={fwd}"] + NO_SCRATCH))
+            for dense in (0, 1):
+                obj = os.path.join(OBJ, f"slab_{tname}_{'fwd' if fwd else 'bwd'}{'_dense' if dense else ''}.o")
+                units.append((obj, os.path.join(CSRC, "cgbn_slab_inst.hip"),
+                              [f"-DCGBN_INST_T={t}", f"-DCGBN_INST_FWD={fwd}", f"-DCGBN_INST_DENSE={dense}"] + ([] if dense else NO_SCRATCH)))
     return units
 
 

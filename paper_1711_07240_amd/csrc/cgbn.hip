@@ -53,18 +53,26 @@ CGBN_FUSED_BIG_SMALL(CGBN_DECL_B2)
 #undef CGBN_DECL_F2
 #undef CGBN_DECL_B2
 // ... and the column-slab kernels in cgbn_slab_inst.hip
-#define CGBN_DECL_SF(P_, SOLO_)                                                          \
-    extern template __global__ void slab_forward<float, 0, P_, SOLO_>(SlabArgs);         \
-    extern template __global__ void slab_forward<float, 1, P_, SOLO_>(SlabArgs);         \
-    extern template __global__ void slab_forward<float, 2, P_, SOLO_>(SlabArgs);         \
-    extern template __global__ void slab_forward<bf16_t, 0, P_, SOLO_>(SlabArgs);        \
-    extern template __global__ void slab_forward<bf16_t, 1, P_, SOLO_>(SlabArgs);        \
-    extern template __global__ void slab_forward<bf16_t, 2, P_, SOLO_>(SlabArgs);
-#define CGBN_DECL_SB(P_, SOLO_)                                                          \
-    extern template __global__ void slab_backward<float, 0, P_, SOLO_>(SlabArgs);        \
-    extern template __global__ void slab_backward<float, 1, P_, SOLO_>(SlabArgs);        \
-    extern template __global__ void slab_backward<bf16_t, 0, P_, SOLO_>(SlabArgs);       \
-    extern template __global__ void slab_backward<bf16_t, 1, P_, SOLO_>(SlabArgs);
+#define CGBN_DECL_SF(P_, SOLO_)                                                                 \
+    extern template __global__ void slab_forward<float, 0, P_, SOLO_, false>(SlabArgs);         \
+    extern template __global__ void slab_forward<float, 1, P_, SOLO_, false>(SlabArgs);         \
+    extern template __global__ void slab_forward<float, 2, P_, SOLO_, false>(SlabArgs);         \
+    extern template __global__ void slab_forward<bf16_t, 0, P_, SOLO_, false>(SlabArgs);        \
+    extern template __global__ void slab_forward<bf16_t, 1, P_, SOLO_, false>(SlabArgs);        \
+    extern template __global__ void slab_forward<bf16_t, 2, P_, SOLO_, false>(SlabArgs);
+#define CGBN_DECL_SB(P_, SOLO_)                                                                 \
+    extern template __global__ void slab_backward<float, 0, P_, SOLO_, false>(SlabArgs);        \
+    extern template __global__ void slab_backward<float, 1, P_, SOLO_, false>(SlabArgs);        \
+    extern template __global__ void slab_backward<bf16_t, 0, P_, SOLO_, false>(SlabArgs);       \
+    extern template __global__ void slab_backward<bf16_t, 1, P_, SOLO_, false>(SlabArgs);
+#define CGBN_DECL_SD(T_, ACT_)                                                                  \
+    extern template __global__ void slab_forward<T_, ACT_, kSlabDenseForward, false, true>(SlabArgs); \
+    extern template __global__ void slab_backward<T_, ACT_, kSlabDenseBackward, false, true>(SlabArgs);
+CGBN_DECL_SD(float, 0)
+CGBN_DECL_SD(float, 1)
+CGBN_DECL_SD(bf16_t, 0)
+CGBN_DECL_SD(bf16_t, 1)
+#undef CGBN_DECL_SD
 CGBN_SLAB_FORWARD_P(CGBN_DECL_SF)
 CGBN_SLAB_BACKWARD_P(CGBN_DECL_SB)
 #undef CGBN_DECL_SF
@@ -1042,10 +1050,16 @@ cgbn_status launch_slab_kernel(KernelT kernel, const Plan& p, const SlabPlan& s,
 template <typename T, bool FWD, int ACT>
 cgbn_status launch_slab_t(const Plan& p, const SlabPlan& s, const SlabArgs& A, hipStream_t st)
 {
+    constexpr int dense = FWD ? kSlabDenseForward : kSlabDenseBackward;
+    if constexpr (!FWD || ACT != 2)
+        if (s.U > 1 && s.P == dense && s.total_units > compute_units()) {
+            if constexpr (FWD) return launch_slab_kernel(slab_forward<T, ACT, dense, false, true>, p, s, A, st);
+            else return launch_slab_kernel(slab_backward<T, ACT, dense, false, true>, p, s, A, st);
+        }
 #define CGBN_SLAB_CASE(P_, SOLO_)                                                                               \
     if (s.P == P_ && (s.U == 1) == SOLO_) {                                                                     \
-        if constexpr (FWD) return launch_slab_kernel(slab_forward<T, ACT, P_, SOLO_>, p, s, A, st);             \
-        else return launch_slab_kernel(slab_backward<T, ACT, P_, SOLO_>, p, s, A, st);                          \
+        if constexpr (FWD) return launch_slab_kernel(slab_forward<T, ACT, P_, SOLO_, false>, p, s, A, st);      \
+        else return launch_slab_kernel(slab_backward<T, ACT, P_, SOLO_, false>, p, s, A, st);                   \
     }
     if constexpr (FWD) { CGBN_SLAB_FORWARD_P(CGBN_SLAB_CASE) } else { CGBN_SLAB_BACKWARD_P(CGBN_SLAB_CASE) }
 #undef CGBN_SLAB_CASE

@@ -558,9 +558,11 @@ __device__ __forceinline__ const u32x4& slab_fetched(const u32x4* ext, int slot,
 // Launch bounds.  The plan counts one workgroup per compute unit where there are several units, which leaves a wavefront
 // 256 registers; only variants that need no more than 128 anyway are held to them.  (P = 18 held to 128 kept 20 to 60
 // bytes a lane in memory: forward of 256 x 1024 planes of 7x7 bf16 24.3 us, not held 21.7; of 67200 x 256 channels-last 26.8 and 24.6;
-// backward, P = 9, of 26980 x 296 26.8 and 24.5.)
-template <typename T, int ACT, int P, bool SOLO>
-__global__ __launch_bounds__(kSlabThreads, P * (ACT == 2 ? 2 : 1) <= (SOLO ? 4 : 12) ? 4 : 2) void slab_forward(SlabArgs A)
+// backward, P = 9, of 26980 x 296 26.8 and 24.5.)  DENSE: held all the same, two workgroups per compute unit, where there are
+// more units than compute units: forward of 164 x 800 planes of 11x16 bf16, 500 units, 36.4 us, so 30.7; backward of 149 x 696 of 10x12, 435
+// units, 30.3 and 26.1.
+template <typename T, int ACT, int P, bool SOLO, bool DENSE>
+__global__ __launch_bounds__(kSlabThreads, DENSE || P * (ACT == 2 ? 2 : 1) <= (SOLO ? 4 : 12) ? 4 : 2) void slab_forward(SlabArgs A)
 {
     constexpr int VEC = 16 / (int)sizeof(T);
     constexpr bool EARLY = ACT == 2 && P <= 20;
@@ -796,8 +798,8 @@ __global__ __launch_bounds__(kSlabThreads, P * (ACT == 2 ? 2 : 1) <= (SOLO ? 4 :
 // P: vectors per thread and tensor.  ACT != 0: dy is first masked by the stored output (A.aux) being positive; the
 // output's vectors are loaded beside the other two where the registers allow (P <= 10), else through the storage x takes
 // afterwards.
-template <typename T, int ACT, int P, bool SOLO>
-__global__ __launch_bounds__(kSlabThreads, P * (ACT != 0 ? 3 : 2) <= (SOLO ? 8 : 12) ? 4 : 2) void slab_backward(SlabArgs A)
+template <typename T, int ACT, int P, bool SOLO, bool DENSE>
+__global__ __launch_bounds__(kSlabThreads, DENSE || P * (ACT != 0 ? 3 : 2) <= (SOLO ? 8 : 12) ? 4 : 2) void slab_backward(SlabArgs A)
 {
     constexpr int VEC = 16 / (int)sizeof(T);
     constexpr bool THREE = ACT != 0 && P <= (SOLO ? 10 : 6);
@@ -1003,5 +1005,7 @@ __global__ __launch_bounds__(kSlabThreads, P * (ACT != 0 ? 3 : 2) <= (SOLO ? 8 :
 // X(vectors per thread (and tensor), one unit per slab)
 #define CGBN_SLAB_FORWARD_P(X) X(4, true) X(8, true) X(10, true) X(12, true) X(20, true) X(6, false) X(12, false) X(18, false) X(28, false) X(36, false)
 #define CGBN_SLAB_BACKWARD_P(X) X(4, true) X(6, true) X(8, true) X(10, true) X(12, true) X(20, true) X(6, false) X(9, false) X(14, false) X(18, false)
+// the variants built DENSE too (the forward without a shortcut)
+constexpr int kSlabDenseForward = 18, kSlabDenseBackward = 9;
 
 }  // namespace cgbn
