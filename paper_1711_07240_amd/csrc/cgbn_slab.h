@@ -336,7 +336,11 @@ template <bool FWD, class F> __device__ __forceinline__ bool slab_hand_over(cons
                         int have = 0;
                         for (unsigned i = 0; i < A.bitmap_words; ++i) have += __popc(ld_agent(bitmap + i));
                         if (have >= moved) { L.fix = 1; break; }
-                        if (wall_clock64() - t0 > kSlabBackstopTicks) { atomicExch(A.sync + 1, 1u); break; }
+                        if (wall_clock64() - t0 > kSlabBackstopTicks) {
+                            atomicExch(A.sync + 1, 1u);
+                            L.skip = 2;               // (the marked units' values stay unwritten: the statistics say so)
+                            break;
+                        }
                         __builtin_amdgcn_s_sleep(1);
                     }
                 }

@@ -199,6 +199,23 @@ def test_units_that_stop_waiting_relu(act):
     assert all(torch.equal(a, b) for a, b in zip(want, got)) and _error_word(p) == 0
 
 
+@pytest.mark.parametrize("shape,direction,P", [((100, 688, 10, 12, 4, "NCHW", "f32"), "sfwd", 18), ((37, 1104, 19, 23, 1, "NCHW", "bf16"), "sfwd", 18),
+                                               ((64, 528, 12, 12, 8, "NCHW", "f32"), "sbwd", 9), ((64, 1040, 12, 12, 8, "NCHW", "bf16"), "sbwd", 9)],
+                         ids=["forward-f32", "forward-bf16", "backward-f32", "backward-bf16"])
+def test_more_units_than_compute_units(shape, direction, P):
+    """The variants built a second time with half the registers, for launches of 257 units and more."""
+    print(f"[case] slab dense {shape}", flush=True)
+    n, c, h, w, k, layout, dtype = shape
+    get = lambda key: L.cgbn_plan_get(n, c, h, w, layout, dtype, k, f"{direction}_{key}")
+    assert get("P") == P and get("U") > 1 and get("U") * get("slabs") > 256
+    wl, d, p = _problem(shape)
+    p.forward()
+    p.backward()
+    assert L.cgbn_get_tuning("last_forward_slab" if direction == "sfwd" else "last_backward_slab") == 1
+    G.check_against_oracle(p.results(), _reference(wl, d), dtype, "dense")
+    assert _error_word(p) == 0
+
+
 @pytest.mark.parametrize("groups", [4, 23, 48])
 def test_several_rounds_of_units(groups):
     """A small persistent grid: a workgroup walks units of many slabs, whose order is spread over the row (whole rounds
