@@ -297,6 +297,10 @@ const char* cgbn_status_string(cgbn_status status);
  *   "spin_limit"       polls before a device-side wait gives up (0: at once; for tests of that path)
  *   "wait_us"          microseconds of wall-clock time before it gives up (default 100000); once one wait
  *                      of a launch has given up, its later waits do so at once
+ * The column-slab kernels take "fused", "one_sweep_stats", "nt_store", "fused_groups" (never fewer than a slab's units) and
+ * "spin_limit"; there a unit that waits longer (or 300 us, 30 us once some unit has) gives nothing up, it moves
+ * on and is finished by another.  "cooperative", "big_lds", "stagger", "stagger_us", "stagger_phases" and "wait_us" do not
+ * concern them; their own backstop, for waits that end within microseconds in a sound launch, is a second.
  * cgbn_get_tuning returns -1 for an unknown key. */
 cgbn_status cgbn_set_tuning(const char* key, long long value);
 /* also readable: "last_forward_fused", "last_backward_fused" (1 if the last
@@ -319,8 +323,8 @@ long long cgbn_get_tuning(const char* key);
  * "IPU" (images per unit), "U" (units per channel), "tp" / "TL" (tiles per large plane, tile
  * elements), "rows", "rps", "G", "big" (0, or which LDS variant), "total_units".
  * Column-slab kernels, prefix "sfwd_" or "sbwd_" ("sfwds_": the forward with a shortcut, "sbwdm_": the masked backward): "ok" (the shape takes them instead of
- * sweeps), "first" (... also before the single-launch NCHW kernels), "vecs" (16-byte vectors per row of the matrix), "R" (its rows), "cpc" (columns per channel), "cols" (vectors per
- * slab), "slabs", "nch" (channels per slab, rounded up to a power of two), "rpp" (rows per pass),
+ * sweeps), "first" (... also before the single-launch NCHW kernels), "vecs" (16-byte vectors per row of
+ * the matrix), "R" (its rows), "cpc" (columns per channel), "cols" (vectors per slab), "slabs", "nch" (channels per slab, rounded up to a power of two), "rpp" (rows per pass),
  * "tpc" (threads that add one channel's partial sums), "U" (units per slab), "rpu" (rows per unit),
  * "P" (vectors per thread of the kernel variant). */
 long long cgbn_plan_get(int N, int C, int H, int W, cgbn_layout layout, cgbn_dtype dtype, int K,

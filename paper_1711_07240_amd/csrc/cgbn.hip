@@ -1006,10 +1006,9 @@ SlabArgs slab_args(const Plan& p, const SlabPlan& s, char* ws)
     A.rows = reinterpret_cast<unsigned long long*>(ws + p.off_part0);
     A.sync = reinterpret_cast<unsigned*>(ws + p.off_sync);
     A.R = s.R; A.row_bytes = s.row_bytes;
-    A.M = p.M; A.inv_M_f64 = 1.0 / p.M; A.inv_M = (float)(1.0 / p.M);
+    A.inv_M_f64 = 1.0 / p.M; A.inv_M = (float)(1.0 / p.M);
     A.vecs = s.vecs; A.cols = s.cols; A.ncols = s.cols * (16 / p.eb); A.rpp = s.rpp;
     A.cpc = s.cpc; A.nch = s.nch; A.tpc = s.tpc; A.rch = A.ncols / s.cpc;
-    while ((1 << A.nsh) < s.nch) ++A.nsh;
     A.C = p.C; A.slabs = s.slabs; A.U = s.U; A.rpu = s.rpu; A.total_units = (int)s.total_units;
     A.G = s.U < kWave ? ceil_pow2(s.U) : kWave;
     A.pivot_stride = p.layout == CGBN_NCHW ? p.HW : 1;

@@ -56,13 +56,13 @@ struct SlabArgs {
     unsigned* sync;
     long long R;          // rows of the matrix
     long long row_bytes;
-    double M, inv_M_f64, eps;
+    double inv_M_f64, eps;
     float inv_M;
     int vecs;             // 16-byte vectors per row
     int cols, ncols;      // vector columns of a slab, its element columns
     int rpp;              // rows per pass
     int rch;                  // channels per slab
-    int cpc, nch, nsh, tpc;   // columns per channel, rch rounded up to a power of two 2^nsh, threads that add one channel's partial sums
+    int cpc, nch, tpc;    // columns per channel, rch rounded up to a power of two, threads that add one channel's partial sums
     int C, slabs, U, rpu; // rpu: rows per unit
     int total_units;
     int G;                // lanes that add up one channel's rows

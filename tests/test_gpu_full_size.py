@@ -30,11 +30,11 @@ def _as_f64_dev(t, dtype):
 
 # every workload on the path the library takes by itself; the two extremes of the single-launch kernels
 # (few huge planes, many tiny ones) also on the multi-sweep kernels a shape falls back to
-# (the channels-last workloads run on the multi-sweep kernels in any case: by default with the forward's statistics
-# from one sweep over x, and once more with a sweep each for the sums and the squared deviations)
+# (the channels-last workloads take the column-slab kernels by themselves; then as separate sweeps, with the forward's
+# statistics from one sweep over x; and the forward with a sweep each for the sums and the squared deviations)
 @pytest.mark.parametrize("name,fused,one_sweep", [("cfg1", 1, 1), ("cfg2", 1, 1), ("cfg3", 1, 1), ("cfg4", 1, 1), ("cfg4b", 1, 1),
-                                                  ("cfg1", 0, 1), ("cfg3", 0, 1), ("cfg4", 1, 0), ("cfg4b", 1, 0), ("cfg1", 0, 0)],
-                         ids=["cfg1", "cfg2", "cfg3", "cfg4", "cfg4b", "cfg1-sweeps", "cfg3-sweeps", "cfg4-two-pass", "cfg4b-two-pass",
+                                                  ("cfg1", 0, 1), ("cfg3", 0, 1), ("cfg4", 0, 1), ("cfg4b", 0, 1), ("cfg4", 1, 0), ("cfg4b", 1, 0), ("cfg1", 0, 0)],
+                         ids=["cfg1", "cfg2", "cfg3", "cfg4", "cfg4b", "cfg1-sweeps", "cfg3-sweeps", "cfg4-sweeps", "cfg4b-sweeps", "cfg4-two-pass", "cfg4b-two-pass",
                               "cfg1-sweeps-two-pass"])
 def test_full_size(name, fused, one_sweep):
     from paper_1711_07240_amd import cgbn as L

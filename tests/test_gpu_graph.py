@@ -25,6 +25,16 @@ CASES = [
 @pytest.mark.parametrize("name,wl", CASES, ids=[c[0] for c in CASES])
 def test_captured_step_replays_to_the_eager_result(name, wl):
     print(f"[case] graph {name}", flush=True)
+    sweeps = name == "channels-last-sweeps"       # (by itself this shape takes the column-slab kernels)
+    L.cgbn_set_tuning("fused", 0 if sweeps else 1)
+    try:
+        _captured_step(name, wl)
+        assert not sweeps or L.cgbn_get_tuning("last_forward_slab") == L.cgbn_get_tuning("last_backward_slab") == 0
+    finally:
+        L.cgbn_set_tuning("fused", 1)
+
+
+def _captured_step(name, wl):
     d = synth.make_inputs(wl)
     p = G.Problem(d["x"], d["dy"], d["gamma"], d["beta"], wl.eps, wl.layout, wl.dtype, wl.K)
     p.forward()

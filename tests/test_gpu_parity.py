@@ -385,7 +385,7 @@ LIMITS = [
     ("large-planes-384-rows", dict(N=96, C=1, H=300, W=500, K=48, layout="NCHW", dtype="f32"), 1),
     # (its backward has 8 tiles per plane: 776 units per channel, more than workgroups fit the device at once)
     ("large-planes-388-rows", dict(N=97, C=1, H=300, W=500, K=1, layout="NCHW", dtype="f32"), (1, 0)),
-    # channels-last: more partial rows than one combine pass of 64 lanes per shard
+    # channels-last: more partial rows than one combine pass of 64 lanes per shard (as sweeps; else column slabs)
     ("nhwc-one-shard-many-pieces", dict(N=1, C=8, H=700, W=900, K=1, layout="NHWC", dtype="bf16"), 0),
 ]
 
@@ -416,7 +416,7 @@ def test_channels_last_combine_lane_groups(name, kw, path):
     and joins their sums in lane order: every lane count, ragged rows per lane, both statistics variants (the
     `path` fixture's two multi-sweep settings)."""
     if path:
-        pytest.skip("channels-last shapes take the multi-sweep kernels either way")
+        pytest.skip("whole launches take the column-slab kernels: no row lanes")
     wl = BASE.scaled(name=name, **kw)
     old = L.cgbn_get_tuning("piece_bytes")
     try:

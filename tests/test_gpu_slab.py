@@ -75,6 +75,11 @@ def _outputs(p):
     return [t.clone() for t in (p.y, p.dx, p.mean, p.invstd, p.mean_lo, p.dgamma, p.dbeta)]
 
 
+def _moved_on(p):
+    """Some unit of the last launch has moved on."""
+    return int(p.ws[8:12].view(torch.int32).item()) != 0
+
+
 def _error_word(p):
     return int(p.ws[4:8].view(torch.int32).item())
 
@@ -166,7 +171,7 @@ def test_units_that_stop_waiting_are_finished_by_another(name, shape, units):
         p.backward()
         torch.cuda.synchronize()
         _ran_here()
-        assert _error_word(p) == 0
+        assert _error_word(p) == 0 and _moved_on(p)
         for a, b in zip(want, _outputs(p)):
             assert torch.equal(a, b)
         x, dy = p.x.clone(), p.dy.clone()
@@ -196,7 +201,7 @@ def test_units_that_stop_waiting_relu(act):
         t.zero_()
     with _Knobs(spin_limit=0):
         got = step()
-    assert all(torch.equal(a, b) for a, b in zip(want, got)) and _error_word(p) == 0
+    assert all(torch.equal(a, b) for a, b in zip(want, got)) and _error_word(p) == 0 and _moved_on(p)
 
 
 @pytest.mark.parametrize("shape,direction,P", [((100, 688, 10, 12, 4, "NCHW", "f32"), "sfwd", 18), ((37, 1104, 19, 23, 1, "NCHW", "bf16"), "sfwd", 18),
@@ -266,14 +271,15 @@ def test_units_fetched_ahead(shape, slabs):
     for spin in (None, 0):
         with _Knobs(fused_groups=slabs * max(get("sfwd_U"), get("sbwd_U")), **({} if spin is None else {"spin_limit": spin})):
             assert all(torch.equal(a, b) for a, b in zip(want, step()))
+            assert spin is None or _moved_on(p)
 
 
 @pytest.mark.parametrize("shape", [(2, 16, 30, 40, 2, "NHWC", "f32"), (4, 64, 40, 50, 4, "NHWC", "f32"),
                                    (4, 64, 40, 50, 4, "NHWC", "bf16")], ids=["one-unit", "several-f32", "several-bf16"])
 @pytest.mark.parametrize("sigmas", [6.0, 12.0, 5000.0])
 def test_first_value_far_from_the_mean(shape, sigmas):
-    """The pass under the loads takes its squares about the channel's first value; where that lies more than 8 standard
-    deviations from the mean the kernel makes a second pass."""
+    """The pass under the loads takes its squares about the threads' own means: the channel's first value, the pivot of the
+    sums, may lie anywhere."""
     def outlier(x):
         for c in (1, 14):
             ch = x[..., c]

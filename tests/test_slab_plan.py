@@ -1,5 +1,6 @@
 """Host-side planning of the column-slab kernels without a GPU: for thousands of seeded shapes the numbers the kernels
-index by cover the matrix exactly, fit the registers, the LDS and the workspace, and change no limit."""
+index by cover the matrix exactly, fit the registers, the LDS and the workspace, and push no workspace over the static
+scratch."""
 
 import numpy as np
 import pytest
@@ -78,8 +79,7 @@ def test_random_shapes(seed, layout):
             taken += _check(shape)
         except AssertionError as e:
             raise AssertionError(f"{shape}: {e}") from e
-    if layout == "NHWC":
-        assert taken > 1200
+    assert taken > (2400 if layout == "NHWC" else 1500)          # (four plans a shape)
 
 
 def test_detector_layers():
