@@ -471,18 +471,22 @@ void make_slab_plan(int N, int C, long long HW, int layout, int eb, long long ro
         s->R = (long long)N * HW;
         s->row_bytes = (long long)C * eb;
         s->cpc = 1;
-        if (s->R <= few_pixels(forward, second, s->row_bytes) || (forward && !second && s->R <= 5120 && s->R * s->row_bytes <= 6000000)) {
-            const int cols = s->vecs < 2 || (!forward && s->vecs <= cus) ? 1 : 2;
-            if (cut_slabs(s, C, cols, cols * vec, 1, row_words, cus, forward)) return;
-        }
+        const int pair = s->vecs < 2 || (!forward && s->vecs <= cus) ? 1 : 2;
+        if ((s->R <= few_pixels(forward, second, s->row_bytes) || (forward && !second && s->R <= 5120 && s->R * s->row_bytes <= 6000000)) &&
+            cut_slabs(s, C, pair, pair * vec, 1, row_words, cus, forward))
+            return;
         // about 8 vectors, as even as the row allows
         const int slabs = s->vecs < 12 ? 1 : (s->vecs + 4) / 8, cols = (s->vecs + slabs - 1) / slabs;
-        if (cut_slabs_in_units(s, C, cols, ceil_pow2(cols * vec), row_words, cus, forward, second) && forward && second && s->P > 20 &&
-            s->row_bytes <= 4096) {
-            const int inflight = cus / s->U, rounds = (s->slabs + inflight - 1) / inflight;
-            if (eb == 4 ? rounds > 1 || !(s->U % 8 == 0 || (s->row_bytes % 128 == 0 && cols == 8))
-                        : rounds > 1 && s->total_units * 3 < 2LL * rounds * cus)
-                s->ok = 0;
+        if (cut_slabs_in_units(s, C, cols, ceil_pow2(cols * vec), row_words, cus, forward, second)) {
+            if (forward && second && s->P > 20 && s->row_bytes <= 4096) {
+                const int inflight = cus / s->U, rounds = (s->slabs + inflight - 1) / inflight;
+                if (eb == 4 ? rounds > 1 || !(s->U % 8 == 0 || (s->row_bytes % 128 == 0 && cols == 8))
+                            : rounds > 1 && s->total_units * 3 < 2LL * rounds * cus)
+                    s->ok = 0;
+            }
+        } else if (s->R <= 3072) {
+            // (more slabs than compute units, sharing lines: still one workgroup each rather than the sweeps)
+            cut_slabs(s, C, pair, pair * vec, 1, row_words, cus, forward);
         }
         return;
     }

@@ -95,5 +95,8 @@ def test_detector_layers():
     assert L.cgbn_plan_get(*large, "sfwd_ok") == 1 and L.cgbn_plan_get(*large, "sfwds_ok") == 0
     head = (28, 32, 9, 12, "NHWC", "f32", 4)
     assert L.cgbn_plan_get(*head, "sfwd_U") == 1 and L.cgbn_plan_get(*head, "sbwdm_U") > 1
+    # 2700 to 3072 pixels are one workgroup a slab where no number of units takes them (more slabs than compute units, sharing lines)
+    wide = (15, 3304, 4, 51, "NHWC", "f32", 3)
+    assert all(L.cgbn_plan_get(*wide, f"{d}_ok") == 1 for d in ("sfwd", "sfwds", "sbwd", "sbwdm"))
     odd = (16, 250, 50, 84, "NHWC", "bf16", 8)                  # channels that are no whole vectors
     assert L.cgbn_plan_get(*odd, "sfwd_ok") == 0 and L.cgbn_plan_get(*odd, "sbwd_ok") == 0
