@@ -422,13 +422,15 @@ bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_wor
     return best >= 2 && cut_slabs(s, C, cols, nch, best, row_words, cus, forward);
 }
 
-// channels-last: up to how many pixels a slab is one workgroup (rows of at most 64 bytes: a workgroup shares its lines with few others)
+// channels-last: up to how many pixels a slab is one workgroup.  (Rows shorter than a line: a workgroup shares its lines with few
+// others; rows that are no whole lines: units share them.)
 long long few_pixels(bool forward, bool second, long long row_bytes)
 {
     if (row_bytes <= 64 || (forward && !second)) return 3072;
-    if (forward) return 2560;
-    if (!second) return 2688;
-    return row_bytes < 1024 ? 1536 : row_bytes <= 4096 ? 2112 : 1280;
+    if (row_bytes < 128) return !forward && second ? 2304 : 3072;
+    if (forward) return row_bytes >= 1024 && row_bytes % 128 != 0 ? 3072 : 2560;
+    if (!second) return row_bytes >= 1024 && row_bytes <= 3072 ? 3072 : 2688;
+    return row_bytes < 1024 ? 1792 : row_bytes <= 4096 ? 2112 : 1280;
 }
 
 // Which calls take the column-slab kernels, and how they are cut.  `second`: the forward adds a shortcut, the backward is
@@ -446,7 +448,8 @@ long long few_pixels(bool forward, bool second, long long row_bytes)
 //     line per request), wider ones make a slab's rows more than the hand-over bears.
 //   - a shortcut that does not fit the registers beside x (P > 20) is fetched batch by batch during the write-out, each batch behind the
 //     stores of the one before.  That is slower than the sweeps for float in several rounds (304290 x 192 172 us, so 275; 67200 x 1024
-//     201, 209), for float slabs that share lines unless their units are in whole eights (224400 x 80 67, 80), and for bf16 in
+//     201, 209), for float slabs that share lines unless their units are short and in whole eights (224400 x 80 67, 80; 31970 x 456
+//     53, 61), and for bf16 in
 //     rounds that are not well filled (45560 x 832 5 %); it is faster where rows of more than 4 KiB crowd the sweeps (164724 x 1376 fp32
 //     269, 198).
 //
@@ -456,7 +459,8 @@ long long few_pixels(bool forward, bool second, long long row_bytes)
 //     kernels move one plane per wavefront at a time and leave most of its lanes idle.  Measured, them -> here, forward / backward us: fp32 256 x 1024 planes of 4x4 100 /
 //     135 -> 12 / 14, bf16 16 x 2048 of 8x8 19 / 17 -> 8.3 / 8.0; with few channels and images they stay ahead: fp32 8 x 256
 //     of 16x20 6.3 / 5.6 against 6.4 / 6.4, bf16 16 x 256 of 20x20 7.6 / 7.4 against 11.5 / 12.  Not with a second tensor, more than
-//     16 passes and few slabs: bf16 20 x 24 of 13x21 with shortcut 12.6 against 14.8, 20 x 48 of 15x23 masked 13.8 against 16.5.
+//     16 passes and few slabs: bf16 20 x 24 of 13x21 with shortcut 12.6 against 14.8, 20 x 48 of 15x23 masked 13.8 against 16.5, 101 x 32 of 7x11
+//     12.9 against 16.4 (with more slabs, 228 x 64 of 5x7, 18.7 against 14.7 here).
 //   - several units per slab from 6 MB on (below, the hand-over costs what a launch less saves), and there before the
 //     single-launch kernels while planes are at most 1 KiB and the tensor 200 MB (backward: 512 bytes, float 800, 100 MB): bf16 256 x 1024 of 7x7 31 / 37 -> 23 /
 //     26, of 12x12 110 / 125 -> 49 / 60; fp32 100 x 1024 of 16x20 75 / 97 against 86 / 124.
@@ -480,7 +484,7 @@ void make_slab_plan(int N, int C, long long HW, int layout, int eb, long long ro
         if (cut_slabs_in_units(s, C, cols, ceil_pow2(cols * vec), row_words, cus, forward, second)) {
             if (forward && second && s->P > 20 && s->row_bytes <= 4096) {
                 const int inflight = cus / s->U, rounds = (s->slabs + inflight - 1) / inflight;
-                if (eb == 4 ? rounds > 1 || !(s->U % 8 == 0 || (s->row_bytes % 128 == 0 && cols == 8))
+                if (eb == 4 ? rounds > 1 || !((s->U % 8 == 0 && s->P <= 28) || (s->row_bytes % 128 == 0 && cols == 8))
                             : rounds > 1 && s->total_units * 3 < 2LL * rounds * cus)
                     s->ok = 0;
             }
@@ -500,7 +504,7 @@ void make_slab_plan(int N, int C, long long HW, int layout, int eb, long long ro
     while (nch * 2 <= kSlabMaxChannels && nch < C && (long long)nch / vec * HW < 8) nch *= 2;
     const int cols = (int)(nch / vec * HW), rpp = kSlabThreads / cols;
     if (N <= rpp * slab_most(forward, true) && cut_slabs(s, C, cols, nch, 1, row_words, cus, forward)) {
-        if (second && N > 16 * rpp && s->slabs < 16) s->ok = 0;
+        if (second && N > 16 * rpp && s->slabs < (rpp <= 2 ? 16 : 5)) s->ok = 0;
         s->first = !f.ok || f.U > 1 || (C >= 1024 && s->P <= (forward ? 12 : 8)) ||
                    (N >= 24 && C >= 128 && s->P <= (forward ? 8 : 4));
         return;

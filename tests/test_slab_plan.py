@@ -93,6 +93,8 @@ def test_detector_layers():
     # a second tensor: float shortcuts in several rounds go to the sweeps, masked backwards of this many pixels to several units
     large = (10, 192, 161, 189, "NHWC", "f32", 2)
     assert L.cgbn_plan_get(*large, "sfwd_ok") == 1 and L.cgbn_plan_get(*large, "sfwds_ok") == 0
+    shared = (17, 80, 90, 135, "NHWC", "f32", 1)                # slabs that share lines, the longest units
+    assert L.cgbn_plan_get(*shared, "sfwd_P") == 36 and L.cgbn_plan_get(*shared, "sfwds_ok") == 0
     head = (28, 32, 9, 12, "NHWC", "f32", 4)
     assert L.cgbn_plan_get(*head, "sfwd_U") == 1 and L.cgbn_plan_get(*head, "sbwdm_U") > 1
     # 2700 to 3072 pixels are one workgroup a slab where no number of units takes them (more slabs than compute units, sharing lines)
