@@ -7,6 +7,7 @@
 #include "cgbn_fused_list.h"
 #include "cgbn_slab.h"
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstring>
@@ -189,6 +190,10 @@ struct Plan {
     // partial sums
     int rows, rps, G;
     long long grid;       // workgroups of one sweep
+    // Channels-last, C no multiple of a 16-byte vector: `group` neighbouring pixels are whole vectors, C * group / vec of them, and are
+    // taken as one pixel of C * group columns, column j a value of channel j % C.  1: no grouping.  (A thread that loads one
+    // value at a time moves 2 or 4 bytes an instruction.)  `may_group`: what grouped() makes of this plan, 1 if nothing.
+    int group, may_group;
     FusedPlan ff, fb;     // register-resident path, forward and backward
     SlabPlan sf, sb;      // column-slab path
     SlabPlan sfs, sbm;    // ... of a forward with a shortcut, of a masked backward
@@ -531,9 +536,9 @@ int compute_units()
 // fastest when the shards are cut into equal pieces and the grid is a whole multiple of the
 // compute-unit count (one or two workgroups per unit: 5.7 TB/s against 4.0 with ragged,
 // unbalanced pieces), and every further row of partials costs time in the combine step.
-// So: the fewest pieces per shard, between 128 KiB and 4 MiB each, that fill the last
+// So: the fewest pieces per shard, between `least_bytes` (128 KiB) and 4 MiB each, that fill the last
 // round of workgroups best.
-long long reduce_pieces(long long spix, int K, int ctiles, int rpp, long long tile_row_bytes)
+long long reduce_pieces(long long spix, int K, int ctiles, int rpp, long long tile_row_bytes, long long least_bytes)
 {
     const long long quantum = 4LL * rpp;                 // four pixels per thread and pass
     const int cus = compute_units();
@@ -544,7 +549,7 @@ long long reduce_pieces(long long spix, int K, int ctiles, int rpp, long long ti
     for (long long pps = first; pps <= first + 2LL * cus; ++pps) {
         long long PL = (spix + pps - 1) / pps;
         PL = (PL + quantum - 1) / quantum * quantum;
-        if (PL * tile_row_bytes < (128LL << 10) && pps > first) break;   // too short from here on
+        if (PL * tile_row_bytes < least_bytes && pps > first) break;   // too short from here on
         const long long grid = (spix + PL - 1) / PL * K * ctiles;
         const long long rounds = (grid + cus - 1) / cus;
         const double fill = (double)grid / (double)(rounds * cus);
@@ -553,6 +558,83 @@ long long reduce_pieces(long long spix, int K, int ctiles, int rpp, long long ti
     }
     long long PL = (spix + best_pps - 1) / best_pps;
     return (PL + quantum - 1) / quantum * quantum;
+}
+
+// Pixel runs of the channels-last sweeps over `spix` pixels of `cols` columns a shard (p->vec, K given).  False: too many.
+bool cut_pixels(const Tuning& T, long long spix, int cols, int K, Plan* p)
+{
+    p->cv = cols / p->vec;
+    p->TW = p->cv < kThreads ? p->cv : kThreads;
+    p->ctiles = (p->cv + p->TW - 1) / p->TW;
+    p->rpp = kThreads / p->TW;
+    p->spix = spix;
+    long long PL;
+    if (T.piece_bytes > 0) {
+        PL = T.piece_bytes / ((long long)cols * p->eb);
+        PL -= PL % (4 * p->rpp);                           // four pixels per thread and pass
+        if (PL < 4 * p->rpp) PL = 4 * p->rpp;
+    } else {
+        // (grouped pixels: sweeps are all there is, also for small tensors, and a handful of workgroups would leave the chip idle)
+        PL = reduce_pieces(p->spix, K, p->ctiles, p->rpp, (long long)p->TW * p->vec * p->eb, p->group > 1 ? 16 << 10 : 128 << 10);
+    }
+    if (PL > p->spix) PL = p->spix;
+    p->PL = (int)PL;
+    long long pps = (p->spix + PL - 1) / PL;
+    if (pps * K > 0x3fffffffLL) return false;
+    p->pps = (int)pps;
+    p->rows = (int)(pps * K);
+    p->rps = (int)pps;
+    p->grid = (long long)p->rows * p->ctiles;
+    // Pixel runs of the elementwise sweeps: 32 KiB; shorter, but at least four pixels a thread, where that leaves less than two
+    // workgroups a compute unit.  Measured, 32 / 64 / 128 KiB, us: with fixed statistics 2 x 200 x 336 x 256 bf16 24.5 / 25.7 / 28.7, fp32 50.2 /
+    // 54.0 / 58.5, 4 x 100 x 100 x 64 bf16 3.9 / 4.7 / 6.1; as the last sweep of a forward / backward of 64 x 50 x 84 x 512 bf16 169 / 249, 173 / 256,
+    // 176 / 264, fp32 316 / 485, 319 / 502, 325 / 515.
+    for (int two = 0; two < 2; ++two) {
+        const long long quantum = 4 * p->rpp;
+        long long bytes = T.map_piece_bytes > 0 ? T.map_piece_bytes : 32768, PLm, ppsm;
+        for (;; bytes /= 2) {
+            PLm = bytes / ((long long)cols * p->eb);
+            PLm -= PLm % quantum;
+            if (PLm < quantum) PLm = quantum;
+            if (PLm > p->spix) PLm = p->spix;
+            ppsm = (p->spix + PLm - 1) / PLm;
+            if (T.map_piece_bytes > 0 || PLm <= quantum || ppsm * K * p->ctiles >= 512) break;
+        }
+        if (ppsm * K > 0x3fffffffLL) return false;
+        const long long gridm = ppsm * K * p->ctiles;
+        if (gridm > 0x7fffffffLL) return false;
+        if (two) { p->PLm2 = (int)PLm; p->ppsm2 = (int)ppsm; p->gridm2 = gridm; }
+        else { p->PLm = (int)PLm; p->ppsm = (int)ppsm; p->gridm = gridm; }
+    }
+    return p->grid <= 0x7fffffffLL;
+}
+
+// The plan with pixels grouped (see Plan::group).  Where a shard is no whole number of groups, the tensor is taken as one shard: the
+// calls that use this plan hand out pooled sums only.  False: the tensor is no whole number of groups, or a group more than one tile.
+// Measured, value by value -> grouped, forward / backward us: 16 x 60 x 61 x 187 bf16 49.7 / 72.3 -> 32.9 / 34.8, fp32 39.8 / 53.0 -> 35.3 /
+// 42.5.
+bool group_pixels(const Plan& p, Plan* q)
+{
+    const int vec = 16 / p.eb;
+    int g = vec;
+    for (int c = p.C; c % 2 == 0 && g > 1; c /= 2) g /= 2;
+    const long long pixels = (long long)p.N * p.HW;
+    if (p.S * p.eb < (256 << 10)) return false;        // (fewer, wider rows of threads then cost more than they gain: 2 x 7 x 9 x 50 fp32 11.6 / 9.2 us, grouped 13.6 / 10.9)
+    if (g == 1 || pixels % g != 0 || (long long)p.C * g > 0x3fffffffLL) return false;
+    *q = p;
+    q->vec = vec;
+    q->group = g;
+    if (pixels / p.K % g != 0) q->K = 1;
+    if (!cut_pixels(p.t, pixels / q->K / g, p.C * g, q->K, q)) return false;
+    // (several tiles: a channel's columns lie in different workgroups, so every column needs a row; forward / backward of 8 x 50 x 60 x 766
+    // bf16 58 / 71 us, value by value 43 / 61)
+    return q->ctiles == 1;
+}
+Plan grouped(const Plan& p)
+{
+    Plan q = p;
+    if (p.may_group > 1) group_pixels(p, &q);
+    return q;
 }
 
 cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, int dtype, int K, Plan* p)
@@ -569,6 +651,7 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
     if (S > (1LL << 40)) return CGBN_ERR_SHAPE;
     std::memset(p, 0, sizeof(*p));
     p->t = T;
+    p->group = p->may_group = 1;
     p->N = N; p->C = C; p->H = H; p->W = W; p->K = K; p->layout = layout; p->dtype = dtype;
     p->eb = dtype == CGBN_F32 ? 4 : 2;
     p->HW = (int)HW;
@@ -605,43 +688,7 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
         p->rps = p->ips * p->sp;
     } else {
         p->vec = (C % full_vec == 0) ? full_vec : 1;
-        p->cv = C / p->vec;
-        p->TW = p->cv < kThreads ? p->cv : kThreads;
-        p->ctiles = (p->cv + p->TW - 1) / p->TW;
-        p->rpp = kThreads / p->TW;
-        p->spix = (long long)p->ips * HW;
-        long long PL;
-        if (T.piece_bytes > 0) {
-            PL = T.piece_bytes / ((long long)C * p->eb);
-            PL -= PL % (4 * p->rpp);                           // four pixels per thread and pass
-            if (PL < 4 * p->rpp) PL = 4 * p->rpp;
-        } else {
-            PL = reduce_pieces(p->spix, K, p->ctiles, p->rpp, (long long)p->TW * p->vec * p->eb);
-        }
-        if (PL > p->spix) PL = p->spix;
-        p->PL = (int)PL;
-        long long pps = (p->spix + PL - 1) / PL;
-        if (pps * K > 0x3fffffffLL) return CGBN_ERR_SHAPE;
-        p->pps = (int)pps;
-        p->rows = (int)(pps * K);
-        p->rps = (int)pps;
-        p->grid = (long long)p->rows * p->ctiles;
-        // Pixel runs of the elementwise sweeps.  Measured (fwd normalise / bwd dx, us): bf16 64x50x84x512 64 KiB 186 / 288,
-        // 128 KiB 168 / 285, 256 KiB 173 / 296; fp32 16x50x84x1024 32 KiB 175 / 260, 64 KiB 157 / 270, 128 KiB 159 / 274
-        // (the same order on 64, 256 and 2048 channels): bf16 128 KiB; fp32 64 KiB with one input tensor, 32 KiB with more.
-        for (int two = 0; two < 2; ++two) {
-            const long long bytes = T.map_piece_bytes > 0 ? T.map_piece_bytes : p->eb == 2 ? 131072 : two ? 32768 : 65536;
-            long long PLm = bytes / ((long long)C * p->eb);
-            PLm -= PLm % (4 * p->rpp);
-            if (PLm < 4 * p->rpp) PLm = 4 * p->rpp;
-            if (PLm > p->spix) PLm = p->spix;
-            long long ppsm = (p->spix + PLm - 1) / PLm;
-            if (ppsm * K > 0x3fffffffLL) return CGBN_ERR_SHAPE;
-            const long long gridm = ppsm * K * p->ctiles;
-            if (gridm > 0x7fffffffLL) return CGBN_ERR_SHAPE;
-            if (two) { p->PLm2 = (int)PLm; p->ppsm2 = (int)ppsm; p->gridm2 = gridm; }
-            else { p->PLm = (int)PLm; p->ppsm = (int)ppsm; p->gridm = gridm; }
-        }
+        if (!cut_pixels(T, (long long)p->ips * HW, C, K, p)) return CGBN_ERR_SHAPE;
     }
     if (p->grid > 0x7fffffffLL || (long long)p->rows * C > (1LL << 33)) return CGBN_ERR_SHAPE;
     int G = 1;
@@ -664,6 +711,18 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
     size_t sync = align256(((size_t)kSyncHeader + 4 * (size_t)C) * sizeof(unsigned));
     size_t part = align256((size_t)C * max_rows * sizeof(float));
     size_t sh = align256((size_t)K * C * sizeof(double));
+    if (layout == CGBN_NHWC && p->vec == 1) {
+        // (its rows may be more, but not so many that the workspace no longer fits the static scratch)
+        Plan q;
+        if (group_pixels(*p, &q)) {
+            const size_t more = align256((size_t)C * (q.rows > max_rows ? q.rows : max_rows) * sizeof(float));
+            if (more == part || (more <= std::max(2 * part, (size_t)(512u << 10)) &&
+                                 sync + 2 * more + 2 * sh + align256((size_t)C * sizeof(float)) <= (size_t)CGBN_STATIC_SCRATCH_BYTES)) {
+                part = more;
+                p->may_group = q.group;
+            }
+        }
+    }
     // The column-slab path keeps its rows where the other paths keep theirs and the shard sums (the four arrays are adjacent)
     // and makes that room larger only up to a MiB, or twice the rows of the others while the workspace still fits the static
     // scratch, so that it changes no limit.
@@ -712,7 +771,8 @@ SweepArgs sweep_args(const Plan& p)
 {
     SweepArgs A;
     std::memset(&A, 0, sizeof(A));
-    A.S = p.S; A.N = p.N; A.C = p.C; A.HW = p.HW; A.rows = p.rows;
+    A.ch = p.C; A.group = p.group;
+    A.S = p.S; A.N = p.N; A.C = p.C * p.group; A.HW = p.HW; A.rows = p.rows;
     A.L = p.L; A.sp = p.sp;
     A.cv = p.cv; A.TW = p.TW; A.ctiles = p.ctiles; A.rpp = p.rpp; A.PL = p.PL; A.pps = p.pps;
     A.spix = p.spix;
@@ -805,7 +865,9 @@ cgbn_status launch_combine(int mode, const Plan& p, char* ws, float* out0, float
     A.clear_word = reinterpret_cast<unsigned*>(ws + p.off_sync) + 1;
     // values per row partial: a chunk of a plane (the last chunk shorter), a whole plane, or a pixel run of a shard
     if (p.layout == CGBN_NCHW) { A.row_mod = p.sp; A.row_full = (p.wave_mode || p.tiny) ? p.HW : p.L; A.row_total = p.HW; }
-    else { A.row_mod = p.pps; A.row_full = p.PL; A.row_total = p.spix; }
+    else {
+        A.row_mod = p.pps; A.row_full = (long long)p.PL * p.group; A.row_total = p.spix * p.group;
+    }
     dim3 block(kThreads);
     if (p.layout == CGBN_NHWC) {       // a row's channels side by side: 16 channels per workgroup
         constexpr int RL = kThreads / kCombineChannels;
@@ -1165,6 +1227,7 @@ cgbn_status cgbn_normalize(const void* x, int N, int C, int H, int W, cgbn_layou
     Plan p;
     CGBN_TRY(make_plan(tuning_now(), N, C, H, W, (int)layout, (int)dtype, 1, &p));
     if (!aligned16(x) || !aligned16(y)) return CGBN_ERR_ALIGN;
+    p = grouped(p);
     SweepArgs A = sweep_args(p);
     A.x = x; A.out = y; A.mean = mean; A.mean_lo = mean_lo; A.invstd = invstd; A.gamma = gamma; A.beta = beta;
     return launch_map(EL_NORM, p, A, static_cast<hipStream_t>(stream));
@@ -1212,6 +1275,7 @@ cgbn_status cgbn_backward_dx(const void* dy, const void* x, int N, int C, int H,
     Plan p;
     CGBN_TRY(make_plan(tuning_now(), N, C, H, W, (int)layout, (int)dtype, 1, &p));
     if (!aligned16(x) || !aligned16(dy) || !aligned16(dx)) return CGBN_ERR_ALIGN;
+    p = grouped(p);
     SweepArgs A = sweep_args(p);
     A.x = x; A.dy = dy; A.out = dx; A.mean = mean; A.mean_lo = mean_lo; A.invstd = invstd;
     A.gamma = gamma; A.dgamma = dgamma; A.dbeta = dbeta;
@@ -1227,6 +1291,7 @@ cgbn_status cgbn_frozen_forward(const void* x, int N, int C, int H, int W, cgbn_
     CGBN_TRY(make_plan(tuning_now(), N, C, H, W, (int)layout, (int)dtype, 1, &p));
     if (!eps_ok(eps)) return CGBN_ERR_EPS;
     if (!aligned16(x) || !aligned16(y)) return CGBN_ERR_ALIGN;
+    p = grouped(p);
     SweepArgs A = sweep_args(p);
     A.x = x; A.out = y; A.mean = fixed_mean; A.invstd = fixed_var; A.gamma = gamma; A.beta = beta; A.eps = eps;
     return launch_map(EL_FROZEN, p, A, static_cast<hipStream_t>(stream));
@@ -1240,6 +1305,7 @@ cgbn_status cgbn_frozen_backward(const void* dy, int N, int C, int H, int W, cgb
     CGBN_TRY(make_plan(tuning_now(), N, C, H, W, (int)layout, (int)dtype, 1, &p));
     if (!eps_ok(eps)) return CGBN_ERR_EPS;
     if (!aligned16(dy) || !aligned16(dx)) return CGBN_ERR_ALIGN;
+    p = grouped(p);
     SweepArgs A = sweep_args(p);
     A.x = dy; A.out = dx; A.invstd = fixed_var; A.gamma = gamma; A.eps = eps;
     return launch_map(EL_SCALE, p, A, static_cast<hipStream_t>(stream));
@@ -1316,6 +1382,7 @@ cgbn_status forward_impl(const Tuning& T, const void* x, const void* shortcut, b
         return f32 ? launch_slab_t<float, true, 0>(p, sp, F, st) : launch_slab_t<bf16_t, true, 0>(p, sp, F, st);
     }
 
+    p = grouped(p);
     SweepArgs A = sweep_args(p);
     A.x = x; A.part0 = part0;
     if (p.t.one_sweep_stats) {
@@ -1394,6 +1461,7 @@ cgbn_status backward_impl(const Tuning& T, const void* dy, const void* y, const 
         return f32 ? launch_slab_t<float, false, 0>(p, sp, F, st) : launch_slab_t<bf16_t, false, 0>(p, sp, F, st);
     }
 
+    p = grouped(p);
     SweepArgs A = sweep_args(p);
     A.x = x; A.dy = dy; A.mean = mean; A.mean_lo = mean_lo; A.invstd = invstd;
     A.part0 = reinterpret_cast<float*>(ws + p.off_part0);
@@ -1608,6 +1676,19 @@ long long cgbn_plan_get(int N, int C, int H, int W, cgbn_layout layout, cgbn_dty
         if (!std::strcmp(k, "rpu")) return s.rpu;
         if (!std::strcmp(k, "P")) return s.P;
         if (!std::strcmp(k, "R")) return s.R;
+        return -1;
+    }
+    if (!std::strcmp(key, "may_group")) return p.may_group;
+    if (!std::strncmp(key, "grouped_", 8)) {
+        const Plan q = grouped(p);
+        const char* k = key + 8;
+        if (!std::strcmp(k, "K")) return q.K;
+        if (!std::strcmp(k, "cv")) return q.cv;
+        if (!std::strcmp(k, "ctiles")) return q.ctiles;
+        if (!std::strcmp(k, "rows")) return q.rows;
+        if (!std::strcmp(k, "spix")) return q.spix;
+        if (!std::strcmp(k, "PL")) return q.PL;
+        if (!std::strcmp(k, "pps")) return q.pps;
         return -1;
     }
     if (!std::strcmp(key, "wave_mode")) return p.wave_mode;

@@ -69,6 +69,7 @@ struct SweepArgs {
     int tg;                   // tiny planes: planes per workgroup (a power of two, 8 ... 256)
     // NHWC
     int cv, TW, ctiles, rpp, PL, pps;
+    int ch, group;            // channels; pixels that make up one pixel of C = ch * group columns (see Plan::group)
     long long spix;           // pixels per shard
     long long pivot_stride;   // elements between the first values of consecutive channels
     float inv_M;
@@ -100,13 +101,10 @@ template <> struct Elem<float> {
     static constexpr int VEC = 4;
     static __device__ __forceinline__ float load1(const float* p) { return *p; }
     static __device__ __forceinline__ void store1(float* p, float v) { *p = v; }
-    static __device__ __forceinline__ void loadv(const float* p, float (&f)[4])
-    {
-        f32x4 v = *reinterpret_cast<const f32x4*>(p);
-        f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
-    }
     typedef f32x4 Raw;       // 16 bytes as they are stored
     static __device__ __forceinline__ Raw load_raw(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+    static __device__ __forceinline__ void unpack(const Raw& v, float (&f)[4]) { f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w; }
+    static __device__ __forceinline__ void loadv(const float* p, float (&f)[4]) { unpack(load_raw(p), f); }
     static __device__ __forceinline__ void storev(float* p, const float (&f)[4], int nt)
     {
         f32x4 v = {f[0], f[1], f[2], f[3]};
@@ -119,16 +117,16 @@ template <> struct Elem<bf16_t> {
     static constexpr int VEC = 8;
     static __device__ __forceinline__ float load1(const bf16_t* p) { return bf16_to_f32(p->bits); }
     static __device__ __forceinline__ void store1(bf16_t* p, float v) { p->bits = (uint16_t)f32_to_bf16(v); }
-    static __device__ __forceinline__ void loadv(const bf16_t* p, float (&f)[8])
+    typedef u32x4 Raw;
+    static __device__ __forceinline__ Raw load_raw(const bf16_t* p) { return *reinterpret_cast<const u32x4*>(p); }
+    static __device__ __forceinline__ void unpack(const Raw& v, float (&f)[8])
     {
-        u32x4 v = *reinterpret_cast<const u32x4*>(p);
         f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xffff0000u);
         f[2] = __uint_as_float(v.y << 16); f[3] = __uint_as_float(v.y & 0xffff0000u);
         f[4] = __uint_as_float(v.z << 16); f[5] = __uint_as_float(v.z & 0xffff0000u);
         f[6] = __uint_as_float(v.w << 16); f[7] = __uint_as_float(v.w & 0xffff0000u);
     }
-    typedef u32x4 Raw;
-    static __device__ __forceinline__ Raw load_raw(const bf16_t* p) { return *reinterpret_cast<const u32x4*>(p); }
+    static __device__ __forceinline__ void loadv(const bf16_t* p, float (&f)[8]) { unpack(load_raw(p), f); }
     static __device__ __forceinline__ void storev(bf16_t* p, const float (&f)[8], int nt)
     {
         u32x4 v;
@@ -143,10 +141,16 @@ template <> struct Elem<bf16_t> {
 
 // VEC-wide access for the channels-last kernels (V == Elem<T>::VEC or 1)
 template <typename T, int V> struct Access {
+    typedef typename Elem<T>::Raw Raw;
+    static __device__ __forceinline__ Raw load_raw(const T* p) { return Elem<T>::load_raw(p); }
+    static __device__ __forceinline__ void unpack(const Raw& v, float (&f)[V]) { Elem<T>::unpack(v, f); }
     static __device__ __forceinline__ void load(const T* p, float (&f)[V]) { Elem<T>::loadv(p, f); }
     static __device__ __forceinline__ void store(T* p, const float (&f)[V], int nt) { Elem<T>::storev(p, f, nt); }
 };
 template <typename T> struct Access<T, 1> {
+    typedef float Raw;
+    static __device__ __forceinline__ Raw load_raw(const T* p) { return Elem<T>::load1(p); }
+    static __device__ __forceinline__ void unpack(const Raw& v, float (&f)[1]) { f[0] = v; }
     static __device__ __forceinline__ void load(const T* p, float (&f)[1]) { f[0] = Elem<T>::load1(p); }
     static __device__ __forceinline__ void store(T* p, const float (&f)[1], int) { Elem<T>::store1(p, f[0]); }
 };
@@ -756,6 +760,37 @@ __global__ __launch_bounds__(kThreads) void nchw_map_tiny(SweepArgs A)
 // NHWC: the C channels of a pixel are contiguous; a thread owns V channels
 // --------------------------------------------------------------------------
 
+// V neighbouring channels' values of a per-channel array (4-byte aligned).  One or two wide loads: as V loads whose lanes lie 4 V
+// bytes apart, a wavefront's constants cost more address cycles than 16 KiB of its data.
+template <int V> __device__ __forceinline__ void load_channels(const float* p, float (&f)[V])
+{
+    __builtin_memcpy(f, p, sizeof(f));
+}
+// The constants of V neighbouring columns from column c on.
+template <typename T, int OP, int V> __device__ __forceinline__ void reduce_consts_of(const SweepArgs& A, int c, ChanConst (&k)[V])
+{
+    if (A.group != 1) {
+        c %= A.ch;
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            k[e] = reduce_consts<T, OP>(A, c);
+            if (++c == A.ch) c = 0;
+        }
+        return;
+    }
+    float mu[V], lo[V], is[V];
+    if (OP == OP_SUM || OP == OP_MOMENTS) {
+        Access<T, V>::load(static_cast<const T*>(A.x) + c, mu);
+    } else {
+        load_channels<V>(A.mean + c, mu);
+        if (A.mean_lo) load_channels<V>(A.mean_lo + c, lo);
+    }
+    if (op_has_dy(OP)) load_channels<V>(A.invstd + c, is);
+#pragma unroll
+    for (int e = 0; e < V; ++e)         // (as reduce_consts)
+        k[e] = {mu[e], !(OP == OP_SUM || OP == OP_MOMENTS) && A.mean_lo ? lo[e] : 0.f, op_has_dy(OP) ? is[e] : 0.f, 0.f, 0.f, 0.f};
+}
+
 // Workgroup = (row, column tile).  A row is a run of up to PL pixels of one
 // shard; a column tile is TW vectors of V channels.  Thread t works on vector
 // column t % TW of pixels t / TW, t / TW + rpp, ...
@@ -784,8 +819,7 @@ __global__ __launch_bounds__(kThreads) void nhwc_reduce(SweepArgs A)
     for (int e = 0; e < V; ++e) { a0[e] = 0.f; a1[e] = 0.f; }
     if (active) {
         ChanConst kc[V];
-#pragma unroll
-        for (int e = 0; e < V; ++e) kc[e] = reduce_consts<T, OP>(A, cb + e);
+        reduce_consts_of<T, OP, V>(A, cb, kc);
         const T* px = static_cast<const T*>(A.x) + pix0 * A.C + cb;
         const T* pd = static_cast<const T*>(A.dy) + pix0 * A.C + cb;
         const T* py = static_cast<const T*>(A.aux) + pix0 * A.C + cb;
@@ -838,26 +872,39 @@ __global__ __launch_bounds__(kThreads) void nhwc_reduce(SweepArgs A)
                 for (int e = 0; e < V; ++e)
                     accumulate<OP>(kc[e], xv[u][e], DY ? dv[u][e] : 0.f, Y ? yv[u][e] : 0.f, a0[e], a1[e]);
         }
-        for (; i < npix; i += rpp) {
-            float xv[V], dv[V], yv[V];
-            Access<T, V>::load(px + (long long)i * C, xv);
-            if constexpr (OP == OP_MOMENTS) {
-                const float rn = cnt > 0.f ? __builtin_amdgcn_rcpf(cnt) : 0.f;
-                const float wj = cnt * __builtin_amdgcn_rcpf(cnt + 1.f);
+        // what is left, four loads together (beyond the end the last pixel again)
+        for (; i < npix; i += 4 * rpp) {
+            typename Access<T, V>::Raw rx[4], rd[4], ry[4];
 #pragma unroll
-                for (int e = 0; e < V; ++e) {
-                    const float v = xv[e] - kc[e].mu;
-                    const float d = v - a0[e] * rn;
-                    a1[e] += (d * d) * wj;
-                    a0[e] += v;
-                }
-                cnt += 1.f;
-                continue;
+            for (int u = 0; u < 4; ++u) {
+                const long long o = (long long)min(i + u * rpp, npix - 1) * C;
+                rx[u] = Access<T, V>::load_raw(px + o);
+                if (DY) rd[u] = Access<T, V>::load_raw(pd + o);
+                if (Y) ry[u] = Access<T, V>::load_raw(py + o);
             }
-            if (DY) Access<T, V>::load(pd + (long long)i * C, dv);
-            if (Y) Access<T, V>::load(py + (long long)i * C, yv);
 #pragma unroll
-            for (int e = 0; e < V; ++e) accumulate<OP>(kc[e], xv[e], DY ? dv[e] : 0.f, Y ? yv[e] : 0.f, a0[e], a1[e]);
+            for (int u = 0; u < 4; ++u) {
+                if (i + u * rpp >= npix) break;
+                float xv[V], dv[V], yv[V];
+                Access<T, V>::unpack(rx[u], xv);
+                if constexpr (OP == OP_MOMENTS) {
+                    const float rn = cnt > 0.f ? __builtin_amdgcn_rcpf(cnt) : 0.f;
+                    const float wj = cnt * __builtin_amdgcn_rcpf(cnt + 1.f);
+#pragma unroll
+                    for (int e = 0; e < V; ++e) {
+                        const float v = xv[e] - kc[e].mu;
+                        const float d = v - a0[e] * rn;
+                        a1[e] += (d * d) * wj;
+                        a0[e] += v;
+                    }
+                    cnt += 1.f;
+                } else {
+                    if (DY) Access<T, V>::unpack(rd[u], dv);
+                    if (Y) Access<T, V>::unpack(ry[u], yv);
+#pragma unroll
+                    for (int e = 0; e < V; ++e) accumulate<OP>(kc[e], xv[e], DY ? dv[e] : 0.f, Y ? yv[e] : 0.f, a0[e], a1[e]);
+                }
+            }
         }
     }
     // fold the rpp pixel rows of the workgroup, in a fixed order
@@ -870,35 +917,87 @@ __global__ __launch_bounds__(kThreads) void nhwc_reduce(SweepArgs A)
         }
     }
     __syncthreads();
-    for (int o = t; o < nout; o += kThreads) {
-        int ch = ct * nout + o;
-        if (ch >= A.C) continue;
+    // (grouped pixels: one tile, and the columns of a channel, A.ch apart, are joined too)
+    const int outs = A.group == 1 ? nout : A.ch;
+    for (int o = t; o < outs; o += kThreads) {
+        const int ch = ct * nout + o;
+        if (ch >= A.ch) continue;
         float s0 = 0.f, s1 = 0.f;
         if constexpr (OP == OP_MOMENTS) {
             // the pixel rows' summaries joined in row order; row rr took pixels rr, rr + rpp, ... of the piece
             Run acc = {0.f, 0.f, 0.f};
-            for (int rr = 0; rr < A.rpp; ++rr) {
-                const int n_rr = rr < npix ? (npix - rr + A.rpp - 1) / A.rpp : 0;
-                Run part = {(float)n_rr, sm[(0 * A.rpp + rr) * nout + o], sm[(1 * A.rpp + rr) * nout + o]};
-                acc = run_join(acc, part);
-            }
+            for (int q = o; q < nout; q += outs)
+                for (int rr = 0; rr < A.rpp; ++rr) {
+                    const int n_rr = rr < npix ? (npix - rr + A.rpp - 1) / A.rpp : 0;
+                    Run part = {(float)n_rr, sm[(0 * A.rpp + rr) * nout + q], sm[(1 * A.rpp + rr) * nout + q]};
+                    acc = run_join(acc, part);
+                }
             s0 = acc.S;
             s1 = acc.M2;
         } else {
-            for (int rr = 0; rr < A.rpp; ++rr) {
-                s0 += sm[(0 * A.rpp + rr) * nout + o];
-                if (Q == 2) s1 += sm[(1 * A.rpp + rr) * nout + o];
-            }
+            for (int q = o; q < nout; q += outs)
+                for (int rr = 0; rr < A.rpp; ++rr) {
+                    s0 += sm[(0 * A.rpp + rr) * nout + q];
+                    if (Q == 2) s1 += sm[(1 * A.rpp + rr) * nout + q];
+                }
         }
-        size_t po = (size_t)row * A.C + ch;          // consecutive threads, consecutive floats: whole lines per store
+        size_t po = (size_t)row * A.ch + ch;          // consecutive threads, consecutive floats: whole lines per store
         A.part0[po] = s0;
         if (Q == 2) A.part1[po] = s1;
     }
 }
 
+// The constants of V neighbouring columns, in two steps: what they are formed from is loaded, then formed.
+template <int EL, int V> struct MapConsts {
+    static constexpr bool FIXED = EL == EL_FROZEN || EL == EL_SCALE;
+    float mu[V], lo[V], is[V], g[V], b[V], c2[V];
+    __device__ __forceinline__ void load(const SweepArgs& A, int c)
+    {
+        const float* pb = EL == EL_SCALE ? nullptr : FIXED || el_is_norm(EL) ? A.beta : A.dbeta;
+        const bool low = !FIXED && A.mean_lo != nullptr;
+#pragma unroll
+        for (int e = 0; e < V; ++e) mu[e] = lo[e] = b[e] = c2[e] = 0.f;
+        if (A.group == 1) {
+            load_channels<V>(A.invstd + c, is);
+            load_channels<V>(A.gamma + c, g);
+            if (EL != EL_SCALE) { load_channels<V>(A.mean + c, mu); load_channels<V>(pb + c, b); }
+            if (low) load_channels<V>(A.mean_lo + c, lo);
+            if (!FIXED && !el_is_norm(EL)) load_channels<V>(A.dgamma + c, c2);
+            asm volatile("");        // (or the compiler merges these loads with the single ones below)
+        } else {
+            c %= A.ch;
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                is[e] = A.invstd[c];
+                g[e] = A.gamma[c];
+                if (EL != EL_SCALE) { mu[e] = A.mean[c]; b[e] = pb[c]; }
+                if (low) lo[e] = A.mean_lo[c];
+                if (!FIXED && !el_is_norm(EL)) c2[e] = A.dgamma[c];
+                if (++c == A.ch) c = 0;
+            }
+        }
+    }
+    __device__ __forceinline__ void form(const SweepArgs& A, ChanConst (&k)[V])      // (as map_consts)
+    {
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            const float i = FIXED ? 1.0f / sqrtf(is[e] + A.eps) : is[e];
+            const bool dx = !FIXED && !el_is_norm(EL);
+            k[e] = {mu[e], lo[e], i, g[e] * i, dx ? b[e] * A.inv_M : b[e], dx ? c2[e] * A.inv_M : 0.f};
+        }
+    }
+};
+
+// Elementwise, HBM bound: one thread, one vector column, UNR pixels at a time.  A workgroup has 16 to 256 KiB to move, a few chunks a
+// thread, so what stands before the first chunk counts: its loads are issued before the channels' constants are formed, and
+// with fixed statistics, where a constant is a square root and a division, a workgroup with at least as many rows of threads as a vector
+// has channels forms each channel's once.  What is left
+// after the first chunk is loaded four pixels at a time (lanes beyond the end read the last pixel again).
 template <typename T, int V, int EL>
 __global__ __launch_bounds__(kThreads) void nhwc_map(SweepArgs A)
 {
+    constexpr bool IN2 = el_has_2(EL), IN3 = el_has_3(EL), FIXED = EL == EL_FROZEN || EL == EL_SCALE;
+    __shared__ float fixed[EL == EL_FROZEN ? 3 : 1][FIXED ? kThreads : 1];
     long long b = A.reverse ? (long long)gridDim.x - 1 - blockIdx.x : (long long)blockIdx.x;
     int ct = (int)(b % A.ctiles);
     int row = (int)(b / A.ctiles);
@@ -910,59 +1009,83 @@ __global__ __launch_bounds__(kThreads) void nhwc_map(SweepArgs A)
     int t = threadIdx.x;
     int col = t % A.TW, r = t / A.TW;
     int vc = ct * A.TW + col;
-    if (!(r < A.rpp && vc < A.cv)) return;
-    int cb = vc * V;
-    ChanConst kc[V];
-#pragma unroll
-    for (int e = 0; e < V; ++e) kc[e] = map_consts<EL>(A, cb + e);
+    const bool active = r < A.rpp && vc < A.cv;
+    int cb = active ? vc * V : 0;
+    if (!active) npix = 0;
     const T* px = static_cast<const T*>(A.x) + pix0 * A.C + cb;
     const T* pd = static_cast<const T*>(A.dy) + pix0 * A.C + cb;
     const T* py = static_cast<const T*>(A.aux) + pix0 * A.C + cb;
     T* po = static_cast<T*>(A.out) + pix0 * A.C + cb;
     T* po2 = A.out2 ? static_cast<T*>(A.out2) + pix0 * A.C + cb : nullptr;
-    constexpr bool IN2 = el_has_2(EL), IN3 = el_has_3(EL);
     const long long C = A.C;
     const int rpp = A.rpp;
-    int i = r;
-    // loads in flight per lane and tensor: as many as the registers allow next to the other operands (measured on
-    // 64 x 50 x 84 x 512 bf16, normalise / dx: 4 each 110 / 166 us, 16 / 8 99 / 160)
-    constexpr int UNR = IN3 ? 4 : IN2 ? 8 : 16;
-    for (; i + (UNR - 1) * rpp < npix; i += UNR * rpp) {
-        float xv[UNR][V], v2[UNR][V], v3[UNR][V];
+    // loads in flight per lane and tensor: what a piece of 32 KiB has for a thread
+    constexpr int UNR = IN3 ? 4 : 8;
+    typename Access<T, V>::Raw xv[UNR], v2[UNR], v3[UNR];      // (as stored: unpacked, 16 of them would take half the wavefronts)
+    // N pixels from i on, i + u * rpp the u-th; `last`: the last pixel there is to read
+    auto load = [&](auto n_, int i, int last) __attribute__((always_inline)) {
+        constexpr int n = decltype(n_)::value;
 #pragma unroll
-        for (int u = 0; u < UNR; ++u) Access<T, V>::load(px + (long long)(i + u * rpp) * C, xv[u]);
+        for (int u = 0; u < n; ++u) xv[u] = Access<T, V>::load_raw(px + (long long)min(i + u * rpp, last) * C);
         if (IN2) {
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) Access<T, V>::load(pd + (long long)(i + u * rpp) * C, v2[u]);
+            for (int u = 0; u < n; ++u) v2[u] = Access<T, V>::load_raw(pd + (long long)min(i + u * rpp, last) * C);
         }
         if (IN3) {
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) Access<T, V>::load(py + (long long)(i + u * rpp) * C, v3[u]);
+            for (int u = 0; u < n; ++u) v3[u] = Access<T, V>::load_raw(py + (long long)min(i + u * rpp, last) * C);
         }
-#pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-            float o[V], dz[V];
-#pragma unroll
-            for (int e = 0; e < V; ++e) {
-                dz[e] = 0.f;
-                o[e] = map_value<EL>(kc[e], xv[u][e], IN2 ? v2[u][e] : 0.f, IN3 ? v3[u][e] : 0.f, dz[e]);
-            }
-            Access<T, V>::store(po + (long long)(i + u * rpp) * C, o, A.nt);
-            if (IN3 && po2) Access<T, V>::store(po2 + (long long)(i + u * rpp) * C, dz, A.nt);
-        }
-    }
-    for (; i < npix; i += rpp) {
-        float xv[V], v2[V], v3[V], o[V], dz[V];
-        Access<T, V>::load(px + (long long)i * C, xv);
-        if (IN2) Access<T, V>::load(pd + (long long)i * C, v2);
-        if (IN3) Access<T, V>::load(py + (long long)i * C, v3);
+    };
+    ChanConst kc[V];
+    auto write = [&](int u, int i) __attribute__((always_inline)) {
+        float f[V], f2[V], f3[V], o[V], dz[V];
+        Access<T, V>::unpack(xv[u], f);
+        if (IN2) Access<T, V>::unpack(v2[u], f2);
+        if (IN3) Access<T, V>::unpack(v3[u], f3);
 #pragma unroll
         for (int e = 0; e < V; ++e) {
             dz[e] = 0.f;
-            o[e] = map_value<EL>(kc[e], xv[e], IN2 ? v2[e] : 0.f, IN3 ? v3[e] : 0.f, dz[e]);
+            o[e] = map_value<EL>(kc[e], f[e], IN2 ? f2[e] : 0.f, IN3 ? f3[e] : 0.f, dz[e]);
         }
         Access<T, V>::store(po + (long long)i * C, o, A.nt);
         if (IN3 && po2) Access<T, V>::store(po2 + (long long)i * C, dz, A.nt);
+    };
+    constexpr int nolimit = 0x7fffffff;
+    int i = r;
+    const bool whole = i + (UNR - 1) * rpp < npix, shared = FIXED && (A.group == 1 ? rpp >= V : A.ch <= kThreads);
+    // (the constants' loads first: they are waited for first, and the first stores leave while the chunk's last loads are under way)
+    MapConsts<EL, V> consts;
+    if (!shared) consts.load(A, cb);
+    if (whole) load(std::integral_constant<int, UNR>{}, i, nolimit);
+    if (shared) {
+        // (no more channels than threads: rpp * TW <= kThreads)
+        const int c0 = A.group == 1 ? ct * A.TW * V : 0, channels = A.group == 1 ? A.TW * V : A.ch;
+        if (t < channels && c0 + t < A.ch) {
+            const ChanConst f = map_consts<EL>(A, c0 + t);
+            fixed[0][t] = f.g;
+            if constexpr (EL == EL_FROZEN) { fixed[1][t] = f.mu; fixed[2][t] = f.b; }
+        }
+        __syncthreads();
+        int o = active ? col * V % channels : 0;
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            kc[e] = {0.f, 0.f, 0.f, fixed[0][o], 0.f, 0.f};
+            if constexpr (EL == EL_FROZEN) { kc[e].mu = fixed[1][o]; kc[e].b = fixed[2][o]; }
+            if (++o == channels) o = 0;
+        }
+    } else {
+        consts.form(A, kc);
+    }
+    if (whole) {
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) write(u, i + u * rpp);
+        i += UNR * rpp;
+    }
+    for (; i < npix; i += 4 * rpp) {
+        load(std::integral_constant<int, 4>{}, i, npix - 1);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (i + u * rpp < npix) write(u, i + u * rpp);
     }
 }
 
