@@ -4,18 +4,21 @@ The host code and the multi-sweep kernels are one translation unit; the NCHW
 single-launch kernels are instantiated in ten more (element type x direction
 x activation), the column-slab kernels in eight (element type x direction x
 register limit),
-compiled side by side, then everything is linked into one shared library."""
+compiled side by side, then everything is linked into one shared library.  The
+binding's extension is one C file."""
 
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libcgbn.so")
+CALL = os.path.join(PKG, "_cgbn_call.so")
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -53,6 +56,16 @@ def _units(obj_dir):
     return units
 
 
+def build_call(verbose: bool = True) -> str:
+    """The binding's extension (csrc/cgbn_call.c)."""
+    cmd = [os.environ.get("CC", "gcc"), "-O2", "-std=c11", "-Wall", "-fPIC", "-shared", "-I", sysconfig.get_paths()["include"],
+           "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "cgbn_call.c"), "-o", CALL]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return CALL
+
+
 def build(verbose: bool = True, jobs: int | None = None, extra_flags=(), lib: str = LIB, obj_dir: str = OBJ) -> str:
     """Compile and link; `extra_flags` (e.g. a -D for an instrumented build), `lib` and
     `obj_dir` let a second flavour of the library be built beside the product one."""
@@ -68,6 +81,8 @@ def build(verbose: bool = True, jobs: int | None = None, extra_flags=(), lib: st
         subprocess.run(cmd, check=True)
         return obj
 
+    if lib == LIB:
+        build_call(verbose)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         objs = list(ex.map(compile_one, units))
     cmd = [HIPCC, "--offload-arch=gfx950", "-fno-gpu-rdc", "-shared", "-fPIC", "-o", lib] + objs

@@ -1,6 +1,6 @@
-"""ctypes binding of libcgbn.so: same names and argument order as include/cgbn.h.
+"""Binding of libcgbn.so: same names and argument order as include/cgbn.h.
 
-Argument marshalling only.  Tensors are passed as anything with a
+Argument marshalling only, by ctypes; for the calls of a training step by a small extension (csrc/cgbn_call.c).  Tensors are passed as anything with a
 `data_ptr()` (a torch tensor on the GPU) or as a raw integer device address;
 `None` becomes NULL.  Every step of the path runs in the library's kernels.
 If the library has not been built this module raises on first use; there is
@@ -10,11 +10,14 @@ no fallback of any kind.
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 from typing import Optional
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libcgbn.so")
+CALL_PATH = os.path.join(_HERE, "_cgbn_call.so")
 
 CGBN_NCHW, CGBN_NHWC = 0, 1
 CGBN_F32, CGBN_BF16 = 0, 1
@@ -63,6 +66,7 @@ SIGNATURES = {
 }
 
 _lib = None
+_call = None        # the extension, bound to the library's functions
 
 
 class CgbnError(RuntimeError):
@@ -73,19 +77,35 @@ class CgbnError(RuntimeError):
 
 def lib() -> ctypes.CDLL:
     """Load libcgbn.so (once).  Raises if it is missing: build it first."""
-    global _lib
+    global _lib, _call
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
+        missing = [p for p in (LIB_PATH, CALL_PATH) if not os.path.exists(p)]
+        if missing:
             raise ImportError(
-                f"{LIB_PATH} is not built; run `python -c 'import __graft_entry__ as g; g.build()'` "
+                f"{missing[0]} is not built; run `python -c 'import __graft_entry__ as g; g.build()'` "
                 "or `python paper_1711_07240_amd/build.py`")
         handle = ctypes.CDLL(LIB_PATH)
         for name, (res, args) in SIGNATURES.items():
             fn = getattr(handle, name)
             fn.restype = res
             fn.argtypes = args
-        _lib = handle
+        loader = importlib.machinery.ExtensionFileLoader("_cgbn_call", CALL_PATH)
+        call = importlib.util.module_from_spec(importlib.util.spec_from_loader("_cgbn_call", loader))
+        loader.exec_module(call)
+        call.bind(tuple(ctypes.cast(getattr(handle, "cgbn_" + n), ctypes.c_void_p).value for n in
+                        ("forward", "forward_relu", "backward", "backward_relu", "frozen_forward", "frozen_backward")),
+                  LAYOUTS, DTYPES, _stream)
+        _lib, _call = handle, call
     return _lib
+
+
+def _calls():
+    if _call is None:
+        lib()
+    return _call
+
+
+_torch = None
 
 
 def _ptr(t) -> Optional[int]:
@@ -102,8 +122,13 @@ def _nbytes(t) -> int:
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        return int(torch.cuda.current_stream().cuda_stream) or None
+        global _torch
+        if _torch is None:
+            import torch
+            _torch = torch
+        if _torch.cuda.is_initialized():      # what the next line gives, without a Stream object for it
+            return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice()) or None
+        return int(_torch.cuda.current_stream().cuda_stream) or None
     if isinstance(stream, int):
         return stream or None
     return int(stream.cuda_stream) or None
@@ -140,10 +165,10 @@ def cgbn_workspace_status(workspace, gave_up, stream=None) -> None:
 
 def cgbn_forward(x, N, C, H, W, layout, K, gamma, beta, eps, y, mean, invstd,
                  dtype="f32", mean_lo=None, workspace=None, workspace_bytes=None, stream=None) -> None:
-    wb = _nbytes(workspace) if workspace_bytes is None and workspace is not None else (workspace_bytes or 0)
-    _check(lib().cgbn_forward(_ptr(x), N, C, H, W, _enum(LAYOUTS, layout), K, _ptr(gamma), _ptr(beta),
-                              float(eps), _ptr(y), _ptr(mean), _ptr(invstd), _enum(DTYPES, dtype),
-                              _ptr(mean_lo), _ptr(workspace), wb, _stream(stream)), "cgbn_forward")
+    code = (_call or _calls()).forward(x, N, C, H, W, layout, K, gamma, beta, eps, y, mean, invstd, dtype, mean_lo, workspace,
+                                       workspace_bytes, stream)
+    if code:
+        _check(code, "cgbn_forward")
 
 
 def cgbn_forward_static(x, N, C, H, W, layout, K, gamma, beta, eps, y, mean, invstd,
@@ -155,28 +180,26 @@ def cgbn_forward_static(x, N, C, H, W, layout, K, gamma, beta, eps, y, mean, inv
 
 def cgbn_backward(dy, x, mean, invstd, gamma, dx, dgamma, dbeta, N, C, H, W, layout, K,
                   dtype="f32", mean_lo=None, workspace=None, workspace_bytes=None, stream=None) -> None:
-    wb = _nbytes(workspace) if workspace_bytes is None and workspace is not None else (workspace_bytes or 0)
-    _check(lib().cgbn_backward(_ptr(dy), _ptr(x), _ptr(mean), _ptr(invstd), _ptr(gamma), _ptr(dx),
-                               _ptr(dgamma), _ptr(dbeta), N, C, H, W, _enum(LAYOUTS, layout), K,
-                               _enum(DTYPES, dtype), _ptr(mean_lo), _ptr(workspace), wb,
-                               _stream(stream)), "cgbn_backward")
+    code = (_call or _calls()).backward(dy, x, mean, invstd, gamma, dx, dgamma, dbeta, N, C, H, W, layout, K, dtype, mean_lo, workspace,
+                                        workspace_bytes, stream)
+    if code:
+        _check(code, "cgbn_backward")
 
 
 def cgbn_forward_relu(x, shortcut, N, C, H, W, layout, K, gamma, beta, eps, y, mean, invstd,
                       dtype="f32", mean_lo=None, workspace=None, workspace_bytes=None, stream=None) -> None:
-    wb = _nbytes(workspace) if workspace_bytes is None and workspace is not None else (workspace_bytes or 0)
-    _check(lib().cgbn_forward_relu(_ptr(x), _ptr(shortcut), N, C, H, W, _enum(LAYOUTS, layout), K, _ptr(gamma),
-                                   _ptr(beta), float(eps), _ptr(y), _ptr(mean), _ptr(invstd), _enum(DTYPES, dtype),
-                                   _ptr(mean_lo), _ptr(workspace), wb, _stream(stream)), "cgbn_forward_relu")
+    code = (_call or _calls()).forward_relu(x, shortcut, N, C, H, W, layout, K, gamma, beta, eps, y, mean, invstd, dtype, mean_lo, workspace,
+                                            workspace_bytes, stream)
+    if code:
+        _check(code, "cgbn_forward_relu")
 
 
 def cgbn_backward_relu(dy, y, x, mean, invstd, gamma, dx, dshortcut, dgamma, dbeta, N, C, H, W, layout, K,
                        dtype="f32", mean_lo=None, workspace=None, workspace_bytes=None, stream=None) -> None:
-    wb = _nbytes(workspace) if workspace_bytes is None and workspace is not None else (workspace_bytes or 0)
-    _check(lib().cgbn_backward_relu(_ptr(dy), _ptr(y), _ptr(x), _ptr(mean), _ptr(invstd), _ptr(gamma), _ptr(dx),
-                                    _ptr(dshortcut), _ptr(dgamma), _ptr(dbeta), N, C, H, W,
-                                    _enum(LAYOUTS, layout), K, _enum(DTYPES, dtype), _ptr(mean_lo),
-                                    _ptr(workspace), wb, _stream(stream)), "cgbn_backward_relu")
+    code = (_call or _calls()).backward_relu(dy, y, x, mean, invstd, gamma, dx, dshortcut, dgamma, dbeta, N, C, H, W, layout, K, dtype,
+                                             mean_lo, workspace, workspace_bytes, stream)
+    if code:
+        _check(code, "cgbn_backward_relu")
 
 
 def cgbn_shard_sum(x, N, C, H, W, layout, K, dtype, s, workspace, workspace_bytes=None, stream=None) -> None:
@@ -232,15 +255,15 @@ def cgbn_backward_dx(dy, x, N, C, H, W, layout, dtype, mean, mean_lo, invstd, ga
 
 
 def cgbn_frozen_forward(x, N, C, H, W, layout, dtype, fixed_mean, fixed_var, gamma, beta, eps, y, stream=None) -> None:
-    _check(lib().cgbn_frozen_forward(_ptr(x), N, C, H, W, _enum(LAYOUTS, layout), _enum(DTYPES, dtype),
-                                     _ptr(fixed_mean), _ptr(fixed_var), _ptr(gamma), _ptr(beta), float(eps),
-                                     _ptr(y), _stream(stream)), "cgbn_frozen_forward")
+    code = (_call or _calls()).frozen_forward(x, N, C, H, W, layout, dtype, fixed_mean, fixed_var, gamma, beta, eps, y, stream)
+    if code:
+        _check(code, "cgbn_frozen_forward")
 
 
 def cgbn_frozen_backward(dy, N, C, H, W, layout, dtype, fixed_var, gamma, eps, dx, stream=None) -> None:
-    _check(lib().cgbn_frozen_backward(_ptr(dy), N, C, H, W, _enum(LAYOUTS, layout), _enum(DTYPES, dtype),
-                                      _ptr(fixed_var), _ptr(gamma), float(eps), _ptr(dx), _stream(stream)),
-           "cgbn_frozen_backward")
+    code = (_call or _calls()).frozen_backward(dy, N, C, H, W, layout, dtype, fixed_var, gamma, eps, dx, stream)
+    if code:
+        _check(code, "cgbn_frozen_backward")
 
 
 def cgbn_update_running_stats(mean, mean_lo, invstd, eps, M, C, momentum, unbiased, running_mean, running_var,

@@ -12,7 +12,9 @@
 #include <cmath>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
+#include <new>
 #include <type_traits>
 #include <utility>
 
@@ -139,8 +141,10 @@ struct Tuning {
 // The knobs are process-wide; every call works on ONE copy of them taken under the lock when it starts
 // (tuning_now), so a knob changed by another thread in the middle of a call cannot make the plan, the
 // workspace check and the launches of that call disagree.
+// `version` counts the changes of the knobs.
 Tuning g_tune;
 std::mutex g_tune_lock;
+std::atomic<unsigned> g_tune_version{0};
 Tuning tuning_now()
 {
     std::lock_guard<std::mutex> hold(g_tune_lock);
@@ -754,6 +758,42 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
     return CGBN_OK;
 }
 
+// The plan of a call, from this thread's last plans or made anew.  A plan follows from its key alone: the sizes, the knobs (by
+// their version: a plan made while they change is not kept) and the device.  Making one takes 2 us, 9 with a large shard
+// channels-last, of the 10 us a small call took on the host; a training run comes back to the same few dozen layers.
+struct KeptPlan {
+    Plan p, g;            // g: grouped(p)
+    int key[8];
+    unsigned version;
+    bool valid = false;
+};
+constexpr int kKeptPlans = 64;
+cgbn_status plan_of(int N, int C, int H, int W, int layout, int dtype, int K, const Plan** p, const Plan** grouped_p = nullptr)
+{
+    static thread_local std::unique_ptr<KeptPlan> kept[kKeptPlans];
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess) { (void)hipGetLastError(); dev = -1; }
+    const int key[8] = {N, C, H, W, layout, dtype, K, dev};
+    unsigned hash = 0;
+    for (int v : key) hash = (hash ^ (unsigned)v) * 0x9e3779b1u, hash ^= hash >> 15;
+    std::unique_ptr<KeptPlan>& k = kept[hash % kKeptPlans];
+    const unsigned version = g_tune_version.load(std::memory_order_acquire);
+    if (!k || !k->valid || k->version != version || std::memcmp(k->key, key, sizeof(key)) != 0) {
+        if (!k) k.reset(new (std::nothrow) KeptPlan);
+        if (!k) return CGBN_ERR_HIP;
+        k->valid = false;
+        const cgbn_status s = make_plan(tuning_now(), N, C, H, W, layout, dtype, K, &k->p);
+        if (s != CGBN_OK) return s;
+        k->g = grouped(k->p);
+        std::memcpy(k->key, key, sizeof(key));
+        k->version = version;
+        k->valid = g_tune_version.load(std::memory_order_acquire) == version;
+    }
+    *p = &k->p;
+    if (grouped_p) *grouped_p = &k->g;
+    return CGBN_OK;
+}
+
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 cgbn_status check_ws(const Plan& p, const void* ws, size_t bytes)
@@ -1149,9 +1189,9 @@ extern "C" {
 
 size_t cgbn_workspace_bytes(int N, int C, int H, int W, cgbn_layout layout, cgbn_dtype dtype, int K)
 {
-    Plan p;
-    if (make_plan(tuning_now(), N, C, H, W, (int)layout, (int)dtype, K, &p) != CGBN_OK) return 0;
-    return p.bytes;
+    const Plan* p;
+    if (plan_of(N, C, H, W, (int)layout, (int)dtype, K, &p) != CGBN_OK) return 0;
+    return p->bytes;
 }
 
 size_t cgbn_workspace_error_offset(int N, int C, int H, int W, cgbn_layout layout, cgbn_dtype dtype, int K)
@@ -1224,10 +1264,10 @@ cgbn_status cgbn_normalize(const void* x, int N, int C, int H, int W, cgbn_layou
                            const float* gamma, const float* beta, void* y, void* stream)
 {
     if (!x || !mean || !invstd || !gamma || !beta || !y) return CGBN_ERR_NULL;
-    Plan p;
-    CGBN_TRY(make_plan(tuning_now(), N, C, H, W, (int)layout, (int)dtype, 1, &p));
+    const Plan *plan, *grouped_plan;
+    CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, 1, &plan, &grouped_plan));
+    const Plan& p = *grouped_plan;
     if (!aligned16(x) || !aligned16(y)) return CGBN_ERR_ALIGN;
-    p = grouped(p);
     SweepArgs A = sweep_args(p);
     A.x = x; A.out = y; A.mean = mean; A.mean_lo = mean_lo; A.invstd = invstd; A.gamma = gamma; A.beta = beta;
     return launch_map(EL_NORM, p, A, static_cast<hipStream_t>(stream));
@@ -1272,10 +1312,10 @@ cgbn_status cgbn_backward_dx(const void* dy, const void* x, int N, int C, int H,
                              void* dx, void* stream)
 {
     if (!dy || !x || !mean || !invstd || !gamma || !dgamma || !dbeta || !dx) return CGBN_ERR_NULL;
-    Plan p;
-    CGBN_TRY(make_plan(tuning_now(), N, C, H, W, (int)layout, (int)dtype, 1, &p));
+    const Plan *plan, *grouped_plan;
+    CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, 1, &plan, &grouped_plan));
+    const Plan& p = *grouped_plan;
     if (!aligned16(x) || !aligned16(dy) || !aligned16(dx)) return CGBN_ERR_ALIGN;
-    p = grouped(p);
     SweepArgs A = sweep_args(p);
     A.x = x; A.dy = dy; A.out = dx; A.mean = mean; A.mean_lo = mean_lo; A.invstd = invstd;
     A.gamma = gamma; A.dgamma = dgamma; A.dbeta = dbeta;
@@ -1287,11 +1327,11 @@ cgbn_status cgbn_frozen_forward(const void* x, int N, int C, int H, int W, cgbn_
                                 const float* gamma, const float* beta, float eps, void* y, void* stream)
 {
     if (!x || !fixed_mean || !fixed_var || !gamma || !beta || !y) return CGBN_ERR_NULL;
-    Plan p;
-    CGBN_TRY(make_plan(tuning_now(), N, C, H, W, (int)layout, (int)dtype, 1, &p));
+    const Plan *plan, *grouped_plan;
+    CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, 1, &plan, &grouped_plan));
+    const Plan& p = *grouped_plan;
     if (!eps_ok(eps)) return CGBN_ERR_EPS;
     if (!aligned16(x) || !aligned16(y)) return CGBN_ERR_ALIGN;
-    p = grouped(p);
     SweepArgs A = sweep_args(p);
     A.x = x; A.out = y; A.mean = fixed_mean; A.invstd = fixed_var; A.gamma = gamma; A.beta = beta; A.eps = eps;
     return launch_map(EL_FROZEN, p, A, static_cast<hipStream_t>(stream));
@@ -1301,11 +1341,11 @@ cgbn_status cgbn_frozen_backward(const void* dy, int N, int C, int H, int W, cgb
                                  const float* fixed_var, const float* gamma, float eps, void* dx, void* stream)
 {
     if (!dy || !fixed_var || !gamma || !dx) return CGBN_ERR_NULL;
-    Plan p;
-    CGBN_TRY(make_plan(tuning_now(), N, C, H, W, (int)layout, (int)dtype, 1, &p));
+    const Plan *plan, *grouped_plan;
+    CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, 1, &plan, &grouped_plan));
+    const Plan& p = *grouped_plan;
     if (!eps_ok(eps)) return CGBN_ERR_EPS;
     if (!aligned16(dy) || !aligned16(dx)) return CGBN_ERR_ALIGN;
-    p = grouped(p);
     SweepArgs A = sweep_args(p);
     A.x = dy; A.out = dx; A.invstd = fixed_var; A.gamma = gamma; A.eps = eps;
     return launch_map(EL_SCALE, p, A, static_cast<hipStream_t>(stream));
@@ -1331,14 +1371,15 @@ cgbn_status cgbn_update_running_stats(const float* mean, const float* mean_lo, c
 namespace {
 
 // Algorithm 1, optionally followed by "+ shortcut" and a ReLU (relu == true)
-cgbn_status forward_impl(const Tuning& T, const void* x, const void* shortcut, bool relu, int N, int C, int H, int W,
+cgbn_status forward_impl(const void* x, const void* shortcut, bool relu, int N, int C, int H, int W,
                          cgbn_layout layout, int K, const float* gamma, const float* beta, float eps,
                          void* y, float* mean, float* invstd, cgbn_dtype dtype, float* mean_lo,
                          void* workspace, size_t workspace_bytes, void* stream)
 {
     if (!x || !gamma || !beta || !y || !mean || !invstd) return CGBN_ERR_NULL;
-    Plan p;
-    CGBN_TRY(make_plan(T, N, C, H, W, (int)layout, (int)dtype, K, &p));
+    const Plan *plan, *grouped_plan;
+    CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, K, &plan, &grouped_plan));
+    const Plan& p = *plan;
     if (!eps_ok(eps)) return CGBN_ERR_EPS;
     if (!aligned16(x) || !aligned16(y) || !aligned16(shortcut)) return CGBN_ERR_ALIGN;
     CGBN_TRY(check_ws(p, workspace, workspace_bytes));
@@ -1382,8 +1423,8 @@ cgbn_status forward_impl(const Tuning& T, const void* x, const void* shortcut, b
         return f32 ? launch_slab_t<float, true, 0>(p, sp, F, st) : launch_slab_t<bf16_t, true, 0>(p, sp, F, st);
     }
 
-    p = grouped(p);
-    SweepArgs A = sweep_args(p);
+    const Plan& q = *grouped_plan;
+    SweepArgs A = sweep_args(q);
     A.x = x; A.part0 = part0;
     if (p.t.one_sweep_stats) {
         // Steps 1-10 from ONE sweep over x: every row partial is (sum about the pivot, M2 about the row's own
@@ -1391,28 +1432,28 @@ cgbn_status forward_impl(const Tuning& T, const void* x, const void* shortcut, b
         // the pooled mean by the pairwise update M2 + M2' + (mean' - mean)^2 n n'/(n + n') (steps 6-10: the same
         // number, term for term, as summing (x - mean)^2 directly).  Then step 11: 3 sweeps of the tensor instead of 4.
         A.part1 = reinterpret_cast<float*>(ws + p.off_part1);
-        CGBN_TRY(launch_reduce(OP_MOMENTS, p, A, st));
-        CGBN_TRY(launch_combine(CM_MOMENTS, p, ws, mean, mlo, mean_lo, nullptr, nullptr, (double)eps, x, st, invstd));
+        CGBN_TRY(launch_reduce(OP_MOMENTS, q, A, st));
+        CGBN_TRY(launch_combine(CM_MOMENTS, q, ws, mean, mlo, mean_lo, nullptr, nullptr, (double)eps, x, st, invstd));
         A.mean = mean; A.mean_lo = mlo; A.invstd = invstd; A.gamma = gamma; A.beta = beta; A.out = y;
         A.reverse = rev; A.dy = shortcut;
-        return launch_map(!relu ? EL_NORM : shortcut ? EL_NORM_ADD_RELU : EL_NORM_RELU, p, A, st);
+        return launch_map(!relu ? EL_NORM : shortcut ? EL_NORM_ADD_RELU : EL_NORM_RELU, q, A, st);
     }
     // steps 1-3 then 4-5
-    CGBN_TRY(launch_reduce(OP_SUM, p, A, st));
-    CGBN_TRY(launch_combine(CM_MEAN, p, ws, mean, mlo, mean_lo, sh0, nullptr, 0.0, x, st));
+    CGBN_TRY(launch_reduce(OP_SUM, q, A, st));
+    CGBN_TRY(launch_combine(CM_MEAN, q, ws, mean, mlo, mean_lo, sh0, nullptr, 0.0, x, st));
     // steps 6-8 then 9-10
     A.mean = mean; A.mean_lo = mlo; A.reverse = rev;
-    CGBN_TRY(launch_reduce(OP_SQDEV, p, A, st));
-    CGBN_TRY(launch_combine(CM_INVSTD, p, ws, invstd, nullptr, nullptr, sh0, nullptr, (double)eps, nullptr, st));
+    CGBN_TRY(launch_reduce(OP_SQDEV, q, A, st));
+    CGBN_TRY(launch_combine(CM_INVSTD, q, ws, invstd, nullptr, nullptr, sh0, nullptr, (double)eps, nullptr, st));
     // step 11
     A.invstd = invstd; A.gamma = gamma; A.beta = beta; A.out = y; A.reverse = 0;
     A.dy = shortcut;
-    return launch_map(!relu ? EL_NORM : shortcut ? EL_NORM_ADD_RELU : EL_NORM_RELU, p, A, st);
+    return launch_map(!relu ? EL_NORM : shortcut ? EL_NORM_ADD_RELU : EL_NORM_RELU, q, A, st);
 }
 
 // The backward; with `y` (the stored output of the ReLU variant) dy is first masked by y > 0
 // and `dshortcut`, if not null, receives the masked dy.
-cgbn_status backward_impl(const Tuning& T, const void* dy, const void* y, const void* x, const float* mean, const float* invstd,
+cgbn_status backward_impl(const void* dy, const void* y, const void* x, const float* mean, const float* invstd,
                           const float* gamma, void* dx, void* dshortcut, float* dgamma, float* dbeta,
                           int N, int C, int H, int W, cgbn_layout layout, int K,
                           cgbn_dtype dtype, const float* mean_lo,
@@ -1420,8 +1461,9 @@ cgbn_status backward_impl(const Tuning& T, const void* dy, const void* y, const 
 {
     if (!dy || !x || !mean || !invstd || !gamma || !dx || !dgamma || !dbeta) return CGBN_ERR_NULL;
     const bool relu = y != nullptr;
-    Plan p;
-    CGBN_TRY(make_plan(T, N, C, H, W, (int)layout, (int)dtype, K, &p));
+    const Plan *plan, *grouped_plan;
+    CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, K, &plan, &grouped_plan));
+    const Plan& p = *plan;
     if (!aligned16(x) || !aligned16(dy) || !aligned16(dx) || !aligned16(y) || !aligned16(dshortcut)) return CGBN_ERR_ALIGN;
     if (dshortcut && dshortcut == dx) return CGBN_ERR_ALIAS;
     CGBN_TRY(check_ws(p, workspace, workspace_bytes));
@@ -1461,19 +1503,19 @@ cgbn_status backward_impl(const Tuning& T, const void* dy, const void* y, const 
         return f32 ? launch_slab_t<float, false, 0>(p, sp, F, st) : launch_slab_t<bf16_t, false, 0>(p, sp, F, st);
     }
 
-    p = grouped(p);
-    SweepArgs A = sweep_args(p);
+    const Plan& q = *grouped_plan;
+    SweepArgs A = sweep_args(q);
     A.x = x; A.dy = dy; A.mean = mean; A.mean_lo = mean_lo; A.invstd = invstd;
     A.part0 = reinterpret_cast<float*>(ws + p.off_part0);
     A.part1 = reinterpret_cast<float*>(ws + p.off_part1);
     A.reverse = rev;
     A.aux = y; A.out2 = dshortcut;
-    CGBN_TRY(launch_reduce(relu ? OP_BWD_RELU : OP_BWD, p, A, st));
-    CGBN_TRY(launch_combine(CM_BWD, p, ws, dbeta, dgamma, nullptr,
+    CGBN_TRY(launch_reduce(relu ? OP_BWD_RELU : OP_BWD, q, A, st));
+    CGBN_TRY(launch_combine(CM_BWD, q, ws, dbeta, dgamma, nullptr,
                             reinterpret_cast<double*>(ws + p.off_sh0), reinterpret_cast<double*>(ws + p.off_sh1),
                             0.0, nullptr, st));
     A.gamma = gamma; A.dgamma = dgamma; A.dbeta = dbeta; A.out = dx; A.reverse = 0;
-    return launch_map(relu ? EL_DX_RELU : EL_DX, p, A, st);
+    return launch_map(relu ? EL_DX_RELU : EL_DX, q, A, st);
 }
 
 }  // namespace
@@ -1486,7 +1528,7 @@ cgbn_status cgbn_forward(const void* x, int N, int C, int H, int W, cgbn_layout 
                          cgbn_dtype dtype, float* mean_lo,
                          void* workspace, size_t workspace_bytes, void* stream)
 {
-    return forward_impl(tuning_now(), x, nullptr, false, N, C, H, W, layout, K, gamma, beta, eps, y, mean, invstd, dtype, mean_lo,
+    return forward_impl(x, nullptr, false, N, C, H, W, layout, K, gamma, beta, eps, y, mean, invstd, dtype, mean_lo,
                         workspace, workspace_bytes, stream);
 }
 
@@ -1497,15 +1539,14 @@ cgbn_status cgbn_forward_static(const void* x, int N, int C, int H, int W, cgbn_
 {
     // every argument error is answered before the device is asked for anything
     if (!x || !gamma || !beta || !y || !mean || !invstd) return CGBN_ERR_NULL;
-    const Tuning T = tuning_now();
-    Plan p;
-    CGBN_TRY(make_plan(T, N, C, H, W, (int)layout, (int)dtype, K, &p));
+    const Plan* p;
+    CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, K, &p));
     if (!eps_ok(eps)) return CGBN_ERR_EPS;
     if (!aligned16(x) || !aligned16(y)) return CGBN_ERR_ALIGN;
-    if (p.bytes > (size_t)CGBN_STATIC_SCRATCH_BYTES) return CGBN_ERR_SCRATCH;
+    if (p->bytes > (size_t)CGBN_STATIC_SCRATCH_BYTES) return CGBN_ERR_SCRATCH;
     void* ws = nullptr;
     CGBN_TRY(scratch_of_current_device(&ws));
-    return forward_impl(T, x, nullptr, false, N, C, H, W, layout, K, gamma, beta, eps, y, mean, invstd, dtype, mean_lo,
+    return forward_impl(x, nullptr, false, N, C, H, W, layout, K, gamma, beta, eps, y, mean, invstd, dtype, mean_lo,
                         ws, (size_t)CGBN_STATIC_SCRATCH_BYTES, stream);
 }
 
@@ -1515,7 +1556,7 @@ cgbn_status cgbn_backward(const void* dy, const void* x, const float* mean, cons
                           cgbn_dtype dtype, const float* mean_lo,
                           void* workspace, size_t workspace_bytes, void* stream)
 {
-    return backward_impl(tuning_now(), dy, nullptr, x, mean, invstd, gamma, dx, nullptr, dgamma, dbeta, N, C, H, W, layout, K,
+    return backward_impl(dy, nullptr, x, mean, invstd, gamma, dx, nullptr, dgamma, dbeta, N, C, H, W, layout, K,
                          dtype, mean_lo, workspace, workspace_bytes, stream);
 }
 
@@ -1524,7 +1565,7 @@ cgbn_status cgbn_forward_relu(const void* x, const void* shortcut, int N, int C,
                               void* y, float* mean, float* invstd, cgbn_dtype dtype, float* mean_lo,
                               void* workspace, size_t workspace_bytes, void* stream)
 {
-    return forward_impl(tuning_now(), x, shortcut, true, N, C, H, W, layout, K, gamma, beta, eps, y, mean, invstd, dtype, mean_lo,
+    return forward_impl(x, shortcut, true, N, C, H, W, layout, K, gamma, beta, eps, y, mean, invstd, dtype, mean_lo,
                         workspace, workspace_bytes, stream);
 }
 
@@ -1535,7 +1576,7 @@ cgbn_status cgbn_backward_relu(const void* dy, const void* y, const void* x, con
                                void* workspace, size_t workspace_bytes, void* stream)
 {
     if (!y) return CGBN_ERR_NULL;
-    return backward_impl(tuning_now(), dy, y, x, mean, invstd, gamma, dx, dshortcut, dgamma, dbeta, N, C, H, W, layout, K,
+    return backward_impl(dy, y, x, mean, invstd, gamma, dx, dshortcut, dgamma, dbeta, N, C, H, W, layout, K,
                          dtype, mean_lo, workspace, workspace_bytes, stream);
 }
 
@@ -1617,6 +1658,7 @@ cgbn_status cgbn_set_tuning(const char* key, long long value)
     }
     std::lock_guard<std::mutex> hold(g_tune_lock);
     *slot = value;
+    g_tune_version.fetch_add(1, std::memory_order_release);
     return CGBN_OK;
 }
 

@@ -1,0 +1,108 @@
+"""The extension that marshals the training step's calls converts its arguments as ctypes does (on calls that the library refuses, so
+that nothing is launched), and a plan kept from an earlier call is the plan a fresh thread makes."""
+
+import threading
+
+import numpy as np
+import pytest
+
+from paper_1711_07240_amd import cgbn as L
+
+P = 1 << 20          # an aligned address that is never followed: every call below is refused
+
+
+class Buffer:
+    """What the binding asks of a tensor."""
+    def __init__(self, address, count=0, size=1):
+        self.address, self.count, self.size = address, count, size
+
+    def data_ptr(self):
+        return self.address
+
+    def numel(self):
+        return self.count
+
+    def element_size(self):
+        return self.size
+
+
+FORWARD = dict(x=P, N=2, C=8, H=4, W=4, layout=0, K=1, gamma=P, beta=P, eps=1e-5, y=P, mean=P, invstd=P, dtype=0, mean_lo=None,
+               workspace=P, workspace_bytes=0, stream=0)
+BACKWARD = dict(dy=P, x=P, mean=P, invstd=P, gamma=P, dx=P, dgamma=P, dbeta=P, N=2, C=8, H=4, W=4, layout=0, K=1, dtype=0, mean_lo=None,
+                workspace=P, workspace_bytes=0, stream=0)
+FROZEN = dict(x=P, N=2, C=8, H=4, W=4, layout=0, dtype=0, fixed_mean=P, fixed_var=P, gamma=P, beta=P, eps=-1.0, y=P, stream=0)
+CALLS = {
+    "cgbn_forward": FORWARD,
+    "cgbn_forward_relu": {"x": P, "shortcut": None, **{k: v for k, v in FORWARD.items() if k != "x"}},
+    "cgbn_backward": BACKWARD,
+    "cgbn_backward_relu": {"dy": P, "y": P, "x": P, "mean": P, "invstd": P, "gamma": P, "dx": P, "dshortcut": None,
+                           **{k: v for k, v in BACKWARD.items() if k not in ("dy", "x", "mean", "invstd", "gamma", "dx")}},
+    "cgbn_frozen_forward": FROZEN,
+    "cgbn_frozen_backward": dict(dy=P, N=2, C=8, H=4, W=4, layout=0, dtype=0, fixed_var=P, gamma=P, eps=-1.0, dx=P, stream=0),
+}
+
+
+def _code(fn, kw):
+    try:
+        getattr(L, fn)(**kw)
+    except L.CgbnError as e:
+        return e.code
+    return L.CGBN_OK
+
+
+def _ctypes_code(fn, kw):
+    return getattr(L.lib(), fn)(*kw.values())
+
+
+@pytest.mark.parametrize("fn", CALLS)
+def test_status_codes_as_by_ctypes(fn):
+    base = CALLS[fn]
+    assert _code(fn, base) == _ctypes_code(fn, base) != L.CGBN_OK
+    changes = [{k: None} for k, v in base.items() if v == P] + [{k: 0} for k, v in base.items() if v == P]
+    changes += [{k: P + 4} for k, v in base.items() if v == P]
+    changes += [{"N": 0}, {"C": -1}, {"H": (1 << 32) + 4}, {"layout": 7}, {"dtype": 9}, {"eps": float("nan")}, {"K": 3}, {"mean_lo": P}, {"workspace_bytes": 1 << 40}]
+    for c in changes:
+        kw = {**base, **{k: v for k, v in c.items() if k in base}}
+        if kw.get("workspace_bytes") == 1 << 40 and kw.get("eps", -1.0) > 0 and "x" in kw:
+            kw["x"] = P + 4                    # (else the call would not be refused)
+        elif kw.get("workspace_bytes") == 1 << 40:
+            kw["dx"] = P + 4
+        assert _code(fn, kw) == _ctypes_code(fn, kw) != L.CGBN_OK, (fn, c)
+
+
+def test_names_tensors_and_sizes():
+    assert _code("cgbn_forward", {**FORWARD, "layout": "NHWC", "dtype": "bf16"}) == _ctypes_code("cgbn_forward", {**FORWARD, "layout": 1, "dtype": 1})
+    need = L.cgbn_workspace_bytes(2, 8, 4, 4, "NCHW", "f32", 1)
+    # (ws too small: workspace; large enough: the eps that comes before it is what is refused)
+    assert _code("cgbn_forward", {**FORWARD, "workspace": Buffer(P, need // 4 - 1, 4), "workspace_bytes": None}) == \
+        _ctypes_code("cgbn_forward", {**FORWARD, "workspace_bytes": need - 4})
+    assert _code("cgbn_forward", {**FORWARD, "x": Buffer(P + 8), "workspace_bytes": need}) == _ctypes_code("cgbn_forward", {**FORWARD, "x": P + 8, "workspace_bytes": need})
+    for bad, error in (({"layout": "NCWH"}, KeyError), ({"x": "text"}, AttributeError), ({"N": 2.5}, TypeError), ({"eps": "a"}, ValueError)):
+        with pytest.raises(error):
+            L.cgbn_forward(**{**FORWARD, **bad})
+    with pytest.raises(TypeError):
+        L.cgbn_forward(P)
+
+
+def test_kept_plans():
+    """More shapes than are kept, in two orders, with a knob changed in between; another thread keeps nothing yet."""
+    r = np.random.default_rng(3)
+    shapes = []
+    for _ in range(150):
+        K = int(r.integers(1, 5))
+        shapes.append((K * int(r.integers(1, 9)), int(r.integers(1, 300)), int(r.integers(1, 60)), int(r.integers(1, 60)),
+                       str(r.choice(["NCHW", "NHWC"])), str(r.choice(["f32", "bf16"])), K))
+    sizes = lambda order: {s: L.cgbn_workspace_bytes(*s) for s in order}
+    first = sizes(shapes)
+    assert all(v > 0 for v in first.values()) and sizes(reversed(shapes)) == first
+    assert L.cgbn_workspace_bytes(0, *shapes[0][1:]) == 0 and L.cgbn_workspace_bytes(*shapes[0]) == first[shapes[0]]
+    L.cgbn_set_tuning("piece_bytes", 4096)
+    try:
+        changed, fresh = sizes(shapes), {}
+        t = threading.Thread(target=lambda: fresh.update(sizes(shapes)))
+        t.start()
+        t.join()
+        assert changed == fresh and changed != first
+    finally:
+        L.cgbn_set_tuning("piece_bytes", 0)
+    assert sizes(shapes) == first
