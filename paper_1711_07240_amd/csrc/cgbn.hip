@@ -1144,6 +1144,7 @@ cgbn_status launch_slab_kernel(KernelT kernel, const Plan& p, const SlabPlan& s,
         if (groups < s.total_units) {
             const int polling = ((A.rch + s.U - 1) / s.U * A.G + kWave - 1) / kWave;      // wavefronts with channels to add up
             A.prefetch = polling < kSlabWaves ? polling : 0;
+            A.ahead = A.inflight == 1 ? 1 : 2;           // see SlabAhead
             A.stagger = A.inflight == 2 ? 600u : (A.inflight == 3 || A.inflight == 4 ? 250u : 0u);      // see slab_stagger
         }
         const long long words = 2 * slab_row_words(s);

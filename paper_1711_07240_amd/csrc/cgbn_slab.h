@@ -72,6 +72,7 @@ struct SlabArgs {
     unsigned spin_limit;
     unsigned stagger;     // start-up stagger: 100 MHz ticks per slab in flight
     int prefetch;         // several rounds: the wavefronts from this one on fetch the next unit's first passes into LDS during the hand-over
+    int ahead;            // ... 2: all passes the LDS has room for; 1: the first kSlabAheadFew (backward)
     unsigned bitmap_words;    // per slab
     unsigned cpc_magic;       // 2^32 / cpc, rounded up: i / cpc is the high word of i * cpc_magic for the small i here
 };
@@ -515,7 +516,11 @@ __device__ __forceinline__ void slab_stagger(const SlabArgs& A)
 // polls would queue behind their loads; always the first) fetches its part of the next unit's first passes straight into LDS.
 // Measured, without -> with, us: fp32 67200 x 1024 forward 141 -> 129, backward 224 -> 204, fp32 268800 x 512 304 -> 276 and
 // 454 -> 440, bf16 268800 x 512 151 -> 146 and 247 -> 239.
+// With one slab in flight everyone is in the hand-over at the same time, and what a compute unit fetches stands before its polls, which
+// its L1 answers in order: there the backward fetches two passes of the eight (backward, eight -> two: 268800 x 512 bf16 233 -> 222 us, with a
+// mask 287 -> 280, fp32 430 -> 416; with two or more in flight the eight are better, fp32 67200 x 1024 194, two 204).
 constexpr int kSlabAhead = kSlabWaves - 1;         // wavefronts that fetch ahead
+constexpr int kSlabAheadFew = 2;
 struct SlabAhead {
     SlabPass ps;
     const char* base[2];
@@ -528,11 +533,12 @@ struct SlabAhead {
         base[0] = b0 + g.base;
         base[1] = b1 + g.base;
     }
-    template <int PRE, int TENSORS> __device__ __forceinline__ void fetch(u32x4* ext)
+    // the first N passes, into slots for PRE
+    template <int PRE, int TENSORS, int N = PRE> __device__ __forceinline__ void fetch(u32x4* ext)
     {
         const int w = __builtin_amdgcn_readfirstlane((int)(fresh(threadIdx.x) >> 6)) - 1;
 #pragma unroll
-        for (int i = 0; i < PRE; ++i)
+        for (int i = 0; i < N; ++i)
 #pragma unroll
             for (int q = 0; q < TENSORS; ++q) {
                 __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(base[q] + ps.lane(i)),
@@ -863,19 +869,28 @@ __global__ __launch_bounds__(kSlabThreads, DENSE || P * (ACT != 0 ? 3 : 2) <= (S
                     yu += ps.advance(i);
                 }
             };
-            if (PRE != 0 && __builtin_amdgcn_readfirstlane(fetched) != 0) {
-                unroll_planes<PRE>([&](auto i_) __attribute__((always_inline)) {
-                    constexpr int i = decltype(i_)::value;
-                    gd[i] = slab_fetched(ext, i, t);
-                    xd[i] = slab_fetched(ext, PRE + i, t);
-                    gu += ps.advance(i);
-                    if constexpr (ACT == 0) xu += ps.advance(i);
-                    else yu += ps.advance(i);
-                });
-            } else {
-                unroll_planes<PRE>([&](auto i_) __attribute__((always_inline)) {
-                    load(i_, gd[decltype(i_)::value], xd[decltype(i_)::value]);
-                });
+            // passes [FROM, FROM + N) from the LDS or from memory
+            auto first = [&](auto from_, auto n_, bool in_lds) __attribute__((always_inline)) {
+                constexpr int from = decltype(from_)::value;
+                if (in_lds) {
+                    unroll_planes<decltype(n_)::value>([&](auto i_) __attribute__((always_inline)) {
+                        constexpr int i = from + decltype(i_)::value;
+                        gd[i] = slab_fetched(ext, i, t);
+                        xd[i] = slab_fetched(ext, PRE + i, t);
+                        gu += ps.advance(i);
+                        if constexpr (ACT == 0) xu += ps.advance(i);
+                        else yu += ps.advance(i);
+                    });
+                } else {
+                    unroll_planes<decltype(n_)::value>([&](auto i_) __attribute__((always_inline)) {
+                        constexpr int i = from + decltype(i_)::value;
+                        load(IntC<i>{}, gd[i], xd[i]);
+                    });
+                }
+            };
+            if constexpr (PRE != 0) {
+                first(IntC<0>{}, IntC<kSlabAheadFew>{}, __builtin_amdgcn_readfirstlane(fetched) != 0);
+                first(IntC<kSlabAheadFew>{}, IntC<PRE - kSlabAheadFew>{}, __builtin_amdgcn_readfirstlane(fetched) == 2);
             }
             unroll_planes<P - PRE>([&](auto i_) __attribute__((always_inline)) {
                 constexpr int i = PRE + decltype(i_)::value;
@@ -924,8 +939,10 @@ __global__ __launch_bounds__(kSlabThreads, DENSE || P * (ACT != 0 ? 3 : 2) <= (S
             mine = slab_hand_over<false>(A, L, slab, u, [&] {
                 if constexpr (PRE != 0)
                     if (A.prefetch != 0 && unit + (int)gridDim.x < A.total_units) {
-                        SlabAhead(A, unit + (int)gridDim.x, gb, ACT == 0 ? xb : ab).template fetch<PRE, 2>(ext);
-                        fetched = 1;
+                        SlabAhead next(A, unit + (int)gridDim.x, gb, ACT == 0 ? xb : ab);
+                        if (A.ahead == 2) next.template fetch<PRE, 2>(ext);
+                        else next.template fetch<PRE, 2, kSlabAheadFew>(ext);
+                        fetched = A.ahead;
                     }
             });
             ok = L.skip != 2;
