@@ -78,6 +78,19 @@ CGBN_DECL_SD(bf16_t, 1)
 #undef CGBN_DECL_SD
 CGBN_SLAB_FORWARD_P(CGBN_DECL_SF)
 CGBN_SLAB_BACKWARD_P(CGBN_DECL_SB)
+#define CGBN_DECL_SN(P_)                                                                        \
+    extern template __global__ void slab_forward<float, 0, P_, true, false, 8>(SlabArgs);       \
+    extern template __global__ void slab_forward<float, 1, P_, true, false, 8>(SlabArgs);       \
+    extern template __global__ void slab_forward<float, 2, P_, true, false, 8>(SlabArgs);       \
+    extern template __global__ void slab_forward<bf16_t, 0, P_, true, false, 8>(SlabArgs);      \
+    extern template __global__ void slab_forward<bf16_t, 1, P_, true, false, 8>(SlabArgs);      \
+    extern template __global__ void slab_forward<bf16_t, 2, P_, true, false, 8>(SlabArgs);      \
+    extern template __global__ void slab_backward<float, 0, P_, true, false, 8>(SlabArgs);      \
+    extern template __global__ void slab_backward<float, 1, P_, true, false, 8>(SlabArgs);      \
+    extern template __global__ void slab_backward<bf16_t, 0, P_, true, false, 8>(SlabArgs);     \
+    extern template __global__ void slab_backward<bf16_t, 1, P_, true, false, 8>(SlabArgs);
+CGBN_SLAB_NARROW_P(CGBN_DECL_SN)
+#undef CGBN_DECL_SN
 #undef CGBN_DECL_SF
 #undef CGBN_DECL_SB
 #undef CGBN_DECL_FX
@@ -173,6 +186,7 @@ struct SlabPlan {
     int first;            // ... and faster than the single-launch NCHW kernels, where the shape can take those too
     int cols, vecs, rpp, cpc, nch, tpc, slabs, U, rpu;
     int P;                // vectors per thread of the kernel variant
+    int vb;               // bytes of a vector
     long long R, row_bytes, total_units;
 };
 
@@ -201,6 +215,7 @@ struct Plan {
     FusedPlan ff, fb;     // register-resident path, forward and backward
     SlabPlan sf, sb;      // column-slab path
     SlabPlan sfs, sbm;    // ... of a forward with a shortcut, of a masked backward
+    SlabPlan nf, nb, nfs, nbm;    // the same with 8-byte vectors: taken in their place where ok
     // workspace layout (byte offsets)
     size_t off_part0, off_part1, off_sh0, off_sh1, off_mlo, off_sync, bytes;
 };
@@ -359,6 +374,7 @@ long long slab_row_words(const SlabPlan& s) { return (long long)s.slabs * s.nch 
 // `row_words`: 8-byte words the workspace has room for (a channel's row is two a unit, its results two more).
 bool cut_slabs(SlabPlan* s, int C, int cols, int nch, long long U, long long row_words, int cus, bool forward)
 {
+    s->vb = 16;
     s->cols = cols;
     s->nch = nch;
     s->rpp = kSlabThreads / cols;
@@ -521,6 +537,40 @@ void make_slab_plan(int N, int C, long long HW, int layout, int eb, long long ro
     if (N * s->row_bytes < 6000000) return;
     if (cut_slabs_in_units(s, C, cols, nch, row_words, cus, forward, second))
         s->first = !f.ok || (f.U > 1 && (forward ? HW * eb <= 1024 && N * s->row_bytes <= 200000000 : HW * eb <= (eb == 2 ? 512 : 800) && N * s->row_bytes <= 100000000));
+}
+
+// NCHW calls whose plan `s` has 16-byte vectors: one of 8-byte vectors in its place (see SlabVector).
+void make_narrow_plan(int N, int C, long long HW, int eb, bool forward, bool second, const SlabPlan& s, int cus, SlabPlan* n)
+{
+    std::memset(n, 0, sizeof(*n));
+    const int vec = 8 / eb;
+    if (!s.ok || s.cpc != HW || (s.U == 1 && 2 * s.slabs > cus)) return;
+    // (float, four vectors a thread at most: there is little to share out; backward of 67 x 224 planes of 4x5 5.0, so 5.1, masked 5.6, 5.8)
+    if (eb == 4 && s.P <= 4 && (!forward || second)) return;
+    // (float, masked, many vectors: three tensors' loads on all compute units; 208 x 512 planes of 5x8 10 % slower, 216 x 40 of 4x7 6 %)
+    if (eb == 4 && s.P > 8 && !forward && second) return;
+    int nch = vec;
+    while (nch * 2 <= kSlabMaxChannels && nch < C && (long long)nch / vec * HW < 8) nch *= 2;
+    *n = s;
+    n->ok = 0;
+    n->vb = 8;
+    n->vecs = s.vecs * 2;
+    n->cols = (int)(nch / vec * HW);
+    n->nch = nch;
+    n->rpp = kSlabThreads / n->cols;
+    n->tpc = nch * kWave <= kSlabThreads ? kWave : kSlabThreads / nch;
+    n->slabs = (n->vecs + n->cols - 1) / n->cols;
+    n->U = 1;
+    n->rpu = N;
+    n->total_units = n->slabs;
+    n->P = 0;
+    const int passes = n->rpp > 0 ? (N + n->rpp - 1) / n->rpp : 0;
+#define CGBN_SLAB_BEST(P_) if (passes > 0 && passes <= P_ && n->P == 0) n->P = P_;
+    CGBN_SLAB_NARROW_P(CGBN_SLAB_BEST)
+#undef CGBN_SLAB_BEST
+    if (!n->P || n->slabs > C || (s.U > 1 && n->slabs > cus)) return;
+    if ((long long)n->rpp * n->row_bytes + (long long)n->cols * 8 > 0x7fffffffLL) return;
+    n->ok = 1;
 }
 
 // compute units of the current device (256 if there is none to ask)
@@ -742,6 +792,12 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
         // (what a second tensor changes: see there)
         if (one.ok && (one.U == 1 ? layout == CGBN_NCHW || one.R > few_pixels(forward, true, one.row_bytes) : forward))
             make_slab_plan(N, C, HW, layout, p->eb, row_words, cus, forward ? p->ff : p->fb, forward, true, &two);
+    }
+    if (layout == CGBN_NCHW) {
+        make_narrow_plan(N, C, HW, p->eb, true, false, p->sf, cus, &p->nf);
+        make_narrow_plan(N, C, HW, p->eb, true, true, p->sfs, cus, &p->nfs);
+        make_narrow_plan(N, C, HW, p->eb, false, false, p->sb, cus, &p->nb);
+        make_narrow_plan(N, C, HW, p->eb, false, true, p->sbm, cus, &p->nbm);
     }
     for (const SlabPlan* s : {&p->sf, &p->sfs, &p->sb, &p->sbm})
         if (s->ok && s->U > 1) {
@@ -1117,7 +1173,7 @@ SlabArgs slab_args(const Plan& p, const SlabPlan& s, char* ws)
     A.sync = reinterpret_cast<unsigned*>(ws + p.off_sync);
     A.R = s.R; A.row_bytes = s.row_bytes;
     A.inv_M_f64 = 1.0 / p.M; A.inv_M = (float)(1.0 / p.M);
-    A.vecs = s.vecs; A.cols = s.cols; A.ncols = s.cols * (16 / p.eb); A.rpp = s.rpp;
+    A.vecs = s.vecs; A.cols = s.cols; A.ncols = s.cols * (s.vb / p.eb); A.rpp = s.rpp;
     A.cpc = s.cpc; A.nch = s.nch; A.tpc = s.tpc; A.rch = A.ncols / s.cpc;
     A.C = p.C; A.slabs = s.slabs; A.U = s.U; A.rpu = s.rpu; A.total_units = (int)s.total_units;
     A.G = s.U < kWave ? ceil_pow2(s.U) : kWave;
@@ -1160,6 +1216,16 @@ cgbn_status launch_slab_kernel(KernelT kernel, const Plan& p, const SlabPlan& s,
 template <typename T, bool FWD, int ACT>
 cgbn_status launch_slab_t(const Plan& p, const SlabPlan& s, const SlabArgs& A, hipStream_t st)
 {
+    if (s.vb == 8) {
+#define CGBN_SLAB_CASE(P_)                                                                                      \
+        if (s.P == P_) {                                                                                        \
+            if constexpr (FWD) return launch_slab_kernel(slab_forward<T, ACT, P_, true, false, 8>, p, s, A, st); \
+            else return launch_slab_kernel(slab_backward<T, ACT, P_, true, false, 8>, p, s, A, st);             \
+        }
+        CGBN_SLAB_NARROW_P(CGBN_SLAB_CASE)
+#undef CGBN_SLAB_CASE
+        return CGBN_ERR_HIP;
+    }
     constexpr int dense = FWD ? kSlabDenseForward : kSlabDenseBackward;
     if constexpr (!FWD || ACT != 2)
         if (s.U > 1 && s.P == dense && s.total_units > compute_units()) {
@@ -1391,9 +1457,9 @@ cgbn_status forward_impl(const void* x, const void* shortcut, bool relu, int N, 
     float* mlo = reinterpret_cast<float*>(ws + p.off_mlo);
     const int rev = (int)p.t.reverse;
 
-    const SlabPlan& sp = shortcut ? p.sfs : p.sf;
-    const bool slab = p.t.fused && p.t.one_sweep_stats && sp.ok;
-    if (p.t.fused && p.ff.ok && !(slab && sp.first)) {
+    const SlabPlan& wide = shortcut ? p.sfs : p.sf;
+    const bool slab = p.t.fused && p.t.one_sweep_stats && wide.ok;
+    if (p.t.fused && p.ff.ok && !(slab && wide.first)) {
         FusedArgs F = fused_args(p, p.ff, ws);
         F.x = x; F.out = y; F.gamma = gamma; F.beta = beta; F.eps = (double)eps; F.aux = shortcut;
         F.mean = mean; F.mean_lo = mlo; F.mean_lo_user = mean_lo; F.invstd = invstd;
@@ -1415,6 +1481,8 @@ cgbn_status forward_impl(const void* x, const void* shortcut, bool relu, int N, 
 
     g_last_forward_slab = slab;
     if (slab) {
+        const SlabPlan& narrow = shortcut ? p.nfs : p.nf;
+        const SlabPlan& sp = narrow.ok ? narrow : wide;
         SlabArgs F = slab_args(p, sp, ws);
         F.x = x; F.dy = shortcut; F.out = y; F.gamma = gamma; F.beta = beta; F.eps = (double)eps;
         F.mean = mean; F.mean_lo = mean_lo; F.invstd = invstd;
@@ -1472,9 +1540,9 @@ cgbn_status backward_impl(const void* dy, const void* y, const void* x, const fl
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int rev = (int)p.t.reverse;
 
-    const SlabPlan& sp = relu ? p.sbm : p.sb;
-    const bool slab = p.t.fused && sp.ok;
-    if (p.t.fused && p.fb.ok && !(slab && sp.first)) {
+    const SlabPlan& wide = relu ? p.sbm : p.sb;
+    const bool slab = p.t.fused && wide.ok;
+    if (p.t.fused && p.fb.ok && !(slab && wide.first)) {
         FusedArgs F = fused_args(p, p.fb, ws);
         F.x = x; F.dy = dy; F.out = dx; F.gamma = gamma; F.aux = y; F.out2 = dshortcut;
         F.mean = const_cast<float*>(mean); F.mean_lo = const_cast<float*>(mean_lo);
@@ -1495,6 +1563,8 @@ cgbn_status backward_impl(const void* dy, const void* y, const void* x, const fl
 
     g_last_backward_slab = slab;
     if (slab) {
+        const SlabPlan& narrow = relu ? p.nbm : p.nb;
+        const SlabPlan& sp = narrow.ok ? narrow : wide;
         SlabArgs F = slab_args(p, sp, ws);
         F.x = x; F.dy = dy; F.aux = y; F.out = dx; F.out2 = dshortcut; F.gamma = gamma;
         F.mean = const_cast<float*>(mean); F.mean_lo = const_cast<float*>(mean_lo); F.invstd = const_cast<float*>(invstd);
@@ -1702,9 +1772,11 @@ long long cgbn_plan_get(int N, int C, int H, int W, cgbn_layout layout, cgbn_dty
         if (!std::strcmp(k, "total_units")) return f.total_units;
         return -1;
     }
-    if (!std::strncmp(key, "sfwd_", 5) || !std::strncmp(key, "sbwd_", 5) || !std::strncmp(key, "sfwds_", 6) || !std::strncmp(key, "sbwdm_", 6)) {
-        const bool second = key[4] != '_';
-        const SlabPlan& s = key[1] == 'b' ? (second ? p.sbm : p.sb) : (second ? p.sfs : p.sf);
+    if ((key[0] == 's' || key[0] == 'n') && (!std::strncmp(key + 1, "fwd_", 4) || !std::strncmp(key + 1, "bwd_", 4) ||
+                                             !std::strncmp(key + 1, "fwds_", 5) || !std::strncmp(key + 1, "bwdm_", 5))) {
+        const bool second = key[4] != '_', narrow = key[0] == 'n';
+        const SlabPlan& s = key[1] == 'b' ? (second ? (narrow ? p.nbm : p.sbm) : (narrow ? p.nb : p.sb))
+                                          : (second ? (narrow ? p.nfs : p.sfs) : (narrow ? p.nf : p.sf));
         const char* k = key + (second ? 6 : 5);
         if (!std::strcmp(k, "ok")) return s.ok;
         if (!std::strcmp(k, "first")) return s.first;

@@ -393,12 +393,12 @@ struct SlabGeom {
     int n;                    // rows of the unit
     long long base;           // byte offset of the unit's first row, first column
 };
-__device__ __forceinline__ SlabGeom slab_geometry(const SlabArgs& A, int slab, int u)
+__device__ __forceinline__ SlabGeom slab_geometry(const SlabArgs& A, int slab, int u, int vb = 16)
 {
     SlabGeom g;
     const long long row0 = (long long)u * A.rpu, left = A.R - row0;
     g.n = (int)(left < A.rpu ? left : A.rpu);
-    g.base = row0 * A.row_bytes + (long long)slab * A.cols * 16;
+    g.base = row0 * A.row_bytes + (long long)slab * A.cols * vb;
     return g;
 }
 
@@ -410,7 +410,17 @@ __device__ __forceinline__ int slab_of_block(int b, int G)
     return xcd * q + min(xcd, rem) + i;
 }
 
-__device__ __forceinline__ void slab_forget(u32x4& v) { asm volatile("" : "+v"(v)); }    // (see forget)
+template <class V> __device__ __forceinline__ void slab_forget(V& v) { asm volatile("" : "+v"(v)); }    // (see forget)
+
+// VB: bytes of a thread's vectors.  8: one workgroup a slab, NCHW with small planes.  A slab starts and ends on whole vectors, so half the
+// vector is half the channels: twice the workgroups where 16 bytes give at most half the compute units one (what bounds those
+// calls is what one compute unit gets, 50 GB/s of what misses its L1, and its share of the sums), and a workgroup for every slab that would
+// else be two units with their hand-over and a launch that prepares it.  Measured, 16 -> 8 bytes, forward / backward us: bf16
+// 16 x 256 planes of 13x21 (32 workgroups, 64) 11.7 / 12.1 -> 7.9 / 8.3; 256 x 1024 of 7x7 (two units each of 128 slabs, 256 slabs) 21.6 / 24.3 ->
+// 15.5 / 18.2; fp32 113 x 120 of 7x9 8.8 / 8.5 -> 7.0 / 7.3.
+template <int VB> struct SlabVector;
+template <> struct SlabVector<16> { typedef u32x4 V; };
+template <> struct SlabVector<8> { typedef u32x2 V; };
 
 // Several units: the order in which the slabs are taken.  Those in flight together are spread evenly over the row, and a
 // round moves on by one slab: neighbouring columns at a long row stride would crowd the memory channels (measured,
@@ -423,32 +433,32 @@ __device__ __forceinline__ int slab_of_turn(const SlabArgs& A, int turn)
     return j * q + min(j, rem) + k;
 }
 
-template <bool NT> __device__ __forceinline__ void slab_load(const char* p, u32x4& d)
+template <bool NT, class V> __device__ __forceinline__ void slab_load(const char* p, V& d)
 {
-    d = NT ? __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)) : *reinterpret_cast<const u32x4*>(p);
+    d = NT ? __builtin_nontemporal_load(reinterpret_cast<const V*>(p)) : *reinterpret_cast<const V*>(p);
 }
-__device__ __forceinline__ void slab_store(char* p, const u32x4& d, int nt)
+template <class V> __device__ __forceinline__ void slab_store(char* p, const V& d, int nt)
 {
-    if (nt) __builtin_nontemporal_store(d, reinterpret_cast<u32x4*>(p));
-    else *reinterpret_cast<u32x4*>(p) = d;
+    if (nt) __builtin_nontemporal_store(d, reinterpret_cast<V*>(p));
+    else *reinterpret_cast<V*>(p) = d;
 }
-template <typename T> __device__ __forceinline__ void slab_unpack(const u32x4& d, float (&f)[16 / sizeof(T)])
+template <typename T, class V> __device__ __forceinline__ void slab_unpack(const V& d, float (&f)[sizeof(V) / sizeof(T)])
 {
     constexpr int EPW = Packed<T>::EPW;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < (int)sizeof(V) / 4; ++q) {
         float g[EPW];
         Packed<T>::unpack(d[q], g);
 #pragma unroll
         for (int e = 0; e < EPW; ++e) f[q * EPW + e] = g[e];
     }
 }
-template <typename T> __device__ __forceinline__ u32x4 slab_pack(const float (&f)[16 / sizeof(T)])
+template <typename T, class V> __device__ __forceinline__ V slab_pack(const float (&f)[sizeof(V) / sizeof(T)])
 {
     constexpr int EPW = Packed<T>::EPW;
-    u32x4 d;
+    V d;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < (int)sizeof(V) / 4; ++q) {
         float g[EPW];
 #pragma unroll
         for (int e = 0; e < EPW; ++e) g[e] = f[q * EPW + e];
@@ -490,10 +500,10 @@ struct SlabPass {
     __device__ __forceinline__ unsigned lane(int i) const { return i < nr ? loff : 0u; }
     __device__ __forceinline__ long long advance(int i) const { return i + 1 < passes ? step : 0; }
 };
-__device__ __forceinline__ SlabPass slab_pass(const SlabArgs& A, int n, bool live, int r, int col)
+__device__ __forceinline__ SlabPass slab_pass(const SlabArgs& A, int n, bool live, int r, int col, int vb = 16)
 {
     SlabPass p;
-    p.loff = fresh(live ? (unsigned)r * (unsigned)A.row_bytes + (unsigned)col * 16u : 0u);
+    p.loff = fresh(live ? (unsigned)r * (unsigned)A.row_bytes + (unsigned)(col * vb) : 0u);
     p.nr = live ? (n - r + A.rpp - 1) / A.rpp : 0;
     p.passes = (n + A.rpp - 1) / A.rpp;
     p.step = (long long)A.rpp * A.row_bytes;
@@ -571,11 +581,13 @@ __device__ __forceinline__ const u32x4& slab_fetched(const u32x4* ext, int slot,
 // backward, P = 9, of 26980 x 296 26.8 and 24.5.)  DENSE: held all the same, two workgroups per compute unit, where there are
 // more units than compute units: forward of 164 x 800 planes of 11x16 bf16, 500 units, 36.4 us, so 30.7; backward of 149 x 696 of 10x12, 435
 // units, 30.3 and 26.1.
-template <typename T, int ACT, int P, bool SOLO, bool DENSE>
-__global__ __launch_bounds__(kSlabThreads, DENSE || P * (ACT == 2 ? 2 : 1) <= (SOLO ? 4 : 12) ? 4 : 2) void slab_forward(SlabArgs A)
+template <typename T, int ACT, int P, bool SOLO, bool DENSE, int VB = 16>
+__global__ __launch_bounds__(kSlabThreads, DENSE || P * VB / 16 * (ACT == 2 ? 2 : 1) <= (SOLO ? 4 : 12) ? 4 : 2) void slab_forward(SlabArgs A)
 {
-    constexpr int VEC = 16 / (int)sizeof(T);
-    constexpr bool EARLY = ACT == 2 && P <= 20;
+    static_assert(VB == 16 || SOLO, "8-byte vectors: one workgroup a slab");
+    typedef typename SlabVector<VB>::V V;
+    constexpr int VEC = VB / (int)sizeof(T);
+    constexpr bool EARLY = ACT == 2 && P * VB / 16 <= 20;
     constexpr int PRE = !SOLO && P >= 28 ? 16 : 0;
     __shared__ SlabLds L;
     __shared__ u32x4 ext[PRE ? PRE * kSlabAhead * kWave : 1];
@@ -595,15 +607,15 @@ __global__ __launch_bounds__(kSlabThreads, DENSE || P * (ACT == 2 ? 2 : 1) <= (S
         const int slab = SOLO ? unit : slab_of_turn(A, turn);
         const int c0 = slab * A.rch;
         const bool live = r < A.rpp && slab * A.cols + col < A.vecs;
-        const SlabGeom g = slab_geometry(A, slab, u);
-        const SlabPass ps = slab_pass(A, g.n, live, r, col);
-        u32x4 d[P], s[EARLY ? P : 1];
+        const SlabGeom g = slab_geometry(A, slab, u, VB);
+        const SlabPass ps = slab_pass(A, g.n, live, r, col, VB);
+        V d[P], s[EARLY ? P : 1];
         // ---- pivots, then the unit's vectors
         const SlabChannels<VEC> cl(A, col);
         float piv[VEC];
         if (A.cpc == 1) {
-            u32x4 pw;
-            slab_load<false>(xb + (long long)slab * A.cols * 16 + (live ? (unsigned)col * 16u : 0u), pw);
+            V pw;
+            slab_load<false>(xb + (long long)slab * A.cols * VB + (live ? (unsigned)(col * VB) : 0u), pw);
             slab_unpack<T>(pw, piv);
         } else {
 #pragma unroll
@@ -622,7 +634,7 @@ __global__ __launch_bounds__(kSlabThreads, DENSE || P * (ACT == 2 ? 2 : 1) <= (S
             if (PRE != 0 && __builtin_amdgcn_readfirstlane(fetched) != 0) {
                 unroll_planes<PRE>([&](auto i_) __attribute__((always_inline)) {
                     constexpr int i = decltype(i_)::value;
-                    d[i] = slab_fetched(ext, i, t);
+                    if constexpr (VB == 16) d[i] = slab_fetched(ext, i, t);
                     xu += ps.advance(i);
                 });
             } else {
@@ -737,7 +749,7 @@ __global__ __launch_bounds__(kSlabThreads, DENSE || P * (ACT == 2 ? 2 : 1) <= (S
             const SlabChannels<VEC> c3(A, (int)fresh((unsigned)col));
 #pragma unroll
             for (int e = 0; e < VEC; ++e) { mu[e] = L.k0[c3[e]]; gsc[e] = L.k1[c3[e]]; bsh[e] = L.k2[c3[e]]; }
-            auto value = [&](const u32x4& v, const u32x4& w) __attribute__((always_inline)) {
+            auto value = [&](const V& v, const V& w) __attribute__((always_inline)) {
                 float f[VEC], h[VEC];
                 slab_unpack<T>(v, f);
                 if constexpr (ACT == 2) slab_unpack<T>(w, h);
@@ -748,7 +760,7 @@ __global__ __launch_bounds__(kSlabThreads, DENSE || P * (ACT == 2 ? 2 : 1) <= (S
                     if (ACT != 0) z = z < 0.f ? 0.f : z;
                     f[e] = z;
                 }
-                return slab_pack<T>(f);
+                return slab_pack<T, V>(f);
             };
             // (every load has landed, and the compiler knows it: see wait_vector_memory)
             wait_vector_memory();
@@ -760,7 +772,7 @@ __global__ __launch_bounds__(kSlabThreads, DENSE || P * (ACT == 2 ? 2 : 1) <= (S
                 unroll_planes<P / B>([&](auto i_) __attribute__((always_inline)) {
                     constexpr int i0 = decltype(i_)::value * B;
                     if (i0 < ps.passes) {
-                        u32x4 b[B];
+                        V b[B];
 #pragma unroll
                         for (int j = 0; j < B; ++j)
                             if (i0 + j < ps.nr) slab_load<!SOLO>(ru + j * ps.step + ps.loff, b[j]);
@@ -787,7 +799,7 @@ __global__ __launch_bounds__(kSlabThreads, DENSE || P * (ACT == 2 ? 2 : 1) <= (S
                     const SlabGeom m = slab_geometry(A, slab, k);
                     for (int i = r; live && i < m.n; i += A.rpp) {
                         const long long o = m.base + (long long)i * A.row_bytes + (long long)col * 16;
-                        u32x4 v, w = {0u, 0u, 0u, 0u};
+                        V v, w = {};
                         slab_load<false>(xb + o, v);
                         if constexpr (ACT == 2) slab_load<false>(rb + o, w);
                         slab_store(yb + o, value(v, w), 0);
@@ -808,11 +820,13 @@ __global__ __launch_bounds__(kSlabThreads, DENSE || P * (ACT == 2 ? 2 : 1) <= (S
 // P: vectors per thread and tensor.  ACT != 0: dy is first masked by the stored output (A.aux) being positive; the
 // output's vectors are loaded beside the other two where the registers allow (P <= 10), else through the storage x takes
 // afterwards.
-template <typename T, int ACT, int P, bool SOLO, bool DENSE>
-__global__ __launch_bounds__(kSlabThreads, DENSE || P * (ACT != 0 ? 3 : 2) <= (SOLO ? 8 : 12) ? 4 : 2) void slab_backward(SlabArgs A)
+template <typename T, int ACT, int P, bool SOLO, bool DENSE, int VB = 16>
+__global__ __launch_bounds__(kSlabThreads, DENSE || P * VB / 16 * (ACT != 0 ? 3 : 2) <= (SOLO ? 8 : 12) ? 4 : 2) void slab_backward(SlabArgs A)
 {
-    constexpr int VEC = 16 / (int)sizeof(T);
-    constexpr bool THREE = ACT != 0 && P <= (SOLO ? 10 : 6);
+    static_assert(VB == 16 || SOLO, "8-byte vectors: one workgroup a slab");
+    typedef typename SlabVector<VB>::V V;
+    constexpr int VEC = VB / (int)sizeof(T);
+    constexpr bool THREE = ACT != 0 && P * VB / 16 <= (SOLO ? 10 : 6);
     constexpr int PRE = !SOLO && P >= 14 ? 8 : 0;
     __shared__ SlabLds L;
     __shared__ u32x4 ext[PRE ? 2 * PRE * kSlabAhead * kWave : 1];
@@ -834,12 +848,12 @@ __global__ __launch_bounds__(kSlabThreads, DENSE || P * (ACT != 0 ? 3 : 2) <= (S
         const int slab = SOLO ? unit : slab_of_turn(A, turn);
         const int c0 = slab * A.rch;
         const bool live = r < A.rpp && slab * A.cols + col < A.vecs;
-        const SlabGeom g = slab_geometry(A, slab, u);
-        const SlabPass ps = slab_pass(A, g.n, live, r, col);
-        u32x4 xd[P], gd[P], yd[THREE ? P : 1];
-        auto mask = [&](u32x4& v, const u32x4& y) __attribute__((always_inline)) {
+        const SlabGeom g = slab_geometry(A, slab, u, VB);
+        const SlabPass ps = slab_pass(A, g.n, live, r, col, VB);
+        V xd[P], gd[P], yd[THREE ? P : 1];
+        auto mask = [&](V& v, const V& y) __attribute__((always_inline)) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = mask_by_positive<T>(v[q], y[q]);
+            for (int q = 0; q < VB / 4; ++q) v[q] = mask_by_positive<T>(v[q], y[q]);
         };
         const SlabChannels<VEC> cl(A, col);
         float mu[VEC];
@@ -855,7 +869,7 @@ __global__ __launch_bounds__(kSlabThreads, DENSE || P * (ACT != 0 ? 3 : 2) <= (S
             const char* gu = gb + g.base;
             const char* xu = xb + g.base;
             const char* yu = ab + g.base;
-            auto load = [&](auto i_, u32x4& dg, u32x4& dx) __attribute__((always_inline)) {
+            auto load = [&](auto i_, V& dg, V& dx) __attribute__((always_inline)) {
                 constexpr int i = decltype(i_)::value;
                 slab_load<!SOLO>(gu + ps.lane(i), dg);
                 gu += ps.advance(i);
@@ -875,8 +889,10 @@ __global__ __launch_bounds__(kSlabThreads, DENSE || P * (ACT != 0 ? 3 : 2) <= (S
                 if (in_lds) {
                     unroll_planes<decltype(n_)::value>([&](auto i_) __attribute__((always_inline)) {
                         constexpr int i = from + decltype(i_)::value;
-                        gd[i] = slab_fetched(ext, i, t);
-                        xd[i] = slab_fetched(ext, PRE + i, t);
+                        if constexpr (VB == 16) {
+                            gd[i] = slab_fetched(ext, i, t);
+                            xd[i] = slab_fetched(ext, PRE + i, t);
+                        }
                         gu += ps.advance(i);
                         if constexpr (ACT == 0) xu += ps.advance(i);
                         else yu += ps.advance(i);
@@ -973,7 +989,7 @@ __global__ __launch_bounds__(kSlabThreads, DENSE || P * (ACT != 0 ? 3 : 2) <= (S
                 k0[e] = L.k0[c3[e]]; gsc[e] = L.k1[c3[e]]; nk2[e] = L.k2[c3[e]];
                 if constexpr (SOLO) c1[e] = L.k3[c3[e]];
             }
-            auto value = [&](const u32x4& vx, const u32x4& vg) __attribute__((always_inline)) {
+            auto value = [&](const V& vx, const V& vg) __attribute__((always_inline)) {
                 float fx[VEC], fg[VEC];
                 slab_unpack<T>(vx, fx);
                 slab_unpack<T>(vg, fg);
@@ -982,7 +998,7 @@ __global__ __launch_bounds__(kSlabThreads, DENSE || P * (ACT != 0 ? 3 : 2) <= (S
                     if constexpr (SOLO) fg[e] = gsc[e] * (fg[e] - c1[e]) + (nk2[e] * (fx[e] - mu[e]) + k0[e]);
                     else fg[e] = nk2[e] * (fx[e] - mu[e]) + (gsc[e] * fg[e] + k0[e]);
                 }
-                return slab_pack<T>(fg);
+                return slab_pack<T, V>(fg);
             };
             wait_vector_memory();
             char* ou = ob + g.base;
@@ -1003,7 +1019,7 @@ __global__ __launch_bounds__(kSlabThreads, DENSE || P * (ACT != 0 ? 3 : 2) <= (S
                     const SlabGeom m = slab_geometry(A, slab, k);
                     for (int i = r; live && i < m.n; i += A.rpp) {
                         const long long o = m.base + (long long)i * A.row_bytes + (long long)col * 16;
-                        u32x4 vx, vg, vy;
+                        V vx, vg, vy;
                         slab_load<false>(xb + o, vx);
                         slab_load<false>(gb + o, vg);
                         if constexpr (ACT != 0) {
@@ -1026,6 +1042,8 @@ __global__ __launch_bounds__(kSlabThreads, DENSE || P * (ACT != 0 ? 3 : 2) <= (S
 // X(vectors per thread (and tensor), one unit per slab)
 #define CGBN_SLAB_FORWARD_P(X) X(4, true) X(8, true) X(10, true) X(12, true) X(20, true) X(6, false) X(12, false) X(18, false) X(28, false) X(36, false)
 #define CGBN_SLAB_BACKWARD_P(X) X(4, true) X(6, true) X(8, true) X(10, true) X(12, true) X(20, true) X(6, false) X(9, false) X(14, false) X(18, false)
+// vectors per thread (and tensor) of the variants with 8-byte vectors
+#define CGBN_SLAB_NARROW_P(X) X(8) X(12) X(16) X(20) X(28)
 // the variants built DENSE too (the forward without a shortcut)
 constexpr int kSlabDenseForward = 18, kSlabDenseBackward = 9;
 

@@ -17,11 +17,21 @@ template __global__ void slab_backward<CGBN_INST_T, 1, kSlabDenseBackward, false
     template __global__ void slab_forward<CGBN_INST_T, 1, P_, SOLO_, false>(SlabArgs);     \
     template __global__ void slab_forward<CGBN_INST_T, 2, P_, SOLO_, false>(SlabArgs);
 CGBN_SLAB_FORWARD_P(CGBN_X)
+#define CGBN_Y(P_)                                                                         \
+    template __global__ void slab_forward<CGBN_INST_T, 0, P_, true, false, 8>(SlabArgs);   \
+    template __global__ void slab_forward<CGBN_INST_T, 1, P_, true, false, 8>(SlabArgs);   \
+    template __global__ void slab_forward<CGBN_INST_T, 2, P_, true, false, 8>(SlabArgs);
+CGBN_SLAB_NARROW_P(CGBN_Y)
 #else
 #define CGBN_X(P_, SOLO_)                                                                  \
     template __global__ void slab_backward<CGBN_INST_T, 0, P_, SOLO_, false>(SlabArgs);    \
     template __global__ void slab_backward<CGBN_INST_T, 1, P_, SOLO_, false>(SlabArgs);
 CGBN_SLAB_BACKWARD_P(CGBN_X)
+#define CGBN_Y(P_)                                                                         \
+    template __global__ void slab_backward<CGBN_INST_T, 0, P_, true, false, 8>(SlabArgs);  \
+    template __global__ void slab_backward<CGBN_INST_T, 1, P_, true, false, 8>(SlabArgs);
+CGBN_SLAB_NARROW_P(CGBN_Y)
 #endif
 #undef CGBN_X
+#undef CGBN_Y
 }  // namespace cgbn
