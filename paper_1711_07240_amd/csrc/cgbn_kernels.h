@@ -872,21 +872,34 @@ __global__ __launch_bounds__(kThreads) void nhwc_reduce(SweepArgs A)
                 for (int e = 0; e < V; ++e)
                     accumulate<OP>(kc[e], xv[u][e], DY ? dv[u][e] : 0.f, Y ? yv[u][e] : 0.f, a0[e], a1[e]);
         }
-        // what is left, four loads together (beyond the end the last pixel again)
-        for (; i < npix; i += 4 * rpp) {
-            typename Access<T, V>::Raw rx[4], rd[4], ry[4];
+        // What is left.  With a second tensor four loads of each together (beyond the end the last pixel again): shard sums of the
+        // backward, 10 x 193 x 278 x 176 fp32, 150 -> 132 us.  With x alone one at a time: four cost the plain sum more than they gain
+        // (64 x 40 x 40 x 1376 bf16 68, four 78; 64 x 50 x 84 x 512 58, 62) and change nothing for fp32 or the other sums.
+        if constexpr (DY) {
+            for (; i < npix; i += 4 * rpp) {
+                typename Access<T, V>::Raw rx[4], rd[4], ry[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const long long o = (long long)min(i + u * rpp, npix - 1) * C;
-                rx[u] = Access<T, V>::load_raw(px + o);
-                if (DY) rd[u] = Access<T, V>::load_raw(pd + o);
-                if (Y) ry[u] = Access<T, V>::load_raw(py + o);
+                for (int u = 0; u < 4; ++u) {
+                    const long long o = (long long)min(i + u * rpp, npix - 1) * C;
+                    rx[u] = Access<T, V>::load_raw(px + o);
+                    rd[u] = Access<T, V>::load_raw(pd + o);
+                    if (Y) ry[u] = Access<T, V>::load_raw(py + o);
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (i + u * rpp >= npix) break;
+                    float xv[V], dv[V], yv[V];
+                    Access<T, V>::unpack(rx[u], xv);
+                    Access<T, V>::unpack(rd[u], dv);
+                    if (Y) Access<T, V>::unpack(ry[u], yv);
+#pragma unroll
+                    for (int e = 0; e < V; ++e) accumulate<OP>(kc[e], xv[e], dv[e], Y ? yv[e] : 0.f, a0[e], a1[e]);
+                }
             }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if (i + u * rpp >= npix) break;
-                float xv[V], dv[V], yv[V];
-                Access<T, V>::unpack(rx[u], xv);
+        } else {
+            for (; i < npix; i += rpp) {
+                float xv[V];
+                Access<T, V>::load(px + (long long)i * C, xv);
                 if constexpr (OP == OP_MOMENTS) {
                     const float rn = cnt > 0.f ? __builtin_amdgcn_rcpf(cnt) : 0.f;
                     const float wj = cnt * __builtin_amdgcn_rcpf(cnt + 1.f);
@@ -899,10 +912,8 @@ __global__ __launch_bounds__(kThreads) void nhwc_reduce(SweepArgs A)
                     }
                     cnt += 1.f;
                 } else {
-                    if (DY) Access<T, V>::unpack(rd[u], dv);
-                    if (Y) Access<T, V>::unpack(ry[u], yv);
 #pragma unroll
-                    for (int e = 0; e < V; ++e) accumulate<OP>(kc[e], xv[e], DY ? dv[e] : 0.f, Y ? yv[e] : 0.f, a0[e], a1[e]);
+                    for (int e = 0; e < V; ++e) accumulate<OP>(kc[e], xv[e], 0.f, 0.f, a0[e], a1[e]);
                 }
             }
         }
@@ -917,7 +928,8 @@ __global__ __launch_bounds__(kThreads) void nhwc_reduce(SweepArgs A)
         }
     }
     __syncthreads();
-    // (grouped pixels: one tile, and the columns of a channel, A.ch apart, are joined too)
+    // (grouped pixels: one tile, and the columns of a channel, A.ch apart, are joined too.  In a loop of their own: inside one the chain
+    // of additions, all that is left to do with many rows of threads, takes longer; shard sums of 2 x 100 x 168 x 16 bf16 9.4 us, so 11.9)
     const int outs = A.group == 1 ? nout : A.ch;
     for (int o = t; o < outs; o += kThreads) {
         const int ch = ct * nout + o;
@@ -926,20 +938,26 @@ __global__ __launch_bounds__(kThreads) void nhwc_reduce(SweepArgs A)
         if constexpr (OP == OP_MOMENTS) {
             // the pixel rows' summaries joined in row order; row rr took pixels rr, rr + rpp, ... of the piece
             Run acc = {0.f, 0.f, 0.f};
-            for (int q = o; q < nout; q += outs)
+            auto fold = [&](int q) __attribute__((always_inline)) {
                 for (int rr = 0; rr < A.rpp; ++rr) {
                     const int n_rr = rr < npix ? (npix - rr + A.rpp - 1) / A.rpp : 0;
                     Run part = {(float)n_rr, sm[(0 * A.rpp + rr) * nout + q], sm[(1 * A.rpp + rr) * nout + q]};
                     acc = run_join(acc, part);
                 }
+            };
+            fold(o);
+            for (int q = o + outs; q < nout; q += outs) fold(q);
             s0 = acc.S;
             s1 = acc.M2;
         } else {
-            for (int q = o; q < nout; q += outs)
+            auto fold = [&](int q) __attribute__((always_inline)) {
                 for (int rr = 0; rr < A.rpp; ++rr) {
                     s0 += sm[(0 * A.rpp + rr) * nout + q];
                     if (Q == 2) s1 += sm[(1 * A.rpp + rr) * nout + q];
                 }
+            };
+            fold(o);
+            for (int q = o + outs; q < nout; q += outs) fold(q);
         }
         size_t po = (size_t)row * A.ch + ch;          // consecutive threads, consecutive floats: whole lines per store
         A.part0[po] = s0;
