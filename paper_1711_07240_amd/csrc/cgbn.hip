@@ -684,6 +684,18 @@ bool group_pixels(const Plan& p, Plan* q)
     // bf16 58 / 71 us, value by value 43 / 61)
     return q->ctiles == 1;
 }
+// Whether a reduction (over dy too, or x alone) groups pixels: a thread that takes few values one by one has little to gain, and the
+// wider rows of threads keep fewer workgroups busy.  Measured, values a thread one by one: time one by one, grouped, us: forward bf16
+// 16 x 4 x 6 x 414 24: 12.5, 15.6; 24 x 8 x 8 x 414 64: 14.9, 16.4; 15 x 32 x 52 x 13 87: 18.5, 14.6; 8 x 14 x 14 x 302 196: 23.0, 14.3; backward
+// 64 x 7 x 8 x 98 28: 14.7, 16.0 (masked 15.9, 16.5); 32 x 7 x 8 x 150 56: 14.6, 14.3; 16 x 8 x 8 x 203 64: 15.1, 14.5 (masked 18.2, 15.1);
+// fp32 forward 106 x 4 x 5 x 163 20: 16.4, 17.2; masked 11 x 4 x 6 x 414 24: 10.9, 12.1; 16 x 8 x 8 x 203 64: 15.1, 11.7.
+// Where a shard is no whole number of groups its pixels are pooled, which leaves fewer rows to join: always (backward 200 x 5 x 5 x 34 fp32
+// 21.3, 11.4; bf16 21.1, 13.6).
+bool group_sums(const Plan& p, bool with_dy)
+{
+    if (p.may_group == 1) return false;
+    return p.spix % p.may_group != 0 || p.PL / p.rpp >= (with_dy ? 40 : 80);
+}
 Plan grouped(const Plan& p)
 {
     Plan q = p;
@@ -822,9 +834,11 @@ struct KeptPlan {
     int key[8];
     unsigned version;
     bool valid = false;
+    // the plan of a channels-last reduction whose sums are handed out pooled
+    const Plan& sums(bool with_dy) const { return group_sums(p, with_dy) ? g : p; }
 };
 constexpr int kKeptPlans = 64;
-cgbn_status plan_of(int N, int C, int H, int W, int layout, int dtype, int K, const Plan** p, const Plan** grouped_p = nullptr)
+cgbn_status plan_of(int N, int C, int H, int W, int layout, int dtype, int K, const KeptPlan** out)
 {
     static thread_local std::unique_ptr<KeptPlan> kept[kKeptPlans];
     int dev = -1;
@@ -845,8 +859,7 @@ cgbn_status plan_of(int N, int C, int H, int W, int layout, int dtype, int K, co
         k->version = version;
         k->valid = g_tune_version.load(std::memory_order_acquire) == version;
     }
-    *p = &k->p;
-    if (grouped_p) *grouped_p = &k->g;
+    *out = k.get();
     return CGBN_OK;
 }
 
@@ -1256,9 +1269,9 @@ extern "C" {
 
 size_t cgbn_workspace_bytes(int N, int C, int H, int W, cgbn_layout layout, cgbn_dtype dtype, int K)
 {
-    const Plan* p;
-    if (plan_of(N, C, H, W, (int)layout, (int)dtype, K, &p) != CGBN_OK) return 0;
-    return p->bytes;
+    const KeptPlan* k;
+    if (plan_of(N, C, H, W, (int)layout, (int)dtype, K, &k) != CGBN_OK) return 0;
+    return k->p.bytes;
 }
 
 size_t cgbn_workspace_error_offset(int N, int C, int H, int W, cgbn_layout layout, cgbn_dtype dtype, int K)
@@ -1331,9 +1344,9 @@ cgbn_status cgbn_normalize(const void* x, int N, int C, int H, int W, cgbn_layou
                            const float* gamma, const float* beta, void* y, void* stream)
 {
     if (!x || !mean || !invstd || !gamma || !beta || !y) return CGBN_ERR_NULL;
-    const Plan *plan, *grouped_plan;
-    CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, 1, &plan, &grouped_plan));
-    const Plan& p = *grouped_plan;
+    const KeptPlan* k;
+    CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, 1, &k));
+    const Plan& p = k->g;
     if (!aligned16(x) || !aligned16(y)) return CGBN_ERR_ALIGN;
     SweepArgs A = sweep_args(p);
     A.x = x; A.out = y; A.mean = mean; A.mean_lo = mean_lo; A.invstd = invstd; A.gamma = gamma; A.beta = beta;
@@ -1379,9 +1392,9 @@ cgbn_status cgbn_backward_dx(const void* dy, const void* x, int N, int C, int H,
                              void* dx, void* stream)
 {
     if (!dy || !x || !mean || !invstd || !gamma || !dgamma || !dbeta || !dx) return CGBN_ERR_NULL;
-    const Plan *plan, *grouped_plan;
-    CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, 1, &plan, &grouped_plan));
-    const Plan& p = *grouped_plan;
+    const KeptPlan* k;
+    CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, 1, &k));
+    const Plan& p = k->g;
     if (!aligned16(x) || !aligned16(dy) || !aligned16(dx)) return CGBN_ERR_ALIGN;
     SweepArgs A = sweep_args(p);
     A.x = x; A.dy = dy; A.out = dx; A.mean = mean; A.mean_lo = mean_lo; A.invstd = invstd;
@@ -1394,9 +1407,9 @@ cgbn_status cgbn_frozen_forward(const void* x, int N, int C, int H, int W, cgbn_
                                 const float* gamma, const float* beta, float eps, void* y, void* stream)
 {
     if (!x || !fixed_mean || !fixed_var || !gamma || !beta || !y) return CGBN_ERR_NULL;
-    const Plan *plan, *grouped_plan;
-    CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, 1, &plan, &grouped_plan));
-    const Plan& p = *grouped_plan;
+    const KeptPlan* k;
+    CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, 1, &k));
+    const Plan& p = k->g;
     if (!eps_ok(eps)) return CGBN_ERR_EPS;
     if (!aligned16(x) || !aligned16(y)) return CGBN_ERR_ALIGN;
     SweepArgs A = sweep_args(p);
@@ -1408,9 +1421,9 @@ cgbn_status cgbn_frozen_backward(const void* dy, int N, int C, int H, int W, cgb
                                  const float* fixed_var, const float* gamma, float eps, void* dx, void* stream)
 {
     if (!dy || !fixed_var || !gamma || !dx) return CGBN_ERR_NULL;
-    const Plan *plan, *grouped_plan;
-    CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, 1, &plan, &grouped_plan));
-    const Plan& p = *grouped_plan;
+    const KeptPlan* k;
+    CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, 1, &k));
+    const Plan& p = k->g;
     if (!eps_ok(eps)) return CGBN_ERR_EPS;
     if (!aligned16(dy) || !aligned16(dx)) return CGBN_ERR_ALIGN;
     SweepArgs A = sweep_args(p);
@@ -1444,9 +1457,9 @@ cgbn_status forward_impl(const void* x, const void* shortcut, bool relu, int N, 
                          void* workspace, size_t workspace_bytes, void* stream)
 {
     if (!x || !gamma || !beta || !y || !mean || !invstd) return CGBN_ERR_NULL;
-    const Plan *plan, *grouped_plan;
-    CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, K, &plan, &grouped_plan));
-    const Plan& p = *plan;
+    const KeptPlan* k;
+    CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, K, &k));
+    const Plan& p = k->p;
     if (!eps_ok(eps)) return CGBN_ERR_EPS;
     if (!aligned16(x) || !aligned16(y) || !aligned16(shortcut)) return CGBN_ERR_ALIGN;
     CGBN_TRY(check_ws(p, workspace, workspace_bytes));
@@ -1492,7 +1505,7 @@ cgbn_status forward_impl(const void* x, const void* shortcut, bool relu, int N, 
         return f32 ? launch_slab_t<float, true, 0>(p, sp, F, st) : launch_slab_t<bf16_t, true, 0>(p, sp, F, st);
     }
 
-    const Plan& q = *grouped_plan;
+    const Plan &q = k->sums(false), &m = k->g;
     SweepArgs A = sweep_args(q);
     A.x = x; A.part0 = part0;
     if (p.t.one_sweep_stats) {
@@ -1503,9 +1516,10 @@ cgbn_status forward_impl(const void* x, const void* shortcut, bool relu, int N, 
         A.part1 = reinterpret_cast<float*>(ws + p.off_part1);
         CGBN_TRY(launch_reduce(OP_MOMENTS, q, A, st));
         CGBN_TRY(launch_combine(CM_MOMENTS, q, ws, mean, mlo, mean_lo, nullptr, nullptr, (double)eps, x, st, invstd));
-        A.mean = mean; A.mean_lo = mlo; A.invstd = invstd; A.gamma = gamma; A.beta = beta; A.out = y;
+        A = sweep_args(m);
+        A.x = x; A.mean = mean; A.mean_lo = mlo; A.invstd = invstd; A.gamma = gamma; A.beta = beta; A.out = y;
         A.reverse = rev; A.dy = shortcut;
-        return launch_map(!relu ? EL_NORM : shortcut ? EL_NORM_ADD_RELU : EL_NORM_RELU, q, A, st);
+        return launch_map(!relu ? EL_NORM : shortcut ? EL_NORM_ADD_RELU : EL_NORM_RELU, m, A, st);
     }
     // steps 1-3 then 4-5
     CGBN_TRY(launch_reduce(OP_SUM, q, A, st));
@@ -1515,9 +1529,10 @@ cgbn_status forward_impl(const void* x, const void* shortcut, bool relu, int N, 
     CGBN_TRY(launch_reduce(OP_SQDEV, q, A, st));
     CGBN_TRY(launch_combine(CM_INVSTD, q, ws, invstd, nullptr, nullptr, sh0, nullptr, (double)eps, nullptr, st));
     // step 11
-    A.invstd = invstd; A.gamma = gamma; A.beta = beta; A.out = y; A.reverse = 0;
+    A = sweep_args(m);
+    A.x = x; A.mean = mean; A.mean_lo = mlo; A.invstd = invstd; A.gamma = gamma; A.beta = beta; A.out = y;
     A.dy = shortcut;
-    return launch_map(!relu ? EL_NORM : shortcut ? EL_NORM_ADD_RELU : EL_NORM_RELU, q, A, st);
+    return launch_map(!relu ? EL_NORM : shortcut ? EL_NORM_ADD_RELU : EL_NORM_RELU, m, A, st);
 }
 
 // The backward; with `y` (the stored output of the ReLU variant) dy is first masked by y > 0
@@ -1530,9 +1545,9 @@ cgbn_status backward_impl(const void* dy, const void* y, const void* x, const fl
 {
     if (!dy || !x || !mean || !invstd || !gamma || !dx || !dgamma || !dbeta) return CGBN_ERR_NULL;
     const bool relu = y != nullptr;
-    const Plan *plan, *grouped_plan;
-    CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, K, &plan, &grouped_plan));
-    const Plan& p = *plan;
+    const KeptPlan* k;
+    CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, K, &k));
+    const Plan& p = k->p;
     if (!aligned16(x) || !aligned16(dy) || !aligned16(dx) || !aligned16(y) || !aligned16(dshortcut)) return CGBN_ERR_ALIGN;
     if (dshortcut && dshortcut == dx) return CGBN_ERR_ALIAS;
     CGBN_TRY(check_ws(p, workspace, workspace_bytes));
@@ -1574,19 +1589,22 @@ cgbn_status backward_impl(const void* dy, const void* y, const void* x, const fl
         return f32 ? launch_slab_t<float, false, 0>(p, sp, F, st) : launch_slab_t<bf16_t, false, 0>(p, sp, F, st);
     }
 
-    const Plan& q = *grouped_plan;
+    const Plan &q = k->sums(true), &m = k->g;
     SweepArgs A = sweep_args(q);
     A.x = x; A.dy = dy; A.mean = mean; A.mean_lo = mean_lo; A.invstd = invstd;
     A.part0 = reinterpret_cast<float*>(ws + p.off_part0);
     A.part1 = reinterpret_cast<float*>(ws + p.off_part1);
     A.reverse = rev;
-    A.aux = y; A.out2 = dshortcut;
+    A.aux = y;
     CGBN_TRY(launch_reduce(relu ? OP_BWD_RELU : OP_BWD, q, A, st));
     CGBN_TRY(launch_combine(CM_BWD, q, ws, dbeta, dgamma, nullptr,
                             reinterpret_cast<double*>(ws + p.off_sh0), reinterpret_cast<double*>(ws + p.off_sh1),
                             0.0, nullptr, st));
-    A.gamma = gamma; A.dgamma = dgamma; A.dbeta = dbeta; A.out = dx; A.reverse = 0;
-    return launch_map(relu ? EL_DX_RELU : EL_DX, q, A, st);
+    A = sweep_args(m);
+    A.x = x; A.dy = dy; A.mean = mean; A.mean_lo = mean_lo; A.invstd = invstd;
+    A.aux = y; A.out2 = dshortcut;
+    A.gamma = gamma; A.dgamma = dgamma; A.dbeta = dbeta; A.out = dx;
+    return launch_map(relu ? EL_DX_RELU : EL_DX, m, A, st);
 }
 
 }  // namespace
@@ -1610,11 +1628,11 @@ cgbn_status cgbn_forward_static(const void* x, int N, int C, int H, int W, cgbn_
 {
     // every argument error is answered before the device is asked for anything
     if (!x || !gamma || !beta || !y || !mean || !invstd) return CGBN_ERR_NULL;
-    const Plan* p;
-    CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, K, &p));
+    const KeptPlan* k;
+    CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, K, &k));
     if (!eps_ok(eps)) return CGBN_ERR_EPS;
     if (!aligned16(x) || !aligned16(y)) return CGBN_ERR_ALIGN;
-    if (p->bytes > (size_t)CGBN_STATIC_SCRATCH_BYTES) return CGBN_ERR_SCRATCH;
+    if (k->p.bytes > (size_t)CGBN_STATIC_SCRATCH_BYTES) return CGBN_ERR_SCRATCH;
     void* ws = nullptr;
     CGBN_TRY(scratch_of_current_device(&ws));
     return forward_impl(x, nullptr, false, N, C, H, W, layout, K, gamma, beta, eps, y, mean, invstd, dtype, mean_lo,
@@ -1794,6 +1812,8 @@ long long cgbn_plan_get(int N, int C, int H, int W, cgbn_layout layout, cgbn_dty
         return -1;
     }
     if (!std::strcmp(key, "may_group")) return p.may_group;
+    if (!std::strcmp(key, "group_sums")) return group_sums(p, false);
+    if (!std::strcmp(key, "group_sums_dy")) return group_sums(p, true);
     if (!std::strncmp(key, "grouped_", 8)) {
         const Plan q = grouped(p);
         const char* k = key + 8;

@@ -769,7 +769,7 @@ template <int V> __device__ __forceinline__ void load_channels(const float* p, f
 // The constants of V neighbouring columns from column c on.
 template <typename T, int OP, int V> __device__ __forceinline__ void reduce_consts_of(const SweepArgs& A, int c, ChanConst (&k)[V])
 {
-    if (A.group != 1) {
+    if (V != 1 && A.group != 1) {
         c %= A.ch;
 #pragma unroll
         for (int e = 0; e < V; ++e) {
@@ -928,40 +928,56 @@ __global__ __launch_bounds__(kThreads) void nhwc_reduce(SweepArgs A)
         }
     }
     __syncthreads();
-    // (grouped pixels: one tile, and the columns of a channel, A.ch apart, are joined too.  In a loop of their own: inside one the chain
-    // of additions, all that is left to do with many rows of threads, takes longer; shard sums of 2 x 100 x 168 x 16 bf16 9.4 us, so 11.9)
-    const int outs = A.group == 1 ? nout : A.ch;
-    for (int o = t; o < outs; o += kThreads) {
-        const int ch = ct * nout + o;
-        if (ch >= A.ch) continue;
-        float s0 = 0.f, s1 = 0.f;
-        if constexpr (OP == OP_MOMENTS) {
-            // the pixel rows' summaries joined in row order; row rr took pixels rr, rr + rpp, ... of the piece
-            Run acc = {0.f, 0.f, 0.f};
-            auto fold = [&](int q) __attribute__((always_inline)) {
-                for (int rr = 0; rr < A.rpp; ++rr) {
-                    const int n_rr = rr < npix ? (npix - rr + A.rpp - 1) / A.rpp : 0;
-                    Run part = {(float)n_rr, sm[(0 * A.rpp + rr) * nout + q], sm[(1 * A.rpp + rr) * nout + q]};
-                    acc = run_join(acc, part);
-                }
-            };
-            fold(o);
-            for (int q = o + outs; q < nout; q += outs) fold(q);
-            s0 = acc.S;
-            s1 = acc.M2;
-        } else {
-            auto fold = [&](int q) __attribute__((always_inline)) {
-                for (int rr = 0; rr < A.rpp; ++rr) {
-                    s0 += sm[(0 * A.rpp + rr) * nout + q];
-                    if (Q == 2) s1 += sm[(1 * A.rpp + rr) * nout + q];
-                }
-            };
-            fold(o);
-            for (int q = o + outs; q < nout; q += outs) fold(q);
+    // the pixel rows' sums of column o; OP_MOMENTS: their summaries joined in row order, row rr took pixels rr, rr + rpp, ... of the piece
+    auto fold = [&](int o) __attribute__((always_inline)) {
+        Run f = {0.f, 0.f, 0.f};
+        for (int rr = 0; rr < A.rpp; ++rr) {
+            const float s0 = sm[(0 * A.rpp + rr) * nout + o], s1 = Q == 2 ? sm[(1 * A.rpp + rr) * nout + o] : 0.f;
+            if constexpr (OP == OP_MOMENTS) {
+                const int n_rr = rr < npix ? (npix - rr + A.rpp - 1) / A.rpp : 0;
+                f = run_join(f, {(float)n_rr, s0, s1});
+            } else {
+                f.S += s0;
+                f.M2 += s1;
+            }
         }
-        size_t po = (size_t)row * A.ch + ch;          // consecutive threads, consecutive floats: whole lines per store
-        A.part0[po] = s0;
-        if (Q == 2) A.part1[po] = s1;
+        return f;
+    };
+    auto store = [&](int ch, const Run& f) __attribute__((always_inline)) {
+        const size_t po = (size_t)row * A.ch + ch;    // consecutive threads, consecutive floats: whole lines per store
+        A.part0[po] = f.S;
+        if (Q == 2) A.part1[po] = f.M2;
+    };
+    if (V == 1 || A.group == 1) {
+        for (int o = t; o < nout; o += kThreads) {
+            const int ch = ct * nout + o;
+            if (ch < A.ch) store(ch, fold(o));
+        }
+        return;
+    }
+    // Grouped pixels, one tile: every column by itself, then a channel's columns, A.ch apart, in order.  (With few channels the chain of
+    // joins is what such a workgroup takes longest for: one thread a channel for all of them, forward of 15 x 32 x 52 x 13 bf16 31.6 us,
+    // so 14.6; value by value 18.5.)
+    if (A.rpp > 1) {
+        for (int o = t; o < nout; o += kThreads) {
+            const Run f = fold(o);
+            sm[o] = f.S;
+            if (Q == 2) sm[A.rpp * nout + o] = f.M2;
+        }
+        __syncthreads();
+    }
+    for (int ch = t; ch < A.ch; ch += kThreads) {
+        Run f = {0.f, 0.f, 0.f};
+        for (int o = ch; o < nout; o += A.ch) {
+            const float s0 = sm[o], s1 = Q == 2 ? sm[A.rpp * nout + o] : 0.f;
+            if constexpr (OP == OP_MOMENTS) {
+                f = run_join(f, {(float)npix, s0, s1});
+            } else {
+                f.S += s0;
+                f.M2 += s1;
+            }
+        }
+        store(ch, f);
     }
 }
 

@@ -26,7 +26,15 @@ CASES = [
     (2, 2, 300, 300, "bf16", 2, 4),           # one vector a group
     (2, 6, 200, 211, "f32", 1, 2),
     (3, 50, 9, 8, "f32", 3, 1),               # a small tensor
+    (15, 13, 32, 52, "bf16", 15, 8),          # few channels, many rows of threads: what is joined is most of a workgroup's work
+    (16, 11, 60, 60, "f32", 4, 4),
+    (24, 414, 8, 8, "bf16", 24, 4),           # the forward's sums value by value, the backward's grouped
+    (16, 414, 4, 6, "bf16", 16, 4),           # both value by value, the elementwise sweeps grouped
+    (32, 98, 14, 14, "f32", 32, 2),           # ragged last pass of grouped rows
+    (200, 34, 5, 5, "bf16", 200, 4),          # shards of 25 pixels: pooled
 ]
+# sums (of x alone, with dy) that group pixels, where pixels may be grouped at all
+ONE_BY_ONE = {(24, 414, 8, 8): (0, 1), (16, 414, 4, 6): (0, 0)}
 FROZEN = CASES + [(2, 1024, 13, 9, "bf16", 1, 1), (1, 2048, 5, 7, "f32", 1, 1), (3, 64, 37, 11, "bf16", 1, 1), (2, 256, 3, 1, "f32", 1, 1)]
 
 
@@ -52,6 +60,7 @@ def test_plan(case):
     shape = (N, C, H, W, "NHWC", dtype, K)
     get = lambda k: L.cgbn_plan_get(*shape, k)
     assert get("may_group") == group
+    assert (get("group_sums"), get("group_sums_dy")) == (ONE_BY_ONE.get((N, C, H, W), (1, 1)) if group > 1 else (0, 0))
     if group > 1:
         g = lambda k: get("grouped_" + k)
         assert C * group % (16 // (4 if dtype == "f32" else 2)) == 0 and g("ctiles") == 1
