@@ -991,25 +991,11 @@ template <int EL, int V> struct MapConsts {
         const bool low = !FIXED && A.mean_lo != nullptr;
 #pragma unroll
         for (int e = 0; e < V; ++e) mu[e] = lo[e] = b[e] = c2[e] = 0.f;
-        if (A.group == 1) {
-            load_channels<V>(A.invstd + c, is);
-            load_channels<V>(A.gamma + c, g);
-            if (EL != EL_SCALE) { load_channels<V>(A.mean + c, mu); load_channels<V>(pb + c, b); }
-            if (low) load_channels<V>(A.mean_lo + c, lo);
-            if (!FIXED && !el_is_norm(EL)) load_channels<V>(A.dgamma + c, c2);
-            asm volatile("");        // (or the compiler merges these loads with the single ones below)
-        } else {
-            c %= A.ch;
-#pragma unroll
-            for (int e = 0; e < V; ++e) {
-                is[e] = A.invstd[c];
-                g[e] = A.gamma[c];
-                if (EL != EL_SCALE) { mu[e] = A.mean[c]; b[e] = pb[c]; }
-                if (low) lo[e] = A.mean_lo[c];
-                if (!FIXED && !el_is_norm(EL)) c2[e] = A.dgamma[c];
-                if (++c == A.ch) c = 0;
-            }
-        }
+        load_channels<V>(A.invstd + c, is);
+        load_channels<V>(A.gamma + c, g);
+        if (EL != EL_SCALE) { load_channels<V>(A.mean + c, mu); load_channels<V>(pb + c, b); }
+        if (low) load_channels<V>(A.mean_lo + c, lo);
+        if (!FIXED && !el_is_norm(EL)) load_channels<V>(A.dgamma + c, c2);
     }
     __device__ __forceinline__ void form(const SweepArgs& A, ChanConst (&k)[V])      // (as map_consts)
     {
@@ -1022,16 +1008,20 @@ template <int EL, int V> struct MapConsts {
     }
 };
 
-// Elementwise, HBM bound: one thread, one vector column, UNR pixels at a time.  A workgroup has 16 to 256 KiB to move, a few chunks a
-// thread, so what stands before the first chunk counts: its loads are issued before the channels' constants are formed, and
-// with fixed statistics, where a constant is a square root and a division, a workgroup with at least as many rows of threads as a vector
-// has channels forms each channel's once.  What is left
+// Floats a channel's constants take in LDS.
+template <int EL> constexpr int map_const_words() { return EL == EL_SCALE ? 1 : EL == EL_FROZEN ? 3 : el_is_norm(EL) ? 4 : 6; }
+
+// Elementwise, HBM bound: one thread, one vector column, UNR pixels at a time.  A workgroup has at most 32 KiB to move, a chunk or two a
+// thread, so what stands before the first chunk counts: its loads are issued before the channels' constants are formed.  Each
+// channel's are formed once, in LDS, with fixed statistics, where a constant is a square root and a division, if there are at least as many
+// rows of threads as a vector has channels; and with grouped pixels, whose columns' channels do not lie side by side (every thread its
+// columns' own one by one, us: dx of 83 x 38 x 52 x 115 bf16 33.6, so 25; 40 x 16 x 21 x 161 fp32 8.9, 6.4).  What is left
 // after the first chunk is loaded four pixels at a time (lanes beyond the end read the last pixel again).
 template <typename T, int V, int EL>
 __global__ __launch_bounds__(kThreads) void nhwc_map(SweepArgs A)
 {
     constexpr bool IN2 = el_has_2(EL), IN3 = el_has_3(EL), FIXED = EL == EL_FROZEN || EL == EL_SCALE;
-    __shared__ float fixed[EL == EL_FROZEN ? 3 : 1][FIXED ? kThreads : 1];
+    extern __shared__ float lds_consts[];        // of the workgroup's channels: [map_const_words][channels]
     long long b = A.reverse ? (long long)gridDim.x - 1 - blockIdx.x : (long long)blockIdx.x;
     int ct = (int)(b % A.ctiles);
     int row = (int)(b / A.ctiles);
@@ -1086,25 +1076,39 @@ __global__ __launch_bounds__(kThreads) void nhwc_map(SweepArgs A)
     };
     constexpr int nolimit = 0x7fffffff;
     int i = r;
-    const bool whole = i + (UNR - 1) * rpp < npix, shared = FIXED && (A.group == 1 ? rpp >= V : A.ch <= kThreads);
+    const bool whole = i + (UNR - 1) * rpp < npix, shared = V != 1 && (A.group != 1 || (FIXED && rpp >= V));
     // (the constants' loads first: they are waited for first, and the first stores leave while the chunk's last loads are under way)
     MapConsts<EL, V> consts;
     if (!shared) consts.load(A, cb);
     if (whole) load(std::integral_constant<int, UNR>{}, i, nolimit);
     if (shared) {
-        // (no more channels than threads: rpp * TW <= kThreads)
+        // (without groups no more channels than threads: rpp * TW <= kThreads)
         const int c0 = A.group == 1 ? ct * A.TW * V : 0, channels = A.group == 1 ? A.TW * V : A.ch;
-        if (t < channels && c0 + t < A.ch) {
-            const ChanConst f = map_consts<EL>(A, c0 + t);
-            fixed[0][t] = f.g;
-            if constexpr (EL == EL_FROZEN) { fixed[1][t] = f.mu; fixed[2][t] = f.b; }
+        auto put = [&](int c, const ChanConst& f) __attribute__((always_inline)) {
+            lds_consts[c] = f.g;
+            if constexpr (EL != EL_SCALE) { lds_consts[channels + c] = f.mu; lds_consts[2 * channels + c] = f.b; }
+            if constexpr (!FIXED) lds_consts[3 * channels + c] = f.mulo;
+            if constexpr (!FIXED && !el_is_norm(EL)) { lds_consts[4 * channels + c] = f.istd; lds_consts[5 * channels + c] = f.c2; }
+        };
+        if (channels <= kThreads) {
+            if (t < channels && c0 + t < A.ch) put(t, map_consts<EL>(A, c0 + t));
+        } else {
+            // two at a time, their loads under way together
+            for (int c = t; c < channels; c += 2 * kThreads) {
+                const int c2 = min(c + kThreads, channels - 1);
+                const ChanConst f = map_consts<EL>(A, c), f2 = map_consts<EL>(A, c2);
+                put(c, f);
+                put(c2, f2);
+            }
         }
         __syncthreads();
         int o = active ? col * V % channels : 0;
 #pragma unroll
         for (int e = 0; e < V; ++e) {
-            kc[e] = {0.f, 0.f, 0.f, fixed[0][o], 0.f, 0.f};
-            if constexpr (EL == EL_FROZEN) { kc[e].mu = fixed[1][o]; kc[e].b = fixed[2][o]; }
+            kc[e] = {0.f, 0.f, 0.f, lds_consts[o], 0.f, 0.f};
+            if constexpr (EL != EL_SCALE) { kc[e].mu = lds_consts[channels + o]; kc[e].b = lds_consts[2 * channels + o]; }
+            if constexpr (!FIXED) kc[e].mulo = lds_consts[3 * channels + o];
+            if constexpr (!FIXED && !el_is_norm(EL)) { kc[e].istd = lds_consts[4 * channels + o]; kc[e].c2 = lds_consts[5 * channels + o]; }
             if (++o == channels) o = 0;
         }
     } else {

@@ -32,8 +32,11 @@ CASES = [
     (16, 414, 4, 6, "bf16", 16, 4),           # both value by value, the elementwise sweeps grouped
     (32, 98, 14, 14, "f32", 32, 2),           # ragged last pass of grouped rows
     (200, 34, 5, 5, "bf16", 200, 4),          # shards of 25 pixels: pooled
+    (4, 414, 50, 60, "f32", 4, 2),            # more channels than threads: constants in two rounds
+    (2, 306, 24, 32, "f32", 2, 2),            # ... of a small tensor: with a second input value by value
 ]
 # sums (of x alone, with dy) that group pixels, where pixels may be grouped at all
+MAP2_ONE_BY_ONE = {(2, 306, 24, 32)}          # elementwise sweeps with a second input
 ONE_BY_ONE = {(24, 414, 8, 8): (0, 1), (16, 414, 4, 6): (0, 0)}
 FROZEN = CASES + [(2, 1024, 13, 9, "bf16", 1, 1), (1, 2048, 5, 7, "f32", 1, 1), (3, 64, 37, 11, "bf16", 1, 1), (2, 256, 3, 1, "f32", 1, 1)]
 
@@ -61,6 +64,7 @@ def test_plan(case):
     get = lambda k: L.cgbn_plan_get(*shape, k)
     assert get("may_group") == group
     assert (get("group_sums"), get("group_sums_dy")) == (ONE_BY_ONE.get((N, C, H, W), (1, 1)) if group > 1 else (0, 0))
+    assert (get("group_map"), get("group_map2")) == ((1, (N, C, H, W) not in MAP2_ONE_BY_ONE) if group > 1 else (0, 0))
     if group > 1:
         g = lambda k: get("grouped_" + k)
         assert C * group % (16 // (4 if dtype == "f32" else 2)) == 0 and g("ctiles") == 1
