@@ -643,11 +643,14 @@ bool cut_pixels(const Tuning& T, long long spix, int cols, int K, Plan* p)
     // workgroups a compute unit.  Measured, 32 / 64 / 128 KiB, us: with fixed statistics 2 x 200 x 336 x 256 bf16 24.5 / 25.7 / 28.7, fp32 50.2 /
     // 54.0 / 58.5, 4 x 100 x 100 x 64 bf16 3.9 / 4.7 / 6.1; as the last sweep of a forward / backward of 64 x 50 x 84 x 512 bf16 169 / 249, 173 / 256,
     // 176 / 264, fp32 316 / 485, 319 / 502, 325 / 515.
+    //   Value by value 16 values a thread, two chunks: 32 KiB of a row of several tiles are few pixels, of a narrow one many.  Fixed
+    // statistics / dx, 32 KiB -> 16 values: 67 x 68 x 69 x 87 bf16 27.3 / 46 -> 24.1 / 31, fp32 331 x 441 x 149 41.1 / 51.6 -> 36.6 / 46.7,
+    // 9 x 79 x 85 x 249 20.6 / 33.8 -> 20.2 / 32.1.
     for (int two = 0; two < 2; ++two) {
         const long long quantum = 4 * p->rpp;
         long long bytes = T.map_piece_bytes > 0 ? T.map_piece_bytes : 32768, PLm, ppsm;
         for (;; bytes /= 2) {
-            PLm = bytes / ((long long)cols * p->eb);
+            PLm = p->vec == 1 && T.map_piece_bytes == 0 ? bytes / 2048 * p->rpp : bytes / ((long long)cols * p->eb);
             PLm -= PLm % quantum;
             if (PLm < quantum) PLm = quantum;
             if (PLm > p->spix) PLm = p->spix;

@@ -872,34 +872,31 @@ __global__ __launch_bounds__(kThreads) void nhwc_reduce(SweepArgs A)
                 for (int e = 0; e < V; ++e)
                     accumulate<OP>(kc[e], xv[u][e], DY ? dv[u][e] : 0.f, Y ? yv[u][e] : 0.f, a0[e], a1[e]);
         }
-        // What is left.  With a second tensor four loads of each together (beyond the end the last pixel again): shard sums of the
-        // backward, 10 x 193 x 278 x 176 fp32, 150 -> 132 us.  With x alone one at a time: four cost the plain sum more than they gain
-        // (64 x 40 x 40 x 1376 bf16 68, four 78; 64 x 50 x 84 x 512 58, 62) and change nothing for fp32 or the other sums.
-        if constexpr (DY) {
-            for (; i < npix; i += 4 * rpp) {
-                typename Access<T, V>::Raw rx[4], rd[4], ry[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const long long o = (long long)min(i + u * rpp, npix - 1) * C;
-                    rx[u] = Access<T, V>::load_raw(px + o);
-                    rd[u] = Access<T, V>::load_raw(pd + o);
-                    if (Y) ry[u] = Access<T, V>::load_raw(py + o);
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if (i + u * rpp >= npix) break;
-                    float xv[V], dv[V], yv[V];
-                    Access<T, V>::unpack(rx[u], xv);
-                    Access<T, V>::unpack(rd[u], dv);
-                    if (Y) Access<T, V>::unpack(ry[u], yv);
-#pragma unroll
-                    for (int e = 0; e < V; ++e) accumulate<OP>(kc[e], xv[e], dv[e], Y ? yv[e] : 0.f, a0[e], a1[e]);
-                }
-            }
-        } else {
+        // What is left, four loads together (beyond the end the last pixel again): shard sums of the backward, 10 x 193 x 278 x 176 fp32, 150 ->
+        // 132 us.  The plain sum by whole vectors one at a time: four cost it more than they gain (64 x 40 x 40 x 1376 bf16 68, four 78;
+        // 64 x 50 x 84 x 512 58, 62).
+        if constexpr (OP == OP_SUM && V != 1) {
             for (; i < npix; i += rpp) {
                 float xv[V];
                 Access<T, V>::load(px + (long long)i * C, xv);
+#pragma unroll
+                for (int e = 0; e < V; ++e) accumulate<OP>(kc[e], xv[e], 0.f, 0.f, a0[e], a1[e]);
+            }
+        }
+        for (; i < npix; i += 4 * rpp) {
+            typename Access<T, V>::Raw rx[4], rd[4], ry[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const long long o = (long long)min(i + u * rpp, npix - 1) * C;
+                rx[u] = Access<T, V>::load_raw(px + o);
+                if (DY) rd[u] = Access<T, V>::load_raw(pd + o);
+                if (Y) ry[u] = Access<T, V>::load_raw(py + o);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (i + u * rpp >= npix) break;
+                float xv[V], dv[V], yv[V];
+                Access<T, V>::unpack(rx[u], xv);
                 if constexpr (OP == OP_MOMENTS) {
                     const float rn = cnt > 0.f ? __builtin_amdgcn_rcpf(cnt) : 0.f;
                     const float wj = cnt * __builtin_amdgcn_rcpf(cnt + 1.f);
@@ -912,8 +909,10 @@ __global__ __launch_bounds__(kThreads) void nhwc_reduce(SweepArgs A)
                     }
                     cnt += 1.f;
                 } else {
+                    if (DY) Access<T, V>::unpack(rd[u], dv);
+                    if (Y) Access<T, V>::unpack(ry[u], yv);
 #pragma unroll
-                    for (int e = 0; e < V; ++e) accumulate<OP>(kc[e], xv[e], 0.f, 0.f, a0[e], a1[e]);
+                    for (int e = 0; e < V; ++e) accumulate<OP>(kc[e], xv[e], DY ? dv[e] : 0.f, Y ? yv[e] : 0.f, a0[e], a1[e]);
                 }
             }
         }
@@ -948,7 +947,9 @@ __global__ __launch_bounds__(kThreads) void nhwc_reduce(SweepArgs A)
         A.part0[po] = f.S;
         if (Q == 2) A.part1[po] = f.M2;
     };
-    if (V == 1 || A.group == 1) {
+    // (a value at a time there are no groups; bfloat16 is asked all the same, which leaves the code before it in a better order: masked shard
+    // sums of 107 x 20 x 29 x 449 122 us, not asked 131; fp32 94.3 not asked, 95.2)
+    if ((V == 1 && sizeof(T) == 4) || A.group == 1) {
         for (int o = t; o < nout; o += kThreads) {
             const int ch = ct * nout + o;
             if (ch < A.ch) store(ch, fold(o));
@@ -1016,7 +1017,7 @@ template <int EL> constexpr int map_const_words() { return EL == EL_SCALE ? 1 : 
 // channel's are formed once, in LDS, with fixed statistics, where a constant is a square root and a division, if there are at least as many
 // rows of threads as a vector has channels; and with grouped pixels, whose columns' channels do not lie side by side (every thread its
 // columns' own one by one, us: dx of 83 x 38 x 52 x 115 bf16 33.6, so 25; 40 x 16 x 21 x 161 fp32 8.9, 6.4).  What is left
-// after the first chunk is loaded four pixels at a time (lanes beyond the end read the last pixel again).
+// after the whole chunks is loaded four pixels at a time (lanes beyond the end read the last pixel again).
 template <typename T, int V, int EL>
 __global__ __launch_bounds__(kThreads) void nhwc_map(SweepArgs A)
 {
@@ -1076,10 +1077,19 @@ __global__ __launch_bounds__(kThreads) void nhwc_map(SweepArgs A)
     };
     constexpr int nolimit = 0x7fffffff;
     int i = r;
-    const bool whole = i + (UNR - 1) * rpp < npix, shared = V != 1 && (A.group != 1 || (FIXED && rpp >= V));
-    // (the constants' loads first: they are waited for first, and the first stores leave while the chunk's last loads are under way)
+    bool whole = i + (UNR - 1) * rpp < npix;
+    const bool shared = V != 1 && (A.group != 1 || (FIXED && rpp >= V));
+    // (the constants' loads first: they are waited for first, and the first stores leave while the chunk's last loads are under way.  Of
+    // single values, whose chunks are short, the constants are formed first too: fixed statistics 23 x 37 x 63 x 298 bf16 20.3 -> 18.4 us,
+    // 67 x 68 x 69 x 87 24.1 -> 21.6)
     MapConsts<EL, V> consts;
-    if (!shared) consts.load(A, cb);
+    if (!shared) {
+        consts.load(A, cb);
+        if (V == 1) {
+            consts.form(A, kc);
+            asm volatile("" : "+v"(kc[0].g), "+v"(kc[0].mu));
+        }
+    }
     if (whole) load(std::integral_constant<int, UNR>{}, i, nolimit);
     if (shared) {
         // (without groups no more channels than threads: rpp * TW <= kThreads)
@@ -1111,13 +1121,15 @@ __global__ __launch_bounds__(kThreads) void nhwc_map(SweepArgs A)
             if constexpr (!FIXED && !el_is_norm(EL)) { kc[e].istd = lds_consts[4 * channels + o]; kc[e].c2 = lds_consts[5 * channels + o]; }
             if (++o == channels) o = 0;
         }
-    } else {
+    } else if (V != 1) {
         consts.form(A, kc);
     }
-    if (whole) {
+    while (whole) {
 #pragma unroll
         for (int u = 0; u < UNR; ++u) write(u, i + u * rpp);
         i += UNR * rpp;
+        whole = i + (UNR - 1) * rpp < npix;
+        if (whole) load(std::integral_constant<int, UNR>{}, i, nolimit);
     }
     for (; i < npix; i += 4 * rpp) {
         load(std::integral_constant<int, 4>{}, i, npix - 1);

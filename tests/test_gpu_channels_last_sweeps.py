@@ -48,3 +48,76 @@ def test_shard_sums(shape, dtype):
     for got, want, scale in ((s, x.double().sum((1, 2)), size), (v, (d * d).sum((1, 2)), H * W), (a, g.sum((1, 2)), size),
                              (b, (g * d * invstd.double()).sum((1, 2)), size)):
         assert float(((got - want).abs() / want.abs().clamp(min=scale)).max()) <= 1e-4
+
+
+MAPS = [
+    # value by value (pixels no whole number of groups): a row of threads, many, several tiles; chunks, leftovers, a piece of one pixel
+    (3, 7, 9, 87), (1, 61, 53, 11), (1, 9, 37, 298), (1, 5, 33, 834), (1, 3, 1, 601), (1, 1, 17, 257),
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_map_pieces_value_by_value(dtype):
+    for N, H, W, C in [m for m in MAPS if m[3] % 4]:
+        get = lambda k: L.cgbn_plan_get(N, C, H, W, "NHWC", dtype, 1, k)
+        assert get("vec") == 1 and get("may_group") == 1
+        for pl, pp in (("PLm", "ppsm"), ("PLm2", "ppsm2")):
+            PL, pps, rpp, spix = get(pl), get(pp), get("rpp"), N * H * W
+            assert pps == -(-spix // PL) and (PL == spix or PL % (4 * rpp) == 0)
+            assert PL <= 16 * rpp, "two chunks a thread at most"
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", MAPS, ids=str)
+def test_elementwise(shape, dtype):
+    """Every elementwise sweep, per-channel vectors 4, 8 and 12 bytes off a 16-byte boundary: they need be no more than floats."""
+    N, H, W, C = shape
+    print("[case] elementwise", shape, dtype, flush=True)
+    x, dy, normal = _draw(N, H, W, C, dtype)
+    short = normal(N, H, W, C).to(TORCH[dtype])
+    def vec(make, off):
+        a = torch.empty(C + 4, device=G.DEV)
+        assert a.data_ptr() % 16 == 0
+        a[off:off + C] = make
+        return a[off:off + C]
+    rand = lambda: torch.rand(C, device=G.DEV)
+    mean, lo, invstd, gamma, beta = vec(normal(C), 1), vec(1e-8 * normal(C), 2), vec(0.5 + rand(), 3), vec(0.5 + rand(), 1), vec(normal(C), 2)
+    var, dgamma, dbeta = vec(0.25 + rand(), 3), vec(normal(C), 1), vec(normal(C), 2)
+    x64, dy64, M = x.double(), dy.double(), N * H * W
+    m, g = mean.double() + lo.double(), gamma.double()
+    xhat = (x64 - m) * invstd.double()
+    scale = g / torch.sqrt(var.double() + 1e-5)
+    dims, y = (N, C, H, W, "NHWC"), torch.empty_like(x)
+    def check(want):
+        torch.cuda.synchronize()
+        rms = want.square().mean().sqrt()
+        assert float(((y.double() - want).abs() / want.abs().clamp(min=rms)).max()) <= TOL[dtype]
+        y.zero_()
+    L.cgbn_normalize(x, *dims, dtype, mean, lo, invstd, gamma, beta, y)
+    check(xhat * g + beta.double())
+    L.cgbn_backward_dx(dy, x, *dims, dtype, mean, lo, invstd, gamma, dgamma, dbeta, y)
+    check(g * invstd.double() * (dy64 - dbeta.double() / M - xhat * dgamma.double() / M))
+    L.cgbn_frozen_forward(x, *dims, dtype, mean, var, gamma, beta, 1e-5, y)
+    check((x64 - mean.double()) * scale + beta.double())
+    L.cgbn_frozen_backward(dy, *dims, dtype, var, gamma, 1e-5, y)
+    check(dy64 * scale)
+    # the sweeps with a shortcut and a mask: as the last ones of whole calls
+    ws = _workspace(N, C, H, W, dtype, 1)
+    y, dz, dx = torch.empty_like(x), torch.empty_like(x), torch.empty_like(x)
+    out = [vec(torch.zeros(C, device=G.DEV), o) for o in (1, 2, 3, 1, 3)]
+    old = L.cgbn_get_tuning("fused")
+    L.cgbn_set_tuning("fused", 0)
+    try:
+        L.cgbn_forward_relu(x, short, *dims, 1, gamma, beta, 1e-5, y, out[0], out[1], dtype, out[2], ws)
+        m, i = out[0].double() + out[2].double(), out[1].double()
+        want, stored = ((x64 - m) * i * g + beta.double() + short.double()).clamp(min=0), y.clone()
+        check(want)
+        L.cgbn_backward_relu(dy, stored, x, out[0], out[1], gamma, dx, dz, out[3], out[4], *dims, 1, dtype, out[2], ws)
+        torch.cuda.synchronize()
+        d = dy64 * (stored > 0)
+        assert torch.equal(dz.double(), d)
+        y.copy_(dx)
+        check(g * i * (d - out[4].double() / M - (x64 - m) * i * out[3].double() / M))
+    finally:
+        L.cgbn_set_tuning("fused", old)
