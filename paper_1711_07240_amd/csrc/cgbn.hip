@@ -628,8 +628,12 @@ bool cut_pixels(const Tuning& T, long long spix, int cols, int K, Plan* p)
         PL -= PL % (4 * p->rpp);                           // four pixels per thread and pass
         if (PL < 4 * p->rpp) PL = 4 * p->rpp;
     } else {
-        // (grouped pixels: sweeps are all there is, also for small tensors, and a handful of workgroups would leave the chip idle)
-        PL = reduce_pieces(p->spix, K, p->ctiles, p->rpp, (long long)p->TW * p->vec * p->eb, p->group > 1 ? 16 << 10 : 128 << 10);
+        // (grouped pixels: sweeps are all there is, also for small tensors, and a handful of workgroups would leave the chip idle: pieces from
+        // 16 KiB on while two workgroups a compute unit do not come together.  Not beyond: every row costs the combine step; forward of
+        // 104 x 72 x 103 x 31 fp32, 1248 rows 81 us, 728 rows 70)
+        long long least = 128 << 10;
+        if (p->group > 1) least = std::min(least, std::max(16LL << 10, p->S * p->eb / (2LL * compute_units())));
+        PL = reduce_pieces(p->spix, K, p->ctiles, p->rpp, (long long)p->TW * p->vec * p->eb, least);
     }
     if (PL > p->spix) PL = p->spix;
     p->PL = (int)PL;
@@ -643,14 +647,14 @@ bool cut_pixels(const Tuning& T, long long spix, int cols, int K, Plan* p)
     // workgroups a compute unit.  Measured, 32 / 64 / 128 KiB, us: with fixed statistics 2 x 200 x 336 x 256 bf16 24.5 / 25.7 / 28.7, fp32 50.2 /
     // 54.0 / 58.5, 4 x 100 x 100 x 64 bf16 3.9 / 4.7 / 6.1; as the last sweep of a forward / backward of 64 x 50 x 84 x 512 bf16 169 / 249, 173 / 256,
     // 176 / 264, fp32 316 / 485, 319 / 502, 325 / 515.
-    //   Value by value 16 values a thread, two chunks: 32 KiB of a row of several tiles are few pixels, of a narrow one many.  Fixed
-    // statistics / dx, 32 KiB -> 16 values: 67 x 68 x 69 x 87 bf16 27.3 / 46 -> 24.1 / 31, fp32 331 x 441 x 149 41.1 / 51.6 -> 36.6 / 46.7,
-    // 9 x 79 x 85 x 249 20.6 / 33.8 -> 20.2 / 32.1.
+    //   Value by value at most 16 values a thread, two chunks.  Fixed statistics / dx, 32 KiB -> 16 values: 67 x 68 x 69 x 87 bf16 27.3 / 46 ->
+    // 24.1 / 31, fp32 331 x 441 x 149 41.1 / 51.6 -> 36.6 / 46.7, 9 x 79 x 85 x 249 20.6 / 33.8 -> 20.2 / 32.1.
     for (int two = 0; two < 2; ++two) {
         const long long quantum = 4 * p->rpp;
         long long bytes = T.map_piece_bytes > 0 ? T.map_piece_bytes : 32768, PLm, ppsm;
         for (;; bytes /= 2) {
-            PLm = p->vec == 1 && T.map_piece_bytes == 0 ? bytes / 2048 * p->rpp : bytes / ((long long)cols * p->eb);
+            PLm = bytes / ((long long)cols * p->eb);
+            if (p->vec == 1 && T.map_piece_bytes == 0) PLm = std::min(PLm, bytes / 2048 * p->rpp);
             PLm -= PLm % quantum;
             if (PLm < quantum) PLm = quantum;
             if (PLm > p->spix) PLm = p->spix;
@@ -931,8 +935,9 @@ template <typename T, int EL> void launch_map_t(const Plan& p, const SweepArgs& 
         B.pps = more_inputs ? p.ppsm2 : p.ppsm;
         const bool fixed = EL == EL_FROZEN || EL == EL_SCALE;
         const size_t lds = sizeof(float) * map_const_words<EL>() * (p.group > 1 ? p.C : fixed ? kThreads : 0);
-        if (p.vec == 1) hipLaunchKernelGGL((nhwc_map<T, 1, EL>), grid, block, 0, st, B);
-        else hipLaunchKernelGGL((nhwc_map<T, Elem<T>::VEC, EL>), grid, block, lds, st, B);
+        if (p.vec == 1) hipLaunchKernelGGL((nhwc_map<T, 1, EL, false>), grid, block, 0, st, B);
+        else if (p.group == 1) hipLaunchKernelGGL((nhwc_map<T, Elem<T>::VEC, EL, false>), grid, block, lds, st, B);
+        else hipLaunchKernelGGL((nhwc_map<T, Elem<T>::VEC, EL, true>), grid, block, lds, st, B);
     }
 }
 

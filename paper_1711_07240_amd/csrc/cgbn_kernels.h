@@ -1018,11 +1018,11 @@ template <int EL> constexpr int map_const_words() { return EL == EL_SCALE ? 1 : 
 // rows of threads as a vector has channels; and with grouped pixels, whose columns' channels do not lie side by side (every thread its
 // columns' own one by one, us: dx of 83 x 38 x 52 x 115 bf16 33.6, so 25; 40 x 16 x 21 x 161 fp32 8.9, 6.4).  What is left
 // after the whole chunks is loaded four pixels at a time (lanes beyond the end read the last pixel again).
-template <typename T, int V, int EL>
+template <typename T, int V, int EL, bool GROUP>
 __global__ __launch_bounds__(kThreads) void nhwc_map(SweepArgs A)
 {
     constexpr bool IN2 = el_has_2(EL), IN3 = el_has_3(EL), FIXED = EL == EL_FROZEN || EL == EL_SCALE;
-    extern __shared__ float lds_consts[];        // of the workgroup's channels: [map_const_words][channels]
+    extern __shared__ float lds_consts[];        // of the workgroup's channels, see put()
     long long b = A.reverse ? (long long)gridDim.x - 1 - blockIdx.x : (long long)blockIdx.x;
     int ct = (int)(b % A.ctiles);
     int row = (int)(b / A.ctiles);
@@ -1078,7 +1078,7 @@ __global__ __launch_bounds__(kThreads) void nhwc_map(SweepArgs A)
     constexpr int nolimit = 0x7fffffff;
     int i = r;
     bool whole = i + (UNR - 1) * rpp < npix;
-    const bool shared = V != 1 && (A.group != 1 || (FIXED && rpp >= V));
+    const bool shared = GROUP || (V != 1 && FIXED && rpp >= V);
     // (the constants' loads first: they are waited for first, and the first stores leave while the chunk's last loads are under way.  Of
     // single values, whose chunks are short, the constants are formed first too: fixed statistics 23 x 37 x 63 x 298 bf16 20.3 -> 18.4 us,
     // 67 x 68 x 69 x 87 24.1 -> 21.6)
@@ -1093,14 +1093,16 @@ __global__ __launch_bounds__(kThreads) void nhwc_map(SweepArgs A)
     if (whole) load(std::integral_constant<int, UNR>{}, i, nolimit);
     if (shared) {
         // (without groups no more channels than threads: rpp * TW <= kThreads)
-        const int c0 = A.group == 1 ? ct * A.TW * V : 0, channels = A.group == 1 ? A.TW * V : A.ch;
+        const int c0 = GROUP ? 0 : ct * A.TW * V, channels = GROUP ? A.ch : A.TW * V;
+        const int next = GROUP ? channels : kThreads;        // [words][channels]: the other way round lanes meet in fewer banks
         auto put = [&](int c, const ChanConst& f) __attribute__((always_inline)) {
-            lds_consts[c] = f.g;
-            if constexpr (EL != EL_SCALE) { lds_consts[channels + c] = f.mu; lds_consts[2 * channels + c] = f.b; }
-            if constexpr (!FIXED) lds_consts[3 * channels + c] = f.mulo;
-            if constexpr (!FIXED && !el_is_norm(EL)) { lds_consts[4 * channels + c] = f.istd; lds_consts[5 * channels + c] = f.c2; }
+            float* w = lds_consts + c;
+            w[0] = f.g;
+            if constexpr (EL != EL_SCALE) { w[next] = f.mu; w[2 * next] = f.b; }
+            if constexpr (!FIXED) w[3 * next] = f.mulo;
+            if constexpr (!FIXED && !el_is_norm(EL)) { w[4 * next] = f.istd; w[5 * next] = f.c2; }
         };
-        if (channels <= kThreads) {
+        if (!GROUP || channels <= kThreads) {
             if (t < channels && c0 + t < A.ch) put(t, map_consts<EL>(A, c0 + t));
         } else {
             // two at a time, their loads under way together
@@ -1115,10 +1117,11 @@ __global__ __launch_bounds__(kThreads) void nhwc_map(SweepArgs A)
         int o = active ? col * V % channels : 0;
 #pragma unroll
         for (int e = 0; e < V; ++e) {
-            kc[e] = {0.f, 0.f, 0.f, lds_consts[o], 0.f, 0.f};
-            if constexpr (EL != EL_SCALE) { kc[e].mu = lds_consts[channels + o]; kc[e].b = lds_consts[2 * channels + o]; }
-            if constexpr (!FIXED) kc[e].mulo = lds_consts[3 * channels + o];
-            if constexpr (!FIXED && !el_is_norm(EL)) { kc[e].istd = lds_consts[4 * channels + o]; kc[e].c2 = lds_consts[5 * channels + o]; }
+            const float* w = lds_consts + o;
+            kc[e] = {0.f, 0.f, 0.f, w[0], 0.f, 0.f};
+            if constexpr (EL != EL_SCALE) { kc[e].mu = w[next]; kc[e].b = w[2 * next]; }
+            if constexpr (!FIXED) kc[e].mulo = w[3 * next];
+            if constexpr (!FIXED && !el_is_norm(EL)) { kc[e].istd = w[4 * next]; kc[e].c2 = w[5 * next]; }
             if (++o == channels) o = 0;
         }
     } else if (V != 1) {
@@ -1128,7 +1131,8 @@ __global__ __launch_bounds__(kThreads) void nhwc_map(SweepArgs A)
 #pragma unroll
         for (int u = 0; u < UNR; ++u) write(u, i + u * rpp);
         i += UNR * rpp;
-        whole = i + (UNR - 1) * rpp < npix;
+        // (vectors: a piece is one chunk, and a second load beside the first costs registers, dx of 2 x 200 x 336 x 256 bf16 38 us, so 42)
+        whole = V == 1 && i + (UNR - 1) * rpp < npix;
         if (whole) load(std::integral_constant<int, UNR>{}, i, nolimit);
     }
     for (; i < npix; i += 4 * rpp) {
