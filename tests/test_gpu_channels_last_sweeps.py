@@ -53,6 +53,8 @@ def test_shard_sums(shape, dtype):
 MAPS = [
     # value by value (pixels no whole number of groups): a row of threads, many, several tiles; chunks, leftovers, a piece of one pixel
     (3, 7, 9, 87), (1, 61, 53, 11), (1, 9, 37, 298), (1, 5, 33, 834), (1, 3, 1, 601), (1, 1, 17, 257),
+    # rows of several tiles: pieces of a tile or of the row, ragged ones
+    (2, 7, 11, 2560), (2, 33, 41, 1376), (1, 61, 53, 4104),
 ]
 
 
@@ -65,6 +67,17 @@ def test_map_pieces_value_by_value(dtype):
             PL, pps, rpp, spix = get(pl), get(pp), get("rpp"), N * H * W
             assert pps == -(-spix // PL) and (PL == spix or PL % (4 * rpp) == 0)
             assert PL <= 16 * rpp, "two chunks a thread at most"
+
+
+@pytest.mark.parametrize("dtype,C", [("bf16", 2560), ("bf16", 4104), ("f32", 1376), ("f32", 2052)])
+def test_map_pieces_of_several_tiles(dtype, C):
+    """32 KiB of the tile with one input, and with two of bfloat16; of the row with two of float: in whole passes of four pixels a thread."""
+    get = lambda k: L.cgbn_plan_get(64, C, 40, 50, "NHWC", dtype, 1, k)
+    eb = 4 if dtype == "f32" else 2
+    assert get("ctiles") > 1 and get("rpp") == 1
+    tile, row = get("TW") * get("vec") * eb, C * eb
+    assert get("PLm") == 32768 // tile // 4 * 4 == 8
+    assert get("PLm2") == (8 if dtype == "bf16" else max(4, 32768 // row // 4 * 4))
 
 
 @pytest.mark.gpu
