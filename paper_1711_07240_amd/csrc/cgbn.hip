@@ -650,12 +650,17 @@ bool cut_pixels(const Tuning& T, long long spix, int cols, int K, Plan* p)
     //   Value by value at most 16 values a thread, two chunks.  Fixed statistics / dx, 32 KiB -> 16 values: 67 x 68 x 69 x 87 bf16 27.3 / 46 ->
     // 24.1 / 31, fp32 331 x 441 x 149 41.1 / 51.6 -> 36.6 / 46.7, 9 x 79 x 85 x 249 20.6 / 33.8 -> 20.2 / 32.1.
     //   Rows of several tiles: 32 KiB of a workgroup's own tile (fixed statistics / dx of 8 x 100 x 50 x 2560 bf16, of the whole row 119 / 163 us, of
-    // the tile 98 / 141; fp32 64 x 20 x 20 x 1376 68.4, 65.9), of two fp32 inputs of the whole row (dx of 64 x 20 x 20 x 1376 87 us, of the tile 93).
+    // the tile 98 / 141; fp32 64 x 20 x 20 x 1376 68.4, 65.9), of two fp32 inputs, or more than
+    // two tiles, of the whole row (dx of 64 x 20 x 20 x 1376 87 us, of the tile 93; fixed statistics 64 x 40 x 40 x 2056 300, 326).  96 KiB
+    // where the last tile is shorter, and its workgroups have less, of bf16: 64 x 40 x 40 x 2560 252 / 348 -> 235 / 337, 64 x 40 x 40 x 2056 270 / 352 -> 234 / 313
+    // (fp32 64 x 20 x 20 x 2304 86 us, so 100).
     for (int two = 0; two < 2; ++two) {          // (one input tensor; two or three)
         const long long quantum = 4 * p->rpp;
         long long bytes = T.map_piece_bytes > 0 ? T.map_piece_bytes : 32768, PLm, ppsm;
         for (;; bytes /= 2) {
-            PLm = bytes / (T.map_piece_bytes > 0 || p->vec == 1 || (two && p->eb == 4) ? (long long)cols * p->eb : (long long)p->TW * p->vec * p->eb);
+            const bool row = T.map_piece_bytes > 0 || p->vec == 1 || (p->eb == 4 && (two || p->ctiles > 2));
+            PLm = bytes / (row ? (long long)cols * p->eb : (long long)p->TW * p->vec * p->eb);
+            if (!row && p->eb == 2 && p->cv % p->TW != 0) PLm *= 3;
             if (p->vec == 1 && T.map_piece_bytes == 0) PLm = std::min(PLm, bytes / 2048 * p->rpp);
             PLm -= PLm % quantum;
             if (PLm < quantum) PLm = quantum;

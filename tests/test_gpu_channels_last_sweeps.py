@@ -69,15 +69,18 @@ def test_map_pieces_value_by_value(dtype):
             assert PL <= 16 * rpp, "two chunks a thread at most"
 
 
-@pytest.mark.parametrize("dtype,C", [("bf16", 2560), ("bf16", 4104), ("f32", 1376), ("f32", 2052)])
+@pytest.mark.parametrize("dtype,C", [("bf16", 2560), ("bf16", 4104), ("bf16", 4096), ("f32", 1376), ("f32", 2048), ("f32", 2052)])
 def test_map_pieces_of_several_tiles(dtype, C):
-    """32 KiB of the tile with one input, and with two of bfloat16; of the row with two of float: in whole passes of four pixels a thread."""
+    """32 KiB of the tile with one input, and with two of bfloat16, whose pieces are 96 if the last tile is shorter; of the row with two of
+    float, or more than two tiles: in whole passes of four pixels a thread."""
     get = lambda k: L.cgbn_plan_get(64, C, 40, 50, "NHWC", dtype, 1, k)
     eb = 4 if dtype == "f32" else 2
     assert get("ctiles") > 1 and get("rpp") == 1
     tile, row = get("TW") * get("vec") * eb, C * eb
-    assert get("PLm") == 32768 // tile // 4 * 4 == 8
-    assert get("PLm2") == (8 if dtype == "bf16" else max(4, 32768 // row // 4 * 4))
+    whole = dtype == "f32" or get("cv") % get("TW") == 0
+    by_row = max(4, 32768 // row // 4 * 4)
+    assert get("PLm") == (by_row if dtype == "f32" and get("ctiles") > 2 else (32768 if whole else 98304) // tile // 4 * 4)
+    assert get("PLm2") == (get("PLm") if dtype == "bf16" else by_row)
 
 
 @pytest.mark.gpu
