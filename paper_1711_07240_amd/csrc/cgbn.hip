@@ -202,9 +202,9 @@ struct Plan {
     int tiny, tg;         // tiny planes: `tg` planes of consecutive channels per workgroup
     // NHWC
     int cv, TW, ctiles, rpp, PL, pps;
-    int PLm, ppsm;        // pixel runs of the elementwise sweeps (no rows to keep few): one input tensor ...
-    int PLm2, ppsm2;      // ... and two or three (dx; the shortcut and ReLU variants)
-    long long spix, gridm, gridm2;
+    long long spix;
+    // pixel runs of the elementwise sweeps (no rows to keep few), with one, two (dx; a shortcut) and three (masked dx) input tensors
+    struct { int PL, pps; long long grid; } map[3];
     // partial sums
     int rows, rps, G;
     long long grid;       // workgroups of one sweep
@@ -654,25 +654,26 @@ bool cut_pixels(const Tuning& T, long long spix, int cols, int K, Plan* p)
     // two tiles, of the whole row (dx of 64 x 20 x 20 x 1376 87 us, of the tile 93; fixed statistics 64 x 40 x 40 x 2056 300, 326).  96 KiB
     // where the last tile is shorter, and its workgroups have less, of bf16: 64 x 40 x 40 x 2560 252 / 348 -> 235 / 337, 64 x 40 x 40 x 2056 270 / 352 -> 234 / 313
     // (fp32 64 x 20 x 20 x 2304 86 us, so 100).
-    for (int two = 0; two < 2; ++two) {          // (one input tensor; two or three)
-        const long long quantum = 4 * p->rpp;
-        long long bytes = T.map_piece_bytes > 0 ? T.map_piece_bytes : 32768, PLm, ppsm;
+    //   Vectors of float, two inputs: shorter pieces only where one and a half workgroups a compute unit do not come together (dx of
+    // 13 to 16 MB, 392 to 490 workgroups of 32 KiB, 8.4 / 9.5 us, of 16 KiB 9.1 / 10.6); three: 16 KiB (masked backward of 64 x 50 x 84 x 512 723 ->
+    // 706 us, 64 x 50 x 84 x 1024 1314 -> 1286).
+    const bool f32 = p->eb == 4 && p->vec != 1;
+    for (int inputs = 1; inputs <= 3; ++inputs) {
+        const long long quantum = 4 * p->rpp, cus = compute_units(), enough = f32 && inputs > 1 ? cus * 3 / 2 : cus * 2;
+        const bool row = T.map_piece_bytes > 0 || p->vec == 1 || (f32 && (inputs > 1 || p->ctiles > 2));
+        long long bytes = T.map_piece_bytes > 0 ? T.map_piece_bytes : f32 && inputs == 3 ? 16384 : 32768, PL, pps;
         for (;; bytes /= 2) {
-            const bool row = T.map_piece_bytes > 0 || p->vec == 1 || (p->eb == 4 && (two || p->ctiles > 2));
-            PLm = bytes / (row ? (long long)cols * p->eb : (long long)p->TW * p->vec * p->eb);
-            if (!row && p->eb == 2 && p->cv % p->TW != 0) PLm *= 3;
-            if (p->vec == 1 && T.map_piece_bytes == 0) PLm = std::min(PLm, bytes / 2048 * p->rpp);
-            PLm -= PLm % quantum;
-            if (PLm < quantum) PLm = quantum;
-            if (PLm > p->spix) PLm = p->spix;
-            ppsm = (p->spix + PLm - 1) / PLm;
-            if (T.map_piece_bytes > 0 || PLm <= quantum || ppsm * K * p->ctiles >= 512) break;
+            PL = bytes / (row ? (long long)cols * p->eb : (long long)p->TW * p->vec * p->eb);
+            if (!row && !f32 && p->cv % p->TW != 0) PL *= 3;
+            if (p->vec == 1 && T.map_piece_bytes == 0) PL = std::min(PL, bytes / 2048 * p->rpp);
+            PL -= PL % quantum;
+            if (PL < quantum) PL = quantum;
+            if (PL > p->spix) PL = p->spix;
+            pps = (p->spix + PL - 1) / PL;
+            if (T.map_piece_bytes > 0 || PL <= quantum || pps * K * p->ctiles >= enough) break;
         }
-        if (ppsm * K > 0x3fffffffLL) return false;
-        const long long gridm = ppsm * K * p->ctiles;
-        if (gridm > 0x7fffffffLL) return false;
-        if (two) { p->PLm2 = (int)PLm; p->ppsm2 = (int)ppsm; p->gridm2 = gridm; }
-        else { p->PLm = (int)PLm; p->ppsm = (int)ppsm; p->gridm = gridm; }
+        if (pps * K > 0x3fffffffLL || pps * K * p->ctiles > 0x7fffffffLL) return false;
+        p->map[inputs - 1] = {(int)PL, (int)pps, pps * K * p->ctiles};
     }
     return p->grid <= 0x7fffffffLL;
 }
@@ -935,11 +936,11 @@ template <typename T, int EL> void launch_map_t(const Plan& p, const SweepArgs& 
         else if (p.wave_mode) hipLaunchKernelGGL((nchw_map_wave<T, EL>), grid, block, 0, st, A);
         else hipLaunchKernelGGL((nchw_map_block<T, EL>), grid, block, 0, st, A);
     } else {
-        constexpr bool more_inputs = el_has_2(EL) || el_has_3(EL);
-        dim3 grid((unsigned)(more_inputs ? p.gridm2 : p.gridm));
+        const auto& cut = p.map[el_has_3(EL) ? 2 : el_has_2(EL) ? 1 : 0];
+        dim3 grid((unsigned)cut.grid);
         SweepArgs B = A;              // the elementwise sweeps cut the pixel runs their own way
-        B.PL = more_inputs ? p.PLm2 : p.PLm;
-        B.pps = more_inputs ? p.ppsm2 : p.ppsm;
+        B.PL = cut.PL;
+        B.pps = cut.pps;
         const bool fixed = EL == EL_FROZEN || EL == EL_SCALE;
         const size_t lds = sizeof(float) * map_const_words<EL>() * (p.group > 1 ? p.C : fixed ? kThreads : 0);
         if (p.vec == 1) hipLaunchKernelGGL((nhwc_map<T, 1, EL, false>), grid, block, 0, st, B);
@@ -1864,16 +1865,19 @@ long long cgbn_plan_get(int N, int C, int H, int W, cgbn_layout layout, cgbn_dty
     if (!std::strcmp(key, "rpp")) return p.rpp;
     if (!std::strcmp(key, "PL")) return p.PL;
     if (!std::strcmp(key, "pps")) return p.pps;
-    if (!std::strcmp(key, "PLm")) return p.PLm;
-    if (!std::strcmp(key, "ppsm")) return p.ppsm;
-    if (!std::strcmp(key, "PLm2")) return p.PLm2;
-    if (!std::strcmp(key, "ppsm2")) return p.ppsm2;
-    if (!std::strcmp(key, "gridm2")) return p.gridm2;
+    if (!std::strcmp(key, "PLm")) return p.map[0].PL;
+    if (!std::strcmp(key, "ppsm")) return p.map[0].pps;
+    if (!std::strcmp(key, "PLm2")) return p.map[1].PL;
+    if (!std::strcmp(key, "ppsm2")) return p.map[1].pps;
+    if (!std::strcmp(key, "gridm2")) return p.map[1].grid;
+    if (!std::strcmp(key, "PLm3")) return p.map[2].PL;
+    if (!std::strcmp(key, "ppsm3")) return p.map[2].pps;
+    if (!std::strcmp(key, "gridm3")) return p.map[2].grid;
     if (!std::strcmp(key, "rows")) return p.rows;
     if (!std::strcmp(key, "rps")) return p.rps;
     if (!std::strcmp(key, "G")) return p.G;
     if (!std::strcmp(key, "grid")) return p.grid;
-    if (!std::strcmp(key, "gridm")) return p.gridm;
+    if (!std::strcmp(key, "gridm")) return p.map[0].grid;
     if (!std::strcmp(key, "part_bytes")) return (long long)(p.off_part1 - p.off_part0);
     if (!std::strcmp(key, "shard_bytes")) return (long long)(p.off_sh1 - p.off_sh0);
     return -1;

@@ -137,3 +137,15 @@ def test_elementwise(shape, dtype):
         check(g * i * (d - out[4].double() / M - (x64 - m) * i * out[3].double() / M))
     finally:
         L.cgbn_set_tuning("fused", old)
+
+
+def test_map_pieces_of_vectors():
+    """32 KiB, half of it with three float inputs; shorter where 512 workgroups (384 with two or three float inputs) do not come together."""
+    get = lambda n, c, dtype, k: L.cgbn_plan_get(n, c, 28, 28, "NHWC", dtype, 1, k)
+    for dtype, eb, grids in (("f32", 4, (512, 384, 384)), ("bf16", 2, (512, 512, 512))):
+        for n, c in ((200, 64), (100, 128), (25, 512), (14, 1024)):
+            for i, (suffix, grid) in enumerate(zip(("", "2", "3"), grids)):
+                piece = get(n, c, dtype, "PLm" + suffix) * c * eb
+                assert piece in ((16384, 8192) if i == 2 and dtype == "f32" else (32768, 16384)) and get(n, c, dtype, "gridm" + suffix) >= grid
+    # 427 workgroups of 32 KiB: enough for two float inputs, too few for one
+    assert get(35, 128, "f32", "PLm2") * 512 == 32768 and get(35, 128, "f32", "PLm") * 512 == 16384
