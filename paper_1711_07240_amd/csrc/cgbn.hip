@@ -927,6 +927,9 @@ template <typename T, int OP> void launch_reduce_t(const Plan& p, const SweepArg
     }
 }
 
+// (see MapConsts)
+bool single_consts(const Plan& p) { return p.ctiles == 1 && p.S * p.eb > (256LL << 20); }
+
 template <typename T, int EL> void launch_map_t(const Plan& p, const SweepArgs& A, hipStream_t st)
 {
     dim3 block(kThreads);
@@ -941,6 +944,7 @@ template <typename T, int EL> void launch_map_t(const Plan& p, const SweepArgs& 
         SweepArgs B = A;              // the elementwise sweeps cut the pixel runs their own way
         B.PL = cut.PL;
         B.pps = cut.pps;
+        B.single_consts = single_consts(p);
         const bool fixed = EL == EL_FROZEN || EL == EL_SCALE;
         const size_t lds = sizeof(float) * map_const_words<EL>() * (p.group > 1 ? p.C : fixed ? kThreads : 0);
         if (p.vec == 1) hipLaunchKernelGGL((nhwc_map<T, 1, EL, false>), grid, block, 0, st, B);
@@ -1870,6 +1874,7 @@ long long cgbn_plan_get(int N, int C, int H, int W, cgbn_layout layout, cgbn_dty
     if (!std::strcmp(key, "PLm2")) return p.map[1].PL;
     if (!std::strcmp(key, "ppsm2")) return p.map[1].pps;
     if (!std::strcmp(key, "gridm2")) return p.map[1].grid;
+    if (!std::strcmp(key, "single_consts")) return p.layout == CGBN_NHWC && p.eb == 4 && p.vec == 4 && single_consts(p);
     if (!std::strcmp(key, "PLm3")) return p.map[2].PL;
     if (!std::strcmp(key, "ppsm3")) return p.map[2].pps;
     if (!std::strcmp(key, "gridm3")) return p.map[2].grid;

@@ -69,6 +69,7 @@ struct SweepArgs {
     int tg;                   // tiny planes: planes per workgroup (a power of two, 8 ... 256)
     // NHWC
     int cv, TW, ctiles, rpp, PL, pps;
+    int single_consts;        // channels-last, elementwise: see MapConsts
     int ch, group;            // channels; pixels that make up one pixel of C = ch * group columns (see Plan::group)
     long long spix;           // pixels per shard
     long long pivot_stride;   // elements between the first values of consecutive channels
@@ -985,6 +986,11 @@ __global__ __launch_bounds__(kThreads) void nhwc_reduce(SweepArgs A)
 // The constants of V neighbouring columns, in two steps: what they are formed from is loaded, then formed.
 template <int EL, int V> struct MapConsts {
     static constexpr bool FIXED = EL == EL_FROZEN || EL == EL_SCALE;
+    // Two float inputs: of tensors beyond the memory-side cache, rows of one tile, one float at a time (A.single_consts).  What takes longer there
+    // holds the data's loads back a little, and the sweep as a whole, HBM bound, is faster for it: dx / forward with shortcut of 64 x 50 x 84
+    // x 512 282 / 395 us, by wide loads 294 / 408; 12 x 180 x 301 x 192 258 / 369, 268 / 380.  Level at 210 to 260 MB; below, wide loads: 16 x 100 x
+    // 168 x 64, 69 MB, dx 34.7, so 37.5.  (Several tiles: 64 x 40 x 40 x 1376 dx 334, so 492.)
+    static constexpr bool SINGLE = V == 4 && el_has_2(EL) && !el_has_3(EL);
     float mu[V], lo[V], is[V], g[V], b[V], c2[V];
     __device__ __forceinline__ void load(const SweepArgs& A, int c)
     {
@@ -992,11 +998,25 @@ template <int EL, int V> struct MapConsts {
         const bool low = !FIXED && A.mean_lo != nullptr;
 #pragma unroll
         for (int e = 0; e < V; ++e) mu[e] = lo[e] = b[e] = c2[e] = 0.f;
+        if (SINGLE && A.single_consts) {
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                is[e] = A.invstd[c + e];
+                g[e] = A.gamma[c + e];
+                mu[e] = A.mean[c + e];
+                b[e] = pb[c + e];
+                if (low) lo[e] = A.mean_lo[c + e];
+                if (!el_is_norm(EL)) c2[e] = A.dgamma[c + e];
+                asm volatile("");        // (or the compiler makes them the wide loads)
+            }
+            return;
+        }
         load_channels<V>(A.invstd + c, is);
         load_channels<V>(A.gamma + c, g);
         if (EL != EL_SCALE) { load_channels<V>(A.mean + c, mu); load_channels<V>(pb + c, b); }
         if (low) load_channels<V>(A.mean_lo + c, lo);
         if (!FIXED && !el_is_norm(EL)) load_channels<V>(A.dgamma + c, c2);
+        if (SINGLE) asm volatile("");
     }
     __device__ __forceinline__ void form(const SweepArgs& A, ChanConst (&k)[V])      // (as map_consts)
     {

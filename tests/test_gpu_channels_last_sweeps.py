@@ -149,3 +149,38 @@ def test_map_pieces_of_vectors():
                 assert piece in ((16384, 8192) if i == 2 and dtype == "f32" else (32768, 16384)) and get(n, c, dtype, "gridm" + suffix) >= grid
     # 427 workgroups of 32 KiB: enough for two float inputs, too few for one
     assert get(35, 128, "f32", "PLm2") * 512 == 32768 and get(35, 128, "f32", "PLm") * 512 == 16384
+
+
+def test_single_constants_rule():
+    get = lambda n, c, dtype: L.cgbn_plan_get(n, c, 100, 168, "NHWC", dtype, 1, "single_consts")
+    assert get(16, 256, "f32") == 1 and get(15, 256, "f32") == 0          # 275 and 258 MB
+    assert get(8, 1024, "f32") == 1 and get(8, 1028, "f32") == 0          # one tile, two
+    assert get(64, 256, "bf16") == 0 and get(400, 15, "f32") == 0
+
+
+@pytest.mark.gpu
+def test_single_constants():
+    """Beyond 256 MiB: dx equals, bit by bit, dx of the two halves, each below (their sums and the count both halved, exactly); the forward with a
+    shortcut against float64."""
+    N, H, W, C = 18, 100, 168, 256
+    assert L.cgbn_plan_get(N, C, H, W, "NHWC", "f32", 1, "single_consts") == 1
+    x, dy, normal = _draw(N, H, W, C, "f32")
+    print("[case] single constants", flush=True)
+    mean, lo, invstd, gamma, beta, dgamma, dbeta = normal(C), 1e-8 * normal(C), 0.5 + torch.rand(C, device=G.DEV), 0.5 + torch.rand(C, device=G.DEV), normal(C), normal(C), normal(C)
+    dx, parts = torch.empty_like(x), torch.empty_like(x)
+    L.cgbn_backward_dx(dy, x, N, C, H, W, "NHWC", "f32", mean, lo, invstd, gamma, dgamma, dbeta, dx)
+    for i in (slice(0, 9), slice(9, 18)):
+        L.cgbn_backward_dx(dy[i], x[i], 9, C, H, W, "NHWC", "f32", mean, lo, invstd, gamma, dgamma / 2, dbeta / 2, parts[i])
+    torch.cuda.synchronize()
+    assert torch.equal(dx, parts)
+    ws, y = _workspace(N, C, H, W, "f32", 2), parts
+    old = L.cgbn_get_tuning("fused")
+    L.cgbn_set_tuning("fused", 0)
+    try:
+        L.cgbn_forward_relu(x, dy, N, C, H, W, "NHWC", 2, gamma, beta, 1e-5, y, mean, invstd, "f32", lo, ws)
+    finally:
+        L.cgbn_set_tuning("fused", old)
+    torch.cuda.synchronize()
+    want = (x.double() - mean.double() - lo.double()) * (invstd.double() * gamma.double()) + beta.double() + dy.double()
+    # a handful of roundings of values of up to ten times the standard deviation
+    assert float((y.double() - want.clamp(min=0)).abs().max()) <= 1e-5
