@@ -1,6 +1,7 @@
 """Binding of libcgbn.so: same names and argument order as include/cgbn.h.
 
-Argument marshalling only, by ctypes; for the calls of a training step by a small extension (csrc/cgbn_call.c).  Tensors are passed as anything with a
+Argument marshalling only, by ctypes; the plain calls of a training step by a small extension (csrc/cgbn_call.c), which hands back
+to ctypes what it does not know.  Tensors are passed as anything with a
 `data_ptr()` (a torch tensor on the GPU) or as a raw integer device address;
 `None` becomes NULL.  Every step of the path runs in the library's kernels.
 If the library has not been built this module raises on first use; there is
@@ -167,6 +168,11 @@ def cgbn_forward(x, N, C, H, W, layout, K, gamma, beta, eps, y, mean, invstd,
                  dtype="f32", mean_lo=None, workspace=None, workspace_bytes=None, stream=None) -> None:
     code = (_call or _calls()).forward(x, N, C, H, W, layout, K, gamma, beta, eps, y, mean, invstd, dtype, mean_lo, workspace,
                                        workspace_bytes, stream)
+    if code is NotImplemented:
+        wb = _nbytes(workspace) if workspace_bytes is None and workspace is not None else (workspace_bytes or 0)
+        code = lib().cgbn_forward(_ptr(x), N, C, H, W, _enum(LAYOUTS, layout), K, _ptr(gamma), _ptr(beta),
+            float(eps), _ptr(y), _ptr(mean), _ptr(invstd), _enum(DTYPES, dtype),
+            _ptr(mean_lo), _ptr(workspace), wb, _stream(stream))
     if code:
         _check(code, "cgbn_forward")
 
@@ -182,6 +188,12 @@ def cgbn_backward(dy, x, mean, invstd, gamma, dx, dgamma, dbeta, N, C, H, W, lay
                   dtype="f32", mean_lo=None, workspace=None, workspace_bytes=None, stream=None) -> None:
     code = (_call or _calls()).backward(dy, x, mean, invstd, gamma, dx, dgamma, dbeta, N, C, H, W, layout, K, dtype, mean_lo, workspace,
                                         workspace_bytes, stream)
+    if code is NotImplemented:
+        wb = _nbytes(workspace) if workspace_bytes is None and workspace is not None else (workspace_bytes or 0)
+        code = lib().cgbn_backward(_ptr(dy), _ptr(x), _ptr(mean), _ptr(invstd), _ptr(gamma), _ptr(dx),
+            _ptr(dgamma), _ptr(dbeta), N, C, H, W, _enum(LAYOUTS, layout), K,
+            _enum(DTYPES, dtype), _ptr(mean_lo), _ptr(workspace), wb,
+            _stream(stream))
     if code:
         _check(code, "cgbn_backward")
 
@@ -190,6 +202,11 @@ def cgbn_forward_relu(x, shortcut, N, C, H, W, layout, K, gamma, beta, eps, y, m
                       dtype="f32", mean_lo=None, workspace=None, workspace_bytes=None, stream=None) -> None:
     code = (_call or _calls()).forward_relu(x, shortcut, N, C, H, W, layout, K, gamma, beta, eps, y, mean, invstd, dtype, mean_lo, workspace,
                                             workspace_bytes, stream)
+    if code is NotImplemented:
+        wb = _nbytes(workspace) if workspace_bytes is None and workspace is not None else (workspace_bytes or 0)
+        code = lib().cgbn_forward_relu(_ptr(x), _ptr(shortcut), N, C, H, W, _enum(LAYOUTS, layout), K, _ptr(gamma),
+            _ptr(beta), float(eps), _ptr(y), _ptr(mean), _ptr(invstd), _enum(DTYPES, dtype),
+            _ptr(mean_lo), _ptr(workspace), wb, _stream(stream))
     if code:
         _check(code, "cgbn_forward_relu")
 
@@ -198,6 +215,12 @@ def cgbn_backward_relu(dy, y, x, mean, invstd, gamma, dx, dshortcut, dgamma, dbe
                        dtype="f32", mean_lo=None, workspace=None, workspace_bytes=None, stream=None) -> None:
     code = (_call or _calls()).backward_relu(dy, y, x, mean, invstd, gamma, dx, dshortcut, dgamma, dbeta, N, C, H, W, layout, K, dtype,
                                              mean_lo, workspace, workspace_bytes, stream)
+    if code is NotImplemented:
+        wb = _nbytes(workspace) if workspace_bytes is None and workspace is not None else (workspace_bytes or 0)
+        code = lib().cgbn_backward_relu(_ptr(dy), _ptr(y), _ptr(x), _ptr(mean), _ptr(invstd), _ptr(gamma), _ptr(dx),
+            _ptr(dshortcut), _ptr(dgamma), _ptr(dbeta), N, C, H, W,
+            _enum(LAYOUTS, layout), K, _enum(DTYPES, dtype), _ptr(mean_lo),
+            _ptr(workspace), wb, _stream(stream))
     if code:
         _check(code, "cgbn_backward_relu")
 
@@ -256,12 +279,19 @@ def cgbn_backward_dx(dy, x, N, C, H, W, layout, dtype, mean, mean_lo, invstd, ga
 
 def cgbn_frozen_forward(x, N, C, H, W, layout, dtype, fixed_mean, fixed_var, gamma, beta, eps, y, stream=None) -> None:
     code = (_call or _calls()).frozen_forward(x, N, C, H, W, layout, dtype, fixed_mean, fixed_var, gamma, beta, eps, y, stream)
+    if code is NotImplemented:
+        code = lib().cgbn_frozen_forward(_ptr(x), N, C, H, W, _enum(LAYOUTS, layout), _enum(DTYPES, dtype),
+            _ptr(fixed_mean), _ptr(fixed_var), _ptr(gamma), _ptr(beta), float(eps),
+            _ptr(y), _stream(stream))
     if code:
         _check(code, "cgbn_frozen_forward")
 
 
 def cgbn_frozen_backward(dy, N, C, H, W, layout, dtype, fixed_var, gamma, eps, dx, stream=None) -> None:
     code = (_call or _calls()).frozen_backward(dy, N, C, H, W, layout, dtype, fixed_var, gamma, eps, dx, stream)
+    if code is NotImplemented:
+        code = lib().cgbn_frozen_backward(_ptr(dy), N, C, H, W, _enum(LAYOUTS, layout), _enum(DTYPES, dtype),
+            _ptr(fixed_var), _ptr(gamma), float(eps), _ptr(dx), _stream(stream))
     if code:
         _check(code, "cgbn_frozen_backward")
 

@@ -1,7 +1,8 @@
-/* Argument marshalling of the calls a training step makes, as a CPython extension: the same conversions as ctypes and the helpers in
- * cgbn.py make (None is NULL, a number is an address, anything else is asked for its data_ptr()), at a fifth of the time.  A step of a
- * small layer is host bound: of 9 us a call, ctypes and the helpers took 4.  The library is not linked: bind() is handed
- * the addresses of its functions by whoever loaded it. */
+/* Argument marshalling of the calls a training step makes, as a CPython extension: None is NULL, an int is an address or a number, a tensor is
+ * asked for its data_ptr(); at a fifth of the time that ctypes and the helpers in cgbn.py take for the same (a step of a small layer is
+ * host bound: of 9 us a call they took 4).  Whatever is not so plain (a ctypes object, a wrong type, a name that is not in the table) is
+ * answered NotImplemented before anything is called, and cgbn.py takes the call through ctypes, which accepts or refuses it.  The library is not
+ * linked: bind() is handed the addresses of its functions by whoever loaded it. */
 
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
@@ -30,91 +31,84 @@ static frozen_backward_fn g_frozen_backward;
 static PyObject *g_layouts, *g_dtypes, *g_stream;       /* name -> number; () -> the current stream's address */
 static PyObject *g_data_ptr, *g_numel, *g_element_size;
 
-/* Converters: each does nothing once an exception is set. */
-static void* ptr(PyObject* o)
+/* Converters: each returns 0 and clears *plain for what ctypes has to deal with, and does nothing once *plain is 0. */
+static unsigned long long number(PyObject* o, int* plain)
 {
-    void* v;
-    PyObject *a, *n;
-    if (o == Py_None || PyErr_Occurred()) return NULL;
-    if (PyLong_Check(o)) return (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(o);
-    a = PyObject_CallMethodNoArgs(o, g_data_ptr);
-    if (!a) return NULL;
-    n = PyNumber_Long(a);
+    if (*plain && PyLong_Check(o)) return PyLong_AsUnsignedLongLongMask(o);
+    *plain = 0;
+    return 0;
+}
+/* the number that a method without arguments returns */
+static unsigned long long asked(PyObject* o, PyObject* method, int* plain)
+{
+    unsigned long long v;
+    PyObject* a = PyObject_CallMethodNoArgs(o, method);
+    if (!a) { *plain = 0; return 0; }
+    v = number(a, plain);
     Py_DECREF(a);
-    if (!n) return NULL;
-    v = (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(n);
-    Py_DECREF(n);
     return v;
 }
-static int num(PyObject* o)
+static void* ptr(PyObject* o, int* plain)
 {
-    return PyErr_Occurred() ? 0 : (int)PyLong_AsUnsignedLongMask(o);
+    if (!*plain || o == Py_None) return NULL;
+    return (void*)(uintptr_t)(PyLong_Check(o) ? number(o, plain) : asked(o, g_data_ptr, plain));
 }
-static int name(PyObject* table, PyObject* o)
+static int num(PyObject* o, int* plain)
 {
-    PyObject* v;
-    int r;
-    if (PyErr_Occurred()) return 0;
-    if (PyUnicode_Check(o)) {
-        v = PyObject_GetItem(table, o);       /* KeyError */
-    } else {
-        v = PyNumber_Long(o);
+    return (int)number(o, plain);
+}
+static int name(PyObject* table, PyObject* o, int* plain)
+{
+    if (*plain && PyUnicode_Check(o)) {
+        o = PyDict_GetItemWithError(table, o);        /* borrowed */
+        if (!o) { *plain = 0; return 0; }
     }
-    if (!v) return 0;
-    r = (int)PyLong_AsUnsignedLongMask(v);
-    Py_DECREF(v);
-    return r;
+    return (int)number(o, plain);
 }
-static float real(PyObject* o)
+static float real(PyObject* o, int* plain)
 {
-    PyObject* f;
-    double v;
-    if (PyErr_Occurred()) return 0.f;
-    f = PyNumber_Float(o);
-    if (!f) return 0.f;
-    v = PyFloat_AS_DOUBLE(f);
-    Py_DECREF(f);
-    return (float)v;
+    if (*plain && PyFloat_Check(o)) return (float)PyFloat_AS_DOUBLE(o);
+    *plain = 0;
+    return 0.f;
 }
 /* the workspace's size: what the caller says, else the tensor's own */
-static size_t room(PyObject* workspace, PyObject* bytes)
+static size_t room(PyObject* workspace, PyObject* bytes, int* plain)
 {
-    PyObject *a, *b, *c;
-    size_t v;
-    if (PyErr_Occurred()) return 0;
-    if (bytes != Py_None) return (size_t)PyLong_AsUnsignedLongLongMask(bytes);
+    unsigned long long n;
+    if (!*plain) return 0;
+    if (bytes != Py_None) return (size_t)number(bytes, plain);
     if (workspace == Py_None) return 0;
-    a = PyObject_CallMethodNoArgs(workspace, g_numel);
-    b = a ? PyObject_CallMethodNoArgs(workspace, g_element_size) : NULL;
-    c = b ? PyNumber_Multiply(a, b) : NULL;
-    Py_XDECREF(a);
-    Py_XDECREF(b);
-    if (!c) return 0;
-    v = (size_t)PyLong_AsUnsignedLongLongMask(c);
-    Py_DECREF(c);
-    return v;
+    n = asked(workspace, g_numel, plain);
+    return *plain ? (size_t)(n * asked(workspace, g_element_size, plain)) : 0;
 }
-static void* stream(PyObject* o)
+static void* stream(PyObject* o, int* plain)
 {
-    PyObject* a;
     void* v;
-    if (PyErr_Occurred()) return NULL;
-    if (PyLong_Check(o)) return (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(o);
+    PyObject* a;
+    if (!*plain) return NULL;
+    if (PyLong_Check(o)) return (void*)(uintptr_t)number(o, plain);
     a = PyObject_CallOneArg(g_stream, o);
-    if (!a) return NULL;
-    v = a == Py_None ? NULL : (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(a);
+    if (!a) { *plain = 0; return NULL; }
+    v = a == Py_None ? NULL : (void*)(uintptr_t)number(a, plain);
     Py_DECREF(a);
     return v;
 }
 
 #define ARGS(count_)                                                                                     \
+    int plain = 1;                                                                                       \
     if (n != (count_)) { PyErr_Format(PyExc_TypeError, "%d arguments, %zd given", (count_), n); return NULL; } \
     if (!g_forward) { PyErr_SetString(PyExc_RuntimeError, "bind() first"); return NULL; }
 /* (the launch may wait for room in a queue) */
 #define CALL(call_)                                                                                      \
     do {                                                                                                 \
         cgbn_status s_;                                                                                  \
-        if (PyErr_Occurred()) return NULL;                                                               \
+        if (!plain) {                                                                                    \
+            if (PyErr_Occurred()) {                                                                      \
+                if (!PyErr_ExceptionMatches(PyExc_Exception)) return NULL;       /* an interrupt */      \
+                PyErr_Clear();                                                                           \
+            }                                                                                            \
+            Py_RETURN_NOTIMPLEMENTED;                                                                    \
+        }                                                                                                \
         Py_BEGIN_ALLOW_THREADS                                                                           \
         s_ = (call_);                                                                                    \
         Py_END_ALLOW_THREADS                                                                             \
@@ -125,90 +119,90 @@ static PyObject* forward(PyObject* self, PyObject* const* a, Py_ssize_t n)
 {
     (void)self;
     ARGS(18)
-    const void* x = ptr(a[0]);
-    const int N = num(a[1]), C = num(a[2]), H = num(a[3]), W = num(a[4]), layout = name(g_layouts, a[5]), K = num(a[6]);
-    const float *gamma = ptr(a[7]), *beta = ptr(a[8]);
-    const float eps = real(a[9]);
-    void* y = ptr(a[10]);
-    float *mean = ptr(a[11]), *invstd = ptr(a[12]);
-    const int dtype = name(g_dtypes, a[13]);
-    float* mean_lo = ptr(a[14]);
-    void* ws = ptr(a[15]);
-    const size_t bytes = room(a[15], a[16]);
-    void* st = stream(a[17]);
+    const void* x = ptr(a[0], &plain);
+    const int N = num(a[1], &plain), C = num(a[2], &plain), H = num(a[3], &plain), W = num(a[4], &plain), layout = name(g_layouts, a[5], &plain), K = num(a[6], &plain);
+    const float *gamma = ptr(a[7], &plain), *beta = ptr(a[8], &plain);
+    const float eps = real(a[9], &plain);
+    void* y = ptr(a[10], &plain);
+    float *mean = ptr(a[11], &plain), *invstd = ptr(a[12], &plain);
+    const int dtype = name(g_dtypes, a[13], &plain);
+    float* mean_lo = ptr(a[14], &plain);
+    void* ws = ptr(a[15], &plain);
+    const size_t bytes = room(a[15], a[16], &plain);
+    void* st = stream(a[17], &plain);
     CALL(g_forward(x, N, C, H, W, layout, K, gamma, beta, eps, y, mean, invstd, dtype, mean_lo, ws, bytes, st));
 }
 static PyObject* forward_relu(PyObject* self, PyObject* const* a, Py_ssize_t n)
 {
     (void)self;
     ARGS(19)
-    const void *x = ptr(a[0]), *shortcut = ptr(a[1]);
-    const int N = num(a[2]), C = num(a[3]), H = num(a[4]), W = num(a[5]), layout = name(g_layouts, a[6]), K = num(a[7]);
-    const float *gamma = ptr(a[8]), *beta = ptr(a[9]);
-    const float eps = real(a[10]);
-    void* y = ptr(a[11]);
-    float *mean = ptr(a[12]), *invstd = ptr(a[13]);
-    const int dtype = name(g_dtypes, a[14]);
-    float* mean_lo = ptr(a[15]);
-    void* ws = ptr(a[16]);
-    const size_t bytes = room(a[16], a[17]);
-    void* st = stream(a[18]);
+    const void *x = ptr(a[0], &plain), *shortcut = ptr(a[1], &plain);
+    const int N = num(a[2], &plain), C = num(a[3], &plain), H = num(a[4], &plain), W = num(a[5], &plain), layout = name(g_layouts, a[6], &plain), K = num(a[7], &plain);
+    const float *gamma = ptr(a[8], &plain), *beta = ptr(a[9], &plain);
+    const float eps = real(a[10], &plain);
+    void* y = ptr(a[11], &plain);
+    float *mean = ptr(a[12], &plain), *invstd = ptr(a[13], &plain);
+    const int dtype = name(g_dtypes, a[14], &plain);
+    float* mean_lo = ptr(a[15], &plain);
+    void* ws = ptr(a[16], &plain);
+    const size_t bytes = room(a[16], a[17], &plain);
+    void* st = stream(a[18], &plain);
     CALL(g_forward_relu(x, shortcut, N, C, H, W, layout, K, gamma, beta, eps, y, mean, invstd, dtype, mean_lo, ws, bytes, st));
 }
 static PyObject* backward(PyObject* self, PyObject* const* a, Py_ssize_t n)
 {
     (void)self;
     ARGS(19)
-    const void *dy = ptr(a[0]), *x = ptr(a[1]);
-    const float *mean = ptr(a[2]), *invstd = ptr(a[3]), *gamma = ptr(a[4]);
-    void* dx = ptr(a[5]);
-    float *dgamma = ptr(a[6]), *dbeta = ptr(a[7]);
-    const int N = num(a[8]), C = num(a[9]), H = num(a[10]), W = num(a[11]), layout = name(g_layouts, a[12]), K = num(a[13]);
-    const int dtype = name(g_dtypes, a[14]);
-    const float* mean_lo = ptr(a[15]);
-    void* ws = ptr(a[16]);
-    const size_t bytes = room(a[16], a[17]);
-    void* st = stream(a[18]);
+    const void *dy = ptr(a[0], &plain), *x = ptr(a[1], &plain);
+    const float *mean = ptr(a[2], &plain), *invstd = ptr(a[3], &plain), *gamma = ptr(a[4], &plain);
+    void* dx = ptr(a[5], &plain);
+    float *dgamma = ptr(a[6], &plain), *dbeta = ptr(a[7], &plain);
+    const int N = num(a[8], &plain), C = num(a[9], &plain), H = num(a[10], &plain), W = num(a[11], &plain), layout = name(g_layouts, a[12], &plain), K = num(a[13], &plain);
+    const int dtype = name(g_dtypes, a[14], &plain);
+    const float* mean_lo = ptr(a[15], &plain);
+    void* ws = ptr(a[16], &plain);
+    const size_t bytes = room(a[16], a[17], &plain);
+    void* st = stream(a[18], &plain);
     CALL(g_backward(dy, x, mean, invstd, gamma, dx, dgamma, dbeta, N, C, H, W, layout, K, dtype, mean_lo, ws, bytes, st));
 }
 static PyObject* backward_relu(PyObject* self, PyObject* const* a, Py_ssize_t n)
 {
     (void)self;
     ARGS(21)
-    const void *dy = ptr(a[0]), *y = ptr(a[1]), *x = ptr(a[2]);
-    const float *mean = ptr(a[3]), *invstd = ptr(a[4]), *gamma = ptr(a[5]);
-    void *dx = ptr(a[6]), *dshortcut = ptr(a[7]);
-    float *dgamma = ptr(a[8]), *dbeta = ptr(a[9]);
-    const int N = num(a[10]), C = num(a[11]), H = num(a[12]), W = num(a[13]), layout = name(g_layouts, a[14]), K = num(a[15]);
-    const int dtype = name(g_dtypes, a[16]);
-    const float* mean_lo = ptr(a[17]);
-    void* ws = ptr(a[18]);
-    const size_t bytes = room(a[18], a[19]);
-    void* st = stream(a[20]);
+    const void *dy = ptr(a[0], &plain), *y = ptr(a[1], &plain), *x = ptr(a[2], &plain);
+    const float *mean = ptr(a[3], &plain), *invstd = ptr(a[4], &plain), *gamma = ptr(a[5], &plain);
+    void *dx = ptr(a[6], &plain), *dshortcut = ptr(a[7], &plain);
+    float *dgamma = ptr(a[8], &plain), *dbeta = ptr(a[9], &plain);
+    const int N = num(a[10], &plain), C = num(a[11], &plain), H = num(a[12], &plain), W = num(a[13], &plain), layout = name(g_layouts, a[14], &plain), K = num(a[15], &plain);
+    const int dtype = name(g_dtypes, a[16], &plain);
+    const float* mean_lo = ptr(a[17], &plain);
+    void* ws = ptr(a[18], &plain);
+    const size_t bytes = room(a[18], a[19], &plain);
+    void* st = stream(a[20], &plain);
     CALL(g_backward_relu(dy, y, x, mean, invstd, gamma, dx, dshortcut, dgamma, dbeta, N, C, H, W, layout, K, dtype, mean_lo, ws, bytes, st));
 }
 static PyObject* frozen_forward(PyObject* self, PyObject* const* a, Py_ssize_t n)
 {
     (void)self;
     ARGS(14)
-    const void* x = ptr(a[0]);
-    const int N = num(a[1]), C = num(a[2]), H = num(a[3]), W = num(a[4]), layout = name(g_layouts, a[5]), dtype = name(g_dtypes, a[6]);
-    const float *fixed_mean = ptr(a[7]), *fixed_var = ptr(a[8]), *gamma = ptr(a[9]), *beta = ptr(a[10]);
-    const float eps = real(a[11]);
-    void* y = ptr(a[12]);
-    void* st = stream(a[13]);
+    const void* x = ptr(a[0], &plain);
+    const int N = num(a[1], &plain), C = num(a[2], &plain), H = num(a[3], &plain), W = num(a[4], &plain), layout = name(g_layouts, a[5], &plain), dtype = name(g_dtypes, a[6], &plain);
+    const float *fixed_mean = ptr(a[7], &plain), *fixed_var = ptr(a[8], &plain), *gamma = ptr(a[9], &plain), *beta = ptr(a[10], &plain);
+    const float eps = real(a[11], &plain);
+    void* y = ptr(a[12], &plain);
+    void* st = stream(a[13], &plain);
     CALL(g_frozen_forward(x, N, C, H, W, layout, dtype, fixed_mean, fixed_var, gamma, beta, eps, y, st));
 }
 static PyObject* frozen_backward(PyObject* self, PyObject* const* a, Py_ssize_t n)
 {
     (void)self;
     ARGS(12)
-    const void* dy = ptr(a[0]);
-    const int N = num(a[1]), C = num(a[2]), H = num(a[3]), W = num(a[4]), layout = name(g_layouts, a[5]), dtype = name(g_dtypes, a[6]);
-    const float *fixed_var = ptr(a[7]), *gamma = ptr(a[8]);
-    const float eps = real(a[9]);
-    void* dx = ptr(a[10]);
-    void* st = stream(a[11]);
+    const void* dy = ptr(a[0], &plain);
+    const int N = num(a[1], &plain), C = num(a[2], &plain), H = num(a[3], &plain), W = num(a[4], &plain), layout = name(g_layouts, a[5], &plain), dtype = name(g_dtypes, a[6], &plain);
+    const float *fixed_var = ptr(a[7], &plain), *gamma = ptr(a[8], &plain);
+    const float eps = real(a[9], &plain);
+    void* dx = ptr(a[10], &plain);
+    void* st = stream(a[11], &plain);
     CALL(g_frozen_backward(dy, N, C, H, W, layout, dtype, fixed_var, gamma, eps, dx, st));
 }
 

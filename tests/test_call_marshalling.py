@@ -1,6 +1,7 @@
 """The extension that marshals the training step's calls converts its arguments as ctypes does (on calls that the library refuses, so
 that nothing is launched), and a plan kept from an earlier call is the plan a fresh thread makes."""
 
+import ctypes
 import threading
 
 import numpy as np
@@ -77,11 +78,38 @@ def test_names_tensors_and_sizes():
     assert _code("cgbn_forward", {**FORWARD, "workspace": Buffer(P, need // 4 - 1, 4), "workspace_bytes": None}) == \
         _ctypes_code("cgbn_forward", {**FORWARD, "workspace_bytes": need - 4})
     assert _code("cgbn_forward", {**FORWARD, "x": Buffer(P + 8), "workspace_bytes": need}) == _ctypes_code("cgbn_forward", {**FORWARD, "x": P + 8, "workspace_bytes": need})
-    for bad, error in (({"layout": "NCWH"}, KeyError), ({"x": "text"}, AttributeError), ({"N": 2.5}, TypeError), ({"eps": "a"}, ValueError)):
+    for bad, error in (({"layout": "NCWH"}, KeyError), ({"x": "text"}, AttributeError), ({"N": 2.5}, ctypes.ArgumentError), ({"eps": "a"}, ValueError),
+                       ({"K": None}, ctypes.ArgumentError), ({"workspace": P, "workspace_bytes": None}, AttributeError)):
         with pytest.raises(error):
             L.cgbn_forward(**{**FORWARD, **bad})
     with pytest.raises(TypeError):
         L.cgbn_forward(P)
+
+
+class Parameter:
+    """What ctypes takes for a number."""
+    def __init__(self, value):
+        self._as_parameter_ = value
+
+
+@pytest.mark.parametrize("fn", CALLS)
+def test_what_is_not_plain_goes_through_ctypes(fn):
+    """Numbers as ctypes or numpy objects, sizes beyond an int, a stream object, eps as a number of another type: the same status as with
+    plain ones."""
+    base, sizes = CALLS[fn], ("N", "C", "H", "W", "K", "layout", "dtype")
+    want = _code(fn, base)
+    for make in (np.int64, ctypes.c_int, Parameter, lambda v: v + (1 << 32)):
+        kw = {k: (make(v) if k in sizes and not (make is ctypes.c_int and k in ("layout", "dtype")) else v) for k, v in base.items()}
+        if make is Parameter:
+            kw.update(layout=base["layout"], dtype=base["dtype"])          # (these are converted by int())
+        assert _code(fn, kw) == want != L.CGBN_OK, make
+    class Stream:
+        cuda_stream = 0
+    assert _code(fn, {**base, "stream": Stream()}) == want
+    if "eps" in base:
+        assert _code(fn, {**base, "eps": "1e-5"}) == _code(fn, {**base, "eps": 1e-5}) == _code(fn, {**base, "eps": np.float32(1e-5)})
+    if "workspace_bytes" in base:
+        assert _code(fn, {**base, "workspace_bytes": np.int64(0)}) == _code(fn, {**base, "workspace_bytes": ctypes.c_size_t(0)}) == want
 
 
 def test_kept_plans():
