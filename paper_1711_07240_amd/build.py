@@ -10,15 +10,17 @@ binding's extension is one C file."""
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
 from concurrent.futures import ThreadPoolExecutor
+from importlib.machinery import EXTENSION_SUFFIXES
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libcgbn.so")
-CALL = os.path.join(PKG, "_cgbn_call.so")
+CALL = os.path.join(PKG, "_cgbn_call" + EXTENSION_SUFFIXES[0])
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -56,9 +58,14 @@ def _units(obj_dir):
     return units
 
 
-def build_call(verbose: bool = True) -> str:
-    """The binding's extension (csrc/cgbn_call.c)."""
-    cmd = [os.environ.get("CC", "gcc"), "-O2", "-std=c11", "-Wall", "-fPIC", "-shared", "-I", sysconfig.get_paths()["include"],
+def build_call(verbose: bool = True) -> str | None:
+    """The binding's extension (csrc/cgbn_call.c), for the Python that runs this.  None where that has no headers: the
+    binding then marshals every call through ctypes, which takes longer."""
+    if not os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h")):
+        print(f"no Python.h in {sysconfig.get_paths()['include']}: the binding goes without its extension", flush=True)
+        return None
+    cc = os.environ.get("CC") or shutil.which("gcc") or os.path.join(os.path.dirname(HIPCC), "amdclang")
+    cmd = [cc, "-O2", "-std=c11", "-Wall", "-fPIC", "-shared", "-I", sysconfig.get_paths()["include"],
            "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "cgbn_call.c"), "-o", CALL]
     if verbose:
         print(" ".join(cmd), flush=True)

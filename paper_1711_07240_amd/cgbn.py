@@ -18,7 +18,7 @@ from typing import Optional
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libcgbn.so")
-CALL_PATH = os.path.join(_HERE, "_cgbn_call.so")
+CALL_PATH = os.path.join(_HERE, "_cgbn_call" + importlib.machinery.EXTENSION_SUFFIXES[0])      # built for this very Python
 
 CGBN_NCHW, CGBN_NHWC = 0, 1
 CGBN_F32, CGBN_BF16 = 0, 1
@@ -70,6 +70,11 @@ _lib = None
 _call = None        # the extension, bound to the library's functions
 
 
+class _ByCtypes:
+    """In the place of the extension where it is not built for this Python: every call goes through ctypes."""
+    forward = forward_relu = backward = backward_relu = frozen_forward = frozen_backward = staticmethod(lambda *_: NotImplemented)
+
+
 class CgbnError(RuntimeError):
     def __init__(self, code: int, where: str):
         self.code = code
@@ -80,24 +85,29 @@ def lib() -> ctypes.CDLL:
     """Load libcgbn.so (once).  Raises if it is missing: build it first."""
     global _lib, _call
     if _lib is None:
-        missing = [p for p in (LIB_PATH, CALL_PATH) if not os.path.exists(p)]
-        if missing:
+        if not os.path.exists(LIB_PATH):
             raise ImportError(
-                f"{missing[0]} is not built; run `python -c 'import __graft_entry__ as g; g.build()'` "
+                f"{LIB_PATH} is not built; run `python -c 'import __graft_entry__ as g; g.build()'` "
                 "or `python paper_1711_07240_amd/build.py`")
         handle = ctypes.CDLL(LIB_PATH)
         for name, (res, args) in SIGNATURES.items():
             fn = getattr(handle, name)
             fn.restype = res
             fn.argtypes = args
-        loader = importlib.machinery.ExtensionFileLoader("_cgbn_call", CALL_PATH)
-        call = importlib.util.module_from_spec(importlib.util.spec_from_loader("_cgbn_call", loader))
-        loader.exec_module(call)
-        call.bind(tuple(ctypes.cast(getattr(handle, "cgbn_" + n), ctypes.c_void_p).value for n in
-                        ("forward", "forward_relu", "backward", "backward_relu", "frozen_forward", "frozen_backward")),
-                  LAYOUTS, DTYPES, _stream)
-        _lib, _call = handle, call
+        _lib, _call = handle, _load_extension(handle)
     return _lib
+
+
+def _load_extension(handle):
+    if not os.path.exists(CALL_PATH):
+        return _ByCtypes
+    loader = importlib.machinery.ExtensionFileLoader("_cgbn_call", CALL_PATH)
+    call = importlib.util.module_from_spec(importlib.util.spec_from_loader("_cgbn_call", loader))
+    loader.exec_module(call)
+    call.bind(tuple(ctypes.cast(getattr(handle, "cgbn_" + n), ctypes.c_void_p).value for n in
+                    ("forward", "forward_relu", "backward", "backward_relu", "frozen_forward", "frozen_backward")),
+              LAYOUTS, DTYPES, _stream)
+    return call
 
 
 def _calls():

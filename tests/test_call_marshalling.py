@@ -2,6 +2,7 @@
 that nothing is launched), and a plan kept from an earlier call is the plan a fresh thread makes."""
 
 import ctypes
+import importlib.machinery
 import threading
 
 import numpy as np
@@ -110,6 +111,20 @@ def test_what_is_not_plain_goes_through_ctypes(fn):
         assert _code(fn, {**base, "eps": "1e-5"}) == _code(fn, {**base, "eps": 1e-5}) == _code(fn, {**base, "eps": np.float32(1e-5)})
     if "workspace_bytes" in base:
         assert _code(fn, {**base, "workspace_bytes": np.int64(0)}) == _code(fn, {**base, "workspace_bytes": ctypes.c_size_t(0)}) == want
+
+
+def test_without_the_extension(tmp_path, monkeypatch):
+    """A Python that the extension was not built for: every call answers as with it."""
+    def answers():
+        out = [_code(fn, base) for fn, base in CALLS.items()]
+        out += [_code("cgbn_forward", {**FORWARD, "layout": "NHWC", "dtype": "bf16", "workspace": Buffer(P, 7, 4), "workspace_bytes": None})]
+        return out + [L.cgbn_workspace_bytes(2, 8, 4, 4, "NCHW", "f32", 1)]
+    assert L._calls() is not L._ByCtypes and L.CALL_PATH.endswith(importlib.machinery.EXTENSION_SUFFIXES[0])
+    want = answers()
+    monkeypatch.setattr(L, "CALL_PATH", str(tmp_path / "none.so"))
+    monkeypatch.setattr(L, "_lib", None)
+    monkeypatch.setattr(L, "_call", None)
+    assert answers() == want and L._calls() is L._ByCtypes
 
 
 def test_kept_plans():
