@@ -116,7 +116,7 @@ def _calls():
     return _call
 
 
-_torch = None
+_torch = _raw_stream = None        # _raw_stream: () -> the current stream's address without a Stream object for it, if torch has the means
 
 
 def _ptr(t) -> Optional[int]:
@@ -133,12 +133,14 @@ def _nbytes(t) -> int:
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        global _torch
+        global _torch, _raw_stream
         if _torch is None:
             import torch
+            raw, device = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+            _raw_stream = (lambda: raw(device())) if raw and device else None
             _torch = torch
-        if _torch.cuda.is_initialized():      # what the next line gives, without a Stream object for it
-            return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice()) or None
+        if _raw_stream is not None and _torch.cuda.is_initialized():
+            return _raw_stream() or None
         return int(_torch.cuda.current_stream().cuda_stream) or None
     if isinstance(stream, int):
         return stream or None

@@ -127,6 +127,22 @@ def test_without_the_extension(tmp_path, monkeypatch):
     assert answers() == want and L._calls() is L._ByCtypes
 
 
+@pytest.mark.parametrize("private", [True, False])
+def test_current_stream(private, monkeypatch):
+    """The current stream's address, by torch's private functions or, where a torch has none of them, by the public one."""
+    import torch
+    monkeypatch.setattr(L, "_torch", None)
+    monkeypatch.setattr(L, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("S", (), {"cuda_stream": 7}))
+    if private:
+        monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 10 + device, raising=False)
+    else:
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert L._stream(None) == (13 if private else 7) and L._stream(0) is None and L._stream(5) == 5
+
+
 def test_kept_plans():
     """More shapes than are kept, in two orders, with a knob changed in between; another thread keeps nothing yet."""
     r = np.random.default_rng(3)
