@@ -190,8 +190,10 @@ struct SlabPlan {
     long long R, row_bytes, total_units;
 };
 
+constexpr int kAnyDevice = -2;
 struct Plan {
     Tuning t;             // the knobs this plan was made under (the call's own copy)
+    int device, cus;      // the device whose compute units the plan counts on, and how many; kAnyDevice: it does not depend on one
     int N, C, H, W, K, layout, dtype;
     int eb, vec;          // bytes per element; elements per 16-byte vector (NHWC: 1 if C is not a multiple)
     int HW, ips;
@@ -573,13 +575,20 @@ void make_narrow_plan(int N, int C, long long HW, int eb, bool forward, bool sec
     n->ok = 1;
 }
 
-// compute units of the current device (256 if there is none to ask)
-int compute_units()
+// the current device, -1 if there is none to ask
+int current_device()
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) == hipSuccess && dev >= 0) return dev;
+    (void)hipGetLastError();
+    return -1;
+}
+// its compute units (256 if there is none to ask)
+int compute_units(int dev = current_device())
 {
     static std::atomic<int> known[kMaxDevices];
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 256;
-    cus = known[dev].load(std::memory_order_relaxed);
+    if (dev < 0 || dev >= kMaxDevices) return 256;
+    int cus = known[dev].load(std::memory_order_relaxed);
     if (cus > 0) return cus;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
     known[dev].store(cus, std::memory_order_relaxed);
@@ -592,10 +601,9 @@ int compute_units()
 // unbalanced pieces), and every further row of partials costs time in the combine step.
 // So: the fewest pieces per shard, between `least_bytes` (128 KiB) and 4 MiB each, that fill the last
 // round of workgroups best.
-long long reduce_pieces(long long spix, int K, int ctiles, int rpp, long long tile_row_bytes, long long least_bytes)
+long long reduce_pieces(long long spix, int K, int ctiles, int rpp, long long tile_row_bytes, long long least_bytes, int cus)
 {
     const long long quantum = 4LL * rpp;                 // four pixels per thread and pass
-    const int cus = compute_units();
     const long long max_pixels = (4LL << 20) / tile_row_bytes > quantum ? (4LL << 20) / tile_row_bytes : quantum;
     const long long first = (spix + max_pixels - 1) / max_pixels;      // fewest pieces of at most 4 MiB
     long long best_pps = first;
@@ -632,8 +640,8 @@ bool cut_pixels(const Tuning& T, long long spix, int cols, int K, Plan* p)
         // 16 KiB on while two workgroups a compute unit do not come together.  Not beyond: every row costs the combine step; forward of
         // 104 x 72 x 103 x 31 fp32, 1248 rows 81 us, 728 rows 70)
         long long least = 128 << 10;
-        if (p->group > 1) least = std::min(least, std::max(16LL << 10, p->S * p->eb / (2LL * compute_units())));
-        PL = reduce_pieces(p->spix, K, p->ctiles, p->rpp, (long long)p->TW * p->vec * p->eb, least);
+        if (p->group > 1) least = std::min(least, std::max(16LL << 10, p->S * p->eb / (2LL * p->cus)));
+        PL = reduce_pieces(p->spix, K, p->ctiles, p->rpp, (long long)p->TW * p->vec * p->eb, least, p->cus);
     }
     if (PL > p->spix) PL = p->spix;
     p->PL = (int)PL;
@@ -659,7 +667,7 @@ bool cut_pixels(const Tuning& T, long long spix, int cols, int K, Plan* p)
     // 706 us, 64 x 50 x 84 x 1024 1314 -> 1286).
     const bool f32 = p->eb == 4 && p->vec != 1;
     for (int inputs = 1; inputs <= 3; ++inputs) {
-        const long long quantum = 4 * p->rpp, cus = compute_units(), enough = f32 && inputs > 1 ? cus * 3 / 2 : cus * 2;
+        const long long quantum = 4 * p->rpp, enough = f32 && inputs > 1 ? p->cus * 3 / 2 : p->cus * 2;
         const bool row = T.map_piece_bytes > 0 || p->vec == 1 || (f32 && (inputs > 1 || p->ctiles > 2));
         long long bytes = T.map_piece_bytes > 0 ? T.map_piece_bytes : f32 && inputs == 3 ? 16384 : 32768, PL, pps;
         for (;; bytes /= 2) {
@@ -738,6 +746,7 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
     if (S > (1LL << 40)) return CGBN_ERR_SHAPE;
     std::memset(p, 0, sizeof(*p));
     p->t = T;
+    p->device = kAnyDevice;
     p->group = p->may_group = 1;
     p->N = N; p->C = C; p->H = H; p->W = W; p->K = K; p->layout = layout; p->dtype = dtype;
     p->eb = dtype == CGBN_F32 ? 4 : 2;
@@ -746,6 +755,10 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
     p->S = S;
     p->M = (double)N * (double)HW;
     const int full_vec = 16 / p->eb;
+    if (layout == CGBN_NHWC || (C % full_vec == 0 && HW <= kSlabThreads)) {       // (else neither sweeps nor slab plans need it)
+        p->device = current_device();
+        p->cus = compute_units(p->device);
+    }
     if (layout == CGBN_NCHW) {
         p->vec = full_vec;
         if (T.tiny_planes && HW * p->eb <= kTinyPlaneBytes && C % 8 == 0) {
@@ -817,7 +830,7 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
     size_t room = others > (1u << 20) ? others : (1u << 20);
     if (sync + others + 2 * part + mlo <= (size_t)CGBN_STATIC_SCRATCH_BYTES && others + 2 * part > room) room = others + 2 * part;
     const long long row_words = (long long)(room / sizeof(double));
-    const int cus = C % (16 / p->eb) == 0 && (layout == CGBN_NHWC || HW <= kSlabThreads) ? compute_units() : 0;    // (else no slab plan needs it)
+    const int cus = p->cus;
     for (const bool forward : {true, false}) {
         SlabPlan &one = forward ? p->sf : p->sb, &two = forward ? p->sfs : p->sbm;
         make_slab_plan(N, C, HW, layout, p->eb, row_words, cus, forward ? p->ff : p->fb, forward, false, &one);
@@ -848,39 +861,56 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
 }
 
 // The plan of a call, from this thread's last plans or made anew.  A plan follows from its key alone: the sizes, the knobs (by
-// their version: a plan made while they change is not kept) and the device.  Making one takes 2 us, 9 with a large shard
-// channels-last, of the 10 us a small call took on the host; a training run comes back to the same few dozen layers.
+// their version: a plan made while they change is not kept) and, if it counts compute units, the device.  Making one takes 2 us, 9 with a
+// large shard channels-last, of the 10 us a small call took on the host; a training run comes back to the same few dozen layers.
 struct KeptPlan {
     Plan p, g;            // g: grouped(p)
-    int key[8];
+    int key[7];
     unsigned version;
+    unsigned used;        // when it was last taken
     bool valid = false;
     // the plan of a channels-last reduction whose sums are handed out pooled
     const Plan& sums(bool with_dy) const { return group_sums(p, with_dy) ? g : p; }
     const Plan& map(int tensors) const { return group_map(p, tensors) ? g : p; }
 };
-constexpr int kKeptPlans = 64;
+constexpr int kKeptSets = 64, kKeptWays = 1;
 cgbn_status plan_of(int N, int C, int H, int W, int layout, int dtype, int K, const KeptPlan** out)
 {
-    static thread_local std::unique_ptr<KeptPlan> kept[kKeptPlans];
-    int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess) { (void)hipGetLastError(); dev = -1; }
-    const int key[8] = {N, C, H, W, layout, dtype, K, dev};
+    static thread_local std::unique_ptr<KeptPlan> kept[kKeptSets][kKeptWays];
+    static thread_local unsigned clock = 0;
+    const int key[7] = {N, C, H, W, layout, dtype, K};
     unsigned hash = 0;
     for (int v : key) hash = (hash ^ (unsigned)v) * 0x9e3779b1u, hash ^= hash >> 15;
-    std::unique_ptr<KeptPlan>& k = kept[hash % kKeptPlans];
+    auto& set = kept[hash % kKeptSets];
     const unsigned version = g_tune_version.load(std::memory_order_acquire);
-    if (!k || !k->valid || k->version != version || std::memcmp(k->key, key, sizeof(key)) != 0) {
-        if (!k) k.reset(new (std::nothrow) KeptPlan);
-        if (!k) return CGBN_ERR_HIP;
-        k->valid = false;
-        const cgbn_status s = make_plan(tuning_now(), N, C, H, W, layout, dtype, K, &k->p);
-        if (s != CGBN_OK) return s;
-        k->g = grouped(k->p);
-        std::memcpy(k->key, key, sizeof(key));
-        k->version = version;
-        k->valid = g_tune_version.load(std::memory_order_acquire) == version;
+    int dev = kAnyDevice;          // (asked for only if a plan depends on it)
+    for (auto& k : set) {
+        if (!k || !k->valid || k->version != version || std::memcmp(k->key, key, sizeof(key)) != 0) continue;
+        if (k->p.device != kAnyDevice) {
+            if (dev == kAnyDevice) dev = current_device();
+            if (k->p.device != dev) continue;
+        }
+        k->used = ++clock;
+        *out = k.get();
+        return CGBN_OK;
     }
+    std::unique_ptr<KeptPlan>* room = &set[0];
+    for (auto& k : set) {
+        if (!k || !k->valid || k->version != version) { room = &k; break; }
+        if (clock - k->used > clock - (*room)->used) room = &k;
+    }
+    std::unique_ptr<KeptPlan>& k = *room;
+    Plan p;
+    const cgbn_status s = make_plan(tuning_now(), N, C, H, W, layout, dtype, K, &p);
+    if (s != CGBN_OK) return s;
+    if (!k) k.reset(new (std::nothrow) KeptPlan);
+    if (!k) return CGBN_ERR_HIP;
+    k->p = p;
+    k->g = grouped(p);
+    std::memcpy(k->key, key, sizeof(key));
+    k->version = version;
+    k->used = ++clock;
+    k->valid = g_tune_version.load(std::memory_order_acquire) == version;
     *out = k.get();
     return CGBN_OK;
 }

@@ -256,3 +256,49 @@ def test_invalid_arguments_and_keys():
     assert L.cgbn_plan_get(4, 16, 32, 32, "NCHW", "f32", 3, "grid") == -1      # K does not divide N
     assert L.cgbn_plan_get(4, 16, 32, 32, "NCHW", "f32", 2, "no_such_key") == -1
     assert L.cgbn_plan_get(4, 16, 32, 32, "NCHW", "f32", 2, "fwd_no_such_key") == -1
+
+
+SHIM = """
+static int asked;
+int hipGetDevice(int* device) { ++asked; *device = 0; return 100; }      /* no device */
+int times_asked(void) { return asked; }
+"""
+ASK = """
+import ctypes, sys
+shim = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)                 # found before the runtime's own
+from paper_1711_07240_amd import cgbn as L
+P = 1 << 20
+forward = dict(x=P, N=2, C=8, H=64, W=64, layout=0, K=1, gamma=P, beta=P, eps=1e-5, y=P, mean=P, invstd=P, dtype=0, workspace=P, workspace_bytes=0, stream=0)
+refused = [dict(N=0), dict(K=3), dict(layout=7), dict(x=None), dict(layout=1, N=0), dict(layout=1, dtype=5), dict(H=1 << 30, W=4)]
+for change in refused:
+    try:
+        L.cgbn_forward(**{**forward, **change})
+        sys.exit("not refused")
+    except L.CgbnError:
+        pass
+    static = {k: v for k, v in {**forward, **change}.items() if not k.startswith("workspace")}
+    try:
+        L.cgbn_forward_static(**static)
+        sys.exit("not refused")
+    except L.CgbnError:
+        pass
+for _ in range(2):
+    assert L.cgbn_workspace_bytes(16, 64, 400, 672, "NCHW", "f32", 8) > 0 and L.cgbn_workspace_bytes(2, 7, 3, 3, "NCHW", "f32", 1) > 0
+print(shim.times_asked())
+for _ in range(2):
+    assert L.cgbn_workspace_bytes(2, 64, 8, 8, "NHWC", "f32", 1) > 0
+print(shim.times_asked())
+"""
+
+
+def test_the_device_is_asked_for_only_where_a_plan_depends_on_it(tmp_path):
+    """Refused sizes and NCHW planes beyond the column-slab kernels' initialise no runtime (a process may size its workspace and then fork)."""
+    import subprocess
+    import sys
+    so = str(tmp_path / "shim.so")
+    (tmp_path / "shim.c").write_text(SHIM)
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", so, str(tmp_path / "shim.c")], check=True)
+    out = subprocess.run([sys.executable, "-c", ASK, so], cwd=ROOT, capture_output=True, text=True, timeout=100)
+    assert out.returncode == 0, out.stderr
+    before, after = map(int, out.stdout.split())
+    assert before == 0 and after > 0
