@@ -862,7 +862,9 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
 
 // The plan of a call, from this thread's last plans or made anew.  A plan follows from its key alone: the sizes, the knobs (by
 // their version: a plan made while they change is not kept) and, if it counts compute units, the device.  Making one takes 2 us, 9 with a
-// large shard channels-last, of the 10 us a small call took on the host; a training run comes back to the same few dozen layers.
+// large shard channels-last, of the 10 us a small call took on the host; a training run comes back to the same few dozen layers.  Kept by
+// four to a hash value, the one longest unused making room: with one to a value up to 7 of the 16 layer
+// shapes of a detector, by the image's width, shared one and drove each other out at every step.
 struct KeptPlan {
     Plan p, g;            // g: grouped(p)
     int key[7];
@@ -873,7 +875,8 @@ struct KeptPlan {
     const Plan& sums(bool with_dy) const { return group_sums(p, with_dy) ? g : p; }
     const Plan& map(int tensors) const { return group_map(p, tensors) ? g : p; }
 };
-constexpr int kKeptSets = 64, kKeptWays = 1;
+constexpr int kKeptSets = 128, kKeptWays = 4;
+thread_local unsigned g_plans_made = 0;
 cgbn_status plan_of(int N, int C, int H, int W, int layout, int dtype, int K, const KeptPlan** out)
 {
     static thread_local std::unique_ptr<KeptPlan> kept[kKeptSets][kKeptWays];
@@ -903,6 +906,7 @@ cgbn_status plan_of(int N, int C, int H, int W, int layout, int dtype, int K, co
     Plan p;
     const cgbn_status s = make_plan(tuning_now(), N, C, H, W, layout, dtype, K, &p);
     if (s != CGBN_OK) return s;
+    ++g_plans_made;
     if (!k) k.reset(new (std::nothrow) KeptPlan);
     if (!k) return CGBN_ERR_HIP;
     k->p = p;
@@ -1924,6 +1928,7 @@ long long cgbn_get_tuning(const char* key)
     if (key && !std::strcmp(key, "last_backward_fused")) return g_last_backward_fused.load();
     if (key && !std::strcmp(key, "last_forward_slab")) return g_last_forward_slab.load();
     if (key && !std::strcmp(key, "last_backward_slab")) return g_last_backward_slab.load();
+    if (key && !std::strcmp(key, "plans_made")) return g_plans_made;
     long long* slot = tuning_slot(key);
     if (!slot) return -1;
     std::lock_guard<std::mutex> hold(g_tune_lock);

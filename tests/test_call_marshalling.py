@@ -165,3 +165,25 @@ def test_kept_plans():
     finally:
         L.cgbn_set_tuning("piece_bytes", 0)
     assert sizes(shapes) == first
+
+
+@pytest.mark.parametrize("layout", ["NCHW", "NHWC"])
+def test_layers_of_a_detector_do_not_drive_each_other_out(layout):
+    """The layer shapes of a ResNet-50 with a feature pyramid, at many image widths: a second step makes no plan."""
+    def steps():
+        for width in range(1024, 1344, 32):
+            layers, h, w = [(64, 400, width // 2)], 200, width // 4
+            for c in (64, 128, 256, 512):
+                layers += [(c, h, w), (4 * c, h, w), (256, h, w)]
+                h, w = -(-h // 2), -(-w // 2)
+            layers += [(c, 2 * h, 2 * w) for c in (128, 256, 512)]         # the strided ones, before their stride
+            step = lambda: [L.cgbn_workspace_bytes(2, c, a, b, layout, "bf16", 2) for c, a, b in layers]
+            step()
+            made = L.cgbn_get_tuning("plans_made")
+            step()
+            again[width] = L.cgbn_get_tuning("plans_made") - made
+    again = {}
+    t = threading.Thread(target=steps)
+    t.start()
+    t.join()
+    assert len(again) == 10 and not any(again.values()), again
