@@ -151,10 +151,10 @@ struct Tuning {
     long long stagger_phases = 16;       // ... and the number of classes
     long long wait_us = 100000;          // microseconds after which a device-side wait of the fused kernels gives up
 };
-// The knobs are process-wide; every call works on ONE copy of them taken under the lock when it starts
-// (tuning_now), so a knob changed by another thread in the middle of a call cannot make the plan, the
+// The knobs are process-wide; every call works on ONE copy of them, the one its plan was made under: taken under the lock
+// (tuning_now) when the call starts, or when an earlier call of the thread made the plan, if no knob has changed since (`version` counts
+// the changes).  So a knob changed by another thread in the middle of a call cannot make the plan, the
 // workspace check and the launches of that call disagree.
-// `version` counts the changes of the knobs.
 Tuning g_tune;
 std::mutex g_tune_lock;
 std::atomic<unsigned> g_tune_version{0};
@@ -1513,15 +1513,14 @@ cgbn_status cgbn_update_running_stats(const float* mean, const float* mean_lo, c
 
 namespace {
 
-// Algorithm 1, optionally followed by "+ shortcut" and a ReLU (relu == true)
+// Algorithm 1, optionally followed by "+ shortcut" and a ReLU (relu == true).  `k`: the call's plan, if its caller has it already.
 cgbn_status forward_impl(const void* x, const void* shortcut, bool relu, int N, int C, int H, int W,
                          cgbn_layout layout, int K, const float* gamma, const float* beta, float eps,
                          void* y, float* mean, float* invstd, cgbn_dtype dtype, float* mean_lo,
-                         void* workspace, size_t workspace_bytes, void* stream)
+                         void* workspace, size_t workspace_bytes, void* stream, const KeptPlan* k = nullptr)
 {
     if (!x || !gamma || !beta || !y || !mean || !invstd) return CGBN_ERR_NULL;
-    const KeptPlan* k;
-    CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, K, &k));
+    if (!k) CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, K, &k));
     const Plan& p = k->p;
     if (!eps_ok(eps)) return CGBN_ERR_EPS;
     if (!aligned16(x) || !aligned16(y) || !aligned16(shortcut)) return CGBN_ERR_ALIGN;
@@ -1689,7 +1688,8 @@ cgbn_status cgbn_forward_static(const void* x, int N, int C, int H, int W, cgbn_
                                 void* y, float* mean, float* invstd,
                                 cgbn_dtype dtype, float* mean_lo, void* stream)
 {
-    // every argument error is answered before the device is asked for anything
+    // every argument error is answered before the device is asked for its scratch; one plan, and with it one copy of the knobs, for the check
+    // and the launches
     if (!x || !gamma || !beta || !y || !mean || !invstd) return CGBN_ERR_NULL;
     const KeptPlan* k;
     CGBN_TRY(plan_of(N, C, H, W, (int)layout, (int)dtype, K, &k));
@@ -1699,7 +1699,7 @@ cgbn_status cgbn_forward_static(const void* x, int N, int C, int H, int W, cgbn_
     void* ws = nullptr;
     CGBN_TRY(scratch_of_current_device(&ws));
     return forward_impl(x, nullptr, false, N, C, H, W, layout, K, gamma, beta, eps, y, mean, invstd, dtype, mean_lo,
-                        ws, (size_t)CGBN_STATIC_SCRATCH_BYTES, stream);
+                        ws, (size_t)CGBN_STATIC_SCRATCH_BYTES, stream, k);
 }
 
 cgbn_status cgbn_backward(const void* dy, const void* x, const float* mean, const float* invstd,

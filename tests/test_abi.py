@@ -216,3 +216,52 @@ def test_forward_static_argument_errors_and_size_limit():
     for shape in [(4, 16, 32, 32, "NCHW", "f32", 2), (16, 64, 400, 672, "NCHW", "f32", 8), (16, 256, 200, 336, "NCHW", "f32", 8),
                   (256, 2048, 25, 42, "NCHW", "f32", 128), (64, 512, 50, 84, "NHWC", "bf16", 32)]:
         assert 0 < L.cgbn_workspace_bytes(*shape) <= limit
+
+
+RUNTIME = """
+#include <stddef.h>
+static int (*set_knob)(const char*, long long);
+static int changed, launches;
+void on_scratch(int (*f)(const char*, long long)) { set_knob = f; }
+int counts(int what) { return what ? launches : changed; }
+int hipGetDevice(int* device) { *device = 0; return 0; }
+int hipGetSymbolAddress(void** address, const void* symbol)
+{
+    *address = (void*)(size_t)(1 << 20);
+    changed += set_knob("piece_bytes", 4096) == 0;
+    return 0;
+}
+int __hipPushCallConfiguration() { return 0; }
+int __hipPopCallConfiguration() { return 0; }
+int hipLaunchKernel() { ++launches; return 1; }
+int hipGetLastError(void) { return 1; }
+"""
+CHANGE = """
+import ctypes, sys
+runtime = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)              # found before the runtime's own
+from paper_1711_07240_amd import cgbn as L
+runtime.on_scratch(ctypes.cast(L.lib().cgbn_set_tuning, ctypes.c_void_p))
+L.cgbn_set_tuning("fused", 0)
+P, shape = 1 << 20, (4, 1024, 64, 64, "NHWC", "bf16", 4)
+assert 0 < L.cgbn_workspace_bytes(*shape) <= 16 << 20
+try:
+    L.cgbn_forward_static(P, *shape[:5], 4, P, P, 1e-5, P, P, P, "bf16", None, 0)
+    code = 0
+except L.CgbnError as e:
+    code = e.code
+assert runtime.counts(0) == 1 and L.cgbn_workspace_bytes(*shape) > 16 << 20
+print(code, runtime.counts(1))
+"""
+
+
+def test_static_forward_checks_and_launches_under_one_copy_of_the_knobs(tmp_path):
+    """A knob that would make the scratch too small is set between the check and the launches: the call goes on under the knobs it was checked
+    under (to the launch, which this stand-in for the runtime refuses), and is not refused for a workspace that it has none of."""
+    import subprocess
+    import sys
+    so = str(tmp_path / "runtime.so")
+    (tmp_path / "runtime.c").write_text(RUNTIME)
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", so, str(tmp_path / "runtime.c")], check=True)
+    out = subprocess.run([sys.executable, "-c", CHANGE, so], cwd=ROOT, capture_output=True, text=True, timeout=100)
+    assert out.returncode == 0, out.stderr
+    assert out.stdout.split() == ["8", "1"]
