@@ -305,7 +305,8 @@ const char* cgbn_status_string(cgbn_status status);
 cgbn_status cgbn_set_tuning(const char* key, long long value);
 /* also readable: "last_forward_fused", "last_backward_fused" (1 if the last
  * cgbn_forward / cgbn_backward took the single-launch NCHW kernels), "last_forward_slab",
- * "last_backward_slab" (1 if it took the column-slab kernels), "plans_made" (launch plans the calling thread has
+ * "last_backward_slab" (1 if it took the column-slab kernels), "last_forward_slab_vector",
+ * "last_backward_slab_vector" (the bytes of their vectors, 16 or 8, or 0), "plans_made" (launch plans the calling thread has
  * made: calls come back to the last ones it keeps) */
 long long cgbn_get_tuning(const char* key);
 

@@ -163,7 +163,7 @@ Tuning tuning_now()
     std::lock_guard<std::mutex> hold(g_tune_lock);
     return g_tune;
 }
-std::atomic<long long> g_last_forward_slab{0}, g_last_backward_slab{0};
+std::atomic<long long> g_last_forward_slab{0}, g_last_backward_slab{0};     // bytes of the vectors of the column-slab kernel it took, or 0
 std::atomic<long long> g_last_forward_fused{0}, g_last_backward_fused{0};   // which path the last call took
 #ifdef CGBN_TRACE
 unsigned long long* g_trace = nullptr;
@@ -1554,10 +1554,11 @@ cgbn_status forward_impl(const void* x, const void* shortcut, bool relu, int N, 
     }
     g_last_forward_fused = 0;
 
-    g_last_forward_slab = slab;
+    g_last_forward_slab = 0;
     if (slab) {
         const SlabPlan& narrow = shortcut ? p.nfs : p.nf;
         const SlabPlan& sp = narrow.ok ? narrow : wide;
+        g_last_forward_slab = sp.vb;
         SlabArgs F = slab_args(p, sp, ws);
         F.x = x; F.dy = shortcut; F.out = y; F.gamma = gamma; F.beta = beta; F.eps = (double)eps;
         F.mean = mean; F.mean_lo = mean_lo; F.invstd = invstd;
@@ -1638,10 +1639,11 @@ cgbn_status backward_impl(const void* dy, const void* y, const void* x, const fl
     }
     g_last_backward_fused = 0;
 
-    g_last_backward_slab = slab;
+    g_last_backward_slab = 0;
     if (slab) {
         const SlabPlan& narrow = relu ? p.nbm : p.nb;
         const SlabPlan& sp = narrow.ok ? narrow : wide;
+        g_last_backward_slab = sp.vb;
         SlabArgs F = slab_args(p, sp, ws);
         F.x = x; F.dy = dy; F.aux = y; F.out = dx; F.out2 = dshortcut; F.gamma = gamma;
         F.mean = const_cast<float*>(mean); F.mean_lo = const_cast<float*>(mean_lo); F.invstd = const_cast<float*>(invstd);
@@ -1926,8 +1928,10 @@ long long cgbn_get_tuning(const char* key)
 {
     if (key && !std::strcmp(key, "last_forward_fused")) return g_last_forward_fused.load();
     if (key && !std::strcmp(key, "last_backward_fused")) return g_last_backward_fused.load();
-    if (key && !std::strcmp(key, "last_forward_slab")) return g_last_forward_slab.load();
-    if (key && !std::strcmp(key, "last_backward_slab")) return g_last_backward_slab.load();
+    if (key && !std::strcmp(key, "last_forward_slab")) return g_last_forward_slab.load() != 0;
+    if (key && !std::strcmp(key, "last_forward_slab_vector")) return g_last_forward_slab.load();
+    if (key && !std::strcmp(key, "last_backward_slab")) return g_last_backward_slab.load() != 0;
+    if (key && !std::strcmp(key, "last_backward_slab_vector")) return g_last_backward_slab.load();
     if (key && !std::strcmp(key, "plans_made")) return g_plans_made;
     long long* slot = tuning_slot(key);
     if (!slot) return -1;

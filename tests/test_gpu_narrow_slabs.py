@@ -1,5 +1,6 @@
-"""Column-slab kernels with 8-byte vectors (NCHW, small planes): every variant, ragged slabs and passes, against the float64 oracles with
-the tolerances stated in gpu_harness.py; and their plans, on the host alone."""
+"""Column-slab kernels with 8-byte vectors (NCHW, small planes): ragged slabs and passes, against the float64 oracles with
+the tolerances stated in gpu_harness.py; and their plans, on the host alone.  Some of the shapes have such a plan but take the single-launch
+kernels, which are faster there; every variant is run in test_gpu_slab_variants.py."""
 
 import numpy as np
 import pytest
@@ -56,6 +57,14 @@ def _draw(N, C, H, W, dtype):
     return x, dy, s, r.uniform(0.5, 1.5, C).astype(np.float32), r.normal(0, 0.1, C).astype(np.float32)
 
 
+def _took(case, forward, backward):
+    """The kernels with 8-byte vectors ran wherever their plan stands and does not come behind the single-launch kernels."""
+    g = lambda k: L.cgbn_plan_get(*case[:4], "NCHW", case[4], 1, k)
+    for way, d in (("forward", forward), ("backward", backward)):
+        slab = g("s%s_first" % d) or not g(d[:3] + "_ok")
+        assert L.cgbn_get_tuning("last_%s_slab_vector" % way) == (0 if not slab else 8 if g("n%s_ok" % d) else 16)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("case", CASES, ids=ID)
 def test_forward_backward(case):
@@ -65,6 +74,7 @@ def test_forward_backward(case):
     p = G.Problem(x, dy, gamma, beta, 1e-5, "NCHW", dtype, 1)
     p.forward()
     p.backward()
+    _took(case, "fwd", "bwd")
     wx, wdy = G.widen(x, dtype), G.widen(dy, dtype)
     sums = dict(sum_scale=np.sqrt(N * H * W) * G.rms(wdy))
     G.check_against_oracle(p.results(), O.cgbn_forward_backward_ref(wx, wdy, gamma, beta, 1e-5, "NCHW"), dtype, str(case), **sums)
@@ -72,6 +82,7 @@ def test_forward_backward(case):
     L.cgbn_forward_relu(p.x, sd, *p.shape_args, "NCHW", 1, p.gamma, p.beta, 1e-5, y, p.mean, p.invstd, dtype, p.mean_lo, p.ws)
     L.cgbn_backward_relu(p.dy, y, p.x, p.mean, p.invstd, p.gamma, p.dx, dz, p.dgamma, p.dbeta, *p.shape_args, "NCHW", 1, dtype,
                          p.mean_lo, p.ws)
+    _took(case, "fwds", "bwdm")
     torch.cuda.synchronize()
     y_ref, mean, invstd = R.cgbn_relu_forward_ref(wx, gamma, beta, 1e-5, "NCHW", G.widen(s, dtype))
     wy = G.to_host_f64(y, dtype)
@@ -93,6 +104,7 @@ def test_in_place():
     p = G.Problem(x, dy, gamma, beta, 1e-5, "NCHW", dtype, 1)
     p.forward()
     p.backward()
+    _took(CASES[1], "fwd", "bwd")
     y, dx = p.y.clone(), p.dx.clone()
     p.backward(dx=p.dy)
     p.forward(y=p.x)

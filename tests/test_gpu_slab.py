@@ -19,7 +19,8 @@ pytestmark = pytest.mark.gpu
 
 BASE = synth.WORKLOADS["cfg1"]
 
-# (what it is for, shape): N, C, H, W, K, layout, dtype; the plan's units per slab (1 or "several")
+# (what it is for, shape): N, C, H, W, K, layout, dtype; the units per slab of the plan with 16-byte vectors (1 or "several").  (NCHW with one unit:
+# most of these take 8-byte vectors in its place; every variant of either is in test_gpu_slab_variants.py.)
 SHAPES = [
     ("one-row", (1, 8, 1, 1, 1, "NHWC", "bf16"), 1),
     ("one-vector-ragged-pass", (1, 4, 5, 103, 1, "NHWC", "f32"), 1),
@@ -71,6 +72,15 @@ def _ran_here(forward=True, backward=True):
     assert L.cgbn_get_tuning("last_forward_slab") == forward and L.cgbn_get_tuning("last_backward_slab") == backward
 
 
+def _vectors_are(shape, forward, backward):
+    """The bytes of the vectors of the kernels that ran: 8 where the plan has such a one in the other's place."""
+    n, c, h, w, k, layout, dtype = shape
+    for way, d in (("forward", forward), ("backward", backward)):
+        want = 8 if L.cgbn_plan_get(n, c, h, w, layout, dtype, k, f"n{d}_ok") else 16
+        assert layout == "NCHW" or want == 16
+        assert L.cgbn_get_tuning(f"last_{way}_slab_vector") == want, way
+
+
 def _outputs(p):
     return [t.clone() for t in (p.y, p.dx, p.mean, p.invstd, p.mean_lo, p.dgamma, p.dbeta)]
 
@@ -108,6 +118,7 @@ def test_against_the_oracle(name, shape, units):
     p.forward()
     p.backward()
     _ran_here()
+    _vectors_are(shape, "fwd", "bwd")
     G.check_against_oracle(p.results(), _reference(wl, d), dtype, name)
     assert _error_word(p) == 0
     first = _outputs(p)
@@ -140,6 +151,7 @@ def test_relu_against_the_oracle(name, shape, units, with_shortcut):
 
     got = step()
     _ran_here()
+    _vectors_are(shape, "fwds" if with_shortcut else "fwd", "bwdm")
     x, dy = G.widen(d["x"], wl.dtype), G.widen(d["dy"], wl.dtype)
     g, b = d["gamma"].astype(np.float64), d["beta"].astype(np.float64)
     y, mean, invstd = R.cgbn_relu_forward_ref(x, g, b, wl.eps, wl.layout, G.widen(sc_host, wl.dtype) if with_shortcut else None)[:3]
@@ -337,6 +349,7 @@ def test_variance_keeps_its_accuracy_wherever_the_first_value_lies(shape, kind):
 
 
 @pytest.mark.parametrize("kind", [1.0, 4.0, 30.0])
+# (... and 8-byte vectors, 26 values a thread)
 @pytest.mark.parametrize("shape", STATISTICS + [(256, 1024, 7, 7, 8, "NCHW", "bf16")], ids=lambda s: "x".join(map(str, s)))
 def test_mean_keeps_its_accuracy(shape, kind):
     """mean + mean_lo in standard deviations, the first value (the pivot of all sums) `kind` of them off.  The only float

@@ -10,6 +10,7 @@ from paper_1711_07240_amd import cgbn as L
 THREADS = 512
 VARIANTS = {("sfwd", True): (4, 8, 10, 12, 20), ("sfwd", False): (6, 12, 18, 28, 36),
             ("sbwd", True): (4, 6, 8, 10, 12, 20), ("sbwd", False): (6, 9, 14, 18)}
+NARROW = (8, 12, 16, 20, 28)                        # ... of those with 8-byte vectors
 MAX_CHANNELS = 128
 STATIC_SCRATCH = 16 << 20
 
@@ -57,6 +58,29 @@ def _check(shape):
     return taken
 
 
+def _check_narrow(shape):
+    """The plans with 8-byte vectors that stand in for those: one workgroup a slab, NCHW, for the same matrix."""
+    N, C, H, W, layout, dtype, K = shape
+    vec = 2 if dtype == "f32" else 4
+    taken = 0
+    for d in ("fwd", "fwds", "bwd", "bwdm"):
+        g, wide = (lambda k: L.cgbn_plan_get(*shape, f"n{d}_{k}")), (lambda k: L.cgbn_plan_get(*shape, f"s{d}_{k}"))
+        if not g("ok"):
+            continue
+        taken += 1
+        cols, vecs, cpc, nch, rpp, tpc, slabs, U, rpu, P, R = (g(k) for k in (
+            "cols", "vecs", "cpc", "nch", "rpp", "tpc", "slabs", "U", "rpu", "P", "R"))
+        assert layout == "NCHW" and wide("ok") and cpc == H * W and R == rpu == N and U == 1
+        assert vecs * vec == C * H * W and 1 <= cols <= THREADS and (slabs - 1) * cols < vecs <= slabs * cols and slabs <= C
+        assert cols * vec == nch * H * W and nch <= MAX_CHANNELS and nch & (nch - 1) == 0
+        assert tpc & (tpc - 1) == 0 and 1 <= tpc <= 64 and tpc * nch <= THREADS
+        assert rpp == THREADS // cols and N <= rpp * P and P in NARROW and (P == 8 or N > rpp * NARROW[NARROW.index(P) - 1])
+        assert rpp * C * H * W * (8 // vec) + cols * 8 < 2 ** 31
+        # no more than half the compute units (of the planning host's default) had a workgroup, or a slab was several units and each is now one
+        assert 2 * wide("slabs") <= 256 if wide("U") == 1 else slabs <= 256
+    return taken
+
+
 def _shapes(count, seed, layout):
     r = np.random.default_rng(seed)
     for _ in range(count):
@@ -73,13 +97,15 @@ def _shapes(count, seed, layout):
 @pytest.mark.parametrize("layout", ["NHWC", "NCHW"])
 @pytest.mark.parametrize("seed", [1, 2])
 def test_random_shapes(seed, layout):
-    taken = 0
+    taken = narrow = 0
     for shape in _shapes(1200, seed, layout):
         try:
             taken += _check(shape)
+            narrow += _check_narrow(shape)
         except AssertionError as e:
             raise AssertionError(f"{shape}: {e}") from e
     assert taken > (2400 if layout == "NHWC" else 1500)          # (four plans a shape)
+    assert narrow == 0 if layout == "NHWC" else narrow > 600
 
 
 def test_detector_layers():
