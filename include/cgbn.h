@@ -257,8 +257,9 @@ cgbn_status cgbn_update_running_stats(const float* mean, const float* mean_lo, c
 const char* cgbn_status_string(cgbn_status status);
 
 /* Launch-shape knobs for measurement sweeps.  They are process-wide; reading and writing
- * them is serialised, and every call of the library works on ONE copy of them taken when it
- * starts, so calls from several host threads are safe and a call never sees half of a
+ * them is serialised, and every call of the library works on ONE copy of them, taken when it
+ * starts (or when its thread made the plan for an earlier call, if no knob has changed
+ * since), so calls from several host threads are safe and a call never sees half of a
  * change.  The workspace size depends on some of them: re-query cgbn_workspace_bytes after
  * a change (a call whose workspace is too small for the knobs it runs under returns
  * CGBN_ERR_WORKSPACE before launching anything).
@@ -268,8 +269,9 @@ const char* cgbn_status_string(cgbn_status status);
  *                      multi-sweep kernels takes a run of 8 ... 256 planes of consecutive channels at once
  *   "piece_bytes"      NHWC reductions: bytes of one pixel range handled by one workgroup (0, the default:
  *                      chosen per shape so that the grid fills the device's compute units evenly)
- *   "map_piece_bytes"  NHWC normalise / dx: the same for the elementwise sweeps (0, the default: 128 KiB for
- *                      bfloat16; for float 64 KiB where the sweep reads one tensor, 32 KiB where it reads more)
+ *   "map_piece_bytes"  NHWC normalise / dx: the same for the elementwise sweeps (0, the default: 32 KiB, 16 for three
+ *                      float tensors; shorter for small tensors, and where C is no whole number of vectors and
+ *                      pixels cannot be grouped; longer for rows of several tiles)
  *   "reverse"          0/1: alternate the sweep direction between consecutive sweeps
  *   "nt_store"         0/1: non-temporal stores for y and dx
  *   "fused"            0/1: register-resident forward/backward in one launch (the NCHW kernels and the
@@ -319,7 +321,12 @@ long long cgbn_get_tuning(const char* key);
  * of shard sums); NCHW: "wave_mode" (one wavefront per plane), "L" / "sp" (chunk elements, chunks
  * per plane); NHWC: "vec" (elements per access), "cv" (accesses per pixel), "TW" / "ctiles"
  * (accesses per pixel handled by one workgroup, workgroups per pixel), "rpp" (pixels per pass),
- * "PL" / "pps" (pixels per piece, pieces per shard; reductions), "PLm" / "ppsm" (elementwise).
+ * "PL" / "pps" (pixels per piece, pieces per shard; reductions), "PLm" / "ppsm" / "gridm" (elementwise with one input;
+ * with a 2 or 3 behind them: two, three inputs), "single_consts" (elementwise with two inputs: constants by single loads).
+ * NHWC, C no multiple of a 16-byte vector ("vec" 1): "may_group" (pixels that are taken as one pixel of whole vectors
+ * where that pays, 1: never), "group_sums" / "group_sums_dy" (reductions of x, of x and dy, that do), "group_map" /
+ * "group_map2" (elementwise sweeps with one input, with more), and of the plan then used "grouped_K", "grouped_cv",
+ * "grouped_ctiles", "grouped_rows", "grouped_spix" (groups per shard), "grouped_PL", "grouped_pps".
  * Single-launch kernels, prefix "fwd_" or "bwd_": "ok" (the shape qualifies), "LB" (bytes per
  * access), "LPPC" (register slots per small plane; 0: large planes), "LPP" (slots a plane fills),
  * "IPU" (images per unit), "U" (units per channel), "tp" / "TL" (tiles per large plane, tile
@@ -328,7 +335,8 @@ long long cgbn_get_tuning(const char* key);
  * sweeps), "first" (... also before the single-launch NCHW kernels), "vecs" (16-byte vectors per row of
  * the matrix), "R" (its rows), "cpc" (columns per channel), "cols" (vectors per slab), "slabs", "nch" (channels per slab, rounded up to a power of two), "rpp" (rows per pass),
  * "tpc" (threads that add one channel's partial sums), "U" (units per slab), "rpu" (rows per unit),
- * "P" (vectors per thread of the kernel variant). */
+ * "P" (vectors per thread of the kernel variant).  Prefix "nfwd_", "nbwd_", "nfwds_", "nbwdm_": the same of the plan with 8-byte
+ * vectors that takes its place if its own "ok" is 1. */
 long long cgbn_plan_get(int N, int C, int H, int W, cgbn_layout layout, cgbn_dtype dtype, int K,
                         const char* key);
 

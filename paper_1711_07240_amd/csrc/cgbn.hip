@@ -137,7 +137,7 @@ struct Tuning {
     long long wave_plane_bytes = 16384;  // NCHW: planes up to this go one per wavefront
     long long tiny_planes = 1;           // NCHW: planes of at most 2 KiB (C a multiple of 8) go several to a workgroup
     long long piece_bytes = 0;           // NHWC reductions: bytes of a pixel run per workgroup; 0 = chosen per shape (see reduce_pieces)
-    long long map_piece_bytes = 0;       // NHWC normalise / dx: the same for the elementwise sweeps; 0 = chosen per dtype and sweep (see map_pieces)
+    long long map_piece_bytes = 0;       // NHWC normalise / dx: the same for the elementwise sweeps; 0 = chosen per shape and sweep (see cut_pixels)
     long long reverse = 1;               // alternate sweep direction so a sweep starts on what the last one left in cache
     long long nt_store = 1;              // non-temporal stores for y and dx
     long long fused = 1;                 // register-resident single-launch path where the shape allows it
@@ -195,7 +195,7 @@ struct Plan {
     Tuning t;             // the knobs this plan was made under (the call's own copy)
     int device, cus;      // the device whose compute units the plan counts on, and how many; kAnyDevice: it does not depend on one
     int N, C, H, W, K, layout, dtype;
-    int eb, vec;          // bytes per element; elements per 16-byte vector (NHWC: 1 if C is not a multiple)
+    int eb, vec;          // bytes per element; elements per access (NHWC: 1 if C is no multiple of a 16-byte vector, see `group`)
     int HW, ips;
     long long S;
     double M;
@@ -541,7 +541,9 @@ void make_slab_plan(int N, int C, long long HW, int layout, int eb, long long ro
         s->first = !f.ok || (f.U > 1 && (forward ? HW * eb <= 1024 && N * s->row_bytes <= 200000000 : HW * eb <= (eb == 2 ? 512 : 800) && N * s->row_bytes <= 100000000));
 }
 
-// NCHW calls whose plan `s` has 16-byte vectors: one of 8-byte vectors in its place (see SlabVector).
+// NCHW calls whose plan `s` has 16-byte vectors: one of 8-byte vectors in its place (see SlabVector), where that leaves at least half the compute
+// units without a workgroup or a slab is several units.  Measured over 140 random shapes, 16 bytes / 8: forward 1.22, with a shortcut 1.21, backward
+// 1.18, masked 1.13 times faster; from 129 to 255 slabs of 16 bytes, where a compute unit would come to hold two of 8, 1.02, 0.97, 0.96, 0.92.
 void make_narrow_plan(int N, int C, long long HW, int eb, bool forward, bool second, const SlabPlan& s, int cus, SlabPlan* n)
 {
     std::memset(n, 0, sizeof(*n));

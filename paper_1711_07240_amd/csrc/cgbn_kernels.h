@@ -1032,7 +1032,7 @@ template <int EL, int V> struct MapConsts {
 // Floats a channel's constants take in LDS.
 template <int EL> constexpr int map_const_words() { return EL == EL_SCALE ? 1 : EL == EL_FROZEN ? 3 : el_is_norm(EL) ? 4 : 6; }
 
-// Elementwise, HBM bound: one thread, one vector column, UNR pixels at a time.  A workgroup has at most 32 KiB to move, a chunk or two a
+// Elementwise, HBM bound: one thread, one vector column, UNR pixels at a time.  A workgroup has some 32 KiB to move, a chunk or two a
 // thread, so what stands before the first chunk counts: its loads are issued before the channels' constants are formed.  Each
 // channel's are formed once, in LDS, with fixed statistics, where a constant is a square root and a division, if there are at least as many
 // rows of threads as a vector has channels; and with grouped pixels, whose columns' channels do not lie side by side (every thread its

@@ -85,7 +85,7 @@ def test_map_pieces_of_several_tiles(dtype, C):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("shape", MAPS, ids=str)
+@pytest.mark.parametrize("shape", MAPS + [(3, 37, 11, 64), (2, 25, 42, 1024), (2, 20, 40, 255), (4, 21, 30, 100)], ids=str)     # (whole vectors, and grouped)
 def test_elementwise(shape, dtype):
     """Every elementwise sweep, per-channel vectors 4, 8 and 12 bytes off a 16-byte boundary: they need be no more than floats."""
     N, H, W, C = shape
