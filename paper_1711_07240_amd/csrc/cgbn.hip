@@ -682,6 +682,11 @@ bool cut_pixels(const Tuning& T, long long spix, int cols, int K, Plan* p)
             pps = (p->spix + PL - 1) / PL;
             if (T.map_piece_bytes > 0 || PL <= quantum || pps * K * p->ctiles >= enough) break;
         }
+        // (a launch has less than 2^32 threads: tensors of 70 GB and more, value by value)
+        while (pps * K * p->ctiles >= (1LL << 32) / kThreads && PL < p->spix) {
+            PL = std::min(2 * PL, p->spix);
+            pps = (p->spix + PL - 1) / PL;
+        }
         if (pps * K > 0x3fffffffLL || pps * K * p->ctiles > 0x7fffffffLL) return false;
         p->map[inputs - 1] = {(int)PL, (int)pps, pps * K * p->ctiles};
     }

@@ -184,3 +184,12 @@ def test_single_constants():
     want = (x.double() - mean.double() - lo.double()) * (invstd.double() * gamma.double()) + beta.double() + dy.double()
     # a handful of roundings of values of up to ten times the standard deviation
     assert float((y.double() - want.clamp(min=0)).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_a_launch_has_less_than_two_to_the_32_threads(dtype):
+    """137 GB and more, value by value and in whole vectors: the pieces grow rather than the grid."""
+    for N, C, H, W in ((1, 2047, 6401, 6400), (9, 127, 8001, 7999), (64, 2048, 800, 800)):
+        get = lambda k: L.cgbn_plan_get(N, C, H, W, "NHWC", dtype, 1, k)
+        for i in ("", "2", "3"):
+            assert 0 < get("gridm" + i) * 256 < 2 ** 32 and get("ppsm" + i) == -(-N * H * W // get("PLm" + i))
