@@ -55,6 +55,19 @@ CGBN_FUSED_BIG_SMALL(CGBN_DECL_F2)
 CGBN_FUSED_BIG_SMALL(CGBN_DECL_B2)
 #undef CGBN_DECL_F2
 #undef CGBN_DECL_B2
+#define CGBN_DECL_E(LPPC_, BIG_, T_, ACT_) extern template __global__ void nchw_fused_forward<T_, 16, LPPC_, ACT_, BIG_, true>(FusedArgs);
+#define CGBN_DECL_FE(LPPC_, BIG_)                                                               \
+    CGBN_DECL_E(LPPC_, BIG_, float, 0) CGBN_DECL_E(LPPC_, BIG_, float, 1) CGBN_DECL_E(LPPC_, BIG_, float, 2) \
+    CGBN_DECL_E(LPPC_, BIG_, bf16_t, 0) CGBN_DECL_E(LPPC_, BIG_, bf16_t, 1) CGBN_DECL_E(LPPC_, BIG_, bf16_t, 2)
+CGBN_FUSED_EDGE_FORWARD(CGBN_DECL_FE)
+#undef CGBN_DECL_E
+#define CGBN_DECL_E(LPPC_, BIG_, T_, ACT_) extern template __global__ void nchw_fused_backward<T_, 16, LPPC_, ACT_, BIG_, true>(FusedArgs);
+#define CGBN_DECL_BE(LPPC_, BIG_)                                                               \
+    CGBN_DECL_E(LPPC_, BIG_, float, 0) CGBN_DECL_E(LPPC_, BIG_, float, 1) CGBN_DECL_E(LPPC_, BIG_, bf16_t, 0) CGBN_DECL_E(LPPC_, BIG_, bf16_t, 1)
+CGBN_FUSED_EDGE_BACKWARD(CGBN_DECL_BE)
+#undef CGBN_DECL_E
+#undef CGBN_DECL_FE
+#undef CGBN_DECL_BE
 // ... and the column-slab kernels in cgbn_slab_inst.hip
 #define CGBN_DECL_SF(P_, SOLO_)                                                                 \
     extern template __global__ void slab_forward<float, 0, P_, SOLO_, false>(SlabArgs);         \
@@ -176,6 +189,7 @@ struct FusedPlan {
     int LB;               // bytes per load: 16 or 8
     int LPPC;             // 0: large planes; else register slots per plane (an instantiated count >= LPP)
     int tp, TL, LPP, IPU, U, rows, rps, G;
+    int edge;             // planes start anywhere: 16-byte loads, the values before and behind whole vectors one by one
     int big;              // 1 (large planes) / 2 (small planes): the variant that stages few rows and keeps more unit data in LDS
     long long total_units;
 };
@@ -215,6 +229,8 @@ struct Plan {
     // value at a time moves 2 or 4 bytes an instruction.)  `may_group`: what grouped() makes of this plan, 1 if nothing.
     int group, may_group;
     FusedPlan ff, fb;     // register-resident path, forward and backward
+    FusedPlan ef, ebw;    // ... with 16-byte loads for planes that are no multiple of 16 bytes, and the calls that take them (see edges_pay):
+    bool edges[4];        // forward, with a shortcut, backward, masked
     SlabPlan sf, sb;      // column-slab path
     SlabPlan sfs, sbm;    // ... of a forward with a shortcut, of a masked backward
     SlabPlan nf, nb, nfs, nbm;    // the same with 8-byte vectors: taken in their place where ok
@@ -225,7 +241,7 @@ struct Plan {
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 void make_fused_plan(const Tuning& T, int N, int C, long long HW, int K, int layout, int eb, int words, int lds_words,
-                     int lds_words_big, int lds_words_big_small, bool forward, FusedPlan* f)
+                     int lds_words_big, int lds_words_big_small, bool forward, bool edge, FusedPlan* f)
 {
     std::memset(f, 0, sizeof(*f));
     if (K > kFusedMaxShards) return;
@@ -233,12 +249,22 @@ void make_fused_plan(const Tuning& T, int N, int C, long long HW, int K, int lay
     int LB = 0;
     for (int lb = 16; lb >= 4; lb >>= 1)
         if (HW % (lb / eb) == 0) { LB = lb; break; }
+    const bool small_edges = (long long)C * HW * eb % 16 == 0;         // a channel's planes all start at the same byte of a vector
+    const long long plane = HW;                        // (HW: what the slots hold of it)
+    if (edge) {
+        if (LB == 16 || plane * eb <= 1024) return;
+        LB = 16;
+        HW = HW * eb / 16 * 16 / eb;
+        f->edge = 1;
+    }
     if (!LB) return;                                   // bfloat16 planes with an odd element count
     const int W = LB / 4, R = words / W, E = LB / eb;
     const long long wave_cap = (long long)R * kWave * E;   // elements one wavefront can hold
     if (LB == 4 && HW > wave_cap) return;              // 4-byte loads only for small planes
     const int ips = N / K;
+    const bool small_edges_or_plain = !edge || small_edges;
     f->LB = LB;
+    if (edge && !small_edges && HW <= wave_cap) return;
     if (HW <= wave_cap) {
         f->LPP = (int)((HW + (long long)kWave * E - 1) / ((long long)kWave * E));
         // register slots per plane: the smallest instantiated count that holds a plane and
@@ -256,7 +282,7 @@ void make_fused_plan(const Tuning& T, int N, int C, long long HW, int K, int lay
 #define CGBN_IS_BUILT(LB_, LPPC_) built = built || (LB == LB_ && lppc == LPPC_);
             CGBN_FUSED_BIG_SMALL(CGBN_IS_BUILT)
 #undef CGBN_IS_BUILT
-            if (built) lds_planes = (lds_words_big_small / W) / lppc;
+            if (built && !(edge && lppc == 2)) lds_planes = (lds_words_big_small / W) / lppc;
             // ... if that makes the channel's units fewer (else the variant only costs its extra slot checks)
             const int regs_only = 4 * (R / lppc), with_lds = 4 * (R / lppc + lds_planes);
             if ((N + with_lds - 1) / with_lds >= (N + regs_only - 1) / regs_only) lds_planes = 0;
@@ -269,7 +295,7 @@ void make_fused_plan(const Tuning& T, int N, int C, long long HW, int K, int lay
         if ((long long)f->IPU * C * HW * eb > 0x7fffffffLL) return;
         f->rows = N;
         f->rps = ips;
-    } else if (LB >= 8 && HW <= (long long)(R + lds_words / W) * kWave * E) {
+    } else if (LB >= 8 && small_edges_or_plain && HW <= (long long)(R + lds_words / W) * kWave * E) {
         // a plane a few slots too long for a wavefront's registers: still one plane per wavefront, the last
         // slots in LDS (four planes per unit instead of the one a "large plane" unit would hold)
         f->LPP = (int)((HW + (long long)kWave * E - 1) / ((long long)kWave * E));
@@ -283,6 +309,7 @@ void make_fused_plan(const Tuning& T, int N, int C, long long HW, int K, int lay
         // large planes: a tile also fills the LDS slots (16-byte loads only); with few rows and shards to
         // stage, the variant with more LDS slots is taken
         const long long gran = (long long)kThreads * E;
+        HW = plane;
         for (int big = (LB == 16 && T.big_lds && K <= kFusedMaxShardsBig) ? 1 : 0; big >= 0; --big) {
             const int lw = big ? lds_words_big : lds_words;
             const long long cap = wave_cap * 4 + (LB == 16 ? (long long)(lw / W) * kThreads * E : 0);
@@ -301,7 +328,7 @@ void make_fused_plan(const Tuning& T, int N, int C, long long HW, int K, int lay
             // a plane of at most half the slots: the same channel's planes of two consecutive images per unit
             const long long unit_slots = R + (LB == 16 ? lw / W : 0);
             const long long plane_slots = (HW * eb + (long long)kThreads * LB - 1) / ((long long)kThreads * LB);
-            if (LB == 16 && tp == 1 && N >= 2 && 2 * plane_slots <= unit_slots && (long long)C * HW * eb <= 0xffffffffLL) {
+            if (LB == 16 && small_edges_or_plain && tp == 1 && N >= 2 && 2 * plane_slots <= unit_slots && (long long)C * HW * eb <= 0xffffffffLL) {
                 f->LPPC = -2;
                 f->U = (N + 1) / 2;
                 f->rows = N;
@@ -313,7 +340,7 @@ void make_fused_plan(const Tuning& T, int N, int C, long long HW, int K, int lay
     // Three or four whole planes per workgroup in workgroup-wide slots, where the layout chosen above is one of the
     // large-plane ones (a tile or two planes per workgroup) and leaves the unit markedly emptier (measured, 64 x 256
     // planes of 100 x 100 floats forward 298 -> 284 us; 128 x 512 planes of 100 x 100 bf16 backward 904 -> 846 us)
-    if (f->LPPC <= 0 && LB == 16 && T.big_lds && K <= kFusedMaxShardsBig && N <= kFusedMaxRowsBig && N >= 2 && (long long)C * HW * eb <= 0xffffffffLL) {
+    if (f->LPPC <= 0 && LB == 16 && small_edges_or_plain && T.big_lds && K <= kFusedMaxShardsBig && N <= kFusedMaxRowsBig && N >= 2 && (long long)C * HW * eb <= 0xffffffffLL) {
         const long long slot_bytes = (long long)kThreads * LB;
         const long long unit_slots = R + lds_words_big / W;                      // of the variant with more unit data in LDS
         const long long plane_bytes = HW * eb, plane_slots = (plane_bytes + slot_bytes - 1) / slot_bytes;
@@ -739,6 +766,48 @@ Plan grouped(const Plan& p)
     return q;
 }
 
+// Which calls on NCHW planes that are no multiple of 16 bytes take the single-launch kernels with 16-byte loads, the values of a plane before and
+// behind its whole vectors one by one (`e`), rather than what there is else (`f`: the same kernels with 8- or 4-byte loads; where that is not ok,
+// sweeps).  Measured over 130 random shapes of 1 to 370 MB, forward / with shortcut / backward / masked, that time over this one's:
+//   - the sweeps: large tensors 1.35 / 1.05 / 1.45 / 1.55 (16 x 64 x 201 x 333 fp32 179 / 226 / 273 / 449 us -> 124 / 198 / 179 / 290, bf16 99 / 116 /
+//     143 / 237 -> 71 / 113 / 97 / 154), channels of one unit 1.7 / 1.4 / 1.9 / 1.9 (4 x 96 of 75 x 57 bf16).  Few units leave the chip idle, and with a
+//     shortcut the write-out waits for it batch by batch: 2 x 24 of 38000 bf16 0.8 / 0.5 / 1.05 / 1.0, 64 x 24 of 27 x 37 0.8 / 0.5 / 0.9 / 0.8.
+//   - 4-byte loads: bf16 from 8 KB on 1.3 / 1.2 / 1.15 / 1.2, below 0.95 / 1.05 / 0.9 / 0.95; float from 9 KB on 1.25, below only where its slots are filled
+//     (4.3 to 5 KB 1.15 to 1.3; 23 x 71, 6.4 slots of 8, 0.96 / 0.84 / 0.88).  Few units of several a channel: 32 x 64 of 39 x 63 with a shortcut 0.8.
+//   - 8-byte loads, which large planes take without further data in LDS: forward beyond 16 KB 1.05 to 1.35 (else 0.9 to 1.05); with a shortcut
+//     0.85 to 1.2; backward 1.2 to 1.45 where three planes of 23 to 29 KB share a workgroup here, bf16 1.4 beyond 16 KB, else 0.9 to 1.05.
+bool edges_pay(const FusedPlan& e, const FusedPlan& f, bool built, long long plane_bytes, long long tensor_bytes, int eb, bool forward, bool second)
+{
+    if (!e.ok) return false;
+    if (!f.ok || !built) {
+        if (plane_bytes <= 2048 && (second || e.U > 1 || e.total_units < 128)) return false;
+        if (forward && second) return tensor_bytes >= 100000000 || (e.U == 1 && e.total_units >= 64 && plane_bytes >= 3500 && plane_bytes <= 16384);
+        return e.total_units >= (e.U == 1 ? 48 : forward ? 256 : 96);
+    }
+    if (f.LB == 4) {
+        if (e.U > 1 && e.total_units < 256) return false;
+        if (eb == 2) return plane_bytes >= 8000;
+        return plane_bytes >= 9000 || (plane_bytes >= 4096 && e.LPPC > 0 && plane_bytes * 100 >= (long long)e.LPPC * 1024 * 85);
+    }
+    if (plane_bytes <= 16384 || (forward && second)) return false;
+    return forward || eb == 2 || (e.LPPC == -3 && plane_bytes >= 23000);
+}
+
+// Which (bytes per access, slots per plane) variants exist for an element type, direction and activation: all of
+// the list header's, except that the float ReLU backward is not built with 4-byte accesses (one slot count
+// excepted; see CGBN_FUSED_RELU_BWD_F32_NARROW).  A shape whose variant is not built takes the multi-sweep kernels.
+constexpr bool fused_built(bool f32, bool forward, int act, int LB, int LPPC)
+{
+    if (f32 && !forward && act == 1 && LB == 4) {
+        bool built = false;
+#define CGBN_IS_BUILT(LB_, LPPC_) built = built || (LB == LB_ && LPPC == LPPC_);
+        CGBN_FUSED_RELU_BWD_F32_NARROW(CGBN_IS_BUILT)
+#undef CGBN_IS_BUILT
+        return built;
+    }
+    return true;
+}
+
 cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, int dtype, int K, Plan* p)
 {
     if (N < 1 || C < 1 || H < 1 || W < 1) return CGBN_ERR_SHAPE;
@@ -801,8 +870,10 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
     int G = 1;
     while (G < kWave && G < p->rps) G <<= 1;
     p->G = G;
-    make_fused_plan(T, N, C, HW, K, layout, p->eb, kFusedWords, kFusedLdsWords, kFusedLdsWordsBig, kFusedLdsWordsBigSmall, true, &p->ff);
-    make_fused_plan(T, N, C, HW, K, layout, p->eb, kFusedWords / 2, kFusedLdsWords / 2, kFusedLdsWordsBig / 2, kFusedLdsWordsBigSmall / 2, false, &p->fb);
+    make_fused_plan(T, N, C, HW, K, layout, p->eb, kFusedWords, kFusedLdsWords, kFusedLdsWordsBig, kFusedLdsWordsBigSmall, true, false, &p->ff);
+    make_fused_plan(T, N, C, HW, K, layout, p->eb, kFusedWords / 2, kFusedLdsWords / 2, kFusedLdsWordsBig / 2, kFusedLdsWordsBigSmall / 2, false, false, &p->fb);
+    make_fused_plan(T, N, C, HW, K, layout, p->eb, kFusedWords, kFusedLdsWords, kFusedLdsWordsBig, kFusedLdsWordsBigSmall, true, true, &p->ef);
+    make_fused_plan(T, N, C, HW, K, layout, p->eb, kFusedWords / 2, kFusedLdsWords / 2, kFusedLdsWordsBig / 2, kFusedLdsWordsBigSmall / 2, false, true, &p->ebw);
     // Tiny planes that would fill less than half of the register slots a single-launch variant reserves for a plane
     // run faster through the multi-sweep kernels for tiny planes (measured, 256 images, fwd / bwd us: fp32 7x7 x 1024
     // channels 46 / 58 against 132 / 105; bf16 14x14 x 1024 channels, forward, 85 against 126.  Half full, fp32
@@ -815,6 +886,13 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
     if (p->ff.ok && p->ff.rows > max_rows) max_rows = p->ff.rows;
     if (p->fb.ok && p->fb.rows > max_rows) max_rows = p->fb.rows;
     // the sync area comes first, so that the error word has the same offset in every workspace
+    for (FusedPlan* f : {&p->ef, &p->ebw})
+        if (f->rows > max_rows) f->ok = 0;                // (no more rows than the other paths have: the workspace stays as it is)
+    for (int i = 0; i < 4; ++i) {
+        const bool forward = i < 2, second = (i & 1) != 0;
+        const FusedPlan& f = forward ? p->ff : p->fb;
+        p->edges[i] = edges_pay(forward ? p->ef : p->ebw, f, fused_built(p->eb == 4, forward, second, f.LB, f.LPPC), HW * p->eb, S * p->eb, p->eb, forward, second);
+    }
     size_t sync = align256(((size_t)kSyncHeader + 4 * (size_t)C) * sizeof(unsigned));
     size_t part = align256((size_t)C * max_rows * sizeof(float));
     size_t sh = align256((size_t)K * C * sizeof(double));
@@ -1160,27 +1238,26 @@ cgbn_status launch_fused_kernel(KernelT kernel, const Tuning& T, const FusedPlan
     return launched();
 }
 
-// Which (bytes per access, slots per plane) variants exist for an element type, direction and activation: all of
-// the list header's, except that the float ReLU backward is not built with 4-byte accesses (one slot count
-// excepted; see CGBN_FUSED_RELU_BWD_F32_NARROW).  A shape whose variant is not built takes the multi-sweep kernels.
-template <typename T, bool FWD, int ACT> constexpr bool fused_built(int LB, int LPPC)
-{
-    if (std::is_same<T, float>::value && !FWD && ACT == 1 && LB == 4) {
-        bool built = false;
-#define CGBN_IS_BUILT(LB_, LPPC_) built = built || (LB == LB_ && LPPC == LPPC_);
-        CGBN_FUSED_RELU_BWD_F32_NARROW(CGBN_IS_BUILT)
-#undef CGBN_IS_BUILT
-        return built;
-    }
-    return true;
-}
-
 // ACT: 0 plain, 1 ReLU, 2 shortcut + ReLU (forward only)
 template <typename T, bool FWD, int ACT>
 cgbn_status launch_fused_t(const Tuning& knobs, const FusedPlan& f, FusedArgs& A, int sync_words, hipStream_t st, bool* taken,
                            double moved_bytes)
 {
     *taken = false;
+    if (f.edge) {
+#define CGBN_FUSED_CASEE(LPPC_, BIG_)                                                                        \
+        if (f.big == BIG_ && f.LPPC == LPPC_) {                                                              \
+            if constexpr (FWD) return launch_fused_kernel(nchw_fused_forward<T, 16, LPPC_, ACT, BIG_, true>, knobs, f, A, sync_words, st, taken, moved_bytes); \
+            else return launch_fused_kernel(nchw_fused_backward<T, 16, LPPC_, ACT, BIG_, true>, knobs, f, A, sync_words, st, taken, moved_bytes); \
+        }
+        if constexpr (FWD) {
+            CGBN_FUSED_EDGE_FORWARD(CGBN_FUSED_CASEE)
+        } else {
+            CGBN_FUSED_EDGE_BACKWARD(CGBN_FUSED_CASEE)
+        }
+#undef CGBN_FUSED_CASEE
+        return CGBN_OK;
+    }
     if (f.big && f.LB == 16 && f.LPPC == 0) {
         if constexpr (FWD) return launch_fused_kernel(nchw_fused_forward<T, 16, 0, ACT, 1>, knobs, f, A, sync_words, st, taken, moved_bytes);
         else return launch_fused_kernel(nchw_fused_backward<T, 16, 0, ACT, 1>, knobs, f, A, sync_words, st, taken, moved_bytes);
@@ -1201,7 +1278,7 @@ cgbn_status launch_fused_t(const Tuning& knobs, const FusedPlan& f, FusedArgs& A
     }
 #undef CGBN_FUSED_CASE1
 #define CGBN_FUSED_CASE2(LB_, LPPC_)                                                                         \
-    if constexpr (fused_built<T, FWD, ACT>(LB_, LPPC_))                                                      \
+    if constexpr (fused_built(std::is_same<T, float>::value, FWD, ACT, LB_, LPPC_))                                                      \
     if (f.big == 2 && f.LB == LB_ && f.LPPC == LPPC_) {                                                      \
         if constexpr (FWD) return launch_fused_kernel(nchw_fused_forward<T, LB_, LPPC_, ACT, 2>, knobs, f, A, sync_words, st, taken, moved_bytes); \
         else return launch_fused_kernel(nchw_fused_backward<T, LB_, LPPC_, ACT, 2>, knobs, f, A, sync_words, st, taken, moved_bytes); \
@@ -1209,7 +1286,7 @@ cgbn_status launch_fused_t(const Tuning& knobs, const FusedPlan& f, FusedArgs& A
     CGBN_FUSED_BIG_SMALL(CGBN_FUSED_CASE2)
 #undef CGBN_FUSED_CASE2
 #define CGBN_FUSED_CASE(LB_, LPPC_)                                                                          \
-    if constexpr (fused_built<T, FWD, ACT>(LB_, LPPC_))                                                      \
+    if constexpr (fused_built(std::is_same<T, float>::value, FWD, ACT, LB_, LPPC_))                                                      \
     if (f.LB == LB_ && f.LPPC == LPPC_) {                                                                    \
         if constexpr (FWD) return launch_fused_kernel(nchw_fused_forward<T, LB_, LPPC_, ACT, 0>, knobs, f, A, sync_words, st, taken, moved_bytes); \
         else return launch_fused_kernel(nchw_fused_backward<T, LB_, LPPC_, ACT, 0>, knobs, f, A, sync_words, st, taken, moved_bytes); \
@@ -1541,20 +1618,21 @@ cgbn_status forward_impl(const void* x, const void* shortcut, bool relu, int N, 
 
     const SlabPlan& wide = shortcut ? p.sfs : p.sf;
     const bool slab = p.t.fused && p.t.one_sweep_stats && wide.ok;
-    if (p.t.fused && p.ff.ok && !(slab && wide.first)) {
-        FusedArgs F = fused_args(p, p.ff, ws);
+    for (const FusedPlan* f : {&p.ef, &p.ff}) {
+        if (!p.t.fused || !f->ok || (f == &p.ef && !p.edges[shortcut != nullptr]) || (slab && wide.first)) continue;
+        FusedArgs F = fused_args(p, *f, ws);
         F.x = x; F.out = y; F.gamma = gamma; F.beta = beta; F.eps = (double)eps; F.aux = shortcut;
         F.mean = mean; F.mean_lo = mlo; F.mean_lo_user = mean_lo; F.invstd = invstd;
         bool taken = false;
         const int sync_words = kSyncHeader + 4 * p.C;
         const bool f32 = p.dtype == CGBN_F32;
         const double moved = (double)p.S * p.eb * (shortcut ? 3.0 : 2.0);
-        cgbn_status st_ = relu && shortcut ? (f32 ? launch_fused_t<float, true, 2>(p.t, p.ff, F, sync_words, st, &taken, moved)
-                                                  : launch_fused_t<bf16_t, true, 2>(p.t, p.ff, F, sync_words, st, &taken, moved))
-                        : relu ? (f32 ? launch_fused_t<float, true, 1>(p.t, p.ff, F, sync_words, st, &taken, moved)
-                                      : launch_fused_t<bf16_t, true, 1>(p.t, p.ff, F, sync_words, st, &taken, moved))
-                               : (f32 ? launch_fused_t<float, true, 0>(p.t, p.ff, F, sync_words, st, &taken, moved)
-                                      : launch_fused_t<bf16_t, true, 0>(p.t, p.ff, F, sync_words, st, &taken, moved));
+        cgbn_status st_ = relu && shortcut ? (f32 ? launch_fused_t<float, true, 2>(p.t, *f, F, sync_words, st, &taken, moved)
+                                                  : launch_fused_t<bf16_t, true, 2>(p.t, *f, F, sync_words, st, &taken, moved))
+                        : relu ? (f32 ? launch_fused_t<float, true, 1>(p.t, *f, F, sync_words, st, &taken, moved)
+                                      : launch_fused_t<bf16_t, true, 1>(p.t, *f, F, sync_words, st, &taken, moved))
+                               : (f32 ? launch_fused_t<float, true, 0>(p.t, *f, F, sync_words, st, &taken, moved)
+                                      : launch_fused_t<bf16_t, true, 0>(p.t, *f, F, sync_words, st, &taken, moved));
         g_last_forward_fused = taken;
         if (taken) g_last_forward_slab = 0;
         if (taken || st_ != CGBN_OK) return st_;
@@ -1627,8 +1705,9 @@ cgbn_status backward_impl(const void* dy, const void* y, const void* x, const fl
 
     const SlabPlan& wide = relu ? p.sbm : p.sb;
     const bool slab = p.t.fused && wide.ok;
-    if (p.t.fused && p.fb.ok && !(slab && wide.first)) {
-        FusedArgs F = fused_args(p, p.fb, ws);
+    for (const FusedPlan* f : {&p.ebw, &p.fb}) {
+        if (!p.t.fused || !f->ok || (f == &p.ebw && !p.edges[relu ? 3 : 2]) || (slab && wide.first)) continue;
+        FusedArgs F = fused_args(p, *f, ws);
         F.x = x; F.dy = dy; F.out = dx; F.gamma = gamma; F.aux = y; F.out2 = dshortcut;
         F.mean = const_cast<float*>(mean); F.mean_lo = const_cast<float*>(mean_lo);
         F.invstd = const_cast<float*>(invstd); F.dgamma = dgamma; F.dbeta = dbeta;
@@ -1636,10 +1715,10 @@ cgbn_status backward_impl(const void* dy, const void* y, const void* x, const fl
         const int sync_words = kSyncHeader + 4 * p.C;
         const bool f32 = p.dtype == CGBN_F32;
         const double moved = (double)p.S * p.eb * (3.0 + (relu ? 1.0 : 0.0) + (dshortcut ? 1.0 : 0.0));
-        cgbn_status st_ = relu ? (f32 ? launch_fused_t<float, false, 1>(p.t, p.fb, F, sync_words, st, &taken, moved)
-                                      : launch_fused_t<bf16_t, false, 1>(p.t, p.fb, F, sync_words, st, &taken, moved))
-                               : (f32 ? launch_fused_t<float, false, 0>(p.t, p.fb, F, sync_words, st, &taken, moved)
-                                      : launch_fused_t<bf16_t, false, 0>(p.t, p.fb, F, sync_words, st, &taken, moved));
+        cgbn_status st_ = relu ? (f32 ? launch_fused_t<float, false, 1>(p.t, *f, F, sync_words, st, &taken, moved)
+                                      : launch_fused_t<bf16_t, false, 1>(p.t, *f, F, sync_words, st, &taken, moved))
+                               : (f32 ? launch_fused_t<float, false, 0>(p.t, *f, F, sync_words, st, &taken, moved)
+                                      : launch_fused_t<bf16_t, false, 0>(p.t, *f, F, sync_words, st, &taken, moved));
         g_last_backward_fused = taken;
         if (taken) g_last_backward_slab = 0;
         if (taken || st_ != CGBN_OK) return st_;
@@ -1843,11 +1922,14 @@ long long cgbn_plan_get(int N, int C, int H, int W, cgbn_layout layout, cgbn_dty
 {
     Plan p;
     if (!key || make_plan(tuning_now(), N, C, H, W, (int)layout, (int)dtype, K, &p) != CGBN_OK) return -1;
-    const bool bwd = !std::strncmp(key, "bwd_", 4);
-    if (bwd || !std::strncmp(key, "fwd_", 4)) {
-        const FusedPlan& f = bwd ? p.fb : p.ff;
-        const char* k = key + 4;
+    const bool edge = !std::strncmp(key, "efwd_", 5) || !std::strncmp(key, "ebwd_", 5);
+    const bool bwd = !std::strncmp(key + edge, "bwd_", 4);
+    if (bwd || !std::strncmp(key + edge, "fwd_", 4)) {
+        const FusedPlan& f = edge ? (bwd ? p.ebw : p.ef) : (bwd ? p.fb : p.ff);
+        const char* k = key + edge + 4;
         if (!std::strcmp(k, "ok")) return f.ok;
+        if (edge && !std::strcmp(k, "taken")) return p.edges[bwd ? 2 : 0];
+        if (edge && !std::strcmp(k, "taken2")) return p.edges[bwd ? 3 : 1];
         if (!std::strcmp(k, "LB")) return f.LB;
         if (!std::strcmp(k, "LPPC")) return f.LPPC;
         if (!std::strcmp(k, "LPP")) return f.LPP;

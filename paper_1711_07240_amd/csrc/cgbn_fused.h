@@ -610,6 +610,7 @@ template <int N, int I = 0, class F> __device__ __forceinline__ void unroll_plan
 struct UnitGeom {
     long long base;   // byte offset in the tensor of the tile (large planes) or of the unit's first plane (small)
     int len;          // bytes in the tile (large planes) or in a plane (small)
+    int head, tail;   // EDGE: base and len are those of the whole 16-byte vectors in it; bytes before and after them
     int n0, n1;       // image range of the unit
     int c, u;
 };
@@ -617,7 +618,12 @@ struct UnitGeom {
 // LPPC == 0: large planes cut into tiles.  LPPC > 0: small planes, one per wavefront at a time, LPPC slots per
 // plane.  LPPC < 0: planes of up to half a tile, -LPPC of them (consecutive images) per workgroup, each in SPW
 // workgroup-wide slots.
-template <typename T, int LB, int LPPC, int R, int SPW = 1>
+//
+// EDGE: planes whose bytes are no multiple of 16, so that planes start anywhere.  The slots hold the 16-byte aligned vectors that lie
+// wholly inside a plane (a tile); the up to 14 bytes before and behind them, its edges, are taken value by value by 16
+// lanes: 8 for those before, 8 for those behind, in one further register for every four planes of a wavefront (small planes) or
+// for all planes of a workgroup.  No access reaches beyond its own plane, so results may be written over the inputs.
+template <typename T, int LB, int LPPC, int R, int SPW = 1, bool EDGE = false>
 struct Slots {
     static constexpr bool SMALL = LPPC > 0;
     static constexpr bool WGP = LPPC < 0;            // several whole planes per workgroup
@@ -637,7 +643,7 @@ struct Slots {
             g.n0 = g.u * ipu;
             g.n1 = min(A.N, g.n0 + ipu);
             g.base = (((long long)g.n0 * A.C + g.c) * A.HW) * (long long)sizeof(T);
-            g.len = A.HW * (int)sizeof(T);
+            g.len = A.HW * (int)sizeof(T);       // (EDGE: all planes of the channel start at the same byte of a vector; the host checks it)
         } else {
             int n = g.u / A.tp, j = g.u - n * A.tp;
             g.base = (((long long)n * A.C + g.c) * A.HW + (long long)j * A.TL) * (long long)sizeof(T);
@@ -645,6 +651,24 @@ struct Slots {
             g.n0 = n;
             g.n1 = n + 1;
         }
+        g.head = g.tail = 0;
+        if constexpr (EDGE) {
+            const int all = g.len;
+            g.head = min((int)(-g.base & 15), all);
+            g.base += g.head;
+            g.len = (all - g.head) & ~15;
+            g.tail = all - g.head - g.len;
+        }
+    }
+    // EDGE: whether thread t (small planes: of wavefront w, register k of PLANES planes a wavefront) holds a value of an edge, and its
+    // byte offset from the unit's base
+    template <int PLANES> static __device__ __forceinline__ bool edge(const FusedArgs& A, const UnitGeom& g, int k, int t, int w, long long& off)
+    {
+        const int l = SMALL ? t & (kWave - 1) : t, i = (l & 7) * (int)sizeof(T);
+        const int pl = SMALL ? 4 * k + (l >> 4) : l >> 4, n = SMALL ? w + 4 * pl : pl;
+        const bool behind = (l & 8) != 0;
+        off = (long long)((unsigned)n * (SMALL || WGP ? A.plane_stride : 0u)) + (behind ? g.len + i : i - g.head);
+        return i < (behind ? g.tail : g.head) && pl < PLANES && g.n0 + n < g.n1;
     }
     static __device__ __forceinline__ unsigned lane_offset(int t)
     {
@@ -662,6 +686,7 @@ struct Slots {
     // is any lane of slot s in use (uniform)
     static __device__ __forceinline__ bool in_use(const FusedArgs& A, const UnitGeom& g, int s, int w)
     {
+        if (SMALL && EDGE) return image(g, s, w) < g.n1 && (always_full(s) || slot_offset(s) < g.len);
         if (SMALL) return image(g, s, w) < g.n1 && (always_full(s) || (s % SPP) < A.LPP);
         if (WGP) return g.n0 + s / SPW < g.n1 && (s % SPW) * (kThreads * LB) < g.len;
         return s * (kThreads * LB) < g.len;
@@ -702,9 +727,10 @@ struct Slots {
 // ---------------------------------------------------------------------------
 // ACT == 1: y = max(0, step 11).  ACT == 2: y = max(0, step 11 + shortcut), the shortcut
 // (A.aux) being read a few slots at a time while the unit is written out.
-template <typename T, int LB, int LPPC, int ACT, int BIG>
+template <typename T, int LB, int LPPC, int ACT, int BIG, bool EDGE = false>
 __global__ __launch_bounds__(kThreads, 3) void nchw_fused_forward(FusedArgs A)
 {
+    static_assert(!EDGE || LB == 16, "planes with edges: 16-byte loads");
     static_assert(BIG == 0 || (BIG == 1 && LPPC <= 0 && LB == 16) || (BIG == 2 && LPPC > 0),
                   "BIG 1: large planes with 16-byte loads; BIG 2: small planes");
     constexpr int W = LB / 4, EPW = Packed<T>::EPW;
@@ -720,8 +746,10 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_forward(FusedArgs A)
                      : SMALL ? (BIG == 2 ? (kFusedLdsWordsBigSmall / W / LPPC) * LPPC : 0)
                              : (LB == 16 ? (BIG ? kFusedLdsWordsBig : kFusedLdsWords) / W : 0);
     constexpr int RT = RS + RL;
-    using SL = Slots<T, LB, LPPC, R, WGP ? RT / (WGP ? -LPPC : 1) : 1>;
+    using SL = Slots<T, LB, LPPC, R, WGP ? RT / (WGP ? -LPPC : 1) : 1, EDGE>;
     constexpr int SPW = WGP ? RT / SL::PPU : 1;
+    constexpr int PLANES = SMALL ? RT / SL::SPP : SL::PPU;                   // planes of a wavefront (small planes) or a workgroup
+    constexpr int NE = !EDGE ? 0 : SMALL ? (PLANES + 3) / 4 : 1;             // registers with values of their edges
     __shared__ ReduceLdsT<BIG> lds;
     __shared__ float s_red[4 * SL::PPU], s_sq[4 * SL::PPU];
     const int t = threadIdx.x, lane = t & (kWave - 1), w = uniform(t >> 6);
@@ -745,6 +773,9 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_forward(FusedArgs A)
         const float pivot = uniform_f(Elem<T>::load1(x + (long long)c * A.HW));
         CGBN_STAMP(0);
 
+        float ev[EDGE ? NE : 1];
+        bool eok[EDGE ? NE : 1];
+
         // ---- read the unit once ------------------------------------------
         // (issuing a unit's loads and stores comes before the arithmetic of the other wavefronts on the SIMD:
         // measured, forward of 256x2048x25x42 fp32 950 -> 932 us, of 16x64x400x672 448 -> 441)
@@ -762,6 +793,13 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_forward(FusedArgs A)
                     else LdsSlot<LB>::fill(src, xu + SL::wave_base(A, s, w), SL::wave_valid(g, s, w), ext, s - RS, w, lane);
                 }
             }
+#pragma unroll
+            for (int k = 0; k < NE; ++k) {
+                long long off;
+                eok[k] = SL::template edge<PLANES>(A, g, k, t, w, off);
+                ev[k] = 0.f;
+                if (eok[k]) ev[k] = Elem<T>::load1(reinterpret_cast<const T*>(xu + off));
+            }
             wait_vector_memory();    // registers and LDS slots have landed, and the compiler knows it
         }
         __builtin_amdgcn_s_setprio(0);
@@ -771,11 +809,16 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_forward(FusedArgs A)
         // turn them into Algorithm 1's sums about the pooled mean (reduce_forward)
         {
             const unsigned loff = SL::lane_offset(t);
-            // one pass over the slots [s0, s1): the elements' sum of (x - centre), or of its square
-            auto pass = [&](auto s0_, auto s1_, float centre, auto square_) __attribute__((always_inline)) -> float {
+            // one pass over the slots [s0, s1) of plane `pl`: the elements' sum of (x - centre), or of its square
+            auto pass = [&](auto pl_, auto s0_, auto s1_, float centre, auto square_) __attribute__((always_inline)) -> float {
                 constexpr int s0 = decltype(s0_)::value, s1 = decltype(s1_)::value;
                 constexpr bool square = decltype(square_)::value;
                 float acc[4] = {0.f, 0.f, 0.f, 0.f};
+                if constexpr (EDGE) {
+                    constexpr int pl = decltype(pl_)::value, k = SMALL ? pl / 4 : 0, quarter = SMALL ? pl % 4 : pl;
+                    const float dv = ev[k] - centre;
+                    if (eok[k] && (SMALL ? lane : t) >> 4 == quarter) acc[0] = square ? dv * dv : dv;
+                }
 #pragma unroll
                 for (int s = s0; s < s1; ++s) {
                     if (s < RS && SL::always_full(s)) {
@@ -814,9 +857,9 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_forward(FusedArgs A)
                     constexpr int pl = decltype(pl_)::value, s0 = pl * SL::SPP;
                     const int n = SL::image(g, s0, w);
                     if (n < g.n1) {
-                        const float tot = pass(IntC<s0>{}, IntC<s0 + SL::SPP>{}, pivot, BoolC<false>{});
+                        const float tot = pass(IntC<pl>{}, IntC<s0>{}, IntC<s0 + SL::SPP>{}, pivot, BoolC<false>{});
                         const float ctr = row_centre(pivot, tot, (float)A.HW);
-                        const float sq = pass(IntC<s0>{}, IntC<s0 + SL::SPP>{}, ctr, BoolC<true>{});
+                        const float sq = pass(IntC<pl>{}, IntC<s0>{}, IntC<s0 + SL::SPP>{}, ctr, BoolC<true>{});
                         if (lane == 0) {
                             if (solo) {
                                 lds.rows[0][n] = tot;
@@ -836,13 +879,13 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_forward(FusedArgs A)
                     constexpr int s0 = WGP ? pl * SPW : 0, s1 = WGP ? (pl + 1) * SPW : RT;
                     const int row = WGP ? g.n0 + pl : g.u;
                     const bool live = !WGP || g.n0 + pl < g.n1;
-                    const float part = pass(IntC<s0>{}, IntC<s1>{}, pivot, BoolC<false>{});
+                    const float part = pass(IntC<pl>{}, IntC<s0>{}, IntC<s1>{}, pivot, BoolC<false>{});
                     if (lane == 0) s_red[4 * pl + w] = part;
                     __syncthreads();
                     const float tot = (s_red[4 * pl] + s_red[4 * pl + 1]) + (s_red[4 * pl + 2] + s_red[4 * pl + 3]);
-                    const float count = (float)(WGP ? A.HW : g.len / (int)sizeof(T));
+                    const float count = (float)(WGP ? A.HW : (g.head + g.len + g.tail) / (int)sizeof(T));
                     const float ctr = row_centre(pivot, tot, count);
-                    const float part2 = pass(IntC<s0>{}, IntC<s1>{}, ctr, BoolC<true>{});
+                    const float part2 = pass(IntC<pl>{}, IntC<s0>{}, IntC<s1>{}, ctr, BoolC<true>{});
                     if (lane == 0) s_sq[4 * pl + w] = part2;
                     __syncthreads();
                     if (t == 0 && live) {
@@ -904,6 +947,13 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_forward(FusedArgs A)
             // the folded constant is beta plus a small correction; x - mu itself is formed as before.
             const float gsc = A.gamma[c] * istd, bsh = A.beta[c] - (A.gamma[c] * istd) * mulo;     // (as scalars: measured 25 % slower here)
             const char* ru = static_cast<const char*>(A.aux) + g.base;
+            float er[EDGE ? NE : 1];
+#pragma unroll
+            for (int k = 0; k < NE; ++k) {
+                long long off;
+                er[k] = 0.f;
+                if (SL::template edge<PLANES>(A, g, k, (int)fresh(t), w, off)) er[k] = Elem<T>::load1(reinterpret_cast<const T*>(ru + off));
+            }
 #pragma unroll
             for (int s0 = 0; s0 < RT; s0 += kBatch) {
                 uint32_t rw[kBatch][W];
@@ -937,6 +987,16 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_forward(FusedArgs A)
                             o[q] = Packed<T>::pack(f);
                         }
                         Words<LB>::store(yu + SL::plane_base(A, s, w) + SL::slot_offset(s) + loff, o, A.nt);
+                    }
+                }
+                if (s0 == 0) {
+#pragma unroll
+                    for (int k = 0; k < NE; ++k) {
+                        long long off;
+                        if (SL::template edge<PLANES>(A, g, k, (int)fresh(t), w, off)) {
+                            const float z = ((ev[k] - mu) * gsc + bsh) + er[k];
+                            Elem<T>::store1(reinterpret_cast<T*>(yu + off), z < 0.f ? 0.f : z);
+                        }
                     }
                 }
             }
@@ -977,6 +1037,15 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_forward(FusedArgs A)
                     Words<LB>::store(yu + SL::plane_base(A, s, w) + SL::slot_offset(s) + loff, o, A.nt);
                 }
             }
+#pragma unroll
+            for (int k = 0; k < NE; ++k) {
+                long long off;
+                if (SL::template edge<PLANES>(A, g, k, (int)fresh(t), w, off)) {
+                    float z = (ev[k] - mu) * gsc + bsh;
+                    if (ACT != 0) z = z < 0.f ? 0.f : z;
+                    Elem<T>::store1(reinterpret_cast<T*>(yu + off), z);
+                }
+            }
         }
         CGBN_STAMP(7);
     }
@@ -988,9 +1057,10 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_forward(FusedArgs A)
 // ACT != 0: dy is first masked by the stored output (A.aux) being positive.  The output's
 // slots pass through the storage that x takes afterwards, so the unit costs one more round
 // of loads but no more registers; the masked dy also goes to A.out2 if that is not null.
-template <typename T, int LB, int LPPC, int ACT, int BIG>
+template <typename T, int LB, int LPPC, int ACT, int BIG, bool EDGE = false>
 __global__ __launch_bounds__(kThreads, 3) void nchw_fused_backward(FusedArgs A)
 {
+    static_assert(!EDGE || LB == 16, "planes with edges: 16-byte loads");
     static_assert(BIG == 0 || (BIG == 1 && LPPC <= 0 && LB == 16) || (BIG == 2 && LPPC > 0),
                   "BIG 1: large planes with 16-byte loads; BIG 2: small planes");
     constexpr int W = LB / 4, EPW = Packed<T>::EPW;
@@ -1004,8 +1074,10 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_backward(FusedArgs A)
                      : SMALL ? (BIG == 2 ? (kFusedLdsWordsBigSmall / 2 / W / LPPC) * LPPC : 0)
                              : (LB == 16 ? (BIG ? kFusedLdsWordsBig : kFusedLdsWords) / 2 / W : 0);   // ... and in LDS
     constexpr int RT = RS + RL;
-    using SL = Slots<T, LB, LPPC, R, WGP ? RT / (WGP ? -LPPC : 1) : 1>;
+    using SL = Slots<T, LB, LPPC, R, WGP ? RT / (WGP ? -LPPC : 1) : 1, EDGE>;
     constexpr int SPW = WGP ? RT / SL::PPU : 1;
+    constexpr int PLANES = SMALL ? RT / SL::SPP : SL::PPU;                   // planes of a wavefront (small planes) or a workgroup
+    constexpr int NE = !EDGE ? 0 : SMALL ? (PLANES + 3) / 4 : 1;             // registers with values of their edges
     __shared__ ReduceLdsT<BIG> lds;
     __shared__ float s_red[8 * SL::PPU];
     const int t = threadIdx.x, lane = t & (kWave - 1), w = uniform(t >> 6);
@@ -1037,6 +1109,22 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_backward(FusedArgs A)
         if (SMALL) gam = load_scalar(A.gamma, c);
         CGBN_STAMP(0);
         __builtin_amdgcn_s_setprio(kMemPrio);       // (as in the forward)
+        float ex[EDGE ? NE : 1], eg[EDGE ? NE : 1];
+        bool eok[EDGE ? NE : 1];
+        // the edges' values of two tensors (no thread's: zeros)
+        auto edges = [&](const char* gp, const char* xp) __attribute__((always_inline)) {
+#pragma unroll
+            for (int k = 0; k < NE; ++k) {
+                long long off;
+                eok[k] = SL::template edge<PLANES>(A, g, k, t, w, off);
+                if (gp) eg[k] = 0.f;
+                ex[k] = 0.f;
+                if (eok[k]) {
+                    if (gp) eg[k] = Elem<T>::load1(reinterpret_cast<const T*>(gp + off));
+                    ex[k] = Elem<T>::load1(reinterpret_cast<const T*>(xp + off));
+                }
+            }
+        };
 
         if (ACT != 0) {
             // round one: dy and the stored output y; mask dy; round two: x over y's storage
@@ -1057,7 +1145,10 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_backward(FusedArgs A)
                     }
                 }
             }
+            edges(gu, yu);
             wait_vector_memory();
+#pragma unroll
+            for (int k = 0; k < NE; ++k) eg[k] = ex[k] > 0.f ? eg[k] : 0.f;
 #pragma unroll
             for (int s = 0; s < RT; ++s) {
                 if (SL::beyond(g, s, w)) break;
@@ -1087,6 +1178,7 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_backward(FusedArgs A)
                     else LdsSlot<LB>::fill(xu + o, xu + SL::wave_base(A, s, w), SL::wave_valid(g, s, w), ext, RL + s - RS, w, lane);
                 }
             }
+            edges(nullptr, xu);
             wait_vector_memory();
         } else {
             const unsigned loff = SL::lane_offset(t);
@@ -1105,6 +1197,7 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_backward(FusedArgs A)
                     }
                 }
             }
+            edges(gu, xu);
             wait_vector_memory();    // registers and LDS slots have landed, and the compiler knows it
         }
         // ---- device sums of dy and dy*xhat ---------------------------------
@@ -1112,6 +1205,14 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_backward(FusedArgs A)
         {
             const unsigned loff = SL::lane_offset(t);
             float a[2] = {0.f, 0.f}, b[2] = {0.f, 0.f};
+            // the edges of plane `pl` into the running sums
+            auto add_edges = [&](int pl) __attribute__((always_inline)) {
+                const int k = SMALL ? pl / 4 : 0;
+                if (eok[k] && (SMALL ? lane : t) >> 4 == (SMALL ? pl % 4 : pl)) {
+                    a[0] += eg[k];
+                    b[0] += eg[k] * (ex[k] - mu);
+                }
+            };
 #pragma unroll
             for (int s = 0; s < RT; ++s) {
                 if (SL::beyond(g, s, w)) break;
@@ -1139,6 +1240,7 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_backward(FusedArgs A)
                 if (SL::ends_plane(s)) {
                     int n = SL::image(g, s, w);
                     if (n < g.n1) {
+                        if constexpr (EDGE) add_edges(s / SL::SPP);
                         float ta = wave_sum(a[0] + a[1]), tb = row_dy_xhat(wave_sum(b[0] + b[1]), ta, mulo, istd);
                         if (lane == 0) {
                             if (solo) {
@@ -1154,6 +1256,7 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_backward(FusedArgs A)
                 }
                 if (SL::ends_wg_plane(s)) {                 // a workgroup-wide plane is complete: its rows
                     const int pl = s / SPW, n = g.n0 + pl;
+                    if constexpr (EDGE) add_edges(pl);
                     float ta = wave_sum(a[0] + a[1]), tb = wave_sum(b[0] + b[1]);
                     if (lane == 0) { s_red[8 * pl + w] = ta; s_red[8 * pl + 4 + w] = tb; }
                     __syncthreads();
@@ -1173,6 +1276,7 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_backward(FusedArgs A)
                 }
             }
             if (!SMALL && !WGP) {
+                if constexpr (EDGE) add_edges(0);
                 float ta = wave_sum(a[0] + a[1]), tb = wave_sum(b[0] + b[1]);
                 if (lane == 0) { s_red[w] = ta; s_red[4 + w] = tb; }
                 __syncthreads();
@@ -1242,6 +1346,14 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_backward(FusedArgs A)
                     if (ACT != 0 && A.out2 != nullptr)
                         Words<LB>::store(static_cast<char*>(A.out2) + g.base + SL::plane_base(A, s, w) + SL::slot_offset(s) + loff,
                                          wg, A.nt);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < NE; ++k) {
+                long long off;
+                if (SL::template edge<PLANES>(A, g, k, (int)fresh(t), w, off)) {
+                    Elem<T>::store1(reinterpret_cast<T*>(ou + off), nk2 * (ex[k] - mu) + (gsc * eg[k] + k0));
+                    if (ACT != 0 && A.out2 != nullptr) Elem<T>::store1(reinterpret_cast<T*>(static_cast<char*>(A.out2) + g.base + off), eg[k]);
                 }
             }
         }

@@ -16,7 +16,11 @@ CGBN_FUSED_WGP_FORWARD(CGBN_X1)
 #undef CGBN_X1
 #define CGBN_X2(LB_, LPPC_) template __global__ void nchw_fused_forward<CGBN_INST_T, LB_, LPPC_, CGBN_INST_ACT, 2>(FusedArgs);
 CGBN_FUSED_BIG_SMALL(CGBN_X2)
+#define CGBN_XE(LPPC_, BIG_) template __global__ void nchw_fused_forward<CGBN_INST_T, 16, LPPC_, CGBN_INST_ACT, BIG_, true>(FusedArgs);
+CGBN_FUSED_EDGE_FORWARD(CGBN_XE)
 #else
+#define CGBN_XE(LPPC_, BIG_) template __global__ void nchw_fused_backward<CGBN_INST_T, 16, LPPC_, CGBN_INST_ACT, BIG_, true>(FusedArgs);
+CGBN_FUSED_EDGE_BACKWARD(CGBN_XE)
 #define CGBN_X(LB_, LPPC_) template __global__ void nchw_fused_backward<CGBN_INST_T, LB_, LPPC_, CGBN_INST_ACT, 0>(FusedArgs);
 #define CGBN_X2(LB_, LPPC_) template __global__ void nchw_fused_backward<CGBN_INST_T, LB_, LPPC_, CGBN_INST_ACT, 2>(FusedArgs);
 template __global__ void nchw_fused_backward<CGBN_INST_T, 16, 0, CGBN_INST_ACT, 1>(FusedArgs);     // big-LDS variants
@@ -38,4 +42,5 @@ CGBN_FUSED_BIG_SMALL(CGBN_X2)
 #endif
 #undef CGBN_X
 #undef CGBN_X2
+#undef CGBN_XE
 }  // namespace cgbn

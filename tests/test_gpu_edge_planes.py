@@ -1,0 +1,170 @@
+"""The single-launch NCHW kernels with 16-byte loads on planes that are no multiple of 16 bytes: every count of slots a plane, tiles and planes
+that share a workgroup, both element types, planes that start at every byte a plane can start at, with and without a second tensor, and results
+written over the inputs.  The plan says whether a call takes them; results against the float64 oracles, with the tolerances stated in gpu_harness.py."""
+
+import os
+import re
+
+import numpy as np
+import pytest
+import torch
+
+import gpu_harness as G
+from oracle import cgbn_oracle as O
+from oracle import cgbn_relu_oracle as R
+from paper_1711_07240_amd import cgbn as L
+from paper_1711_07240_amd import synth
+
+# N, C, H, W, dtype, K
+CASES = [
+    # a plane a wavefront: 2 to 38 slots, one to many planes a wavefront, further planes in LDS (N just beyond the registers' share)
+    (2, 128, 23, 23, "bf16", 2), (5, 48, 25, 43, "bf16", 5), (3, 64, 41, 45, "bf16", 1), (41, 48, 35, 37, "bf16", 1), (33, 64, 37, 55, "bf16", 3),
+    (17, 48, 37, 53, "bf16", 17), (25, 48, 47, 53, "bf16", 5), (2, 64, 53, 57, "bf16", 2), (4, 48, 61, 65, "bf16", 4), (5, 56, 71, 71, "bf16", 1),
+    (3, 48, 77, 79, "bf16", 3), (2, 64, 87, 89, "bf16", 1), (2, 48, 99, 119, "bf16", 2), (3, 48, 121, 131, "bf16", 1), (2, 48, 125, 151, "bf16", 2),
+    (3, 48, 67, 67, "f32", 3), (9, 48, 33, 33, "f32", 3), (25, 48, 35, 35, "f32", 5), (3, 56, 47, 49, "f32", 1), (2, 48, 51, 57, "f32", 2),
+    (4, 48, 53, 75, "f32", 2), (2, 48, 71, 85, "f32", 1), (2, 48, 89, 91, "f32", 2), (2, 48, 91, 103, "f32", 1), (33, 48, 23, 27, "f32", 3),
+    (65, 48, 29, 27, "f32", 5),
+    # planes that share a workgroup: four, three, two; not a whole number of them
+    (6, 64, 141, 145, "bf16", 3), (7, 48, 101, 199, "bf16", 7), (5, 64, 73, 137, "bf16", 5), (6, 96, 100, 127, "bf16", 2), (4, 64, 99, 101, "f32", 2),
+    (3, 64, 101, 115, "f32", 1), (2, 64, 131, 133, "f32", 2), (5, 64, 71, 73, "f32", 5), (5, 64, 77, 79, "f32", 1), (9, 64, 85, 85, "f32", 3),
+    (16, 96, 131, 131, "f32", 4),
+    # tiles: the last one shorter, a few values long; channels that are no whole vectors together
+    (2, 128, 251, 241, "bf16", 2), (1, 130, 301, 303, "bf16", 1), (4, 65, 205, 201, "f32", 2), (2, 129, 149, 151, "f32", 1), (1, 131, 185, 249, "f32", 1),
+    (2, 256, 1, 45061, "f32", 1), (8, 72, 201, 219, "f32", 8),
+]
+ID = lambda c: "%dx%dx%dx%d-%s-k%d" % c
+DIRECTIONS = {"fwd": "efwd_taken", "fwds": "efwd_taken2", "bwd": "ebwd_taken", "bwdm": "ebwd_taken2"}
+
+
+def _variant(case, d):
+    """(slots per plane, LDS split) of the kernel a call takes, None if it takes another."""
+    g = lambda k: L.cgbn_plan_get(*case[:4], "NCHW", *case[4:], k)
+    if not g(DIRECTIONS[d]) or (g("s%s_ok" % d) and g("s%s_first" % d)):
+        return None
+    return g("e%s_LPPC" % d[:3]), g("e%s_big" % d[:3])
+
+
+def _built():
+    text = open(os.path.join(os.path.dirname(L.__file__), "csrc", "cgbn_fused_list.h")).read().replace("\\\n", " ")
+    bodies = dict(re.findall(r"#define CGBN_FUSED_EDGE_(\w+)\(X\)(.*)", text))
+    pairs = lambda name: {(int(a), int(b)) for a, b in re.findall(r"X\((-?\d+), (\d)\)", bodies[name])}
+    return {d: pairs("COMMON") | pairs("FORWARD" if d[0] == "f" else "BACKWARD") for d in DIRECTIONS}
+
+
+def test_every_layout_of_a_plane_is_run():
+    """Each variant of a direction with one tensor less; with the ordinary LDS split large planes run again below."""
+    run = {d: {_variant(case, d) for case in CASES} - {None} for d in DIRECTIONS}
+    for d in ("fwd", "bwd"):
+        assert run[d] | {(0, 0), (-2, 0)} == _built()[d], (d, _built()[d] ^ run[d])
+    assert {(0, 1), (-2, 1), (4, 0), (4, 2)} <= run["fwds"] and {(0, 1), (-2, 1), (-3, 1), (3, 0), (3, 2), (16, 0)} <= run["bwdm"]
+
+
+def _inputs(case):
+    N, C, H, W, dtype, K = case
+    r = np.random.default_rng(N * 1000 + C + H)
+    per = lambda a: a.reshape(1, -1, 1, 1)
+    x = (r.standard_normal((N, C, H, W), dtype=np.float32) * per(r.uniform(0.5, 2, C)) + per(r.uniform(-2, 2, C))).astype(np.float32)
+    dy, s = (r.standard_normal(x.shape, dtype=np.float32) for _ in range(2))
+    if dtype == "bf16":
+        x, dy, s = (synth.f32_to_bf16_bits(a) for a in (x, dy, s))
+    return x, dy, s, r.uniform(0.5, 1.5, C).astype(np.float32), r.normal(0, 0.1, C).astype(np.float32)
+
+
+def _run(case):
+    N, C, H, W, dtype, K = case
+    print("[case] planes with edges", case, flush=True)
+    x, dy, s, gamma, beta = _inputs(case)
+    p = G.Problem(x, dy, gamma, beta, 1e-5, "NCHW", dtype, K)
+    error = L.cgbn_workspace_error_offset(N, C, H, W, "NCHW", dtype, K)
+
+    def took(*directions):
+        torch.cuda.synchronize()
+        assert int(p.ws[error:error + 4].view(torch.int32).item()) == 0
+        for d in directions:
+            assert not _variant(case, d) or L.cgbn_get_tuning("last_%s_fused" % ("forward" if d[0] == "f" else "backward")) == 1, d
+
+    p.forward()
+    p.backward()
+    took("fwd", "bwd")
+    wx, wdy = G.widen(x, dtype), G.widen(dy, dtype)
+    scale = np.sqrt(N * H * W) * G.rms(wdy)           # a channel's sums of gradients: judged on the size they have when nothing cancels
+    plain = p.results()
+    G.check_against_oracle(plain, O.cgbn_forward_backward_ref(wx, wdy, gamma, beta, 1e-5, "NCHW"), dtype, str(case), sum_scale=scale)
+    sd, dz = G.to_dev(s), torch.empty_like(p.x)
+    L.cgbn_forward_relu(p.x, sd, *p.shape_args, "NCHW", K, p.gamma, p.beta, 1e-5, p.y, p.mean, p.invstd, dtype, p.mean_lo, p.ws)
+    L.cgbn_backward_relu(p.dy, p.y, p.x, p.mean, p.invstd, p.gamma, p.dx, dz, p.dgamma, p.dbeta, *p.shape_args, "NCHW", K, dtype, p.mean_lo, p.ws)
+    took("fwds", "bwdm")
+    got = p.results()
+    y, mean, invstd = R.cgbn_relu_forward_ref(wx, gamma, beta, 1e-5, "NCHW", G.widen(s, dtype))[:3]
+    dx, dgamma, dbeta, dzr = R.cgbn_relu_backward_ref(wdy, got["y"], wx, mean, invstd, gamma, "NCHW")[:4]      # (masked by the stored output)
+    G.check_against_oracle(got, dict(y=y, mean=mean, invstd=invstd, dx=dx, dgamma=dgamma, dbeta=dbeta), dtype, str(case), sum_scale=scale)
+    assert np.array_equal(G.to_host_f64(dz, dtype), dzr)
+    # y over the shortcut, dx over the output it is masked by: the same bits
+    kept = p.y.clone()
+    L.cgbn_forward_relu(p.x, sd, *p.shape_args, "NCHW", K, p.gamma, p.beta, 1e-5, sd, p.mean, p.invstd, dtype, p.mean_lo, p.ws)
+    L.cgbn_backward_relu(p.dy, kept, p.x, p.mean, p.invstd, p.gamma, kept, dz, p.dgamma, p.dbeta, *p.shape_args, "NCHW", K, dtype, p.mean_lo, p.ws)
+    torch.cuda.synchronize()
+    assert torch.equal(sd, p.y) and torch.equal(kept, p.dx)
+    # dx over dy, y over x
+    p.forward()
+    p.backward(dx=p.dy)
+    p.forward(y=p.x)
+    torch.cuda.synchronize()
+    assert np.array_equal(G.to_host_f64(p.dy, dtype), plain["dx"]) and np.array_equal(G.to_host_f64(p.x, dtype), plain["y"])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", CASES, ids=ID)
+def test_against_the_oracle(case):
+    _run(case)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [(6, 64, 141, 145, "bf16", 3), (2, 64, 131, 133, "f32", 2), (2, 128, 251, 241, "bf16", 2), (4, 65, 205, 201, "f32", 2)], ids=ID)
+def test_with_the_ordinary_lds_split(case):
+    L.cgbn_set_tuning("big_lds", 0)
+    try:
+        _run(case)
+    finally:
+        L.cgbn_set_tuning("big_lds", 1)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_the_plan_holds_every_plane(dtype):
+    """Slots hold the whole vectors of a plane wherever it starts, the slots read without a look are full, rows fit what the workspace has, and the calls
+    taken are no multiple of 16 bytes."""
+    r = np.random.default_rng(3)
+    eb, taken = (4 if dtype == "f32" else 2), 0
+    for _ in range(4000):
+        N, C = int(r.integers(1, 200)), int(r.choice([8, 16, 24, 48, 64, 100, 256, 1024, 1027]))
+        H, W = int(np.exp(r.uniform(2.5, 6))), int(np.exp(r.uniform(2.5, 6)))
+        K = int(r.choice([k for k in range(1, N + 1) if N % k == 0]))
+        shape = (N, C, H, W, "NCHW", dtype, K)
+        plane = H * W * eb
+        for d, words in (("efwd", 128), ("ebwd", 64)):
+            g = lambda k: L.cgbn_plan_get(*shape, d + "_" + k)
+            if not g("ok"):
+                assert not g("taken") and not g("taken2")
+                continue
+            assert plane % 16 != 0 and plane > 1024 and g("LB") == 16
+            taken += g("taken") + g("taken2")
+            lppc, big, regs = g("LPPC"), g("big"), words // 4
+            lds = {0: 24, 1: 48, 2: 44}[big] * words // 128 // 4
+            assert g("rows") * C * 4 <= L.cgbn_plan_get(*shape, "part_bytes")
+            if lppc:
+                assert C * plane % 16 == 0                               # a channel's planes start at the same byte of a vector
+            # whole vectors in a plane, by where it starts; 16 k of it more than those need not be there
+            most = max((plane - h) // 16 for h in range(0, 16, eb))
+            least = min((plane - h) // 16 for h in range(0, 16, eb))
+            if lppc > 0:
+                full = 0 if lppc <= 2 else max(c for c in (2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32) if c < lppc)
+                full = regs if lppc > regs else full if full * 16 >= regs else 0
+                assert full * 64 <= least and most <= lppc * 64
+                per_wave = 1 if lppc > regs else regs // lppc + (lds // lppc if big == 2 else 0)
+                assert g("IPU") <= 4 * per_wave and g("U") * g("IPU") >= N > (g("U") - 1) * g("IPU")
+                assert lppc <= regs + (lds if lppc > regs else 0)
+            elif lppc < 0:
+                assert most <= (regs + lds) // -lppc * 256 and g("U") == -(-N // -lppc)
+            else:
+                assert g("TL") * eb <= (regs + lds) * 4096 and g("tp") * g("TL") >= H * W > (g("tp") - 1) * g("TL") and g("U") == N * g("tp")
+    assert taken > 1500
