@@ -80,7 +80,7 @@ struct SlabArgs {
 // LDS of a workgroup
 struct SlabLds {
     float part[2][kSlabPartWords];                       // see slab_sum
-    float piv[kSlabMaxChannels], ctr[kSlabMaxChannels];  // forward: pivot, and how far the unit's mean lies from it
+    float piv[kSlabMaxChannels];                         // forward: pivots
     float res[3][kSlabMaxChannels];                      // several units: the channels' results (forward mean, its rest, 1/sqrt; backward dbeta, dgamma)
     float k0[kSlabMaxChannels], k1[kSlabMaxChannels], k2[kSlabMaxChannels], k3[kSlabMaxChannels];   // write-out constants
     int skip, last, fix, wait;  // this unit moves on (2: results are missing for good); it completed the count; there are units for it to finish; the count is complete, the results are not there yet
@@ -132,9 +132,13 @@ template <class F> __device__ __forceinline__ void lanes_add(int lanes, F f)
 // differ in column and row) nor the loads (in channel and row) meet in a bank.  (Folding the row lanes of a wavefront first, in
 // float, left the mean of 2100 x 2048 bf16 1.1e-7 standard deviations off, now 7e-10, and took longer:
 // backward of 2100 x 512 9.6 us, now 8.9; forward 9.4, now 8.7.)
-template <int VEC, int Q, class LDS>
-__device__ __forceinline__ void slab_sum(const SlabArgs& A, LDS& L, float (&v)[Q][VEC], int col, int r, double (&out)[Q])
+// `add(i, x, out)`: adds the Q values x that row lane i left for a column.
+template <int VEC, int Q, class LDS, class F>
+__device__ __forceinline__ void slab_sum(const SlabArgs& A, LDS& L, float (&v)[Q][VEC], int col, int r, double (&out)[2], F add)
 {
+    constexpr int qs = VEC * (kSlabPartWords / 8);        // words between a thread's quantities
+    static_assert(Q * qs <= 2 * kSlabPartWords, "they fit");
+    float* part = L.part[0];
     const int t = (int)fresh(threadIdx.x);
     const int rs = A.rpp + 8, es = A.cols * rs + 8;       // one column a channel: words between columns, between a thread's values
     if (r < A.rpp) {
@@ -142,36 +146,38 @@ __device__ __forceinline__ void slab_sum(const SlabArgs& A, LDS& L, float (&v)[Q
 #pragma unroll
             for (int q = 0; q < Q; ++q)
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) L.part[q][e * es + col * rs + r] = v[q][e];
+                for (int e = 0; e < VEC; ++e) part[q * qs + e * es + col * rs + r] = v[q][e];
         } else {
 #pragma unroll
             for (int q = 0; q < Q; ++q)
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) L.part[q][r * A.ncols + col * VEC + e] = v[q][e];
+                for (int e = 0; e < VEC; ++e) part[q * qs + r * A.ncols + col * VEC + e] = v[q][e];
         }
     }
     __syncthreads();
     const int ch = t / A.tpc, sub = t & (A.tpc - 1);
+    out[0] = out[1] = 0.0;
+    auto take = [&](int i, int w) __attribute__((always_inline)) {
+        float x[Q];
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        double& acc = out[q];
-        acc = 0.0;
-        if (ch * A.cpc < A.ncols) {               // (channels beyond the slab's columns hold zeros)
-            if (A.cpc == 1) {
-                const float* p = L.part[q] + (ch % VEC) * es + (ch / VEC) * rs;
-                for (int i = sub; i < A.rpp; i += A.tpc) acc += (double)p[i];
-            } else {
-                // the channel's cpc columns of every row lane, dealt to its threads
-                for (int k = sub; k < A.rpp * A.cpc; k += A.tpc) {
-                    const int i = (int)__umulhi((unsigned)k, A.cpc_magic), j = k - i * A.cpc;
-                    acc += (double)L.part[q][i * A.ncols + ch * A.cpc + j];
-                }
+        for (int q = 0; q < Q; ++q) x[q] = part[q * qs + w];
+        add(i, x, out);
+    };
+    if (ch * A.cpc < A.ncols) {                   // (channels beyond the slab's columns hold zeros)
+        if (A.cpc == 1) {
+            const int w0 = (ch % VEC) * es + (ch / VEC) * rs;
+            for (int i = sub; i < A.rpp; i += A.tpc) take(i, w0 + i);
+        } else {
+            // the channel's cpc columns of every row lane, dealt to its threads
+            for (int k = sub; k < A.rpp * A.cpc; k += A.tpc) {
+                const int i = (int)__umulhi((unsigned)k, A.cpc_magic), j = k - i * A.cpc;
+                take(i, i * A.ncols + ch * A.cpc + j);
             }
         }
     }
     lanes_add(A.tpc, [&](auto off) __attribute__((always_inline)) {
-#pragma unroll
-        for (int q = 0; q < Q; ++q) out[q] = lane_add<decltype(off)::value>(out[q]);
+        out[0] = lane_add<decltype(off)::value>(out[0]);
+        out[1] = lane_add<decltype(off)::value>(out[1]);
     });
 }
 
@@ -218,11 +224,13 @@ template <class F> __device__ __forceinline__ bool slab_poll(const SlabArgs& A, 
     return false;
 }
 
-// 1 / n to about 1e-14 (a Newton step from the hardware's float reciprocal)
-__device__ __forceinline__ double slab_reciprocal(double n)
+// 1 / n to about 1e-14 (a Newton step from the hardware's float reciprocal); with two steps, to the last bit or two
+template <int STEPS = 1> __device__ __forceinline__ double slab_reciprocal(double n)
 {
-    const double r = (double)__builtin_amdgcn_rcpf((float)n);
-    return r * (2.0 - n * r);
+    double r = (double)__builtin_amdgcn_rcpf((float)n);
+#pragma unroll
+    for (int i = 0; i < STEPS; ++i) r = r * (2.0 - n * r);
+    return r;
 }
 
 // One channel's rows added up by the `G` lanes of a group (lane `gl`), double precision, fixed order; the group's first
@@ -569,8 +577,8 @@ __device__ __forceinline__ const u32x4& slab_fetched(const u32x4* ext, int slot,
 // squared deviations from the thread's own mean, one value at a time (the weights are constants of the unrolled loop):
 //     M2 <- M2 + (x - f - S / i)^2 * i / (i + 1),      S <- S + (x - f).
 // The unit's mean follows from the sums S + n (f - p) about the channel's pivot p, its first stored value; its squared
-// deviations are the sum of M2 + n ((f - p) + S / n - mean)^2 over the threads.  Every term is positive and nothing is a difference
-// of large sums, so it does not matter where the pivot lies.  (A sum of (x - p)^2 with the difference taken off at the
+// deviations are the sum of M2 + n ((f - p) + S / n - mean)^2 over the threads.  Nothing is a difference
+// of large float sums, so it does not matter where the pivot lies.  (A sum of (x - p)^2 with the difference taken off at the
 // end loses (mean - p)^2 / variance times the accuracy of a float sum: relative error of 1/sqrt, the worst of many
 // channels, pivot 4 standard deviations off 8.8e-7, here 6.1e-8; a few activations among zeros, the
 // first of them the pivot, 6.3e-6 and 7.8e-8.)
@@ -679,36 +687,40 @@ __global__ __launch_bounds__(kSlabThreads, DENSE || P * VB / 16 * (ACT == 2 ? 2 
                 }
             }
         });
-        // ---- the unit's
-        const double n_row = (double)g.n * (double)A.cpc;
-        const float cnt = (float)ps.nr, inv_cnt = ps.nr > 0 ? __builtin_amdgcn_rcpf(cnt) : 0.f;
-        float b[1][VEC];
+        // ---- the unit's, in one go: what the means of the threads add to the squared deviations, sum n_t (m_t - m)^2, is taken as
+        // sum S_t^2 / n_t - S^2 / n, in double precision and from the very S_t = n_t (f - p) + sum (x - f) that S is the sum of, so that the
+        // difference is exact to 1e-16 (m / sigma)^2.  S_t as one float would not be exact where f - p is no bfloat16 (mostly zeros, the
+        // pivot not among them: 1/sqrt to 1.5e-7, so 4.7e-8): float keeps its two terms apart.
+        // Summing twice, the second time about the unit's mean, forward us then / now: bf16 2100 x 512 8.7 / 8.2, 2100 x 2048 10.8 / 10.0,
+        // 16 x 256 planes of 13x21 8.4 / 7.8, 256 x 1024 of 7x7 16.5 / 15.5, in units 50960 x 72 18.3 / 17.1; mean + mean_lo 2e-6 / 1.2e-6 at worst.
+        constexpr bool APART = std::is_same<T, float>::value;
+        constexpr int Q = APART ? 3 : 2;
+        float b[Q][VEC];
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
             const float off = first[e] - piv[e];
-            b[0][e] = a[e] + cnt * off;
-            a[e] = a[e] * inv_cnt + off;
+            b[0][e] = APART ? a[e] : a[e] + (float)ps.nr * off;
+            b[1][e] = m2[e];
+            if constexpr (APART) b[2][e] = off;
         }
-        double tot[1], q[1];
-        slab_sum<VEC, 1>(A, L, b, col, r, tot);
-        if (ch < A.nch && sub == 0) {
-            L.piv[ch] = pv;
-            L.ctr[ch] = (float)(tot[0] * slab_reciprocal(n_row));
-        }
-        __syncthreads();
+        double tot[2];
         {
-            const SlabChannels<VEC> c2(A, (int)fresh((unsigned)col));
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-                const float dd = a[e] - L.ctr[c2[e]];
-                b[0][e] = m2[e] + cnt * (dd * dd);
-            }
+            const int whole = g.n - (ps.passes - 1) * A.rpp;      // row lanes with a value in every pass; the others have one less
+            const double n0 = (double)ps.passes, n1 = n0 - 1.0, inv0 = slab_reciprocal<2>(n0), inv1 = ps.passes > 1 ? slab_reciprocal<2>(n1) : 0.0;
+            slab_sum<VEC, Q>(A, L, b, col, r, tot, [&](int i, const float (&x)[Q], double (&o)[2]) __attribute__((always_inline)) {
+                double s = (double)x[0];
+                if constexpr (APART) s += (i < whole ? n0 : n1) * (double)x[Q - 1];
+                o[0] += s;
+                o[1] += (double)x[1] + s * s * (i < whole ? inv0 : inv1);
+            });
         }
-        slab_sum<VEC, 1>(A, L, b, col, r, q);
+        tot[1] -= tot[0] * tot[0] * slab_reciprocal<2>((double)g.n * (double)A.cpc);
+        if (tot[1] < 0.0) tot[1] = 0.0;                           // (a NaN stays)
+        if (!SOLO && ch < A.nch && sub == 0) L.piv[ch] = pv;
         // ---- steps 4-5 and 9-10
         bool ok = true, mine = true;
         if (!SOLO) {
-            if (ch < A.nch && sub == 0) slab_put_row(A, slab, u, ch, tot[0], q[0]);
+            if (ch < A.nch && sub == 0) slab_put_row(A, slab, u, ch, tot[0], tot[1]);
             fetched = 0;
             mine = slab_hand_over<true>(A, L, slab, u, [&] {
                 if constexpr (PRE != 0)
@@ -726,7 +738,7 @@ __global__ __launch_bounds__(kSlabThreads, DENSE || P * VB / 16 * (ACT == 2 ? 2 
                     const double mean = (double)pv + tot[0] * A.inv_M_f64;
                     hi = (float)mean;
                     lo = (float)(mean - (double)hi);
-                    is = (float)rsqrt_f64(q[0] * A.inv_M_f64 + A.eps);
+                    is = (float)rsqrt_f64(tot[1] * A.inv_M_f64 + A.eps);
                 } else {
                     hi = L.res[0][ch];
                     lo = L.res[1][ch];
@@ -943,7 +955,10 @@ __global__ __launch_bounds__(kSlabThreads, DENSE || P * VB / 16 * (ACT != 0 ? 3 
             }
         });
         double tot[2];
-        slab_sum<VEC, 2>(A, L, a, col, r, tot);
+        slab_sum<VEC, 2>(A, L, a, col, r, tot, [](int, const float (&x)[2], double (&o)[2]) __attribute__((always_inline)) {
+            o[0] += (double)x[0];
+            o[1] += (double)x[1];
+        });
         double db = 0.0, dg = 0.0;
         bool ok = true, mine = true;
         if (SOLO) {
