@@ -836,6 +836,7 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_forward(FusedArgs A)
                         } else {
                             LdsSlot<LB>::read(ext, s - RS, t, wv);
                         }
+                        float slot[W];
 #pragma unroll
                         for (int q = 0; q < W; ++q) {
                             float f[EPW];
@@ -843,9 +844,12 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_forward(FusedArgs A)
 #pragma unroll
                             for (int e = 0; e < EPW; ++e) {
                                 const float dv = f[e] - centre;
-                                acc[(q * EPW + e) & 3] += square ? dv * dv : dv;
+                                if (EDGE && !square) slot[q] = e == 0 ? dv : slot[q] + dv;
+                                else acc[(q * EPW + e) & 3] += square ? dv * dv : dv;
                             }
                         }
+                        // (EDGE: a slot's values first: the sweeps that took these planes before sum in short runs too)
+                        if constexpr (EDGE && !square) acc[s & 3] += (slot[0] + slot[1]) + (slot[2] + slot[3]);
                     }
                 }
                 return wave_sum((acc[0] + acc[1]) + (acc[2] + acc[3]));
@@ -1225,6 +1229,7 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_backward(FusedArgs A)
                         LdsSlot<LB>::read(ext, s - RS, t, wg);
                         LdsSlot<LB>::read(ext, RL + s - RS, t, wx);
                     }
+                    float sa[2] = {0.f, 0.f}, sb[2] = {0.f, 0.f};
 #pragma unroll
                     for (int q = 0; q < W; ++q) {
                         float fx[EPW], fg[EPW];
@@ -1232,9 +1237,18 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_backward(FusedArgs A)
                         Packed<T>::unpack(wg[q], fg);
 #pragma unroll
                         for (int e = 0; e < EPW; ++e) {
-                            a[(q * EPW + e) & 1] += fg[e];
-                            b[(q * EPW + e) & 1] += fg[e] * (fx[e] - mu);
+                            if constexpr (EDGE) {             // (a slot's values first, see the forward)
+                                sa[q & 1] = q < 2 && e == 0 ? fg[e] : sa[q & 1] + fg[e];
+                                sb[q & 1] = q < 2 && e == 0 ? fg[e] * (fx[e] - mu) : sb[q & 1] + fg[e] * (fx[e] - mu);
+                            } else {
+                                a[(q * EPW + e) & 1] += fg[e];
+                                b[(q * EPW + e) & 1] += fg[e] * (fx[e] - mu);
+                            }
                         }
+                    }
+                    if constexpr (EDGE) {
+                        a[s & 1] += sa[0] + sa[1];
+                        b[s & 1] += sb[0] + sb[1];
                     }
                 }
                 if (SL::ends_plane(s)) {
