@@ -52,7 +52,7 @@ struct SlabArgs {
     float* invstd;
     float* dgamma;
     float* dbeta;
-    unsigned long long* rows; // per slab: [unit][channel][2] doubles, then [channel][2] pairs of floats, the results
+    unsigned long long* rows; // per slab: [channel][unit][2] doubles, then [channel][2] pairs of floats, the results
     unsigned* sync;
     long long R;          // rows of the matrix
     long long row_bytes;
@@ -186,7 +186,8 @@ __device__ __forceinline__ unsigned slab_bits(float v)      // NaN in canonical 
     return v != v ? 0x7fc00000u : __float_as_uint(v);
 }
 
-// A slab's memory: [unit][channel][2] rows of doubles, then the channels' results (two pairs of floats each), all 8-byte words that
+// A slab's memory: [channel][unit][2] rows of doubles (a channel's lie side by side: they are fetched again and again until they are all
+// there, and by lines that hold nothing else), then the channels' results (two pairs of floats each), all 8-byte words that
 // hold the sentinel until they are written.
 __device__ __forceinline__ unsigned long long* slab_rows(const SlabArgs& A, int slab)
 {
@@ -194,7 +195,7 @@ __device__ __forceinline__ unsigned long long* slab_rows(const SlabArgs& A, int 
 }
 __device__ __forceinline__ void slab_put_row(const SlabArgs& A, int slab, int u, int c, double a, double b)
 {
-    unsigned long long* p = slab_rows(A, slab) + ((size_t)u * A.nch + c) * 2;
+    unsigned long long* p = slab_rows(A, slab) + ((size_t)c * A.U + u) * 2;
     // (NaN in canonical form, as in slab_bits)
     __hip_atomic_store(p, a != a ? 0x7ff8000000000000ull : (unsigned long long)__double_as_longlong(a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(p + 1, b != b ? 0x7ff8000000000000ull : (unsigned long long)__double_as_longlong(b), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -239,21 +240,22 @@ template <bool FWD> __device__ __forceinline__ bool slab_reduce(const SlabArgs& 
 {
     const int gl = (int)fresh(threadIdx.x) & (A.G - 1);
     const bool duty = c < A.rch;
-    unsigned long long* row = slab_rows(A, slab) + 2 * (duty ? c : 0);
+    const unsigned long long* row = slab_rows(A, slab) + ((size_t)(duty ? c : 0) * A.U + gl) * 2;
     unsigned long long v[kSlabRowsPerLane], w[kSlabRowsPerLane];
+#pragma unroll
+    for (int j = 0; j < kSlabRowsPerLane; ++j) v[j] = w[j] = duty && gl + j * A.G < A.U ? ~0ull : 0ull;       // (two words of kRowSentinel: not there yet)
     if (!slab_poll(A, patient, [&] {
             bool there = true;
 #pragma unroll
             for (int j = 0; j < kSlabRowsPerLane; ++j) {
-                v[j] = w[j] = 0ull;
-                if (duty && gl + j * A.G < A.U) {
-                    unsigned long long* p = row + (size_t)(gl + j * A.G) * A.nch * 2;
+                if (v[j] == ~0ull || w[j] == ~0ull) {         // (what has come is not fetched again)
+                    const unsigned long long* p = row + (size_t)(j * A.G) * 2;
                     v[j] = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     w[j] = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
 #pragma unroll
-            for (int j = 0; j < kSlabRowsPerLane; ++j) there &= v[j] != ~0ull && w[j] != ~0ull;       // (two words of kRowSentinel)
+            for (int j = 0; j < kSlabRowsPerLane; ++j) there &= v[j] != ~0ull && w[j] != ~0ull;
             return there;
         }))
         return false;
