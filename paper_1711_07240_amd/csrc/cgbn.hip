@@ -201,6 +201,7 @@ struct SlabPlan {
     int cols, vecs, rpp, cpc, nch, tpc, slabs, U, rpu;
     int P;                // vectors per thread of the kernel variant
     int vb;               // bytes of a vector
+    int shared;           // several rounds of slabs that share lines: neighbours are in flight together (see cut_slabs_in_units)
     long long R, row_bytes, total_units;
 };
 
@@ -233,6 +234,7 @@ struct Plan {
     bool edges[4];        // forward, with a shortcut, backward, masked
     SlabPlan sf, sb;      // column-slab path
     SlabPlan sfs, sbm;    // ... of a forward with a shortcut, of a masked backward
+    SlabPlan xf, xb, xbm; // the same in several rounds of slabs that share lines (no shortcut): taken where the others are not ok
     SlabPlan nf, nb, nfs, nbm;    // the same with 8-byte vectors: taken in their place where ok
     // workspace layout (byte offsets)
     size_t off_part0, off_part1, off_sh0, off_sh1, off_mlo, off_sync, bytes;
@@ -440,7 +442,9 @@ bool cut_slabs(SlabPlan* s, int C, int cols, int nch, long long U, long long row
 // boundaries they share those lines: fp32 22400 x 264, 31 units 23.8 / 28.7, 32 units 21.5 / 24.5; 70200 x 112, 63 units 27.7 / 36.3, 64
 // units 24.3 / 29.7 (rows of whole lines: no difference).  Such slabs must also all be in flight together (measured, fp32
 // 268800 x 136 in four rounds 170 us, the sweeps 101).
-bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_words, int cus, bool forward, bool second)
+//   Such slabs in several rounds (`shared`: at least so many in flight): those in flight are then neighbours, in whole eights of units, so that the
+// lines two of them share are fetched by one XCD at about the same time and only those at the ends of the group twice.  See make_shared_plan.
+bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_words, int cus, bool forward, bool second, int shared = 0)
 {
     const int rpp = kSlabThreads / cols;
     const long long cap = (long long)rpp * slab_most(forward, false);
@@ -450,6 +454,7 @@ bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_wor
     long long most = cus < s->R ? cus : s->R;
     if (most > kSlabRowsPerLane * kWave) most = kSlabRowsPerLane * kWave;
     if (most > row_words / (2 * slabs * nch) - 1) most = row_words / (2 * slabs * nch) - 1;
+    if (shared && most > cus / shared) most = cus / shared;
     const long long top = cus / slabs < most ? cus / slabs : most;
     long long best = 0, best_cost = 0;
     for (int k = 0; k < 12; ++k) {
@@ -458,10 +463,16 @@ bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_wor
         if (U < least || U > most) continue;
         long long cost;
         if (slabs * U > cus / U * U) {
-            if (!lines) continue;
+            if (shared) {
+                U = (U + 7) / 8 * 8;
+                if (U > most || 10 * slabs < 7 * ((slabs + cus / U - 1) / (cus / U)) * (cus / U)) continue;
+            } else if (!lines) {
+                continue;
+            }
             const long long grid = cus / U * U, passes = ((s->R + U - 1) / U + rpp - 1) / rpp;
             cost = (slabs * U + grid - 1) / grid * (passes * 60 + 600);
         } else {
+            if (shared) continue;                             // (one round: as any other)
             if (!lines && U >= 16 && U / 8 * 8 >= least) U = U / 8 * 8;
             const long long passes = ((s->R + U - 1) / U + rpp - 1) / rpp;
             const long long fewest = (s->R + passes * rpp - 1) / (passes * rpp), eights = (fewest + 7) / 8 * 8;
@@ -473,7 +484,11 @@ bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_wor
         }
         if (best == 0 || cost < best_cost) { best = U; best_cost = cost; }
     }
-    return best >= 2 && cut_slabs(s, C, cols, nch, best, row_words, cus, forward);
+    if (best < 2 || !cut_slabs(s, C, cols, nch, best, row_words, cus, forward)) return false;
+    s->shared = shared > 0;
+    // (no unit is empty, so there may be fewer than asked for: they have to be whole eights still)
+    if (shared && s->U % 8 != 0) s->ok = 0;
+    return s->ok != 0;
 }
 
 // channels-last: up to how many pixels a slab is one workgroup.  (Rows shorter than a line: a workgroup shares its lines with few
@@ -566,6 +581,27 @@ void make_slab_plan(int N, int C, long long HW, int layout, int eb, long long ro
     if (N * s->row_bytes < 6000000) return;
     if (cut_slabs_in_units(s, C, cols, nch, row_words, cus, forward, second))
         s->first = !f.ok || (f.U > 1 && (forward ? HW * eb <= 1024 && N * s->row_bytes <= 200000000 : HW * eb <= (eb == 2 ? 512 : 800) && N * s->row_bytes <= 100000000));
+}
+
+// Channels-last calls that no plan above takes, rows of at least 24 vectors that are no whole lines: in several rounds of 128-byte slabs that share
+// lines, where enough of them are in flight and the rounds are at least 70 % full.  Measured over 60 random shapes, sweeps -> so, forward / backward / masked us:
+// fp32 63104 x 1264 (eight and four in flight) 234 / 334 / 645 -> 187 / 281 / 498, 23936 x 1168 (16, ten) 89 / 134 / 243 -> 64 / 90 / 145, 17920 x 1768 (32, 16) 101 /
+// 146 / 230 -> 65 / 107 / 188, bf16 43008 x 936 (ten, five) 69 / 100 / 149 -> 57 / 74 / 120.  Fewer in flight: 97244 x 880 (two) backward 321 -> 345, 238080 x 408 (two, one)
+// 235 / 364 -> 321 / 520, bf16 62424 x 1064 (four) masked 223 -> 249; masked float of rows of one tile, whose sweeps are faster: 37392 x 904 (six)
+// 225 -> 260, 60928 x 808 (four) 339 -> 382.  Rounds two thirds full: bf16 79872 x 496 forward 58 -> 62.  Nine columns a slab: 17920 x 1768 65 / 107, so 89 / 114.
+void make_shared_plan(int N, int C, long long HW, int eb, long long row_words, int cus, bool forward, bool second, const SlabPlan& s, SlabPlan* x)
+{
+    std::memset(x, 0, sizeof(*x));
+    const int vec = 16 / eb;
+    if (s.ok || C % vec != 0 || C / vec < 24) return;
+    x->vecs = C / vec;
+    x->R = (long long)N * HW;
+    x->row_bytes = (long long)C * eb;
+    x->cpc = 1;
+    const int cols = 8;
+    if (x->row_bytes % 128 == 0) return;       // (whole lines)
+    const int flight = forward ? 6 : eb == 2 ? 5 : second && x->vecs <= kThreads ? 8 : 4;
+    cut_slabs_in_units(x, C, cols, ceil_pow2(cols * vec), row_words, cus, forward, second, flight);
 }
 
 // NCHW calls whose plan `s` has 16-byte vectors: one of 8-byte vectors in its place (see SlabVector), where that leaves at least half the compute
@@ -930,7 +966,12 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
         make_narrow_plan(N, C, HW, p->eb, false, false, p->sb, cus, &p->nb);
         make_narrow_plan(N, C, HW, p->eb, false, true, p->sbm, cus, &p->nbm);
     }
-    for (const SlabPlan* s : {&p->sf, &p->sfs, &p->sb, &p->sbm})
+    if (layout == CGBN_NHWC) {
+        make_shared_plan(N, C, HW, p->eb, row_words, cus, true, false, p->sf, &p->xf);
+        make_shared_plan(N, C, HW, p->eb, row_words, cus, false, false, p->sb, &p->xb);
+        make_shared_plan(N, C, HW, p->eb, row_words, cus, false, true, p->sbm, &p->xbm);
+    }
+    for (const SlabPlan* s : {&p->sf, &p->sfs, &p->sb, &p->sbm, &p->xf, &p->xb, &p->xbm})
         if (s->ok && s->U > 1) {
             const size_t need = (size_t)slab_row_words(*s) * sizeof(double);
             if (need > 2 * part + 2 * sh) part = align256((need - 2 * sh + 1) / 2);
@@ -1341,6 +1382,7 @@ SlabArgs slab_args(const Plan& p, const SlabPlan& s, char* ws)
     A.nt = (int)p.t.nt_store && s.U > 1;
     A.spin_limit = (unsigned)p.t.spin_limit;
     A.bitmap_words = (unsigned)((s.U + 31) / 32);
+    A.neighbours = s.shared;
     A.cpc_magic = (unsigned)(((1ULL << 32) + s.cpc - 1) / s.cpc);     // (not used for one column per channel)
     return A;
 }
@@ -1616,7 +1658,7 @@ cgbn_status forward_impl(const void* x, const void* shortcut, bool relu, int N, 
     float* mlo = reinterpret_cast<float*>(ws + p.off_mlo);
     const int rev = (int)p.t.reverse;
 
-    const SlabPlan& wide = shortcut ? p.sfs : p.sf;
+    const SlabPlan& wide = shortcut ? p.sfs : p.xf.ok ? p.xf : p.sf;
     const bool slab = p.t.fused && p.t.one_sweep_stats && wide.ok;
     for (const FusedPlan* f : {&p.ef, &p.ff}) {
         if (!p.t.fused || !f->ok || (f == &p.ef && !p.edges[shortcut != nullptr]) || (slab && wide.first)) continue;
@@ -1703,7 +1745,7 @@ cgbn_status backward_impl(const void* dy, const void* y, const void* x, const fl
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int rev = (int)p.t.reverse;
 
-    const SlabPlan& wide = relu ? p.sbm : p.sb;
+    const SlabPlan& wide = relu ? (p.xbm.ok ? p.xbm : p.sbm) : p.xb.ok ? p.xb : p.sb;
     const bool slab = p.t.fused && wide.ok;
     for (const FusedPlan* f : {&p.ebw, &p.fb}) {
         if (!p.t.fused || !f->ok || (f == &p.ebw && !p.edges[relu ? 3 : 2]) || (slab && wide.first)) continue;
@@ -1944,10 +1986,10 @@ long long cgbn_plan_get(int N, int C, int H, int W, cgbn_layout layout, cgbn_dty
         if (!std::strcmp(k, "total_units")) return f.total_units;
         return -1;
     }
-    if ((key[0] == 's' || key[0] == 'n') && (!std::strncmp(key + 1, "fwd_", 4) || !std::strncmp(key + 1, "bwd_", 4) ||
+    if ((key[0] == 's' || key[0] == 'n' || key[0] == 'x') && (!std::strncmp(key + 1, "fwd_", 4) || !std::strncmp(key + 1, "bwd_", 4) ||
                                              !std::strncmp(key + 1, "fwds_", 5) || !std::strncmp(key + 1, "bwdm_", 5))) {
         const bool second = key[4] != '_', narrow = key[0] == 'n';
-        const SlabPlan& s = key[1] == 'b' ? (second ? (narrow ? p.nbm : p.sbm) : (narrow ? p.nb : p.sb))
+        const SlabPlan& s = key[0] == 'x' ? (key[1] == 'b' ? (second ? p.xbm : p.xb) : p.xf) : key[1] == 'b' ? (second ? (narrow ? p.nbm : p.sbm) : (narrow ? p.nb : p.sb))
                                           : (second ? (narrow ? p.nfs : p.sfs) : (narrow ? p.nf : p.sf));
         const char* k = key + (second ? 6 : 5);
         if (!std::strcmp(k, "ok")) return s.ok;

@@ -74,6 +74,7 @@ struct SlabArgs {
     int prefetch;         // several rounds: the wavefronts from this one on fetch the next unit's first passes into LDS during the hand-over
     int ahead;            // ... 2: all passes the LDS has room for; 1: the first kSlabAheadFew (backward)
     unsigned bitmap_words;    // per slab
+    int neighbours;           // the slabs in flight together lie side by side
     unsigned cpc_magic;       // 2^32 / cpc, rounded up: i / cpc is the high word of i * cpc_magic for the small i here
 };
 
@@ -435,9 +436,10 @@ template <> struct SlabVector<8> { typedef u32x2 V; };
 // Several units: the order in which the slabs are taken.  Those in flight together are spread evenly over the row, and a
 // round moves on by one slab: neighbouring columns at a long row stride would crowd the memory channels (measured,
 // the loads and stores alone, 67200 rows of 4096 bytes: eight neighbouring slabs in flight 154 us, eight spread 114; rows
-// of 1024 bytes 115 either way).  Bijective for any number of slabs.
+// of 1024 bytes 115 either way).  Slabs that share lines lie side by side instead, for their lines.  Bijective for any number of slabs.
 __device__ __forceinline__ int slab_of_turn(const SlabArgs& A, int turn)
 {
+    if (A.neighbours) return turn;
     const int q = A.slabs / A.inflight, rem = A.slabs - q * A.inflight;
     const int k = turn / A.inflight, j = turn - k * A.inflight;
     return j * q + min(j, rem) + k;
