@@ -265,6 +265,8 @@ const char* cgbn_status_string(cgbn_status status);
  * CGBN_ERR_WORKSPACE before launching anything).
  *   "chunk_bytes"      NCHW: bytes of one plane handled by one workgroup
  *   "wave_plane_bytes" NCHW: planes up to this size are handled by one wavefront
+ *   "flat"             0/1 (default 1): NCHW channels that fit one workgroup's registers (up to 64 KiB) go through the
+ *                      flat kernels, one launch with nothing handed over.
  *   "tiny_planes"      0/1 (default 1): NCHW planes of at most 2 KiB, C a multiple of 8: a workgroup of the
  *                      multi-sweep kernels takes a run of 8 ... 256 planes of consecutive channels at once
  *   "piece_bytes"      NHWC reductions: bytes of one pixel range handled by one workgroup (0, the default:

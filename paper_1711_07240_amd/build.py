@@ -51,6 +51,8 @@ def _units(obj_dir):
                 units.append((obj, os.path.join(CSRC, "cgbn_fused_inst.hip"),
                               [f"-DCGBN_INST_T={t}", f"-DCGBN_INST_F32={int(t == 'float')}", f"-DCGBN_INST_FWD={fwd}",
                                f"-DCGBN_INST_ACT={act}"]))
+            units.append((os.path.join(OBJ, f"flat_{tname}_{'fwd' if fwd else 'bwd'}.o"), os.path.join(CSRC, "cgbn_flat_inst.hip"),
+                          [f"-DCGBN_INST_T={t}", f"-DCGBN_INST_F32={int(t == 'float')}", f"-DCGBN_INST_FWD={fwd}"]))
             for dense in (0, 1):
                 obj = os.path.join(OBJ, f"slab_{tname}_{'fwd' if fwd else 'bwd'}{'_dense' if dense else ''}.o")
                 units.append((obj, os.path.join(CSRC, "cgbn_slab_inst.hip"),

@@ -6,6 +6,7 @@
 #include "cgbn_fused.h"
 #include "cgbn_fused_list.h"
 #include "cgbn_slab.h"
+#include "cgbn_flat.h"
 
 #include <algorithm>
 #include <atomic>
@@ -68,6 +69,24 @@ CGBN_FUSED_EDGE_BACKWARD(CGBN_DECL_BE)
 #undef CGBN_DECL_E
 #undef CGBN_DECL_FE
 #undef CGBN_DECL_BE
+// ... the flat kernels in cgbn_flat_inst.hip
+#define CGBN_DECL_L(T_, LB_, S_, WAVES_)                                                        \
+    extern template __global__ void flat_forward<T_, LB_, S_, WAVES_, 0>(FlatArgs);             \
+    extern template __global__ void flat_forward<T_, LB_, S_, WAVES_, 1>(FlatArgs);             \
+    extern template __global__ void flat_forward<T_, LB_, S_, WAVES_, 2>(FlatArgs);             \
+    extern template __global__ void flat_backward<T_, LB_, S_, WAVES_, 0>(FlatArgs);            \
+    extern template __global__ void flat_backward<T_, LB_, S_, WAVES_, 1>(FlatArgs);
+#define CGBN_DECL_LF1(LB_, S_) CGBN_DECL_L(float, LB_, S_, 1)
+#define CGBN_DECL_LF4(LB_, S_) CGBN_DECL_L(float, LB_, S_, 4)
+#define CGBN_DECL_LB1(LB_, S_) CGBN_DECL_L(bf16_t, LB_, S_, 1)
+#define CGBN_DECL_LB4(LB_, S_) CGBN_DECL_L(bf16_t, LB_, S_, 4)
+CGBN_FLAT_ONE(CGBN_DECL_LF1) CGBN_FLAT_FOUR(CGBN_DECL_LF4)
+CGBN_FLAT_ONE(CGBN_DECL_LB1) CGBN_FLAT_FOUR(CGBN_DECL_LB4) CGBN_FLAT_BF16(CGBN_DECL_LB1) CGBN_FLAT_BF16(CGBN_DECL_LB4)
+#undef CGBN_DECL_L
+#undef CGBN_DECL_LF1
+#undef CGBN_DECL_LF4
+#undef CGBN_DECL_LB1
+#undef CGBN_DECL_LB4
 // ... and the column-slab kernels in cgbn_slab_inst.hip
 #define CGBN_DECL_SF(P_, SOLO_)                                                                 \
     extern template __global__ void slab_forward<float, 0, P_, SOLO_, false>(SlabArgs);         \
@@ -162,6 +181,7 @@ struct Tuning {
     long long stagger = 1;               // single-launch kernels: start the channel slots class by class (see choose_stagger)
     long long stagger_us = 0;            // ... start-up delay of the last class (0 = chosen per launch)
     long long stagger_phases = 16;       // ... and the number of classes
+    long long flat = 1;                  // NCHW: channels that fit one workgroup's registers go through the flat kernels
     long long wait_us = 100000;          // microseconds after which a device-side wait of the fused kernels gives up
 };
 // The knobs are process-wide; every call works on ONE copy of them, the one its plan was made under: taken under the lock
@@ -177,7 +197,8 @@ Tuning tuning_now()
     return g_tune;
 }
 std::atomic<long long> g_last_forward_slab{0}, g_last_backward_slab{0};     // bytes of the vectors of the column-slab kernel it took, or 0
-std::atomic<long long> g_last_forward_fused{0}, g_last_backward_fused{0};   // which path the last call took
+std::atomic<long long> g_last_forward_fused{0}, g_last_backward_fused{0};   // which path the last call took: 1 for a single launch of an NCHW call
+std::atomic<long long> g_last_forward_flat{0}, g_last_backward_flat{0};     // ... by a flat kernel
 #ifdef CGBN_TRACE
 unsigned long long* g_trace = nullptr;
 #endif
@@ -192,6 +213,13 @@ struct FusedPlan {
     int edge;             // planes start anywhere: 16-byte loads, the values before and behind whole vectors one by one
     int big;              // 1 (large planes) / 2 (small planes): the variant that stages few rows and keeps more unit data in LDS
     long long total_units;
+};
+
+// Geometry of the flat path (see cgbn_flat.h); the same for both directions.
+struct FlatPlan {
+    int waves;            // wavefronts a channel (1 or 4), 0: the shape cannot take the path
+    int LB, S;            // bytes of a vector, vectors a lane
+    int vecs, total;      // vectors of a plane, of a channel
 };
 
 // Geometry of the column-slab path for one direction (see cgbn_slab.h).
@@ -232,6 +260,8 @@ struct Plan {
     FusedPlan ff, fb;     // register-resident path, forward and backward
     FusedPlan ef, ebw;    // ... with 16-byte loads for planes that are no multiple of 16 bytes, and the calls that take them (see edges_pay):
     bool edges[4];        // forward, with a shortcut, backward, masked
+    FlatPlan flat;        // the flat path, and the calls that take it before all but column slabs that come first:
+    bool flats[4];        // forward, with a shortcut, backward, masked
     SlabPlan sf, sb;      // column-slab path
     SlabPlan sfs, sbm;    // ... of a forward with a shortcut, of a masked backward
     SlabPlan xf, xb, xbm; // the same in several rounds of slabs that share lines (no shortcut): taken where the others are not ok
@@ -372,6 +402,32 @@ void make_fused_plan(const Tuning& T, int N, int C, long long HW, int K, int lay
     f->ok = 1;
 }
 
+
+// A channel's planes in one wavefront or in a workgroup of four: up to 64 registers a lane (16 KiB, 64 KiB), with 2- and 4-byte vectors 32.  One where
+// there are many short channels, us, one / four: forward 3 x 1954 planes of 14x22 fp32 4.7 / 6.0, 2 x 1848 of 27x40 bf16 5.9 / 6.8, 2 x 825 of 8x11 fp32
+// 3.4 / 4.0, 4 x 896 of 32x33 bf16 6.4 / 5.9, 8 x 680 of 14x17 fp32 5.2 / 5.1, 2 x 256 of 13x21 4.1 / 4.3; 2 x 512 of 25x42 bf16 backward 6.5 / 5.0, 2 x 2048 9.3 / 9.9.
+void make_flat_plan(int N, int C, long long HW, int eb, FlatPlan* f)
+{
+    std::memset(f, 0, sizeof(*f));
+    const long long plane = HW * eb;
+    int LB = 16;
+    while (plane % LB != 0) LB /= 2;
+    if (LB < eb || plane / LB > 0xffff || (long long)N * C * plane > 0x7fffffffLL) return;
+    const long long channel = N * plane;
+    const long long total = N * (plane / LB);
+    const int waves = (channel <= 1024 || (channel <= 5000 && C >= 1024)) && total <= 32 * kWave ? 1 : kThreads / kWave;
+    const long long lane = (total + waves * kWave - 1) / (waves * kWave);
+    int S = 0;
+#define CGBN_FLAT_FITS(LB_, S_) if (LB == LB_ && lane <= S_ && (S == 0 || S_ < S)) S = S_;
+    CGBN_FLAT_FOUR(CGBN_FLAT_FITS) CGBN_FLAT_BF16(CGBN_FLAT_FITS)
+#undef CGBN_FLAT_FITS
+    if (S == 0) return;
+    f->waves = waves;
+    f->LB = LB;
+    f->S = S;
+    f->vecs = (int)(plane / LB);
+    f->total = (int)total;
+}
 
 int ceil_pow2(int v)
 {
@@ -844,6 +900,28 @@ constexpr bool fused_built(bool f32, bool forward, int act, int LB, int LPPC)
     return true;
 }
 
+// The flat kernels take what fits them (60 shapes of random sizes up to 60 MB, 1.60 / 1.39 / 1.89 / 1.43 times as fast forward / backward / with a shortcut / masked in the geometric mean
+// as the single-launch kernels and sweeps in their place), but for
+// - masked backwards that have no single-launch kernel with their vectors (see fused_built, callers are told that those are separate sweeps);
+// - backwards with 16-byte vectors of tensors that just outgrow the last-level cache (256 MB, of which a backward's three tensors take three tensors' bytes,
+//   a masked one's five): there the single-launch kernels, whose loads are non-temporal and go ahead of the stores, keep more of their inputs
+//   cached between calls.  Old / flat in us, 8 images of 23x24 fp32: backward of 44 MB 27.6 / 23.0, 62 MB 35.9 / 39.0, 88 MB 49.1 / 54.2, 141 MB 88.1 / 87.9,
+//   212 MB 144 / 131 (16 of 24x30: 147 MB 87.8 / 93.9, 230 MB 145 / 141); masked 26 MB 28.7 / 23.9, 35 MB 35.3 / 37.5, 62 MB 56.6 / 64.2, 88 MB 98.2 / 89.8 (2 of 60x64 bf16 77 MB 78.5 / 85.9); 16 of 24x30 masked 29 MB 32.5 / 30.5, 37 MB
+//   36.5 / 43.6, backward 46 MB 27.9 / 25.0, 60 MB 38.1 / 40.4.  (Non-temporal loads here: 18 MB backward 10.6 -> 12.8, masked 15.6 -> 20.0.)
+// - forwards of 64 registers a lane of such tensors: 16 of 24x30, 60 MB 28.5 / 19.7, 92 MB 37.1 / 40.6;
+// - backwards of 64 registers a lane of 8 bytes each, where a compute unit has several channels or few long planes: 16 of 18x29 fp32, 256 channels
+//   9.1 / 8.7, 400 11.7 / 12.0, 800 17.6 / 19.3; 4 of 52 of 50x45 6.5 / 6.7, 8 of 35 of 43x46 8.2 / 7.3.
+bool flat_pays(const FlatPlan& f, int C, long long plane_bytes, int cus, int direction)
+{
+    if (f.waves == 0) return false;
+    const bool most = flat_words(f.LB, f.S) > 32;
+    const long long bytes = (long long)f.total * f.LB * C;
+    if (direction >= 2 && f.LB == 8 && most) return C <= cus && plane_bytes <= 8192;
+    if (f.LB < 16 || direction == 1) return true;
+    if (direction == 0) return !most || bytes < 90000000LL;
+    return direction == 2 ? bytes < 50000000LL || bytes > 160000000LL : bytes < 32000000LL || bytes > 85000000LL;
+}
+
 cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, int dtype, int K, Plan* p)
 {
     if (N < 1 || C < 1 || H < 1 || W < 1) return CGBN_ERR_SHAPE;
@@ -867,7 +945,8 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
     p->S = S;
     p->M = (double)N * (double)HW;
     const int full_vec = 16 / p->eb;
-    if (layout == CGBN_NHWC || (C % full_vec == 0 && HW <= kSlabThreads)) {       // (else neither sweeps nor slab plans need it)
+    if (layout == CGBN_NCHW && K <= kFusedMaxShards && T.flat) make_flat_plan(N, C, HW, p->eb, &p->flat);
+    if (layout == CGBN_NHWC || (C % full_vec == 0 && HW <= kSlabThreads) || (p->flat.LB == 8 && flat_words(8, p->flat.S) > 32)) {   // (else nothing needs it)
         p->device = current_device();
         p->cus = compute_units(p->device);
     }
@@ -959,6 +1038,10 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
         // (what a second tensor changes: see there)
         if (one.ok && (one.U == 1 ? layout == CGBN_NCHW || one.R > few_pixels(forward, true, one.row_bytes) : forward))
             make_slab_plan(N, C, HW, layout, p->eb, row_words, cus, forward ? p->ff : p->fb, forward, true, &two);
+    }
+    for (int i = 0; i < 4; ++i) {
+        const FusedPlan& f = i < 2 ? p->ff : p->fb;
+        p->flats[i] = flat_pays(p->flat, C, HW * p->eb, cus, i) && !(f.ok && !fused_built(p->eb == 4, i < 2, i & 1, f.LB, f.LPPC));
     }
     if (layout == CGBN_NCHW) {
         make_narrow_plan(N, C, HW, p->eb, true, false, p->sf, cus, &p->nf);
@@ -1444,6 +1527,39 @@ cgbn_status launch_slab_t(const Plan& p, const SlabPlan& s, const SlabArgs& A, h
     return CGBN_ERR_HIP;              // (no such variant: the plan takes its sizes from the same list)
 }
 
+FlatArgs flat_args(const Plan& p, char* ws)
+{
+    FlatArgs A;
+    std::memset(&A, 0, sizeof(A));
+    A.sync = reinterpret_cast<unsigned*>(ws + p.off_sync);
+    A.inv_M_f64 = 1.0 / p.M; A.inv_M = (float)(1.0 / p.M);
+    A.C = p.C;
+    A.vecs = p.flat.vecs; A.total = p.flat.total;
+    A.magic = A.vecs > 1 ? (unsigned)(((1ULL << 32) + A.vecs - 1) / A.vecs) : 0u;
+    A.plane_bytes = (unsigned)(p.HW * p.eb); A.image_bytes = (unsigned)((long long)p.C * p.HW * p.eb);
+    return A;
+}
+
+template <typename T, bool FWD, int ACT> cgbn_status launch_flat_t(const Plan& p, const FlatArgs& A, hipStream_t st)
+{
+    const FlatPlan& f = p.flat;
+    const dim3 grid((unsigned)(f.waves == 1 ? (p.C + 3) / 4 : p.C)), block(kThreads);
+#define CGBN_FLAT_CASE(LB_, S_, WAVES_)                                                                         \
+    if (f.LB == LB_ && f.S == S_ && f.waves == WAVES_) {                                                        \
+        if constexpr (FWD) hipLaunchKernelGGL((flat_forward<T, LB_, S_, WAVES_, ACT>), grid, block, 0, st, A);  \
+        else hipLaunchKernelGGL((flat_backward<T, LB_, S_, WAVES_, ACT>), grid, block, 0, st, A);               \
+        return launched();                                                                                      \
+    }
+#define CGBN_FLAT_CASE1(LB_, S_) CGBN_FLAT_CASE(LB_, S_, 1)
+#define CGBN_FLAT_CASE4(LB_, S_) CGBN_FLAT_CASE(LB_, S_, 4)
+    CGBN_FLAT_ONE(CGBN_FLAT_CASE1) CGBN_FLAT_FOUR(CGBN_FLAT_CASE4)
+    if constexpr (!std::is_same<T, float>::value) { CGBN_FLAT_BF16(CGBN_FLAT_CASE1) CGBN_FLAT_BF16(CGBN_FLAT_CASE4) }
+#undef CGBN_FLAT_CASE
+#undef CGBN_FLAT_CASE1
+#undef CGBN_FLAT_CASE4
+    return CGBN_ERR_HIP;              // (no such variant: the plan takes its sizes from the same list)
+}
+
 bool eps_ok(float eps) { return std::isfinite(eps) && eps > 0.f; }
 
 #define CGBN_TRY(expr) do { cgbn_status s_ = (expr); if (s_ != CGBN_OK) return s_; } while (0)
@@ -1660,6 +1776,18 @@ cgbn_status forward_impl(const void* x, const void* shortcut, bool relu, int N, 
 
     const SlabPlan& wide = shortcut ? p.sfs : p.xf.ok ? p.xf : p.sf;
     const bool slab = p.t.fused && p.t.one_sweep_stats && wide.ok;
+    if (p.t.fused && p.flats[shortcut != nullptr] && !(slab && wide.first)) {
+        FlatArgs F = flat_args(p, ws);
+        F.x = x; F.dy = shortcut; F.out = y; F.gamma = gamma; F.beta = beta; F.eps = (double)eps;
+        F.mean = mean; F.mean_lo = mean_lo; F.invstd = invstd;
+        g_last_forward_fused = g_last_forward_flat = 1;
+        g_last_forward_slab = 0;
+        const bool f32 = p.dtype == CGBN_F32;
+        if (relu && shortcut) return f32 ? launch_flat_t<float, true, 2>(p, F, st) : launch_flat_t<bf16_t, true, 2>(p, F, st);
+        if (relu) return f32 ? launch_flat_t<float, true, 1>(p, F, st) : launch_flat_t<bf16_t, true, 1>(p, F, st);
+        return f32 ? launch_flat_t<float, true, 0>(p, F, st) : launch_flat_t<bf16_t, true, 0>(p, F, st);
+    }
+    g_last_forward_flat = 0;
     for (const FusedPlan* f : {&p.ef, &p.ff}) {
         if (!p.t.fused || !f->ok || (f == &p.ef && !p.edges[shortcut != nullptr]) || (slab && wide.first)) continue;
         FusedArgs F = fused_args(p, *f, ws);
@@ -1747,6 +1875,18 @@ cgbn_status backward_impl(const void* dy, const void* y, const void* x, const fl
 
     const SlabPlan& wide = relu ? (p.xbm.ok ? p.xbm : p.sbm) : p.xb.ok ? p.xb : p.sb;
     const bool slab = p.t.fused && wide.ok;
+    if (p.t.fused && p.flats[relu ? 3 : 2] && !(slab && wide.first)) {
+        FlatArgs F = flat_args(p, ws);
+        F.x = x; F.dy = dy; F.aux = y; F.out = dx; F.out2 = dshortcut; F.gamma = gamma;
+        F.mean = const_cast<float*>(mean); F.mean_lo = const_cast<float*>(mean_lo); F.invstd = const_cast<float*>(invstd);
+        F.dgamma = dgamma; F.dbeta = dbeta;
+        g_last_backward_fused = g_last_backward_flat = 1;
+        g_last_backward_slab = 0;
+        const bool f32 = p.dtype == CGBN_F32;
+        if (relu) return f32 ? launch_flat_t<float, false, 1>(p, F, st) : launch_flat_t<bf16_t, false, 1>(p, F, st);
+        return f32 ? launch_flat_t<float, false, 0>(p, F, st) : launch_flat_t<bf16_t, false, 0>(p, F, st);
+    }
+    g_last_backward_flat = 0;
     for (const FusedPlan* f : {&p.ebw, &p.fb}) {
         if (!p.t.fused || !f->ok || (f == &p.ebw && !p.edges[relu ? 3 : 2]) || (slab && wide.first)) continue;
         FusedArgs F = fused_args(p, *f, ws);
@@ -1911,6 +2051,7 @@ static long long* tuning_slot(const char* key)
     if (!std::strcmp(key, "stagger_us")) return &g_tune.stagger_us;
     if (!std::strcmp(key, "stagger_phases")) return &g_tune.stagger_phases;
     if (!std::strcmp(key, "wait_us")) return &g_tune.wait_us;
+    if (!std::strcmp(key, "flat")) return &g_tune.flat;
     return nullptr;
 }
 
@@ -1919,7 +2060,7 @@ cgbn_status cgbn_set_tuning(const char* key, long long value)
     long long* slot = tuning_slot(key);
     if (!slot) return CGBN_ERR_TUNING;
     if (slot == &g_tune.reverse || slot == &g_tune.nt_store || slot == &g_tune.fused || slot == &g_tune.one_sweep_stats ||
-        slot == &g_tune.cooperative || slot == &g_tune.big_lds || slot == &g_tune.stagger || slot == &g_tune.tiny_planes) {
+        slot == &g_tune.cooperative || slot == &g_tune.big_lds || slot == &g_tune.stagger || slot == &g_tune.tiny_planes || slot == &g_tune.flat) {
         if (value != 0 && value != 1) return CGBN_ERR_TUNING;
     } else if (slot == &g_tune.spin_limit) {
         if (value < 0 || value > 0xffffffffLL) return CGBN_ERR_TUNING;
@@ -2007,6 +2148,19 @@ long long cgbn_plan_get(int N, int C, int H, int W, cgbn_layout layout, cgbn_dty
         if (!std::strcmp(k, "R")) return s.R;
         return -1;
     }
+    if (!std::strncmp(key, "flat_", 5)) {
+        const char* k = key + 5;
+        if (!std::strcmp(k, "waves")) return p.flat.waves;
+        if (!std::strcmp(k, "LB")) return p.flat.LB;
+        if (!std::strcmp(k, "S")) return p.flat.S;
+        if (!std::strcmp(k, "vecs")) return p.flat.vecs;
+        if (!std::strcmp(k, "total")) return p.flat.total;
+        if (!std::strcmp(k, "fwd")) return p.flats[0];
+        if (!std::strcmp(k, "fwds")) return p.flats[1];
+        if (!std::strcmp(k, "bwd")) return p.flats[2];
+        if (!std::strcmp(k, "bwdm")) return p.flats[3];
+        return -1;
+    }
     if (!std::strcmp(key, "may_group")) return p.may_group;
     if (!std::strcmp(key, "group_sums")) return group_sums(p, false);
     if (!std::strcmp(key, "group_sums_dy")) return group_sums(p, true);
@@ -2063,6 +2217,8 @@ long long cgbn_get_tuning(const char* key)
     if (key && !std::strcmp(key, "last_forward_slab_vector")) return g_last_forward_slab.load();
     if (key && !std::strcmp(key, "last_backward_slab")) return g_last_backward_slab.load() != 0;
     if (key && !std::strcmp(key, "last_backward_slab_vector")) return g_last_backward_slab.load();
+    if (key && !std::strcmp(key, "last_forward_flat")) return g_last_forward_flat.load();
+    if (key && !std::strcmp(key, "last_backward_flat")) return g_last_backward_flat.load();
     if (key && !std::strcmp(key, "plans_made")) return g_plans_made;
     long long* slot = tuning_slot(key);
     if (!slot) return -1;

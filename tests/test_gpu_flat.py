@@ -1,0 +1,168 @@
+"""The flat kernels (NCHW channels that fit one wavefront's or one workgroup's registers): every size of vector and count of vectors a lane, one
+wavefront a channel and four, all directions, ragged last vectors, channels that leave a workgroup part empty, results over the inputs.
+Results against the float64 oracles, with the tolerances stated in gpu_harness.py.  And the small shapes of the other tests through the kernels that
+took them before."""
+
+import numpy as np
+import pytest
+import torch
+
+import gpu_harness as G
+from oracle import cgbn_oracle as O
+from oracle import cgbn_relu_oracle as R
+from paper_1711_07240_amd import cgbn as L
+from paper_1711_07240_amd import synth
+
+# N, C, H, W, dtype, K: vectors of 16, 8, 4 and 2 bytes; planes of one vector; totals just below, at and above what a count of vectors holds
+CASES = [
+    (1, 5, 8, 8, "f32", 1), (4, 16, 32, 32, "f32", 2), (8, 7, 16, 32, "f32", 4), (16, 9, 16, 64, "f32", 16), (8, 9, 24, 40, "f32", 2), (16, 3, 32, 32, "f32", 1), (3, 11, 16, 44, "f32", 3),
+    (3, 1026, 10, 10, "f32", 1), (2, 1030, 16, 20, "f32", 2), (5, 1025, 2, 4, "f32", 5), (61, 13, 2, 2, "f32", 61), (1, 1, 64, 256, "f32", 1),
+    (4, 10, 9, 14, "f32", 2), (7, 15, 26, 27, "f32", 7), (8, 9, 46, 43, "f32", 2), (2, 1027, 10, 13, "f32", 1), (3, 1025, 14, 19, "f32", 3), (1, 2, 2, 1, "f32", 1), (2, 1025, 21, 10, "f32", 2),
+    (1, 1027, 33, 36, "f32", 1), (2, 1026, 15, 38, "f32", 2), (1, 1029, 31, 38, "f32", 1),
+    (4, 6, 9, 15, "f32", 2), (5, 7, 27, 29, "f32", 5), (8, 9, 31, 33, "f32", 4), (2, 1027, 9, 11, "f32", 1), (2, 1026, 21, 25, "f32", 2), (1, 3, 7, 7, "f32", 1),
+    (4, 16, 32, 32, "bf16", 2), (8, 7, 32, 64, "bf16", 4), (16, 9, 32, 64, "bf16", 16), (3, 1026, 8, 8, "bf16", 1), (2, 1030, 24, 30, "bf16", 2), (2, 1031, 40, 31, "bf16", 1),
+    (4, 10, 18, 14, "bf16", 2), (7, 15, 26, 54, "bf16", 7), (8, 9, 46, 86, "bf16", 2), (2, 1027, 10, 14, "bf16", 1), (3, 1025, 14, 38, "bf16", 3), (2, 1025, 42, 22, "bf16", 2),
+    (1, 1027, 33, 72, "bf16", 1), (2, 1026, 15, 76, "bf16", 2), (2, 1026, 25, 49, "bf16", 1), (2, 1027, 23, 43, "bf16", 2),
+    (4, 6, 9, 30, "bf16", 2), (5, 7, 27, 58, "bf16", 5), (8, 9, 31, 66, "bf16", 4), (2, 1027, 9, 22, "bf16", 1), (2, 1026, 25, 42, "bf16", 2),
+    (4, 6, 23, 25, "bf16", 2), (5, 7, 35, 45, "bf16", 5), (2, 1027, 9, 11, "bf16", 1), (2, 1026, 25, 41, "bf16", 2), (1, 3, 23, 23, "bf16", 1),
+]
+ID = lambda c: "%dx%dx%dx%d-%s-k%d" % c
+DIRECTIONS = ("fwd", "fwds", "bwd", "bwdm")
+
+
+def _get(case, key):
+    return L.cgbn_plan_get(*case[:4], "NCHW", *case[4:], key)
+
+
+def _takes(case, d):
+    return _get(case, "flat_" + d) == 1 and not (_get(case, "s%s_ok" % d) and _get(case, "s%s_first" % d))
+
+
+def test_every_size_is_run():
+    run = {(c[4], _get(c, "flat_LB"), _get(c, "flat_S"), _get(c, "flat_waves"), d) for c in CASES for d in DIRECTIONS if _takes(c, d)}
+    one = [(16, 4), (16, 8), (8, 8), (8, 16), (4, 16), (4, 32)]
+    two = [(2, 16), (2, 32)]                       # bfloat16 alone
+    want = {(t, lb, s, w) for t in ("f32", "bf16") for w in (1, 4) for lb, s in one + [(16, 16), (8, 32)] * (w == 4) + two * (t == "bf16")}
+    for d in DIRECTIONS:
+        missing = want - {r[:4] for r in run if r[4] == d}
+        # (float masked backwards with 4-byte vectors are separate sweeps)
+        assert missing == ({("f32", 4, s, w) for s in (16, 32) for w in (1, 4)} if d == "bwdm" else set()), (d, missing)
+
+
+def test_plans():
+    r = np.random.default_rng(8)
+    taken = 0
+    for _ in range(5000):
+        dtype = "f32" if r.random() < 0.5 else "bf16"
+        eb = 4 if dtype == "f32" else 2
+        N, C = int(r.integers(1, 65)), int(np.exp(r.uniform(0, 8)))
+        H, W = int(np.exp(r.uniform(0, 5))), int(np.exp(r.uniform(0, 5)))
+        case = (N, C, H, W, dtype, N)
+        g = lambda k: _get(case, "flat_" + k)
+        plane = H * W * eb
+        if not g("waves"):
+            assert not any(g(d) for d in DIRECTIONS)
+            continue
+        taken += 1
+        LB, S, waves, vecs, total = (g(k) for k in ("LB", "S", "waves", "vecs", "total"))
+        assert plane % LB == 0 and (LB == 16 or plane % (2 * LB) != 0) and LB >= eb and vecs * LB == plane and total == N * vecs
+        assert total <= S * waves * 64 and S * max(LB, 4) // 4 in ((16, 32, 64) if LB >= 8 else (16, 32)) and waves in (1, 4)
+        assert S * max(LB, 4) // 4 == 16 or total > S // 2 * waves * 64
+        assert waves == 4 or S * max(LB, 4) // 4 <= 32
+        assert C * N * plane <= 2 ** 31 - 1 and vecs <= 0xffff
+        # the quotient by a multiplication is right for every vector
+        if vecs > 1:
+            magic = -(-2 ** 32 // vecs)
+            k = np.unique(np.r_[np.arange(min(total, 300)), np.arange(0, total, vecs), np.arange(vecs - 1, total, vecs), total - 1]).astype(np.uint64)
+            assert np.array_equal((k * np.uint64(magic)) >> np.uint64(32), k // np.uint64(vecs))
+    assert taken > 2000
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", CASES, ids=ID)
+def test_against_the_oracle(case):
+    N, C, H, W, dtype, K = case
+    print("[case] flat", case, flush=True)
+    r = np.random.default_rng(N * 1000 + C + H)
+    per = lambda a: a.reshape(1, -1, 1, 1)
+    x = (r.standard_normal((N, C, H, W), dtype=np.float32) * per(r.uniform(0.5, 2, C)) + per(r.uniform(-2, 2, C))).astype(np.float32)
+    dy, s = (r.standard_normal(x.shape, dtype=np.float32) for _ in range(2))
+    if dtype == "bf16":
+        x, dy, s = (synth.f32_to_bf16_bits(a) for a in (x, dy, s))
+    eps = 1e-5 if N * H * W > 2 else 0.5              # (two values: dx is a difference of nearly equal terms)
+    gamma, beta = r.uniform(0.5, 1.5, C).astype(np.float32), r.normal(0, 0.1, C).astype(np.float32)
+    p = G.Problem(x, dy, gamma, beta, eps, "NCHW", dtype, K)
+    p.ws.random_(0, 255)                              # whatever the workspace holds
+
+    def took(*directions):
+        torch.cuda.synchronize()
+        for d in directions:
+            assert not _takes(case, d) or L.cgbn_get_tuning("last_%s_flat" % ("forward" if d[0] == "f" else "backward")) == 1, d
+
+    p.forward()
+    error = L.cgbn_workspace_error_offset(N, C, H, W, "NCHW", dtype, K)
+    assert int(p.ws[error:error + 4].view(torch.int32).item()) == 0
+    p.backward()
+    took("fwd", "bwd")
+    wx, wdy = G.widen(x, dtype), G.widen(dy, dtype)
+    scale = np.sqrt(N * H * W) * G.rms(wdy)           # a channel's sums of gradients: judged on the size they have when nothing cancels
+    plain = p.results()
+    G.check_against_oracle(plain, O.cgbn_forward_backward_ref(wx, wdy, gamma, beta, eps, "NCHW"), dtype, str(case), sum_scale=scale)
+    sd, dz = G.to_dev(s), torch.empty_like(p.x)
+    for short in (None, sd):
+        L.cgbn_forward_relu(p.x, short, *p.shape_args, "NCHW", K, p.gamma, p.beta, eps, p.y, p.mean, p.invstd, dtype, p.mean_lo, p.ws)
+        L.cgbn_backward_relu(p.dy, p.y, p.x, p.mean, p.invstd, p.gamma, p.dx, None if short is None else dz, p.dgamma, p.dbeta, *p.shape_args, "NCHW", K,
+                             dtype, p.mean_lo, p.ws)
+        took("fwd" if short is None else "fwds", "bwdm")
+        got = p.results()
+        y, mean, invstd = R.cgbn_relu_forward_ref(wx, gamma, beta, eps, "NCHW", None if short is None else G.widen(s, dtype))[:3]
+        dx, dgamma, dbeta, dzr = R.cgbn_relu_backward_ref(wdy, got["y"], wx, mean, invstd, gamma, "NCHW")[:4]      # (masked by the stored output)
+        G.check_against_oracle(got, dict(y=y, mean=mean, invstd=invstd, dx=dx, dgamma=dgamma, dbeta=dbeta), dtype, str(case), sum_scale=scale)
+        if short is not None:
+            assert np.array_equal(G.to_host_f64(dz, dtype), dzr)
+    # dx over dy, y over x: the same bits
+    p.forward()
+    p.backward(dx=p.dy)
+    p.forward(y=p.x)
+    torch.cuda.synchronize()
+    assert np.array_equal(G.to_host_f64(p.dy, dtype), plain["dx"]) and np.array_equal(G.to_host_f64(p.x, dtype), plain["y"])
+
+
+@pytest.mark.gpu
+def test_nan_and_infinity_stay_in_their_channel():
+    r = np.random.default_rng(4)
+    x = r.standard_normal((4, 9, 16, 16)).astype(np.float32)
+    dy = r.standard_normal(x.shape).astype(np.float32)
+    x[1, 2, 3, 4], x[0, 5, 0, 0], dy[3, 7, 1, 1] = np.nan, np.inf, np.nan
+    p = G.Problem(x, dy, np.ones(9, np.float32), np.zeros(9, np.float32), 1e-5, "NCHW", "f32", 2)
+    p.forward()
+    p.backward()
+    got = p.results()
+    assert L.cgbn_get_tuning("last_forward_flat") == 1 and L.cgbn_get_tuning("last_backward_flat") == 1
+    for c in range(9):
+        finite = [bool(np.all(np.isfinite(got[k][:, c]))) for k in ("y", "dx")] + [bool(np.isfinite(got["invstd"][c]))]
+        assert finite == ([False, False, False] if c in (2, 5) else [True, False, True] if c == 7 else [True, True, True]), c
+
+
+@pytest.mark.gpu
+def test_every_small_shape_through_the_kernels_that_took_it_before():
+    from test_gpu_parity import BASE, SMALL
+    from test_gpu_relu import CASES as RELU, run_relu_case
+    import dataclasses
+    L.cgbn_set_tuning("flat", 0)
+    try:
+        for name, kw in SMALL:
+            wl = BASE.scaled(name=name, **kw)
+            d = synth.make_inputs(wl)
+            p = G.Problem(d["x"], d["dy"], d["gamma"], d["beta"], wl.eps, wl.layout, wl.dtype, wl.K)
+            p.forward()
+            p.backward()
+            ref = O.cgbn_forward_backward_ref(G.widen(d["x"], wl.dtype), G.widen(d["dy"], wl.dtype), d["gamma"].astype(np.float64),
+                                              d["beta"].astype(np.float64), wl.eps, wl.layout)
+            G.check_against_oracle(p.results(), ref, wl.dtype, name)
+            assert L.cgbn_get_tuning("last_forward_flat") == 0
+        for name, kw in RELU:
+            for short in (False, True):
+                run_relu_case(dataclasses.replace(BASE, name=name, **kw), name, short)
+    finally:
+        L.cgbn_set_tuning("flat", 1)
