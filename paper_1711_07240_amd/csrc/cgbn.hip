@@ -76,17 +76,31 @@ CGBN_FUSED_EDGE_BACKWARD(CGBN_DECL_BE)
     extern template __global__ void flat_forward<T_, LB_, S_, WAVES_, 2>(FlatArgs);             \
     extern template __global__ void flat_backward<T_, LB_, S_, WAVES_, 0>(FlatArgs);            \
     extern template __global__ void flat_backward<T_, LB_, S_, WAVES_, 1>(FlatArgs);
+#define CGBN_DECL_L8(LB_, S_)                                                                   \
+    extern template __global__ void flat_forward<float, LB_, S_, 4, 0>(FlatArgs);               \
+    extern template __global__ void flat_forward<float, LB_, S_, 4, 1>(FlatArgs);               \
+    extern template __global__ void flat_forward<float, LB_, S_, 4, 2>(FlatArgs);               \
+    extern template __global__ void flat_forward<bf16_t, LB_, S_, 4, 0>(FlatArgs);              \
+    extern template __global__ void flat_forward<bf16_t, LB_, S_, 4, 1>(FlatArgs);              \
+    extern template __global__ void flat_forward<bf16_t, LB_, S_, 4, 2>(FlatArgs);
+CGBN_FLAT_FOUR_FORWARD(CGBN_DECL_L8)
+#undef CGBN_DECL_L8
 #define CGBN_DECL_LF1(LB_, S_) CGBN_DECL_L(float, LB_, S_, 1)
 #define CGBN_DECL_LF4(LB_, S_) CGBN_DECL_L(float, LB_, S_, 4)
+#define CGBN_DECL_LF16(LB_, S_) CGBN_DECL_L(float, LB_, S_, 16)
 #define CGBN_DECL_LB1(LB_, S_) CGBN_DECL_L(bf16_t, LB_, S_, 1)
 #define CGBN_DECL_LB4(LB_, S_) CGBN_DECL_L(bf16_t, LB_, S_, 4)
-CGBN_FLAT_ONE(CGBN_DECL_LF1) CGBN_FLAT_FOUR(CGBN_DECL_LF4)
-CGBN_FLAT_ONE(CGBN_DECL_LB1) CGBN_FLAT_FOUR(CGBN_DECL_LB4) CGBN_FLAT_BF16(CGBN_DECL_LB1) CGBN_FLAT_BF16(CGBN_DECL_LB4)
+#define CGBN_DECL_LB16(LB_, S_) CGBN_DECL_L(bf16_t, LB_, S_, 16)
+CGBN_FLAT_ONE(CGBN_DECL_LF1) CGBN_FLAT_FOUR(CGBN_DECL_LF4) CGBN_FLAT_SIXTEEN(CGBN_DECL_LF16)
+CGBN_FLAT_ONE(CGBN_DECL_LB1) CGBN_FLAT_FOUR(CGBN_DECL_LB4) CGBN_FLAT_SIXTEEN(CGBN_DECL_LB16)
+CGBN_FLAT_BF16(CGBN_DECL_LB1) CGBN_FLAT_BF16(CGBN_DECL_LB4) CGBN_FLAT_BF16(CGBN_DECL_LB16)
 #undef CGBN_DECL_L
 #undef CGBN_DECL_LF1
 #undef CGBN_DECL_LF4
+#undef CGBN_DECL_LF16
 #undef CGBN_DECL_LB1
 #undef CGBN_DECL_LB4
+#undef CGBN_DECL_LB16
 // ... and the column-slab kernels in cgbn_slab_inst.hip
 #define CGBN_DECL_SF(P_, SOLO_)                                                                 \
     extern template __global__ void slab_forward<float, 0, P_, SOLO_, false>(SlabArgs);         \
@@ -217,7 +231,7 @@ struct FusedPlan {
 
 // Geometry of the flat path (see cgbn_flat.h); the same for both directions.
 struct FlatPlan {
-    int waves;            // wavefronts a channel (1 or 4), 0: the shape cannot take the path
+    int waves;            // wavefronts a channel (1, 4 or 16), 0: the shape cannot take the path
     int LB, S;            // bytes of a vector, vectors a lane
     int vecs, total;      // vectors of a plane, of a channel
 };
@@ -403,9 +417,17 @@ void make_fused_plan(const Tuning& T, int N, int C, long long HW, int K, int lay
 }
 
 
-// A channel's planes in one wavefront or in a workgroup of four: up to 64 registers a lane (16 KiB, 64 KiB), with 2- and 4-byte vectors 32.  One where
-// there are many short channels, us, one / four: forward 3 x 1954 planes of 14x22 fp32 4.7 / 6.0, 2 x 1848 of 27x40 bf16 5.9 / 6.8, 2 x 825 of 8x11 fp32
-// 3.4 / 4.0, 4 x 896 of 32x33 bf16 6.4 / 5.9, 8 x 680 of 14x17 fp32 5.2 / 5.1, 2 x 256 of 13x21 4.1 / 4.3; 2 x 512 of 25x42 bf16 backward 6.5 / 5.0, 2 x 2048 9.3 / 9.9.
+// A channel's planes in one wavefront, in a workgroup of four (up to 64 registers a lane: 16 KiB, 64 KiB; with 2- and 4-byte vectors 32) or in one of
+// sixteen (32: 128 KiB, with 2-byte vectors 64).  One where there are many short channels, us, one / four: forward 3 x 1954 planes of 14x22 fp32 4.7 / 6.0,
+// 2 x 1848 of 27x40 bf16 5.9 / 6.8, 2 x 825 of 8x11 fp32 3.4 / 4.0, 4 x 896 of 32x33 bf16 6.4 / 5.9, 8 x 680 of 14x17 fp32 5.2 / 5.1, 2 x 256 of 13x21
+// 4.1 / 4.3; 2 x 512 of 25x42 bf16 backward 6.5 / 5.0, 2 x 2048 9.3 / 9.9.
+// Sixteen, of which a compute unit holds one workgroup, where every channel has a compute unit: four with 64 registers / sixteen, 16 x 32 planes of 18x29
+// fp32 forward 6.0 / 5.0, 16 x 128 of 36x38 bf16 masked 10.6 / 8.5, 16 x 256 of 24x30 fp32 6.8 / 7.0 and 13.2 / 12.4, 16 x 512 10.5 / 10.7 and 19.1 / 23.1;
+// single-launch kernels with hand-overs / sixteen, 32 x 32 of 24x30 fp32 forward 8.7 / 5.6, backward 11.2 / 6.2, 32 x 256 15.0 / 11.2 and 21.5 / 13.8,
+// 16 x 256 of 29x50 bf16 11.1 / 8.5 and 12.7 / 10.5, 16 x 512 14.9 / 13.7 and 17.1 / 18.3.  And in waves of workgroups where the planes' vectors have 2 bytes,
+// which few other single-launch kernels take: 4 x 2000 of 63x65 47.7 / 40.1 and 73.1 / 55.8, 16 x 512 of 33x35 21.8 / 17.5 and 28.1 / 21.2, 16 x 800 29.0 / 29.9.
+// (The compute units of an MI355X, not of the device at hand: plans of NCHW planes beyond the column slabs' ask no device, see make_plan.)
+constexpr int kFlatUnits = 256;
 void make_flat_plan(int N, int C, long long HW, int eb, FlatPlan* f)
 {
     std::memset(f, 0, sizeof(*f));
@@ -413,15 +435,21 @@ void make_flat_plan(int N, int C, long long HW, int eb, FlatPlan* f)
     int LB = 16;
     while (plane % LB != 0) LB /= 2;
     if (LB < eb || plane / LB > 0xffff || (long long)N * C * plane > 0x7fffffffLL) return;
-    const long long channel = N * plane;
-    const long long total = N * (plane / LB);
-    const int waves = (channel <= 1024 || (channel <= 5000 && C >= 1024)) && total <= 32 * kWave ? 1 : kThreads / kWave;
-    const long long lane = (total + waves * kWave - 1) / (waves * kWave);
-    int S = 0;
+    const long long channel = N * plane, total = N * (plane / LB);
+    auto fits = [&](int waves) {
+        const long long lane = (total + waves * kWave - 1) / (waves * kWave);
+        int S = 0;
 #define CGBN_FLAT_FITS(LB_, S_) if (LB == LB_ && lane <= S_ && (S == 0 || S_ < S)) S = S_;
-    CGBN_FLAT_FOUR(CGBN_FLAT_FITS) CGBN_FLAT_BF16(CGBN_FLAT_FITS)
+        if (waves == 16) { CGBN_FLAT_SIXTEEN(CGBN_FLAT_FITS) } else { CGBN_FLAT_FOUR(CGBN_FLAT_FITS) CGBN_FLAT_FOUR_FORWARD(CGBN_FLAT_FITS) }
+        CGBN_FLAT_BF16(CGBN_FLAT_FITS)
 #undef CGBN_FLAT_FITS
-    if (S == 0) return;
+        return S;
+    };
+    int waves = (channel <= 1024 || (channel <= 5000 && C >= 1024)) && total <= 32 * kWave ? 1 : kThreads / kWave, S = fits(waves);
+    if (S == 0 || (flat_words(LB, S) > 32 && C <= kFlatUnits)) {
+        S = fits(waves = 16);
+        if (S == 0 || !(C <= kFlatUnits || (LB == 2 && (S == 16 || C <= 2 * kFlatUnits)))) return;
+    }
     f->waves = waves;
     f->LB = LB;
     f->S = S;
@@ -909,15 +937,14 @@ constexpr bool fused_built(bool f32, bool forward, int act, int LB, int LPPC)
 //   212 MB 144 / 131 (16 of 24x30: 147 MB 87.8 / 93.9, 230 MB 145 / 141); masked 26 MB 28.7 / 23.9, 35 MB 35.3 / 37.5, 62 MB 56.6 / 64.2, 88 MB 98.2 / 89.8 (2 of 60x64 bf16 77 MB 78.5 / 85.9); 16 of 24x30 masked 29 MB 32.5 / 30.5, 37 MB
 //   36.5 / 43.6, backward 46 MB 27.9 / 25.0, 60 MB 38.1 / 40.4.  (Non-temporal loads here: 18 MB backward 10.6 -> 12.8, masked 15.6 -> 20.0.)
 // - forwards of 64 registers a lane of such tensors: 16 of 24x30, 60 MB 28.5 / 19.7, 92 MB 37.1 / 40.6;
-// - backwards of 64 registers a lane of 8 bytes each, where a compute unit has several channels or few long planes: 16 of 18x29 fp32, 256 channels
-//   9.1 / 8.7, 400 11.7 / 12.0, 800 17.6 / 19.3; 4 of 52 of 50x45 6.5 / 6.7, 8 of 35 of 43x46 8.2 / 7.3.
-bool flat_pays(const FlatPlan& f, int C, long long plane_bytes, int cus, int direction)
+// - backwards of 64 registers a lane in 8-byte vectors: 16 of 18x29 fp32, 400 channels 11.7 / 12.0, 800 17.6 / 19.3.
+bool flat_pays(const FlatPlan& f, int C, int direction)
 {
     if (f.waves == 0) return false;
     const bool most = flat_words(f.LB, f.S) > 32;
     const long long bytes = (long long)f.total * f.LB * C;
-    if (direction >= 2 && f.LB == 8 && most) return C <= cus && plane_bytes <= 8192;
-    if (f.LB < 16 || direction == 1) return true;
+    if (direction >= 2 && f.LB == 8 && most) return false;
+    if (f.LB < 16 || f.waves == 16 || direction == 1) return true;
     if (direction == 0) return !most || bytes < 90000000LL;
     return direction == 2 ? bytes < 50000000LL || bytes > 160000000LL : bytes < 32000000LL || bytes > 85000000LL;
 }
@@ -945,8 +972,7 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
     p->S = S;
     p->M = (double)N * (double)HW;
     const int full_vec = 16 / p->eb;
-    if (layout == CGBN_NCHW && K <= kFusedMaxShards && T.flat) make_flat_plan(N, C, HW, p->eb, &p->flat);
-    if (layout == CGBN_NHWC || (C % full_vec == 0 && HW <= kSlabThreads) || (p->flat.LB == 8 && flat_words(8, p->flat.S) > 32)) {   // (else nothing needs it)
+    if (layout == CGBN_NHWC || (C % full_vec == 0 && HW <= kSlabThreads)) {       // (else neither sweeps nor slab plans need it)
         p->device = current_device();
         p->cus = compute_units(p->device);
     }
@@ -1039,9 +1065,11 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
         if (one.ok && (one.U == 1 ? layout == CGBN_NCHW || one.R > few_pixels(forward, true, one.row_bytes) : forward))
             make_slab_plan(N, C, HW, layout, p->eb, row_words, cus, forward ? p->ff : p->fb, forward, true, &two);
     }
+    // (the images that the single-launch kernels take: callers are told that calls of more are separate sweeps)
+    if (layout == CGBN_NCHW && N <= kFusedMaxRows && K <= kFusedMaxShards && T.flat) make_flat_plan(N, C, HW, p->eb, &p->flat);
     for (int i = 0; i < 4; ++i) {
         const FusedPlan& f = i < 2 ? p->ff : p->fb;
-        p->flats[i] = flat_pays(p->flat, C, HW * p->eb, cus, i) && !(f.ok && !fused_built(p->eb == 4, i < 2, i & 1, f.LB, f.LPPC));
+        p->flats[i] = flat_pays(p->flat, C, i) && !(f.ok && !fused_built(p->eb == 4, i < 2, i & 1, f.LB, f.LPPC));
     }
     if (layout == CGBN_NCHW) {
         make_narrow_plan(N, C, HW, p->eb, true, false, p->sf, cus, &p->nf);
@@ -1543,7 +1571,7 @@ FlatArgs flat_args(const Plan& p, char* ws)
 template <typename T, bool FWD, int ACT> cgbn_status launch_flat_t(const Plan& p, const FlatArgs& A, hipStream_t st)
 {
     const FlatPlan& f = p.flat;
-    const dim3 grid((unsigned)(f.waves == 1 ? (p.C + 3) / 4 : p.C)), block(kThreads);
+    const dim3 grid((unsigned)(f.waves == 1 ? (p.C + 3) / 4 : p.C)), block((unsigned)flat_threads(f.waves));
 #define CGBN_FLAT_CASE(LB_, S_, WAVES_)                                                                         \
     if (f.LB == LB_ && f.S == S_ && f.waves == WAVES_) {                                                        \
         if constexpr (FWD) hipLaunchKernelGGL((flat_forward<T, LB_, S_, WAVES_, ACT>), grid, block, 0, st, A);  \
@@ -1552,11 +1580,14 @@ template <typename T, bool FWD, int ACT> cgbn_status launch_flat_t(const Plan& p
     }
 #define CGBN_FLAT_CASE1(LB_, S_) CGBN_FLAT_CASE(LB_, S_, 1)
 #define CGBN_FLAT_CASE4(LB_, S_) CGBN_FLAT_CASE(LB_, S_, 4)
-    CGBN_FLAT_ONE(CGBN_FLAT_CASE1) CGBN_FLAT_FOUR(CGBN_FLAT_CASE4)
-    if constexpr (!std::is_same<T, float>::value) { CGBN_FLAT_BF16(CGBN_FLAT_CASE1) CGBN_FLAT_BF16(CGBN_FLAT_CASE4) }
+#define CGBN_FLAT_CASE16(LB_, S_) CGBN_FLAT_CASE(LB_, S_, 16)
+    CGBN_FLAT_ONE(CGBN_FLAT_CASE1) CGBN_FLAT_FOUR(CGBN_FLAT_CASE4) CGBN_FLAT_SIXTEEN(CGBN_FLAT_CASE16)
+    if constexpr (FWD) { CGBN_FLAT_FOUR_FORWARD(CGBN_FLAT_CASE4) }
+    if constexpr (!std::is_same<T, float>::value) { CGBN_FLAT_BF16(CGBN_FLAT_CASE1) CGBN_FLAT_BF16(CGBN_FLAT_CASE4) CGBN_FLAT_BF16(CGBN_FLAT_CASE16) }
 #undef CGBN_FLAT_CASE
 #undef CGBN_FLAT_CASE1
 #undef CGBN_FLAT_CASE4
+#undef CGBN_FLAT_CASE16
     return CGBN_ERR_HIP;              // (no such variant: the plan takes its sizes from the same list)
 }
 

@@ -7,7 +7,7 @@
 // its lanes (two in the forward).  Before / now in us, forward and backward: 4 images of 16 channels of 32x32 fp32 5.6 / 3.7 and 4.8 / 3.8; 2 of 1848 of
 // 27x40 bf16 14.6 / 5.9 and 12.9 / 7.5; 2 of 12000 of 24x24 fp32 59.8 / 18.0 and 47.4 / 35.0; 16 of 1720 of 14x22 bf16 22.5 / 9.8 and 18.4 / 11.0.
 //
-// A channel's 64 registers a lane are the most that leaves the masked backward its three tensors.  Vectors are the widest that a plane's bytes allow, so
+// With one or four wavefronts a channel, 64 registers a lane are the most that leaves the masked backward its three tensors; sixteen have 32.  Vectors are the widest that a plane's bytes allow, so
 // that every plane of a channel starts on one; which plane a vector lies in is a quotient by the plane's vectors, formed as a product's high half.
 #pragma once
 
@@ -39,6 +39,9 @@ struct FlatArgs {
 
 // registers of a lane's vectors of one tensor
 constexpr int flat_words(int LB, int S) { return S * (LB < 4 ? 4 : LB) / 4; }
+
+// threads of a workgroup: four channels of one wavefront each, or one channel of all its wavefronts
+constexpr int flat_threads(int waves) { return waves == 1 ? kThreads : waves * kWave; }
 
 // LB bytes as they are stored (2: one bfloat16, in the low half)
 template <int LB> struct FlatVector { typedef uint32_t V __attribute__((ext_vector_type(LB / 4))); };
@@ -107,13 +110,13 @@ template <int WAVES> __device__ __forceinline__ double flat_sum(double v, double
     return v;
 }
 
-// WAVES: wavefronts a channel, 1 or all of a workgroup's.  S: vectors a lane.
+// WAVES: wavefronts a channel, 1, 4 or 16.  S: vectors a lane.
 template <typename T, int LB, int S, int WAVES, int ACT>
-__global__ __launch_bounds__(kThreads, flat_words(LB, S) * (ACT == 2 ? 2 : 1) <= 64 ? 4 : 2) void flat_forward(FlatArgs A)
+__global__ __launch_bounds__(flat_threads(WAVES), flat_words(LB, S) * (ACT == 2 ? 2 : 1) <= 64 ? 4 : 2) void flat_forward(FlatArgs A)
 {
     typedef FlatUnit<T, LB, S> Unit;
     constexpr int E = Unit::E;
-    __shared__ double part[2][kThreads / kWave];
+    __shared__ double part[2][flat_threads(WAVES) / kWave];
     const int t = (int)threadIdx.x, w = uniform(t >> 6), block = slab_of_block(blockIdx.x, gridDim.x);
     if (blockIdx.x == 0 && t == 0) A.sync[1] = 0u;
     const int c = WAVES == 1 ? block * (kThreads / kWave) + w : block;
@@ -187,12 +190,12 @@ __global__ __launch_bounds__(kThreads, flat_words(LB, S) * (ACT == 2 ? 2 : 1) <=
 }
 
 template <typename T, int LB, int S, int WAVES, int ACT>
-__global__ __launch_bounds__(kThreads, flat_words(LB, S) * (ACT != 0 ? 3 : 2) <= 96 ? 4 : 2) void flat_backward(FlatArgs A)
+__global__ __launch_bounds__(flat_threads(WAVES), flat_words(LB, S) * (ACT != 0 ? 3 : 2) <= 96 ? 4 : 2) void flat_backward(FlatArgs A)
 {
     typedef FlatUnit<T, LB, S> Unit;
     typedef typename Unit::V V;
     constexpr int E = Unit::E;
-    __shared__ double part[2][kThreads / kWave];
+    __shared__ double part[2][flat_threads(WAVES) / kWave];
     const int t = (int)threadIdx.x, w = uniform(t >> 6), block = slab_of_block(blockIdx.x, gridDim.x);
     if (blockIdx.x == 0 && t == 0) A.sync[1] = 0u;
     const int c = WAVES == 1 ? block * (kThreads / kWave) + w : block;
@@ -263,9 +266,11 @@ __global__ __launch_bounds__(kThreads, flat_words(LB, S) * (ACT != 0 ? 3 : 2) <=
     }
 }
 
-// X(bytes of a vector, vectors a lane): one wavefront a channel, four.  2-byte vectors: bfloat16 alone.
+// X(bytes of a vector, vectors a lane): one wavefront a channel, four, sixteen.  2-byte vectors: bfloat16 alone.
 #define CGBN_FLAT_ONE(X) X(16, 4) X(16, 8) X(8, 8) X(8, 16) X(4, 16) X(4, 32)
-#define CGBN_FLAT_FOUR(X) CGBN_FLAT_ONE(X) X(16, 16) X(8, 32)
+#define CGBN_FLAT_FOUR(X) CGBN_FLAT_ONE(X) X(16, 16)
+#define CGBN_FLAT_FOUR_FORWARD(X) X(8, 32)
+#define CGBN_FLAT_SIXTEEN(X) CGBN_FLAT_ONE(X)
 #define CGBN_FLAT_BF16(X) X(2, 16) X(2, 32)
 
 }  // namespace cgbn

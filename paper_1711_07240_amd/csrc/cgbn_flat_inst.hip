@@ -15,13 +15,20 @@ namespace cgbn {
 #endif
 #define CGBN_X1(LB_, S_) CGBN_X(LB_, S_, 1)
 #define CGBN_X4(LB_, S_) CGBN_X(LB_, S_, 4)
+#define CGBN_X16(LB_, S_) CGBN_X(LB_, S_, 16)
 CGBN_FLAT_ONE(CGBN_X1)
 CGBN_FLAT_FOUR(CGBN_X4)
+#if CGBN_INST_FWD
+CGBN_FLAT_FOUR_FORWARD(CGBN_X4)
+#endif
+CGBN_FLAT_SIXTEEN(CGBN_X16)
 #if !CGBN_INST_F32
 CGBN_FLAT_BF16(CGBN_X1)
 CGBN_FLAT_BF16(CGBN_X4)
+CGBN_FLAT_BF16(CGBN_X16)
 #endif
 #undef CGBN_X
 #undef CGBN_X1
 #undef CGBN_X4
+#undef CGBN_X16
 }  // namespace cgbn

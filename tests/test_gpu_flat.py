@@ -1,5 +1,5 @@
 """The flat kernels (NCHW channels that fit one wavefront's or one workgroup's registers): every size of vector and count of vectors a lane, one
-wavefront a channel and four, all directions, ragged last vectors, channels that leave a workgroup part empty, results over the inputs.
+wavefront a channel, four and sixteen, all directions, ragged last vectors, channels that leave a workgroup part empty, results over the inputs.
 Results against the float64 oracles, with the tolerances stated in gpu_harness.py.  And the small shapes of the other tests through the kernels that
 took them before."""
 
@@ -17,6 +17,8 @@ from paper_1711_07240_amd import synth
 CASES = [
     (1, 5, 8, 8, "f32", 1), (4, 16, 32, 32, "f32", 2), (8, 7, 16, 32, "f32", 4), (16, 9, 16, 64, "f32", 16), (8, 9, 24, 40, "f32", 2), (16, 3, 32, 32, "f32", 1), (3, 11, 16, 44, "f32", 3),
     (3, 1026, 10, 10, "f32", 1), (2, 1030, 16, 20, "f32", 2), (5, 1025, 2, 4, "f32", 5), (61, 13, 2, 2, "f32", 61), (1, 1, 64, 256, "f32", 1),
+    (16, 260, 24, 30, "f32", 16), (16, 258, 18, 29, "f32", 8), (16, 16, 24, 30, "f32", 2), (32, 7, 36, 28, "f32", 16), (16, 5, 18, 29, "f32", 8), (33, 6, 18, 29, "f32", 33),
+    (13, 5, 27, 33, "f32", 13), (32, 6, 31, 33, "f32", 16),
     (4, 10, 9, 14, "f32", 2), (7, 15, 26, 27, "f32", 7), (8, 9, 46, 43, "f32", 2), (2, 1027, 10, 13, "f32", 1), (3, 1025, 14, 19, "f32", 3), (1, 2, 2, 1, "f32", 1), (2, 1025, 21, 10, "f32", 2),
     (1, 1027, 33, 36, "f32", 1), (2, 1026, 15, 38, "f32", 2), (1, 1029, 31, 38, "f32", 1),
     (4, 6, 9, 15, "f32", 2), (5, 7, 27, 29, "f32", 5), (8, 9, 31, 33, "f32", 4), (2, 1027, 9, 11, "f32", 1), (2, 1026, 21, 25, "f32", 2), (1, 3, 7, 7, "f32", 1),
@@ -24,6 +26,8 @@ CASES = [
     (4, 10, 18, 14, "bf16", 2), (7, 15, 26, 54, "bf16", 7), (8, 9, 46, 86, "bf16", 2), (2, 1027, 10, 14, "bf16", 1), (3, 1025, 14, 38, "bf16", 3), (2, 1025, 42, 22, "bf16", 2),
     (1, 1027, 33, 72, "bf16", 1), (2, 1026, 15, 76, "bf16", 2), (2, 1026, 25, 49, "bf16", 1), (2, 1027, 23, 43, "bf16", 2),
     (4, 6, 9, 30, "bf16", 2), (5, 7, 27, 58, "bf16", 5), (8, 9, 31, 66, "bf16", 4), (2, 1027, 9, 22, "bf16", 1), (2, 1026, 25, 42, "bf16", 2),
+    (16, 260, 36, 38, "bf16", 16), (16, 258, 18, 58, "bf16", 8), (16, 16, 24, 60, "bf16", 2), (32, 7, 36, 56, "bf16", 16), (16, 5, 18, 58, "bf16", 8), (33, 6, 18, 58, "bf16", 33),
+    (13, 5, 27, 66, "bf16", 13), (32, 6, 31, 66, "bf16", 16), (9, 300, 31, 33, "bf16", 3), (23, 4, 33, 43, "bf16", 23), (16, 270, 33, 35, "bf16", 8),
     (4, 6, 23, 25, "bf16", 2), (5, 7, 35, 45, "bf16", 5), (2, 1027, 9, 11, "bf16", 1), (2, 1026, 25, 41, "bf16", 2), (1, 3, 23, 23, "bf16", 1),
 ]
 ID = lambda c: "%dx%dx%dx%d-%s-k%d" % c
@@ -41,12 +45,13 @@ def _takes(case, d):
 def test_every_size_is_run():
     run = {(c[4], _get(c, "flat_LB"), _get(c, "flat_S"), _get(c, "flat_waves"), d) for c in CASES for d in DIRECTIONS if _takes(c, d)}
     one = [(16, 4), (16, 8), (8, 8), (8, 16), (4, 16), (4, 32)]
-    two = [(2, 16), (2, 32)]                       # bfloat16 alone
-    want = {(t, lb, s, w) for t in ("f32", "bf16") for w in (1, 4) for lb, s in one + [(16, 16), (8, 32)] * (w == 4) + two * (t == "bf16")}
     for d in DIRECTIONS:
-        missing = want - {r[:4] for r in run if r[4] == d}
-        # (float masked backwards with 4-byte vectors are separate sweeps)
-        assert missing == ({("f32", 4, s, w) for s in (16, 32) for w in (1, 4)} if d == "bwdm" else set()), (d, missing)
+        want = set()
+        for t in ("f32", "bf16"):
+            sizes = one + [(2, 16), (2, 32)] * (t == "bf16")             # (float masked backwards with 4-byte vectors are separate sweeps)
+            want |= {(t, lb, s, w) for w in (1, 4, 16) for lb, s in sizes if not (d == "bwdm" and t == "f32" and lb == 4)}
+            want |= {(t, 16, 16, 4)} | ({(t, 8, 32, 4)} if d[0] == "f" else set())
+        assert {r[:4] for r in run if r[4] == d} == want, d
 
 
 def test_plans():
@@ -66,9 +71,10 @@ def test_plans():
         taken += 1
         LB, S, waves, vecs, total = (g(k) for k in ("LB", "S", "waves", "vecs", "total"))
         assert plane % LB == 0 and (LB == 16 or plane % (2 * LB) != 0) and LB >= eb and vecs * LB == plane and total == N * vecs
-        assert total <= S * waves * 64 and S * max(LB, 4) // 4 in ((16, 32, 64) if LB >= 8 else (16, 32)) and waves in (1, 4)
+        assert total <= S * waves * 64 and S * max(LB, 4) // 4 in ((16, 32, 64) if LB >= 8 else (16, 32)) and waves in (1, 4, 16)
         assert S * max(LB, 4) // 4 == 16 or total > S // 2 * waves * 64
         assert waves == 4 or S * max(LB, 4) // 4 <= 32
+        assert waves != 16 or total > (8192 if LB == 2 else 32768 // LB)
         assert C * N * plane <= 2 ** 31 - 1 and vecs <= 0xffff
         # the quotient by a multiplication is right for every vector
         if vecs > 1:
