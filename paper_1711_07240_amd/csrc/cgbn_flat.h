@@ -193,7 +193,6 @@ template <typename T, int LB, int S, int WAVES, int ACT>
 __global__ __launch_bounds__(flat_threads(WAVES), flat_words(LB, S) * (ACT != 0 ? 3 : 2) <= 96 ? 4 : 2) void flat_backward(FlatArgs A)
 {
     typedef FlatUnit<T, LB, S> Unit;
-    typedef typename Unit::V V;
     constexpr int E = Unit::E;
     __shared__ double part[2][flat_threads(WAVES) / kWave];
     const int t = (int)threadIdx.x, w = uniform(t >> 6), block = slab_of_block(blockIdx.x, gridDim.x);
