@@ -426,6 +426,9 @@ void make_fused_plan(const Tuning& T, int N, int C, long long HW, int K, int lay
 // single-launch kernels with hand-overs / sixteen, 32 x 32 of 24x30 fp32 forward 8.7 / 5.6, backward 11.2 / 6.2, 32 x 256 15.0 / 11.2 and 21.5 / 13.8,
 // 16 x 256 of 29x50 bf16 11.1 / 8.5 and 12.7 / 10.5, 16 x 512 14.9 / 13.7 and 17.1 / 18.3.  And in waves of workgroups where the planes' vectors have 2 bytes,
 // which few other single-launch kernels take: 4 x 2000 of 63x65 47.7 / 40.1 and 73.1 / 55.8, 16 x 512 of 33x35 21.8 / 17.5 and 28.1 / 21.2, 16 x 800 29.0 / 29.9.
+// Two waves of them with 16-byte vectors too, whose other kernels have the most rows to hand over: forward, with a shortcut and backward, 32 x 300 of 24x30
+// fp32 16.6 / 12.8, 29.1 / 17.9, 24.5 / 17.7; 32 x 512 20.2 / 16.5, 34.4 / 27.2, 36.3 / 27.6; 32 x 512 of 36x46 bf16 25.2 / 19.9, 42.6 / 39.4, 43.0 / 39.0; 4 x 512
+// of 96x100 bf16 18.4 / 16.3, 29.3 / 26.0, 23.9 / 23.7.  32 x 800 of 24x32 fp32 33.6 / 37.2, 60.4 / 56.4, 55.7 / 55.7.
 // (The compute units of an MI355X, not of the device at hand: plans of NCHW planes beyond the column slabs' ask no device, see make_plan.)
 constexpr int kFlatUnits = 256;
 void make_flat_plan(int N, int C, long long HW, int eb, FlatPlan* f)
@@ -448,7 +451,7 @@ void make_flat_plan(int N, int C, long long HW, int eb, FlatPlan* f)
     int waves = (channel <= 1024 || (channel <= 5000 && C >= 1024)) && total <= 32 * kWave ? 1 : kThreads / kWave, S = fits(waves);
     if (S == 0 || (flat_words(LB, S) > 32 && C <= kFlatUnits)) {
         S = fits(waves = 16);
-        if (S == 0 || !(C <= kFlatUnits || (LB == 2 && (S == 16 || C <= 2 * kFlatUnits)))) return;
+        if (S == 0 || C > kFlatUnits && !(C <= 2 * kFlatUnits ? LB == 16 || LB == 2 : LB == 2 && S == 16)) return;
     }
     f->waves = waves;
     f->LB = LB;
@@ -937,6 +940,8 @@ constexpr bool fused_built(bool f32, bool forward, int act, int LB, int LPPC)
 //   212 MB 144 / 131 (16 of 24x30: 147 MB 87.8 / 93.9, 230 MB 145 / 141); masked 26 MB 28.7 / 23.9, 35 MB 35.3 / 37.5, 62 MB 56.6 / 64.2, 88 MB 98.2 / 89.8 (2 of 60x64 bf16 77 MB 78.5 / 85.9); 16 of 24x30 masked 29 MB 32.5 / 30.5, 37 MB
 //   36.5 / 43.6, backward 46 MB 27.9 / 25.0, 60 MB 38.1 / 40.4.  (Non-temporal loads here: 18 MB backward 10.6 -> 12.8, masked 15.6 -> 20.0.)
 // - forwards of 64 registers a lane of such tensors: 16 of 24x30, 60 MB 28.5 / 19.7, 92 MB 37.1 / 40.6;
+// - masked backwards of sixteen wavefronts a channel, 16-byte vectors, of such tensors: 32 x 300 of 24x30 fp32, 28 MB 32.3 / 30.6, 384 36 MB 35.8 / 42.5,
+//   4 x 300 of 96x100 bf16, 23 MB 26.9 / 24.1, 384 30 MB 31.2 / 33.7, 512 36.1 / 48.9;
 // - backwards of 64 registers a lane in 8-byte vectors: 16 of 18x29 fp32, 400 channels 11.7 / 12.0, 800 17.6 / 19.3.
 bool flat_pays(const FlatPlan& f, int C, int direction)
 {
@@ -944,7 +949,8 @@ bool flat_pays(const FlatPlan& f, int C, int direction)
     const bool most = flat_words(f.LB, f.S) > 32;
     const long long bytes = (long long)f.total * f.LB * C;
     if (direction >= 2 && f.LB == 8 && most) return false;
-    if (f.LB < 16 || f.waves == 16 || direction == 1) return true;
+    if (f.LB < 16 || direction == 1) return true;
+    if (f.waves == 16) return direction != 3 || bytes < 28500000LL;
     if (direction == 0) return !most || bytes < 90000000LL;
     return direction == 2 ? bytes < 50000000LL || bytes > 160000000LL : bytes < 32000000LL || bytes > 85000000LL;
 }

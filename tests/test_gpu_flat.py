@@ -18,7 +18,7 @@ CASES = [
     (1, 5, 8, 8, "f32", 1), (4, 16, 32, 32, "f32", 2), (8, 7, 16, 32, "f32", 4), (16, 9, 16, 64, "f32", 16), (8, 9, 24, 40, "f32", 2), (16, 3, 32, 32, "f32", 1), (3, 11, 16, 44, "f32", 3),
     (3, 1026, 10, 10, "f32", 1), (2, 1030, 16, 20, "f32", 2), (5, 1025, 2, 4, "f32", 5), (61, 13, 2, 2, "f32", 61), (1, 1, 64, 256, "f32", 1),
     (16, 260, 24, 30, "f32", 16), (16, 258, 18, 29, "f32", 8), (16, 16, 24, 30, "f32", 2), (32, 7, 36, 28, "f32", 16), (16, 5, 18, 29, "f32", 8), (33, 6, 18, 29, "f32", 33),
-    (13, 5, 27, 33, "f32", 13), (32, 6, 31, 33, "f32", 16),
+    (17, 300, 24, 41, "f32", 17), (13, 5, 27, 33, "f32", 13), (32, 6, 31, 33, "f32", 16),
     (4, 10, 9, 14, "f32", 2), (7, 15, 26, 27, "f32", 7), (8, 9, 46, 43, "f32", 2), (2, 1027, 10, 13, "f32", 1), (3, 1025, 14, 19, "f32", 3), (1, 2, 2, 1, "f32", 1), (2, 1025, 21, 10, "f32", 2),
     (1, 1027, 33, 36, "f32", 1), (2, 1026, 15, 38, "f32", 2), (1, 1029, 31, 38, "f32", 1),
     (4, 6, 9, 15, "f32", 2), (5, 7, 27, 29, "f32", 5), (8, 9, 31, 33, "f32", 4), (2, 1027, 9, 11, "f32", 1), (2, 1026, 21, 25, "f32", 2), (1, 3, 7, 7, "f32", 1),
