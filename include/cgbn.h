@@ -46,8 +46,9 @@
  *     set the "cooperative" knob first: their single-launch kernels wait for sibling
  *     workgroups, and two such grids dispatched together could each end up half resident and
  *     starve the other until the bounded waits give up (error word set, NaN statistics).
- *     (Calls that take the column-slab kernels are exempt: no wait of theirs needs its siblings
- *     resident, see the knob "last_forward_slab" for which calls those are.)
+ *     (Calls that take the column-slab or the flat kernels are exempt: no wait of the former needs its
+ *     siblings resident and the latter have none, see "last_forward_slab" and "last_forward_flat" for
+ *     which calls those are.)
  *     A workspace must never be shared by calls that can overlap.
  *   - Results are bitwise reproducible run to run (fixed summation order, no
  *     floating-point atomics) and depend on K only through rounding.
@@ -265,8 +266,8 @@ const char* cgbn_status_string(cgbn_status status);
  * CGBN_ERR_WORKSPACE before launching anything).
  *   "chunk_bytes"      NCHW: bytes of one plane handled by one workgroup
  *   "wave_plane_bytes" NCHW: planes up to this size are handled by one wavefront
- *   "flat"             0/1 (default 1): NCHW channels that fit one workgroup's registers (up to 64 KiB) go through the
- *                      flat kernels, one launch with nothing handed over.
+ *   "flat"             0/1 (default 1): NCHW channels that fit one workgroup's registers (up to 64 KiB; 128 KiB where
+ *                      channels are few) go through the flat kernels, one launch with nothing handed over
  *   "tiny_planes"      0/1 (default 1): NCHW planes of at most 2 KiB, C a multiple of 8: a workgroup of the
  *                      multi-sweep kernels takes a run of 8 ... 256 planes of consecutive channels at once
  *   "piece_bytes"      NHWC reductions: bytes of one pixel range handled by one workgroup (0, the default:
@@ -311,7 +312,8 @@ cgbn_status cgbn_set_tuning(const char* key, long long value);
  * cgbn_forward / cgbn_backward took the single-launch NCHW kernels), "last_forward_slab",
  * "last_backward_slab" (1 if it took the column-slab kernels), "last_forward_slab_vector",
  * "last_backward_slab_vector" (the bytes of their vectors, 16 or 8, or 0), "plans_made" (launch plans the calling thread has
- * made: calls come back to the last ones it keeps) */
+ * made: calls come back to the last ones it keeps), "last_forward_flat", "last_backward_flat" (1 if it took the flat
+ * kernels; "last_forward_fused" is 1 then too) */
 long long cgbn_get_tuning(const char* key);
 
 /* One number of the launch plan the library would use for this problem under the current
