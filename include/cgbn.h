@@ -334,7 +334,8 @@ long long cgbn_get_tuning(const char* key);
  * Single-launch kernels, prefix "fwd_" or "bwd_": "ok" (the shape qualifies), "LB" (bytes per
  * access), "LPPC" (register slots per small plane; 0: large planes), "LPP" (slots a plane fills),
  * "IPU" (images per unit), "U" (units per channel), "tp" / "TL" (tiles per large plane, tile
- * elements), "rows", "rps", "G", "big" (0, or which LDS variant), "total_units".
+ * elements), "rows", "rps", "G", "big" (0, or which LDS variant), "total_units", "last_plane" (byte offset of a unit's last plane
+ * from its first).
  * Column-slab kernels, prefix "sfwd_" or "sbwd_" ("sfwds_": the forward with a shortcut, "sbwdm_": the masked backward): "ok" (the shape takes them instead of
  * sweeps), "first" (... also before the single-launch NCHW kernels), "vecs" (16-byte vectors per row of
  * the matrix), "R" (its rows), "cpc" (columns per channel), "cols" (vectors per slab), "slabs", "nch" (channels per slab, rounded up to a power of two), "rpp" (rows per pass),

@@ -338,7 +338,7 @@ void make_fused_plan(const Tuning& T, int N, int C, long long HW, int K, int lay
         f->U = (N + per_unit - 1) / per_unit;
         f->IPU = (N + f->U - 1) / f->U;
         // byte offsets inside a unit are 32-bit
-        if ((long long)f->IPU * C * HW * eb > 0x7fffffffLL) return;
+        if ((long long)f->IPU * C * plane * eb > 0x7fffffffLL) return;
         f->rows = N;
         f->rps = ips;
     } else if (LB >= 8 && small_edges_or_plain && HW <= (long long)(R + lds_words / W) * kWave * E) {
@@ -348,7 +348,7 @@ void make_fused_plan(const Tuning& T, int N, int C, long long HW, int K, int lay
         f->LPPC = R + lds_words / W;
         f->U = (N + 3) / 4;
         f->IPU = (N + f->U - 1) / f->U;
-        if ((long long)f->IPU * C * HW * eb > 0x7fffffffLL) return;
+        if ((long long)f->IPU * C * plane * eb > 0x7fffffffLL) return;
         f->rows = N;
         f->rps = ips;
     } else {
@@ -2162,6 +2162,8 @@ long long cgbn_plan_get(int N, int C, int H, int W, cgbn_layout layout, cgbn_dty
         if (!std::strcmp(k, "G")) return f.G;
         if (!std::strcmp(k, "big")) return f.big;
         if (!std::strcmp(k, "total_units")) return f.total_units;
+        // as the kernels form it: where the last plane of a unit that holds several begins
+        if (!std::strcmp(k, "last_plane")) return f.LPPC == 0 ? 0 : (long long)cgbn_plane_offset((f.LPPC > 0 ? f.IPU : -f.LPPC) - 1, fused_args(p, f, nullptr).plane_stride);
         return -1;
     }
     if ((key[0] == 's' || key[0] == 'n' || key[0] == 'x') && (!std::strncmp(key + 1, "fwd_", 4) || !std::strncmp(key + 1, "bwd_", 4) ||

@@ -108,7 +108,7 @@ struct FusedArgs {
     unsigned spin_limit;
     unsigned long long wait_ticks;            // 100 MHz ticks after which a wait gives up
     unsigned stagger_ticks, stagger_phases;   // start-up delay between channel slots (100 MHz ticks; 0 = none)
-    unsigned plane_stride; // small planes: bytes between the same channel's planes of consecutive images
+    unsigned plane_stride; // small planes, several planes a workgroup: bytes between the same channel's planes of consecutive images
 };
 
 constexpr unsigned kRowSentinel = 0xffffffffu;
@@ -667,7 +667,7 @@ struct Slots {
         const int l = SMALL ? t & (kWave - 1) : t, i = (l & 7) * (int)sizeof(T);
         const int pl = SMALL ? 4 * k + (l >> 4) : l >> 4, n = SMALL ? w + 4 * pl : pl;
         const bool behind = (l & 8) != 0;
-        off = (long long)((unsigned)n * (SMALL || WGP ? A.plane_stride : 0u)) + (behind ? g.len + i : i - g.head);
+        off = (SMALL || WGP ? (long long)cgbn_plane_offset(n, A.plane_stride) : 0LL) + (behind ? g.len + i : i - g.head);
         return i < (behind ? g.tail : g.head) && pl < PLANES && g.n0 + n < g.n1;
     }
     static __device__ __forceinline__ unsigned lane_offset(int t)
@@ -694,8 +694,8 @@ struct Slots {
     // uniform byte offset of the slot's plane from the unit's base
     static __device__ __forceinline__ size_t plane_base(const FusedArgs& A, int s, int w)
     {
-        if (SMALL) return (size_t)(w + 4 * (s / SPP)) * A.plane_stride;
-        if (WGP) return (size_t)(s / SPW) * A.plane_stride;
+        if (SMALL) return cgbn_plane_offset(w + 4 * (s / SPP), A.plane_stride);
+        if (WGP) return cgbn_plane_offset(s / SPW, A.plane_stride);
         return 0;
     }
     static constexpr int slot_offset(int s)

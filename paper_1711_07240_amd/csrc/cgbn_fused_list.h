@@ -6,6 +6,8 @@
 // tile each per workgroup.  X(LB, LPPC).
 #pragma once
 
+#include <cstddef>
+
 #define CGBN_FUSED_COMMON_WIDE(X)                                                             \
     X(16, 0) X(8, 0) X(16, -2)                                                                \
     X(16, 2) X(16, 3) X(16, 4) X(16, 5) X(16, 6) X(16, 8) X(16, 10) X(16, 12) X(16, 16)       \
@@ -67,3 +69,6 @@ constexpr int cgbn_full_slots(int lppc, int R)
     }
     return prev * 16 >= R ? prev : 0;
 }
+
+// Byte offset of a unit's n-th plane from its first.  A stride fits 32 bits, n of them need not: two images of 2.2 GiB are beyond.
+constexpr size_t cgbn_plane_offset(int n, unsigned plane_stride) { return (size_t)n * plane_stride; }

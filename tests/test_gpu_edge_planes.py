@@ -137,6 +137,86 @@ def test_with_the_ordinary_lds_split(case):
         L.cgbn_set_tuning("big_lds", 1)
 
 
+# images so large that a unit's planes lie further apart than 32 bits reach: planes that share a workgroup forward (four, three) and backward (three)
+FAR = [(4, 40000, 99, 101, "f32", 1), (4, 40000, 141, 141, "bf16", 1), (3, 60000, 151, 151, "bf16", 1), (3, 80000, 81, 85, "f32", 1), (3, 80000, 117, 119, "bf16", 1)]
+
+
+def test_planes_further_apart_than_32_bits():
+    """Where a unit's last plane begins, formed as the kernels form it, is that many images on."""
+    far = 0
+    r = np.random.default_rng(5)
+    cases = FAR + [(int(r.integers(2, 7)), int(r.integers(20000, 90000)), int(r.integers(60, 160)), int(r.integers(60, 160)), t, 1) for t in ("f32", "bf16") for _ in range(200)]
+    for case in cases:
+        N, C, H, W, dtype, _ = case
+        image = C * H * W * (4 if dtype == "f32" else 2)
+        for d in ("fwd", "bwd", "efwd", "ebwd"):
+            g = lambda k: L.cgbn_plan_get(N, C, H, W, "NCHW", dtype, 1, d + "_" + k)
+            if g("ok") == 1:
+                planes = 1 if g("LPPC") == 0 else g("IPU") if g("LPPC") > 0 else -g("LPPC")
+                assert g("last_plane") == (planes - 1) * image, (case, d)
+                far += d[0] == "e" and g("last_plane") + image > 2 ** 32
+                if g("LPPC") > 0:
+                    assert planes * image < 2 ** 31
+    assert far > 20 and all(any(_variant(c, d) for d in DIRECTIONS) for c in FAR)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [FAR[0], FAR[3]], ids=ID)
+def test_planes_further_apart_than_32_bits_on_the_device(case):
+    """Every value of every output against plain torch in float64, some channels at a time."""
+    N, C, H, W, dtype, K = case
+    print("[case] planes far apart", case, flush=True)
+    gen = torch.Generator(device=G.DEV).manual_seed(9)
+    x, dy, s = (torch.empty(N, C, H, W, device=G.DEV).normal_(generator=gen) for _ in range(3))
+    per = lambda: torch.empty(C, device=G.DEV)
+    gamma, beta = per().uniform_(0.5, 1.5, generator=gen), per().normal_(generator=gen)
+    mean, invstd, mean_lo, dgamma, dbeta = (per() for _ in range(5))
+    out, dz = torch.full_like(x, 7.0), torch.full_like(x, 7.0)
+    ws = torch.empty(L.cgbn_workspace_bytes(N, C, H, W, "NCHW", dtype, K), dtype=torch.uint8, device=G.DEV)
+    col = lambda t, c: t[c].double().view(1, -1, 1, 1)
+    sums = lambda t: t.flatten(2).sum(2).sum(0)
+    chunks = [slice(c, c + 1000) for c in range(0, C, 1000)]
+
+    def worst(got, want):                       # (NaN: fails too)
+        e = float((got.double() - want).abs().max())
+        assert e <= 1e-4, (case, e)
+
+    stats = {}
+    for shortcut in (None, s):
+        if shortcut is None:
+            L.cgbn_forward(x, N, C, H, W, "NCHW", K, gamma, beta, 1e-5, out, mean, invstd, dtype, mean_lo, ws)
+        else:
+            L.cgbn_forward_relu(x, shortcut, N, C, H, W, "NCHW", K, gamma, beta, 1e-5, out, mean, invstd, dtype, mean_lo, ws)
+        for c in chunks:
+            a = x[:, c].double()
+            m = sums(a) / (N * H * W)
+            a -= m.view(1, -1, 1, 1)
+            i = 1 / torch.sqrt(sums(a * a) / (N * H * W) + 1e-5)
+            worst(mean[c], m)
+            worst(invstd[c], i)
+            a = a * i.view(1, -1, 1, 1) * col(gamma, c) + col(beta, c)
+            worst(out[:, c], a if shortcut is None else (a + shortcut[:, c].double()).clamp_(min=0))
+            stats[c.start] = (m, i)
+    y = out.clone()
+    for masked in (False, True):
+        out.fill_(7.0)
+        if masked:
+            L.cgbn_backward_relu(dy, y, x, mean, invstd, gamma, out, dz, dgamma, dbeta, N, C, H, W, "NCHW", K, dtype, mean_lo, ws)
+        else:
+            L.cgbn_backward(dy, x, mean, invstd, gamma, out, dgamma, dbeta, N, C, H, W, "NCHW", K, dtype, mean_lo, ws)
+        for c in chunks:
+            m, i = (v.view(1, -1, 1, 1) for v in stats[c.start])
+            g, h = dy[:, c].double(), (x[:, c].double() - m) * i
+            if masked:
+                g *= y[:, c] > 0
+                assert torch.equal(dz[:, c].double(), g)
+            db, dg = sums(g), sums(g * h)
+            root = (N * H * W) ** 0.5
+            worst(dbeta[c] / root, db / root)
+            worst(dgamma[c] / root, dg / root)
+            worst(out[:, c], (g - (db / root ** 2).view(1, -1, 1, 1) - h * (dg / root ** 2).view(1, -1, 1, 1)) * i * col(gamma, c))
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_the_plan_holds_every_plane(dtype):
     """Slots hold the whole vectors of a plane wherever it starts, the slots read without a look are full, rows fit what the workspace has, and the calls
