@@ -933,7 +933,9 @@ constexpr bool fused_built(bool f32, bool forward, int act, int LB, int LPPC)
 
 // The flat kernels take what fits them (60 shapes of random sizes up to 60 MB, 1.60 / 1.39 / 1.89 / 1.43 times as fast forward / backward / with a shortcut / masked in the geometric mean
 // as the single-launch kernels and sweeps in their place), but for
-// - masked backwards that have no single-launch kernel with their vectors (see fused_built, callers are told that those are separate sweeps);
+// - masked backwards of float planes with 4-byte vectors whose plain backward the single-launch kernels take and whose masked one they are not built
+//   for (see fused_built: separate sweeps).  Those whose plain backward they do not take either (planes of more than 4096 values, tiny ones in many
+//   images) and those they are built for (24 slots) are flat;
 // - backwards with 16-byte vectors of tensors that just outgrow the last-level cache (256 MB, of which a backward's three tensors take three tensors' bytes,
 //   a masked one's five): there the single-launch kernels, whose loads are non-temporal and go ahead of the stores, keep more of their inputs
 //   cached between calls.  Old / flat in us, 8 images of 23x24 fp32: backward of 44 MB 27.6 / 23.0, 62 MB 35.9 / 39.0, 88 MB 49.1 / 54.2, 141 MB 88.1 / 87.9,

@@ -29,6 +29,9 @@ CASES = [
     (16, 260, 36, 38, "bf16", 16), (16, 258, 18, 58, "bf16", 8), (16, 16, 24, 60, "bf16", 2), (32, 7, 36, 56, "bf16", 16), (16, 5, 18, 58, "bf16", 8), (33, 6, 18, 58, "bf16", 33),
     (13, 5, 27, 66, "bf16", 13), (32, 6, 31, 66, "bf16", 16), (9, 300, 31, 33, "bf16", 3), (23, 4, 33, 43, "bf16", 23), (16, 270, 33, 35, "bf16", 8),
     (4, 6, 23, 25, "bf16", 2), (5, 7, 35, 45, "bf16", 5), (2, 1027, 9, 11, "bf16", 1), (2, 1026, 25, 41, "bf16", 2), (1, 3, 23, 23, "bf16", 1),
+    # masked backwards of float planes with 4-byte vectors: planes too long for a wavefront, of 24 slots, and tiny ones in many images
+    (1, 64, 65, 65, "f32", 1), (2, 64, 65, 65, "f32", 2), (3, 217, 45, 129, "f32", 1), (2, 1667, 11, 129, "f32", 1), (1, 2096, 21, 53, "f32", 1),
+    (200, 8, 7, 7, "f32", 5), (163, 16, 7, 7, "f32", 1), (375, 8, 11, 5, "f32", 3),
 ]
 ID = lambda c: "%dx%dx%dx%d-%s-k%d" % c
 DIRECTIONS = ("fwd", "fwds", "bwd", "bwdm")
@@ -48,15 +51,16 @@ def test_every_size_is_run():
     for d in DIRECTIONS:
         want = set()
         for t in ("f32", "bf16"):
-            sizes = one + [(2, 16), (2, 32)] * (t == "bf16")             # (float masked backwards with 4-byte vectors are separate sweeps)
-            want |= {(t, lb, s, w) for w in (1, 4, 16) for lb, s in sizes if not (d == "bwdm" and t == "f32" and lb == 4)}
+            sizes = one + [(2, 16), (2, 32)] * (t == "bf16")
+            # (masked, float, sixteen 4-byte vectors, one wavefront a channel: such calls are column slabs or separate sweeps)
+            want |= {(t, lb, s, w) for w in (1, 4, 16) for lb, s in sizes if (d, t, lb, s, w) != ("bwdm", "f32", 4, 16, 1)}
             want |= {(t, 16, 16, 4)} | ({(t, 8, 32, 4)} if d[0] == "f" else set())
         assert {r[:4] for r in run if r[4] == d} == want, d
 
 
 def test_plans():
     r = np.random.default_rng(8)
-    taken = 0
+    taken = narrow = 0
     for _ in range(5000):
         dtype = "f32" if r.random() < 0.5 else "bf16"
         eb = 4 if dtype == "f32" else 2
@@ -70,6 +74,10 @@ def test_plans():
             continue
         taken += 1
         LB, S, waves, vecs, total = (g(k) for k in ("LB", "S", "waves", "vecs", "total"))
+        if dtype == "f32" and LB == 4:
+            # masked: separate sweeps where the single-launch kernels take the plain backward and are not built for the masked one
+            assert g("bwdm") == (_get(case, "bwd_ok") == 0 or _get(case, "bwd_LPPC") == 24), case
+            narrow += g("bwdm")
         assert plane % LB == 0 and (LB == 16 or plane % (2 * LB) != 0) and LB >= eb and vecs * LB == plane and total == N * vecs
         assert total <= S * waves * 64 and S * max(LB, 4) // 4 in ((16, 32, 64) if LB >= 8 else (16, 32)) and waves in (1, 4, 16)
         assert S * max(LB, 4) // 4 == 16 or total > S // 2 * waves * 64
@@ -81,7 +89,7 @@ def test_plans():
             magic = -(-2 ** 32 // vecs)
             k = np.unique(np.r_[np.arange(min(total, 300)), np.arange(0, total, vecs), np.arange(vecs - 1, total, vecs), total - 1]).astype(np.uint64)
             assert np.array_equal((k * np.uint64(magic)) >> np.uint64(32), k // np.uint64(vecs))
-    assert taken > 2000
+    assert taken > 2000 and narrow > 20
 
 
 @pytest.mark.gpu
