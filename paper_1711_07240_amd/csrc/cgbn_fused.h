@@ -460,6 +460,7 @@ __device__ __forceinline__ float row_centre(float pivot, float s, float n)
 // Backward: a row's sum of dy * xhat from its sums a = sum dy and b = sum dy * (x - mu), mu being the float
 // part of the mean and mulo the rest: xhat = ((x - mu) - mulo) * invstd.
 __device__ __forceinline__ float row_dy_xhat(float b, float a, float mulo, float istd) { return (b - mulo * a) * istd; }
+__device__ __forceinline__ float row_dy_xhat(double b, double a, float mulo, float istd) { return (float)((b - (double)mulo * a) * (double)istd); }
 
 __device__ __forceinline__ double row_sqdev(float s, float q, double n, float pivot, double mean)
 {
@@ -727,6 +728,19 @@ struct Slots {
 // ---------------------------------------------------------------------------
 // ACT == 1: y = max(0, step 11).  ACT == 2: y = max(0, step 11 + shortcut), the shortcut
 // (A.aux) being read a few slots at a time while the unit is written out.
+// EDGE: a channel's pivot.  A row's sum about it is handed over as one float, and these rows are up to six times as long as those of the sweeps that
+// took such planes before; about a single value of the channel the mean came out up to 2.3 times as far off as theirs.  So it is the mean of 16 values
+// spread over the channel's first plane, `v` being lane l's, number l mod 16; a bfloat16 of a bfloat16 tensor (x - pivot then is exact nearly always).
+// If they have no finite mean, the first.
+__device__ __forceinline__ int pivot_index(int lane, int HW) { return (int)((long long)(lane & 15) * HW >> 4); }
+template <typename T> __device__ __forceinline__ float spread_pivot(float v)
+{
+    const float first = __uint_as_float((unsigned)__builtin_amdgcn_readfirstlane((int)__float_as_uint(v)));
+    float p = wave_sum(v * (1.f / kWave));
+    if constexpr (!std::is_same<T, float>::value) p = __uint_as_float(f32_to_bf16(p) << 16);
+    return uniform_f(fabsf(p) <= 3.402823466e38f ? p : first);
+}
+
 template <typename T, int LB, int LPPC, int ACT, int BIG, bool EDGE = false>
 __global__ __launch_bounds__(kThreads, 3) void nchw_fused_forward(FusedArgs A)
 {
@@ -751,7 +765,9 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_forward(FusedArgs A)
     constexpr int PLANES = SMALL ? RT / SL::SPP : SL::PPU;                   // planes of a wavefront (small planes) or a workgroup
     constexpr int NE = !EDGE ? 0 : SMALL ? (PLANES + 3) / 4 : 1;             // registers with values of their edges
     __shared__ ReduceLdsT<BIG> lds;
-    __shared__ float s_red[4 * SL::PPU], s_sq[4 * SL::PPU];
+    // EDGE: a row's sums are joined in double precision (in float the mean, dbeta and dgamma came out further off than from the sweeps' shorter rows)
+    typedef typename std::conditional<EDGE, double, float>::type Sum;
+    __shared__ Sum s_red[4 * SL::PPU], s_sq[4 * SL::PPU];
     const int t = threadIdx.x, lane = t & (kWave - 1), w = uniform(t >> 6);
     const T* x = static_cast<const T*>(A.x);
     const char* xb = static_cast<const char*>(A.x);
@@ -770,7 +786,7 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_forward(FusedArgs A)
         const int c = g.c;
         const char* xu = xb + g.base;
         char* yu = yb + g.base;
-        const float pivot = uniform_f(Elem<T>::load1(x + (long long)c * A.HW));
+        float pivot = EDGE ? Elem<T>::load1(x + (long long)c * A.HW + pivot_index(lane, A.HW)) : uniform_f(Elem<T>::load1(x + (long long)c * A.HW));
         CGBN_STAMP(0);
 
         float ev[EDGE ? NE : 1];
@@ -802,6 +818,7 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_forward(FusedArgs A)
             }
             wait_vector_memory();    // registers and LDS slots have landed, and the compiler knows it
         }
+        if constexpr (EDGE) pivot = spread_pivot<T>(pivot);
         __builtin_amdgcn_s_setprio(0);
 
         // ---- steps 1-3 and 6-8 before the hand-over: per row, the sum about the pivot, then the squared
@@ -810,7 +827,7 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_forward(FusedArgs A)
         {
             const unsigned loff = SL::lane_offset(t);
             // one pass over the slots [s0, s1) of plane `pl`: the elements' sum of (x - centre), or of its square
-            auto pass = [&](auto pl_, auto s0_, auto s1_, float centre, auto square_) __attribute__((always_inline)) -> float {
+            auto pass = [&](auto pl_, auto s0_, auto s1_, float centre, auto square_) __attribute__((always_inline)) -> Sum {
                 constexpr int s0 = decltype(s0_)::value, s1 = decltype(s1_)::value;
                 constexpr bool square = decltype(square_)::value;
                 float acc[4] = {0.f, 0.f, 0.f, 0.f};
@@ -852,7 +869,7 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_forward(FusedArgs A)
                         if constexpr (EDGE && !square) acc[s & 3] += (slot[0] + slot[1]) + (slot[2] + slot[3]);
                     }
                 }
-                return wave_sum((acc[0] + acc[1]) + (acc[2] + acc[3]));
+                return wave_sum((Sum)(acc[0] + acc[1]) + (Sum)(acc[2] + acc[3]));
             };
             if constexpr (SMALL) {
                 // one plane per wavefront at a time: its row is the wavefront's own business
@@ -861,9 +878,9 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_forward(FusedArgs A)
                     constexpr int pl = decltype(pl_)::value, s0 = pl * SL::SPP;
                     const int n = SL::image(g, s0, w);
                     if (n < g.n1) {
-                        const float tot = pass(IntC<pl>{}, IntC<s0>{}, IntC<s0 + SL::SPP>{}, pivot, BoolC<false>{});
+                        const float tot = (float)pass(IntC<pl>{}, IntC<s0>{}, IntC<s0 + SL::SPP>{}, pivot, BoolC<false>{});
                         const float ctr = row_centre(pivot, tot, (float)A.HW);
-                        const float sq = pass(IntC<pl>{}, IntC<s0>{}, IntC<s0 + SL::SPP>{}, ctr, BoolC<true>{});
+                        const float sq = (float)pass(IntC<pl>{}, IntC<s0>{}, IntC<s0 + SL::SPP>{}, ctr, BoolC<true>{});
                         if (lane == 0) {
                             if (solo) {
                                 lds.rows[0][n] = tot;
@@ -883,17 +900,17 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_forward(FusedArgs A)
                     constexpr int s0 = WGP ? pl * SPW : 0, s1 = WGP ? (pl + 1) * SPW : RT;
                     const int row = WGP ? g.n0 + pl : g.u;
                     const bool live = !WGP || g.n0 + pl < g.n1;
-                    const float part = pass(IntC<pl>{}, IntC<s0>{}, IntC<s1>{}, pivot, BoolC<false>{});
+                    const Sum part = pass(IntC<pl>{}, IntC<s0>{}, IntC<s1>{}, pivot, BoolC<false>{});
                     if (lane == 0) s_red[4 * pl + w] = part;
                     __syncthreads();
-                    const float tot = (s_red[4 * pl] + s_red[4 * pl + 1]) + (s_red[4 * pl + 2] + s_red[4 * pl + 3]);
+                    const float tot = (float)((s_red[4 * pl] + s_red[4 * pl + 1]) + (s_red[4 * pl + 2] + s_red[4 * pl + 3]));
                     const float count = (float)(WGP ? A.HW : (g.head + g.len + g.tail) / (int)sizeof(T));
                     const float ctr = row_centre(pivot, tot, count);
-                    const float part2 = pass(IntC<pl>{}, IntC<s0>{}, IntC<s1>{}, ctr, BoolC<true>{});
+                    const Sum part2 = pass(IntC<pl>{}, IntC<s0>{}, IntC<s1>{}, ctr, BoolC<true>{});
                     if (lane == 0) s_sq[4 * pl + w] = part2;
                     __syncthreads();
                     if (t == 0 && live) {
-                        const float sq = (s_sq[4 * pl] + s_sq[4 * pl + 1]) + (s_sq[4 * pl + 2] + s_sq[4 * pl + 3]);
+                        const float sq = (float)((s_sq[4 * pl] + s_sq[4 * pl + 1]) + (s_sq[4 * pl + 2] + s_sq[4 * pl + 3]));
                         if (solo) {
                             lds.rows[0][row] = tot;
                             lds.rows[1][row] = sq;
@@ -1083,7 +1100,8 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_backward(FusedArgs A)
     constexpr int PLANES = SMALL ? RT / SL::SPP : SL::PPU;                   // planes of a wavefront (small planes) or a workgroup
     constexpr int NE = !EDGE ? 0 : SMALL ? (PLANES + 3) / 4 : 1;             // registers with values of their edges
     __shared__ ReduceLdsT<BIG> lds;
-    __shared__ float s_red[8 * SL::PPU];
+    typedef typename std::conditional<EDGE, double, float>::type Sum;        // (see the forward)
+    __shared__ Sum s_red[8 * SL::PPU];
     const int t = threadIdx.x, lane = t & (kWave - 1), w = uniform(t >> 6);
     const char* xb = static_cast<const char*>(A.x);
     const char* gb = static_cast<const char*>(A.dy);
@@ -1255,7 +1273,8 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_backward(FusedArgs A)
                     int n = SL::image(g, s, w);
                     if (n < g.n1) {
                         if constexpr (EDGE) add_edges(s / SL::SPP);
-                        float ta = wave_sum(a[0] + a[1]), tb = row_dy_xhat(wave_sum(b[0] + b[1]), ta, mulo, istd);
+                        const Sum sa = wave_sum((Sum)a[0] + (Sum)a[1]), sb = wave_sum((Sum)b[0] + (Sum)b[1]);
+                        const float ta = (float)sa, tb = row_dy_xhat(sb, sa, mulo, istd);
                         if (lane == 0) {
                             if (solo) {
                                 lds.rows[0][n] = ta;
@@ -1271,13 +1290,14 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_backward(FusedArgs A)
                 if (SL::ends_wg_plane(s)) {                 // a workgroup-wide plane is complete: its rows
                     const int pl = s / SPW, n = g.n0 + pl;
                     if constexpr (EDGE) add_edges(pl);
-                    float ta = wave_sum(a[0] + a[1]), tb = wave_sum(b[0] + b[1]);
+                    const Sum ta = wave_sum((Sum)a[0] + (Sum)a[1]), tb = wave_sum((Sum)b[0] + (Sum)b[1]);
                     if (lane == 0) { s_red[8 * pl + w] = ta; s_red[8 * pl + 4 + w] = tb; }
                     __syncthreads();
                     if (t == 0 && n < g.n1) {
-                        const float ta4 = (s_red[8 * pl] + s_red[8 * pl + 1]) + (s_red[8 * pl + 2] + s_red[8 * pl + 3]);
+                        const Sum sa4 = (s_red[8 * pl] + s_red[8 * pl + 1]) + (s_red[8 * pl + 2] + s_red[8 * pl + 3]);
+                        const float ta4 = (float)sa4;
                         const float tb4 = row_dy_xhat((s_red[8 * pl + 4] + s_red[8 * pl + 5]) + (s_red[8 * pl + 6] + s_red[8 * pl + 7]),
-                                                      ta4, mulo, istd);
+                                                      sa4, mulo, istd);
                         if (solo) {
                             lds.rows[0][n] = ta4;
                             lds.rows[1][n] = tb4;
@@ -1291,12 +1311,13 @@ __global__ __launch_bounds__(kThreads, 3) void nchw_fused_backward(FusedArgs A)
             }
             if (!SMALL && !WGP) {
                 if constexpr (EDGE) add_edges(0);
-                float ta = wave_sum(a[0] + a[1]), tb = wave_sum(b[0] + b[1]);
+                const Sum ta = wave_sum((Sum)a[0] + (Sum)a[1]), tb = wave_sum((Sum)b[0] + (Sum)b[1]);
                 if (lane == 0) { s_red[w] = ta; s_red[4 + w] = tb; }
                 __syncthreads();
                 if (t == 0) {
-                    const float ta4 = (s_red[0] + s_red[1]) + (s_red[2] + s_red[3]);
-                    const float tb4 = row_dy_xhat((s_red[4] + s_red[5]) + (s_red[6] + s_red[7]), ta4, mulo, istd);
+                    const Sum sa4 = (s_red[0] + s_red[1]) + (s_red[2] + s_red[3]);
+                    const float ta4 = (float)sa4;
+                    const float tb4 = row_dy_xhat((s_red[4] + s_red[5]) + (s_red[6] + s_red[7]), sa4, mulo, istd);
                     if (solo) {
                         lds.rows[0][g.u] = ta4;
                         lds.rows[1][g.u] = tb4;

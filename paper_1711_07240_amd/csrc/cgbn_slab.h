@@ -87,34 +87,6 @@ struct SlabLds {
     int skip, last, fix, wait;  // this unit moves on (2: results are missing for good); it completed the count; there are units for it to finish; the count is complete, the results are not there yet
 };
 
-// v plus the value of lane ^ OFF, by vector instructions (__shfl_xor goes through the LDS, which the eight wavefronts of a
-// workgroup share).
-template <int OFF> __device__ __forceinline__ void lane_pair(unsigned v, unsigned& a, unsigned& b)
-{
-    if constexpr (OFF == 32 || OFF == 16) {            // (a, b): the values of the lower and the upper lane of the pair
-        const auto t = OFF == 32 ? __builtin_amdgcn_permlane32_swap(v, v, false, false) : __builtin_amdgcn_permlane16_swap(v, v, false, false);
-        a = t[0];
-        b = t[1];
-    } else {
-        int o = (int)v;
-        if constexpr (OFF == 1) o = __builtin_amdgcn_update_dpp(o, (int)v, 0xB1, 0xf, 0xf, false);        // quad_perm [1,0,3,2]
-        else if constexpr (OFF == 2) o = __builtin_amdgcn_update_dpp(o, (int)v, 0x4E, 0xf, 0xf, false);   // quad_perm [2,3,0,1]
-        else if constexpr (OFF == 4) {
-            o = __builtin_amdgcn_update_dpp(o, (int)v, 0x104, 0xf, 0x5, false);                           // row_shl:4 into banks 0 and 2
-            o = __builtin_amdgcn_update_dpp(o, (int)v, 0x114, 0xf, 0xA, false);                           // row_shr:4 into banks 1 and 3
-        } else o = __builtin_amdgcn_update_dpp(o, (int)v, 0x128, 0xf, 0xf, false);                        // row_ror:8
-        a = v;
-        b = (unsigned)o;
-    }
-}
-template <int OFF> __device__ __forceinline__ double lane_add(double v)
-{
-    const unsigned long long w = (unsigned long long)__double_as_longlong(v);
-    unsigned al, bl, ah, bh;
-    lane_pair<OFF>((unsigned)w, al, bl);
-    lane_pair<OFF>((unsigned)(w >> 32), ah, bh);
-    return __longlong_as_double((long long)(((unsigned long long)ah << 32) | al)) + __longlong_as_double((long long)(((unsigned long long)bh << 32) | bl));
-}
 // Sums over groups of `lanes` lanes (a power of two up to 64, uniform): f(off) adds the lanes that differ in one bit.
 template <class F> __device__ __forceinline__ void lanes_add(int lanes, F f)
 {
