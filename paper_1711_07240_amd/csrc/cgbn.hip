@@ -58,9 +58,11 @@ CGBN_FUSED_BIG_SMALL(CGBN_DECL_B2)
 #undef CGBN_DECL_B2
 #define CGBN_DECL_E(LPPC_, BIG_, T_, ACT_) extern template __global__ void nchw_fused_forward<T_, 16, LPPC_, ACT_, BIG_, true>(FusedArgs);
 #define CGBN_DECL_FE(LPPC_, BIG_)                                                               \
-    CGBN_DECL_E(LPPC_, BIG_, float, 0) CGBN_DECL_E(LPPC_, BIG_, float, 1) CGBN_DECL_E(LPPC_, BIG_, float, 2) \
-    CGBN_DECL_E(LPPC_, BIG_, bf16_t, 0) CGBN_DECL_E(LPPC_, BIG_, bf16_t, 1) CGBN_DECL_E(LPPC_, BIG_, bf16_t, 2)
+    CGBN_DECL_E(LPPC_, BIG_, float, 0) CGBN_DECL_E(LPPC_, BIG_, float, 1) CGBN_DECL_E(LPPC_, BIG_, bf16_t, 0) CGBN_DECL_E(LPPC_, BIG_, bf16_t, 1)
+#define CGBN_DECL_SE(LPPC_, BIG_) CGBN_DECL_E(LPPC_, BIG_, float, 2) CGBN_DECL_E(LPPC_, BIG_, bf16_t, 2)
 CGBN_FUSED_EDGE_FORWARD(CGBN_DECL_FE)
+CGBN_FUSED_EDGE_SHORTCUT(CGBN_DECL_SE)
+#undef CGBN_DECL_SE
 #undef CGBN_DECL_E
 #define CGBN_DECL_E(LPPC_, BIG_, T_, ACT_) extern template __global__ void nchw_fused_backward<T_, 16, LPPC_, ACT_, BIG_, true>(FusedArgs);
 #define CGBN_DECL_BE(LPPC_, BIG_)                                                               \
@@ -891,29 +893,47 @@ Plan grouped(const Plan& p)
 
 // Which calls on NCHW planes that are no multiple of 16 bytes take the single-launch kernels with 16-byte loads, the values of a plane before and
 // behind its whole vectors one by one (`e`), rather than what there is else (`f`: the same kernels with 8- or 4-byte loads; where that is not ok,
-// sweeps).  Measured over 130 random shapes of 1 to 370 MB, forward / with shortcut / backward / masked, that time over this one's:
-//   - the sweeps: large tensors 1.35 / 1.05 / 1.45 / 1.55 (16 x 64 x 201 x 333 fp32 179 / 226 / 273 / 449 us -> 124 / 198 / 179 / 290, bf16 99 / 116 /
-//     143 / 237 -> 71 / 113 / 97 / 154), channels of one unit 1.7 / 1.4 / 1.9 / 1.9 (4 x 96 of 75 x 57 bf16).  Few units leave the chip idle, and with a
-//     shortcut the write-out waits for it batch by batch: 2 x 24 of 38000 bf16 0.8 / 0.5 / 1.05 / 1.0, 64 x 24 of 27 x 37 0.8 / 0.5 / 0.9 / 0.8.
-//   - 4-byte loads: bf16 from 8 KB on 1.3 / 1.2 / 1.15 / 1.2, below 0.95 / 1.05 / 0.9 / 0.95; float from 9 KB on 1.25, below only where its slots are filled
-//     (4.3 to 5 KB 1.15 to 1.3; 23 x 71, 6.4 slots of 8, 0.96 / 0.84 / 0.88).  Few units of several a channel: 32 x 64 of 39 x 63 with a shortcut 0.8.
-//   - 8-byte loads, which large planes take without further data in LDS: forward beyond 16 KB 1.05 to 1.35 (else 0.9 to 1.05); with a shortcut
-//     0.85 to 1.2; backward 1.2 to 1.45 where three planes of 23 to 29 KB share a workgroup here, bf16 1.4 beyond 16 KB, else 0.9 to 1.05.
-bool edges_pay(const FusedPlan& e, const FusedPlan& f, bool built, long long plane_bytes, long long tensor_bytes, int eb, bool forward, bool second)
+// sweeps).  Measured over 1000 random shapes of 0.4 to 400 MB, that time over this one's, geometric means of the calls taken and, in brackets, of those
+// left; single calls lie up to 9 % beside that, the same code in another process does where tensors about fill the 256 MB last-level cache:
+//   - the sweeps: forward 1.25 (0.93), with a shortcut 1.15 (0.95), backward 1.30 (0.83), masked 1.38 (0.91).  Left to them: fewer than 16 channels of several
+//     units, all of whose units read, wait and write together (77 x 8 of 329 x 399 fp32 backward 316 / 497 us, 71 x 8 of 289 x 223 forward 0.67); tiles that fill
+//     too little of a unit (74 x 19 of 109 x 195 bf16 forward 44.5 / 50.5, 20 x 148 of 109 x 103 backward 61.6 / 71.7); few units, which leave the chip idle, and
+//     a few more than are resident at once (58 x 416 of 29 x 45 bf16 forward 45 / 51); with a shortcut, whose write-out waits for it batch by batch, all but
+//     large tensors of well filled units (5 x 80 of 211 x 315 fp32 76 / 95; 15 x 312 of 43 x 69 bf16 28 / 38).
+//   - 4-byte loads: forward 1.20, with a shortcut 1.09, backward 1.07, masked 1.12 for planes of float from 9 KB and of bfloat16 from 8 KB on; few units of several a
+//     channel 0.96, backward from 12.7 KB on 0.99.  Shorter planes of float where their slots are filled: up to 8 KB forward 1.15 from 150 MB on and 1.1 to 1.5
+//     where a channel becomes one unit, else 0.9 to 1.0; with a shortcut 1.2 from 100 MB on, else 0.9; backward 1.08 from 150 MB on, else 0.8 to 1.1; masked 1.05 to 1.25
+//     from 70 MB on without further planes in LDS, else 0.77 to 1.1.
+//   - 8-byte loads, which large planes take without further data in LDS: forward beyond 16 KB 1.15, but 0.62 where a plane a wavefront became a plane a workgroup, 0.95
+//     where few planes that share one leave the chip idle, and 1.04 from 80 to 160 MB, where a backward that follows then takes longer (a step 0.97); backward 1.14
+//     and masked 1.11 where two or three planes share a workgroup, 0.99 and 1.00 for tiles.
+bool edges_pay(const FusedPlan& e, const FusedPlan& f, bool built, int C, long long plane_bytes, long long tensor_bytes, int eb, bool forward, bool second)
 {
     if (!e.ok) return false;
+    const long long unit_bytes = tensor_bytes / e.total_units;
     if (!f.ok || !built) {
         if (plane_bytes <= 2048 && (second || e.U > 1 || e.total_units < 128)) return false;
-        if (forward && second) return tensor_bytes >= 100000000 || (e.U == 1 && e.total_units >= 64 && plane_bytes >= 3500 && plane_bytes <= 16384);
-        return e.total_units >= (e.U == 1 ? 48 : forward ? 256 : 96);
+        if (e.U > 1 && C < 16) return false;
+        const long long thin = forward ? (C < 32 ? 70000 : 52000) : second ? 0 : 33000;
+        if (e.U > 1 && e.LPPC == 0 && unit_bytes < thin && (!forward || tensor_bytes < 200000000)) return false;
+        if (forward && second) return !(e.LPPC > 0 && e.LPPC < 8) && (e.U == 1 ? tensor_bytes >= 100000000 : tensor_bytes >= 160000000 && unit_bytes >= 65000);
+        if (forward && tensor_bytes < 100000000 && e.total_units > 768 && e.total_units < 900) return false;
+        return e.total_units >= (e.U == 1 ? 48 : !forward ? 96 : tensor_bytes >= 60000000 ? 256 : 400);
     }
     if (f.LB == 4) {
-        if (e.U > 1 && e.total_units < 256) return false;
+        if (e.U > 1 && e.total_units < (forward && second ? 400 : 256)) return false;
+        if (!forward && !second && plane_bytes > 12700) return false;
         if (eb == 2) return plane_bytes >= 8000;
-        return plane_bytes >= 9000 || (plane_bytes >= 4096 && e.LPPC > 0 && plane_bytes * 100 >= (long long)e.LPPC * 1024 * 85);
+        if (plane_bytes >= 9000) return true;
+        if (plane_bytes < 4096 || e.LPPC <= 0 || plane_bytes * 100 < (long long)e.LPPC * 1024 * 85) return false;
+        if (plane_bytes > 8192) return true;
+        if (forward && e.U == 1 && (f.U > 1 || (second && e.total_units <= 500))) return true;
+        return !second ? tensor_bytes >= 150000000 : forward ? tensor_bytes >= 100000000 : tensor_bytes >= 70000000 && e.big == 0;
     }
     if (plane_bytes <= 16384 || (forward && second)) return false;
-    return forward || eb == 2 || (e.LPPC == -3 && plane_bytes >= 23000);
+    if (!forward) return (e.LPPC == -3 && e.total_units >= 256 && (eb == 2 || plane_bytes >= 23000)) || (e.LPPC == -2 && e.total_units >= 640 && eb == 2);
+    if (e.LPPC < 0) return e.total_units >= 200;
+    return e.total_units <= f.total_units && !(e.LPPC == 0 && e.U > 40 && C < 16) && (tensor_bytes < 80000000 || tensor_bytes >= 160000000);
 }
 
 // Which (bytes per access, slots per plane) variants exist for an element type, direction and activation: all of
@@ -1040,7 +1060,7 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
     for (int i = 0; i < 4; ++i) {
         const bool forward = i < 2, second = (i & 1) != 0;
         const FusedPlan& f = forward ? p->ff : p->fb;
-        p->edges[i] = edges_pay(forward ? p->ef : p->ebw, f, fused_built(p->eb == 4, forward, second, f.LB, f.LPPC), HW * p->eb, S * p->eb, p->eb, forward, second);
+        p->edges[i] = edges_pay(forward ? p->ef : p->ebw, f, fused_built(p->eb == 4, forward, second, f.LB, f.LPPC), C, HW * p->eb, S * p->eb, p->eb, forward, second);
     }
     size_t sync = align256(((size_t)kSyncHeader + 4 * (size_t)C) * sizeof(unsigned));
     size_t part = align256((size_t)C * max_rows * sizeof(float));
@@ -1410,7 +1430,9 @@ cgbn_status launch_fused_t(const Tuning& knobs, const FusedPlan& f, FusedArgs& A
             if constexpr (FWD) return launch_fused_kernel(nchw_fused_forward<T, 16, LPPC_, ACT, BIG_, true>, knobs, f, A, sync_words, st, taken, moved_bytes); \
             else return launch_fused_kernel(nchw_fused_backward<T, 16, LPPC_, ACT, BIG_, true>, knobs, f, A, sync_words, st, taken, moved_bytes); \
         }
-        if constexpr (FWD) {
+        if constexpr (FWD && ACT == 2) {
+            CGBN_FUSED_EDGE_SHORTCUT(CGBN_FUSED_CASEE)
+        } else if constexpr (FWD) {
             CGBN_FUSED_EDGE_FORWARD(CGBN_FUSED_CASEE)
         } else {
             CGBN_FUSED_EDGE_BACKWARD(CGBN_FUSED_CASEE)

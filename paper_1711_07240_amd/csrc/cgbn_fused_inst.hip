@@ -17,7 +17,11 @@ CGBN_FUSED_WGP_FORWARD(CGBN_X1)
 #define CGBN_X2(LB_, LPPC_) template __global__ void nchw_fused_forward<CGBN_INST_T, LB_, LPPC_, CGBN_INST_ACT, 2>(FusedArgs);
 CGBN_FUSED_BIG_SMALL(CGBN_X2)
 #define CGBN_XE(LPPC_, BIG_) template __global__ void nchw_fused_forward<CGBN_INST_T, 16, LPPC_, CGBN_INST_ACT, BIG_, true>(FusedArgs);
+#if CGBN_INST_ACT == 2
+CGBN_FUSED_EDGE_SHORTCUT(CGBN_XE)
+#else
 CGBN_FUSED_EDGE_FORWARD(CGBN_XE)
+#endif
 #else
 #define CGBN_XE(LPPC_, BIG_) template __global__ void nchw_fused_backward<CGBN_INST_T, 16, LPPC_, CGBN_INST_ACT, BIG_, true>(FusedArgs);
 CGBN_FUSED_EDGE_BACKWARD(CGBN_XE)

@@ -46,11 +46,14 @@
 #define CGBN_FUSED_RELU_BWD_F32_NARROW(X) X(4, 24)
 
 // Planes whose bytes are no multiple of 16, with 16-byte loads and their edges value by value (see Slots): X(LPPC, BIG).
+// (Two or three slots a plane: forwards with a shortcut never come to it, see edges_pay in cgbn.hip.)
 #define CGBN_FUSED_EDGE_COMMON(X)                                                                      \
     X(0, 0) X(0, 1) X(-2, 0) X(-2, 1) X(-3, 1) X(-4, 1)                                                \
-    X(2, 0) X(3, 0) X(4, 0) X(5, 0) X(6, 0) X(8, 0) X(10, 0) X(12, 0) X(16, 0) X(3, 2) X(4, 2) X(5, 2)
-#define CGBN_FUSED_EDGE_FORWARD(X) CGBN_FUSED_EDGE_COMMON(X) X(24, 0) X(32, 0) X(38, 0)
-#define CGBN_FUSED_EDGE_BACKWARD(X) CGBN_FUSED_EDGE_COMMON(X) X(19, 0)
+    X(4, 0) X(5, 0) X(6, 0) X(8, 0) X(10, 0) X(12, 0) X(16, 0) X(4, 2) X(5, 2)
+#define CGBN_FUSED_EDGE_FEW(X) X(2, 0) X(3, 0) X(3, 2)
+#define CGBN_FUSED_EDGE_SHORTCUT(X) CGBN_FUSED_EDGE_COMMON(X) X(24, 0) X(32, 0) X(38, 0)
+#define CGBN_FUSED_EDGE_FORWARD(X) CGBN_FUSED_EDGE_SHORTCUT(X) CGBN_FUSED_EDGE_FEW(X)
+#define CGBN_FUSED_EDGE_BACKWARD(X) CGBN_FUSED_EDGE_COMMON(X) CGBN_FUSED_EDGE_FEW(X) X(19, 0)
 
 // The slot counts the host may choose for small planes, ascending: for a plane of LPP slots it takes the smallest
 // count >= LPP that leaves at most 16 planes per wavefront (count * 16 >= R, R the register slots per tensor) and
