@@ -531,9 +531,9 @@ bool cut_slabs(SlabPlan* s, int C, int cols, int nch, long long U, long long row
 // boundaries they share those lines: fp32 22400 x 264, 31 units 23.8 / 28.7, 32 units 21.5 / 24.5; 70200 x 112, 63 units 27.7 / 36.3, 64
 // units 24.3 / 29.7 (rows of whole lines: no difference).  Such slabs must also all be in flight together (measured, fp32
 // 268800 x 136 in four rounds 170 us, the sweeps 101).
-//   Such slabs in several rounds (`shared`: at least so many in flight): those in flight are then neighbours, in whole eights of units, so that the
+//   Such slabs in several rounds (`shared`: at least so many in flight, the rounds `full` per cent full): those in flight are then neighbours, in whole eights of units, so that the
 // lines two of them share are fetched by one XCD at about the same time and only those at the ends of the group twice.  See make_shared_plan.
-bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_words, int cus, bool forward, bool second, int shared = 0)
+bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_words, int cus, bool forward, bool second, int shared = 0, int full = 0)
 {
     const int rpp = kSlabThreads / cols;
     const long long cap = (long long)rpp * slab_most(forward, false);
@@ -554,7 +554,7 @@ bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_wor
         if (slabs * U > cus / U * U) {
             if (shared) {
                 U = (U + 7) / 8 * 8;
-                if (U > most || 10 * slabs < 7 * ((slabs + cus / U - 1) / (cus / U)) * (cus / U)) continue;
+                if (U > most || 100 * slabs < (cus / U < 8 && full < 84 ? 84 : full) * ((slabs + cus / U - 1) / (cus / U)) * (cus / U)) continue;
             } else if (!lines) {
                 continue;
             }
@@ -673,11 +673,19 @@ void make_slab_plan(int N, int C, long long HW, int layout, int eb, long long ro
 }
 
 // Channels-last calls that no plan above takes, rows of at least 24 vectors that are no whole lines: in several rounds of 128-byte slabs that share
-// lines, where enough of them are in flight and the rounds are at least 70 % full.  Measured over 60 random shapes, sweeps -> so, forward / backward / masked us:
-// fp32 63104 x 1264 (eight and four in flight) 234 / 334 / 645 -> 187 / 281 / 498, 23936 x 1168 (16, ten) 89 / 134 / 243 -> 64 / 90 / 145, 17920 x 1768 (32, 16) 101 /
-// 146 / 230 -> 65 / 107 / 188, bf16 43008 x 936 (ten, five) 69 / 100 / 149 -> 57 / 74 / 120.  Fewer in flight: 97244 x 880 (two) backward 321 -> 345, 238080 x 408 (two, one)
-// 235 / 364 -> 321 / 520, bf16 62424 x 1064 (four) masked 223 -> 249; masked float of rows of one tile, whose sweeps are faster: 37392 x 904 (six)
-// 225 -> 260, 60928 x 808 (four) 339 -> 382.  Rounds two thirds full: bf16 79872 x 496 forward 58 -> 62.  Nine columns a slab: 17920 x 1768 65 / 107, so 89 / 114.
+// lines, where enough of them are in flight and the rounds are well filled.  Measured over 200 random shapes, time of the sweeps over this one's, geometric mean of the
+// calls taken: forward 1.14, backward 1.14, masked 1.24: fp32 63104 x 1264 (eight and four in flight) 234 / 334 / 645 -> 187 / 281 / 498 us, 23936 x 1168 (16, ten)
+// 89 / 134 / 243 -> 64 / 90 / 145, bf16 43008 x 936 (ten, five) 69 / 100 / 149 -> 57 / 74 / 120.  Where the line lies:
+//   - fewer in flight: 97244 x 880 (two) backward 321 -> 345, 238080 x 408 (two, one) 235 / 364 -> 321 / 520, bf16 62424 x 1064 (four) masked 223 -> 249, backward with
+//     four 0.84 to 0.96, and with five to seven of less than 16 slabs (46898 x 840 bf16 0.89); masked float of rows of one tile, whose sweeps are faster:
+//     37392 x 904 (six) 225 -> 260;
+//   - rounds: bf16 forward and backward 84 and 87 % full (16872 x 1656 bf16, 26 slabs by ten, backward 46 -> 54; 19352 x 2032, 32 by ten, 50 -> 62), float with eight and
+//     more in flight 70 % (14280 x 1136, 36 slabs by 16, backward 1.33), with fewer 84 %;
+//   - rows of more than 512 vectors, but for masked calls, and those within a line of 8 KiB, of which the same columns of every row crowd few memory channels:
+//     50400 x 2072 fp32 241 / 362 -> 291 / 380, 26325 x 2040 masked 337 -> 388;
+//   - where the backward is sweeps, only forwards of 150 MB and more in at most 3.5 rounds: 1.16 to 1.37 times as fast (90321 x 568 fp32), a step that calls one directly
+//     after the other 0.95 to 1.04; of the others 1.03, the step 0.91, since the backward's sweeps find nothing of what the forward read in the last-level cache.
+// Nine columns a slab: 17920 x 1768 65 / 107, so 89 / 114.
 void make_shared_plan(int N, int C, long long HW, int eb, long long row_words, int cus, bool forward, bool second, const SlabPlan& s, SlabPlan* x)
 {
     std::memset(x, 0, sizeof(*x));
@@ -689,8 +697,10 @@ void make_shared_plan(int N, int C, long long HW, int eb, long long row_words, i
     x->cpc = 1;
     const int cols = 8;
     if (x->row_bytes % 128 == 0) return;       // (whole lines)
-    const int flight = forward ? 6 : eb == 2 ? 5 : second && x->vecs <= kThreads ? 8 : 4;
-    cut_slabs_in_units(x, C, cols, ceil_pow2(cols * vec), row_words, cus, forward, second, flight);
+    if ((x->vecs > 512 && (forward || !second)) || (x->row_bytes + 128) % 8192 < 256) return;
+    const int flight = forward ? 6 : eb == 2 || !second ? 5 : x->vecs <= kThreads ? 8 : 4;
+    cut_slabs_in_units(x, C, cols, ceil_pow2(cols * vec), row_words, cus, forward, second, flight, forward ? 84 : eb == 2 ? 87 : 70);
+    if (x->ok && !forward && !second && x->slabs < 16 && cus / x->U < 8) x->ok = 0;
 }
 
 // NCHW calls whose plan `s` has 16-byte vectors: one of 8-byte vectors in its place (see SlabVector), where that leaves at least half the compute
@@ -1106,8 +1116,9 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
         make_narrow_plan(N, C, HW, p->eb, false, true, p->sbm, cus, &p->nbm);
     }
     if (layout == CGBN_NHWC) {
-        make_shared_plan(N, C, HW, p->eb, row_words, cus, true, false, p->sf, &p->xf);
         make_shared_plan(N, C, HW, p->eb, row_words, cus, false, false, p->sb, &p->xb);
+        make_shared_plan(N, C, HW, p->eb, row_words, cus, true, false, p->sf, &p->xf);
+        if (p->xf.ok && !p->xb.ok && !p->sb.ok && (S * p->eb < 150000000 || 2 * p->xf.slabs > 7 * (cus / p->xf.U))) p->xf.ok = 0;       // (see make_shared_plan)
         make_shared_plan(N, C, HW, p->eb, row_words, cus, false, true, p->sbm, &p->xbm);
     }
     for (const SlabPlan* s : {&p->sf, &p->sfs, &p->sb, &p->sbm, &p->xf, &p->xb, &p->xbm})
