@@ -335,13 +335,17 @@ long long cgbn_get_tuning(const char* key);
  * access), "LPPC" (register slots per small plane; 0: large planes), "LPP" (slots a plane fills),
  * "IPU" (images per unit), "U" (units per channel), "tp" / "TL" (tiles per large plane, tile
  * elements), "rows", "rps", "G", "big" (0, or which LDS variant), "total_units", "last_plane" (byte offset of a unit's last plane
- * from its first).
+ * from its first).  Prefix "efwd_" or "ebwd_": the same of the plan for planes that are no multiple of 16 bytes, and "taken", "taken2" (calls
+ * take it; calls with a shortcut, masked ones).  Flat kernels: "flat_waves" (wavefronts per channel, 0: the shape does not qualify), "flat_LB" (bytes of a vector),
+ * "flat_S" (vectors per lane), "flat_vecs", "flat_total" (of a plane, of a channel), "flat_fwd", "flat_fwds", "flat_bwd", "flat_bwdm" (calls take them: forward, with a
+ * shortcut, backward, masked).
  * Column-slab kernels, prefix "sfwd_" or "sbwd_" ("sfwds_": the forward with a shortcut, "sbwdm_": the masked backward): "ok" (the shape takes them instead of
  * sweeps), "first" (... also before the single-launch NCHW kernels), "vecs" (16-byte vectors per row of
  * the matrix), "R" (its rows), "cpc" (columns per channel), "cols" (vectors per slab), "slabs", "nch" (channels per slab, rounded up to a power of two), "rpp" (rows per pass),
  * "tpc" (threads that add one channel's partial sums), "U" (units per slab), "rpu" (rows per unit),
  * "P" (vectors per thread of the kernel variant).  Prefix "nfwd_", "nbwd_", "nfwds_", "nbwdm_": the same of the plan with 8-byte
- * vectors that takes its place if its own "ok" is 1. */
+ * vectors that takes its place if its own "ok" is 1.  Prefix "xfwd_", "xbwd_", "xbwdm_": the same of the plan in several rounds of slabs that share lines, where
+ * the others are not "ok". */
 long long cgbn_plan_get(int N, int C, int H, int W, cgbn_layout layout, cgbn_dtype dtype, int K,
                         const char* key);
 

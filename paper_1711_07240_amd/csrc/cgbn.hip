@@ -2204,6 +2204,7 @@ long long cgbn_plan_get(int N, int C, int H, int W, cgbn_layout layout, cgbn_dty
     if ((key[0] == 's' || key[0] == 'n' || key[0] == 'x') && (!std::strncmp(key + 1, "fwd_", 4) || !std::strncmp(key + 1, "bwd_", 4) ||
                                              !std::strncmp(key + 1, "fwds_", 5) || !std::strncmp(key + 1, "bwdm_", 5))) {
         const bool second = key[4] != '_', narrow = key[0] == 'n';
+        if (key[0] == 'x' && key[1] == 'f' && second) return -1;          // (there is none for a forward with a shortcut)
         const SlabPlan& s = key[0] == 'x' ? (key[1] == 'b' ? (second ? p.xbm : p.xb) : p.xf) : key[1] == 'b' ? (second ? (narrow ? p.nbm : p.sbm) : (narrow ? p.nb : p.sb))
                                           : (second ? (narrow ? p.nfs : p.sfs) : (narrow ? p.nf : p.sf));
         const char* k = key + (second ? 6 : 5);

@@ -30,6 +30,7 @@ def _get(case, key):
 def test_every_direction_is_run():
     for d in DIRECTIONS:
         assert sum(_get(c, d + "_ok") for c in CASES) >= 2, d
+    assert all(_get(c, "xfwds_ok") == -1 for c in CASES)          # (no such plan for a forward with a shortcut)
     assert any(_get(c, "xbwd_cols") * _get(c, "xbwd_slabs") > _get(c, "xbwd_vecs") for c in CASES)
 
 
