@@ -313,7 +313,8 @@ cgbn_status cgbn_set_tuning(const char* key, long long value);
  * "last_backward_slab" (1 if it took the column-slab kernels), "last_forward_slab_vector",
  * "last_backward_slab_vector" (the bytes of their vectors, 16 or 8, or 0), "plans_made" (launch plans the calling thread has
  * made: calls come back to the last ones it keeps), "last_forward_flat", "last_backward_flat" (1 if it took the flat
- * kernels; "last_forward_fused" is 1 then too) */
+ * kernels), "last_forward_edge", "last_backward_edge" (1 if it took those for planes that are no multiple of 16 bytes); "last_forward_fused" is 1 in
+ * either case */
 long long cgbn_get_tuning(const char* key);
 
 /* One number of the launch plan the library would use for this problem under the current

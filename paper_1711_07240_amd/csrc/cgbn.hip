@@ -215,6 +215,7 @@ Tuning tuning_now()
 std::atomic<long long> g_last_forward_slab{0}, g_last_backward_slab{0};     // bytes of the vectors of the column-slab kernel it took, or 0
 std::atomic<long long> g_last_forward_fused{0}, g_last_backward_fused{0};   // which path the last call took: 1 for a single launch of an NCHW call
 std::atomic<long long> g_last_forward_flat{0}, g_last_backward_flat{0};     // ... by a flat kernel
+std::atomic<long long> g_last_forward_edge{0}, g_last_backward_edge{0};     // ... by one for planes that are no multiple of 16 bytes
 #ifdef CGBN_TRACE
 unsigned long long* g_trace = nullptr;
 #endif
@@ -1853,13 +1854,13 @@ cgbn_status forward_impl(const void* x, const void* shortcut, bool relu, int N, 
         F.x = x; F.dy = shortcut; F.out = y; F.gamma = gamma; F.beta = beta; F.eps = (double)eps;
         F.mean = mean; F.mean_lo = mean_lo; F.invstd = invstd;
         g_last_forward_fused = g_last_forward_flat = 1;
-        g_last_forward_slab = 0;
+        g_last_forward_slab = g_last_forward_edge = 0;
         const bool f32 = p.dtype == CGBN_F32;
         if (relu && shortcut) return f32 ? launch_flat_t<float, true, 2>(p, F, st) : launch_flat_t<bf16_t, true, 2>(p, F, st);
         if (relu) return f32 ? launch_flat_t<float, true, 1>(p, F, st) : launch_flat_t<bf16_t, true, 1>(p, F, st);
         return f32 ? launch_flat_t<float, true, 0>(p, F, st) : launch_flat_t<bf16_t, true, 0>(p, F, st);
     }
-    g_last_forward_flat = 0;
+    g_last_forward_flat = g_last_forward_edge = 0;
     for (const FusedPlan* f : {&p.ef, &p.ff}) {
         if (!p.t.fused || !f->ok || (f == &p.ef && !p.edges[shortcut != nullptr]) || (slab && wide.first)) continue;
         FusedArgs F = fused_args(p, *f, ws);
@@ -1876,6 +1877,7 @@ cgbn_status forward_impl(const void* x, const void* shortcut, bool relu, int N, 
                                : (f32 ? launch_fused_t<float, true, 0>(p.t, *f, F, sync_words, st, &taken, moved)
                                       : launch_fused_t<bf16_t, true, 0>(p.t, *f, F, sync_words, st, &taken, moved));
         g_last_forward_fused = taken;
+        g_last_forward_edge = taken && f->edge;
         if (taken) g_last_forward_slab = 0;
         if (taken || st_ != CGBN_OK) return st_;
     }
@@ -1953,12 +1955,12 @@ cgbn_status backward_impl(const void* dy, const void* y, const void* x, const fl
         F.mean = const_cast<float*>(mean); F.mean_lo = const_cast<float*>(mean_lo); F.invstd = const_cast<float*>(invstd);
         F.dgamma = dgamma; F.dbeta = dbeta;
         g_last_backward_fused = g_last_backward_flat = 1;
-        g_last_backward_slab = 0;
+        g_last_backward_slab = g_last_backward_edge = 0;
         const bool f32 = p.dtype == CGBN_F32;
         if (relu) return f32 ? launch_flat_t<float, false, 1>(p, F, st) : launch_flat_t<bf16_t, false, 1>(p, F, st);
         return f32 ? launch_flat_t<float, false, 0>(p, F, st) : launch_flat_t<bf16_t, false, 0>(p, F, st);
     }
-    g_last_backward_flat = 0;
+    g_last_backward_flat = g_last_backward_edge = 0;
     for (const FusedPlan* f : {&p.ebw, &p.fb}) {
         if (!p.t.fused || !f->ok || (f == &p.ebw && !p.edges[relu ? 3 : 2]) || (slab && wide.first)) continue;
         FusedArgs F = fused_args(p, *f, ws);
@@ -1974,6 +1976,7 @@ cgbn_status backward_impl(const void* dy, const void* y, const void* x, const fl
                                : (f32 ? launch_fused_t<float, false, 0>(p.t, *f, F, sync_words, st, &taken, moved)
                                       : launch_fused_t<bf16_t, false, 0>(p.t, *f, F, sync_words, st, &taken, moved));
         g_last_backward_fused = taken;
+        g_last_backward_edge = taken && f->edge;
         if (taken) g_last_backward_slab = 0;
         if (taken || st_ != CGBN_OK) return st_;
     }
@@ -2293,7 +2296,9 @@ long long cgbn_get_tuning(const char* key)
     if (key && !std::strcmp(key, "last_backward_slab")) return g_last_backward_slab.load() != 0;
     if (key && !std::strcmp(key, "last_backward_slab_vector")) return g_last_backward_slab.load();
     if (key && !std::strcmp(key, "last_forward_flat")) return g_last_forward_flat.load();
+    if (key && !std::strcmp(key, "last_forward_edge")) return g_last_forward_edge.load();
     if (key && !std::strcmp(key, "last_backward_flat")) return g_last_backward_flat.load();
+    if (key && !std::strcmp(key, "last_backward_edge")) return g_last_backward_edge.load();
     if (key && !std::strcmp(key, "plans_made")) return g_plans_made;
     long long* slot = tuning_slot(key);
     if (!slot) return -1;

@@ -110,7 +110,9 @@ def _run_here(case):
         torch.cuda.synchronize()
         assert int(p.ws[error:error + 4].view(torch.int32).item()) == 0
         for d in directions:
-            assert not _variant(case, d) or L.cgbn_get_tuning("last_%s_fused" % ("forward" if d[0] == "f" else "backward")) == 1, d
+            what = "forward" if d[0] == "f" else "backward"
+            assert L.cgbn_get_tuning("last_%s_edge" % what) == (_variant(case, d) is not None), d
+            assert not _variant(case, d) or L.cgbn_get_tuning("last_%s_fused" % what) == 1, d
 
     p.forward()
     p.backward()
@@ -208,6 +210,7 @@ def test_planes_further_apart_than_32_bits_on_the_device(case):
             L.cgbn_forward(x, N, C, H, W, "NCHW", K, gamma, beta, 1e-5, out, mean, invstd, dtype, mean_lo, ws)
         else:
             L.cgbn_forward_relu(x, shortcut, N, C, H, W, "NCHW", K, gamma, beta, 1e-5, out, mean, invstd, dtype, mean_lo, ws)
+        assert L.cgbn_get_tuning("last_forward_edge") == (_variant(case, "fwd" if shortcut is None else "fwds") is not None)
         for c in chunks:
             a = x[:, c].double()
             m = sums(a) / (N * H * W)
@@ -225,6 +228,7 @@ def test_planes_further_apart_than_32_bits_on_the_device(case):
             L.cgbn_backward_relu(dy, y, x, mean, invstd, gamma, out, dz, dgamma, dbeta, N, C, H, W, "NCHW", K, dtype, mean_lo, ws)
         else:
             L.cgbn_backward(dy, x, mean, invstd, gamma, out, dgamma, dbeta, N, C, H, W, "NCHW", K, dtype, mean_lo, ws)
+        assert L.cgbn_get_tuning("last_backward_edge") == (_variant(case, "bwdm" if masked else "bwd") is not None)
         for c in chunks:
             m, i = (v.view(1, -1, 1, 1) for v in stats[c.start])
             g, h = dy[:, c].double(), (x[:, c].double() - m) * i
