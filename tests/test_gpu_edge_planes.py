@@ -283,15 +283,9 @@ def test_the_plan_holds_every_plane(dtype):
     assert taken > 1500
 
 
-@pytest.mark.gpu
-@pytest.mark.parametrize("case", [(2, 128, 251, 241, "bf16", 1), (6, 64, 141, 145, "bf16", 1), (8, 72, 201, 219, "f32", 1), (13, 88, 113, 149, "f32", 1)], ids=ID)
-def test_no_further_from_64_bits_than_the_sweeps(case):
-    """Of the mean (with its rest), dbeta and dgamma, root mean square over channels and four inputs.  A row of these kernels is as long as several of the
-    sweeps', so what is rounded once a row has to be formed more carefully.  (Measured with a first value as pivot and sums joined in float: mean 1.4 to
-    2.0 times as far off as the sweeps, dbeta 1.1 to 1.2; now 0.3 to 0.7 and 0.6 to 0.8.  A ratio of two such root mean squares is good to 6 %.)"""
+def errors(case, knob):
+    """Root mean squares over channels and four inputs of how far mean (with its rest), dbeta and dgamma are from 64 bits, by (which, the knob's value)."""
     N, C, H, W, dtype, K = case
-    print("[case] errors", case, flush=True)
-    assert any(_variant(case, d) for d in ("fwd", "bwd"))
     gen = torch.Generator(device=G.DEV).manual_seed(31)
     T = torch.float32 if dtype == "f32" else torch.bfloat16
     per, col = lambda: torch.empty(C, device=G.DEV), lambda v: v.view(1, -1, 1, 1)
@@ -308,16 +302,26 @@ def test_no_further_from_64_bits_than_the_sweeps(case):
         sigma = torch.sqrt(sums((xd - col(m)) ** 2) / (N * H * W))
         h = gd * (xd - col(m)) * col(1 / torch.sqrt(sigma ** 2 + 1e-5))
         want = {"mean": (m, sigma), "dbeta": (sums(gd), torch.sqrt(sums(gd * gd))), "dgamma": (sums(h), torch.sqrt(sums(h * h)))}
-        for fused in (0, 1):
-            L.cgbn_set_tuning("fused", fused)
+        for value in (0, 1):
+            L.cgbn_set_tuning(knob, value)
             try:
                 L.cgbn_forward(x, N, C, H, W, "NCHW", K, gamma, beta, 1e-5, out, mean, invstd, dtype, mean_lo, ws)
                 L.cgbn_backward(dy, x, mean, invstd, gamma, out, dgamma, dbeta, N, C, H, W, "NCHW", K, dtype, mean_lo, ws)
             finally:
-                L.cgbn_set_tuning("fused", 1)
+                L.cgbn_set_tuning(knob, 1)
             for k, got in {"mean": mean.double() + mean_lo.double(), "dbeta": dbeta.double(), "dgamma": dgamma.double()}.items():
-                off.setdefault((k, fused), []).append((((got - want[k][0]) / want[k][1]) ** 2).mean())
-    rms = {k: float(torch.stack(v).mean().sqrt()) for k, v in off.items()}
+                off.setdefault((k, value), []).append((((got - want[k][0]) / want[k][1]) ** 2).mean())
+    return {k: float(torch.stack(v).mean().sqrt()) for k, v in off.items()}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [(2, 128, 251, 241, "bf16", 1), (6, 64, 141, 145, "bf16", 1), (8, 72, 201, 219, "f32", 1), (13, 88, 113, 149, "f32", 1)], ids=ID)
+def test_no_further_from_64_bits_than_the_sweeps(case):
+    """A row of these kernels is as long as several of the sweeps', so what is rounded once a row has to be formed more carefully.  (Measured with a first value as pivot and sums joined in float: mean 1.4 to
+    2.0 times as far off as the sweeps, dbeta 1.1 to 1.2; now 0.3 to 0.7 and 0.6 to 0.8.  A ratio of two such root mean squares is good to 6 %.)"""
+    print("[case] errors", case, flush=True)
+    assert any(_variant(case, d) for d in ("fwd", "bwd"))
+    rms = errors(case, "fused")
     for k in ("mean", "dbeta", "dgamma"):
         if _variant(case, "fwd" if k == "mean" else "bwd"):
             assert rms[k, 1] <= rms[k, 0], (case, k, rms)
