@@ -909,7 +909,7 @@ Plan grouped(const Plan& p)
 //   - the sweeps: forward 1.25 (0.93), with a shortcut 1.15 (0.95), backward 1.30 (0.83), masked 1.38 (0.91).  Left to them: fewer than 16 channels of several
 //     units, all of whose units read, wait and write together (77 x 8 of 329 x 399 fp32 backward 316 / 497 us, 71 x 8 of 289 x 223 forward 0.67); tiles that fill
 //     too little of a unit (74 x 19 of 109 x 195 bf16 forward 44.5 / 50.5, 20 x 148 of 109 x 103 backward 61.6 / 71.7); few units, which leave the chip idle, and
-//     a few more than are resident at once (58 x 416 of 29 x 45 bf16 forward 45 / 51); with a shortcut, whose write-out waits for it batch by batch, all but
+//     a few more than are resident at once (58 x 416 of 29 x 45 bf16 forward 45 / 51); many of next to nothing (1 x 3200 of 19 x 31 fp32 masked 20.5 / 23.0); with a shortcut, whose write-out waits for it batch by batch, all but
 //     large tensors of well filled units (5 x 80 of 211 x 315 fp32 76 / 95; 15 x 312 of 43 x 69 bf16 28 / 38).
 //   - 4-byte loads: forward 1.20, with a shortcut 1.09, backward 1.07, masked 1.12 for planes of float from 9 KB and of bfloat16 from 8 KB on; few units of several a
 //     channel 0.96, backward from 12.7 KB on 0.99.  Shorter planes of float where their slots are filled: up to 8 KB forward 1.15 from 150 MB on and 1.1 to 1.5
@@ -925,6 +925,7 @@ bool edges_pay(const FusedPlan& e, const FusedPlan& f, bool built, int C, long l
     if (!f.ok || !built) {
         if (plane_bytes <= 2048 && (second || e.U > 1 || e.total_units < 128)) return false;
         if (e.U > 1 && C < 16) return false;
+        if (unit_bytes < 4096 && e.total_units > 1600) return false;
         const long long thin = forward ? (C < 32 ? 70000 : 52000) : second ? 0 : 33000;
         if (e.U > 1 && e.LPPC == 0 && unit_bytes < thin && (!forward || tensor_bytes < 200000000)) return false;
         if (forward && second) return !(e.LPPC > 0 && e.LPPC < 8) && (e.U == 1 ? tensor_bytes >= 100000000 : tensor_bytes >= 160000000 && unit_bytes >= 65000);
@@ -970,7 +971,8 @@ constexpr bool fused_built(bool f32, bool forward, int act, int LB, int LPPC)
 // - backwards with 16-byte vectors of tensors that just outgrow the last-level cache (256 MB, of which a backward's three tensors take three tensors' bytes,
 //   a masked one's five): there the single-launch kernels, whose loads are non-temporal and go ahead of the stores, keep more of their inputs
 //   cached between calls.  Old / flat in us, 8 images of 23x24 fp32: backward of 44 MB 27.6 / 23.0, 62 MB 35.9 / 39.0, 88 MB 49.1 / 54.2, 141 MB 88.1 / 87.9,
-//   212 MB 144 / 131 (16 of 24x30: 147 MB 87.8 / 93.9, 230 MB 145 / 141); masked 26 MB 28.7 / 23.9, 35 MB 35.3 / 37.5, 62 MB 56.6 / 64.2, 88 MB 98.2 / 89.8 (2 of 60x64 bf16 77 MB 78.5 / 85.9); 16 of 24x30 masked 29 MB 32.5 / 30.5, 37 MB
+//   212 MB 144 / 131 (16 of 24x30: 147 MB 87.8 / 93.9, 230 MB 145 / 141); masked 26 MB 28.7 / 23.9, 35 MB 35.3 / 37.5, 62 MB 56.6 / 64.2, 88 MB 98.2 / 89.8 (2 of 60x64 bf16 77 MB 78.5 / 85.9; 64 registers a lane: 23 x 1896 of 16x31 fp32,
+//   87 MB, 81.0 / 90.8, 16 x 2000 of 24x30 92 MB 98.2 / 96.3); 16 of 24x30 masked 29 MB 32.5 / 30.5, 37 MB
 //   36.5 / 43.6, backward 46 MB 27.9 / 25.0, 60 MB 38.1 / 40.4.  (Non-temporal loads here: 18 MB backward 10.6 -> 12.8, masked 15.6 -> 20.0.)
 // - forwards of 64 registers a lane of such tensors: 16 of 24x30, 60 MB 28.5 / 19.7, 92 MB 37.1 / 40.6;
 // - masked backwards of sixteen wavefronts a channel, 16-byte vectors, of such tensors: 32 x 300 of 24x30 fp32, 28 MB 32.3 / 30.6, 384 36 MB 35.8 / 42.5,
@@ -985,7 +987,7 @@ bool flat_pays(const FlatPlan& f, int C, int direction)
     if (f.LB < 16 || direction == 1) return true;
     if (f.waves == 16) return direction != 3 || bytes < 28500000LL;
     if (direction == 0) return !most || bytes < 90000000LL;
-    return direction == 2 ? bytes < 50000000LL || bytes > 160000000LL : bytes < 32000000LL || bytes > 85000000LL;
+    return direction == 2 ? bytes < 50000000LL || bytes > 160000000LL : bytes < 32000000LL || bytes > (most ? 90000000LL : 85000000LL);
 }
 
 cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, int dtype, int K, Plan* p)

@@ -90,6 +90,7 @@ def test_plans():
             k = np.unique(np.r_[np.arange(min(total, 300)), np.arange(0, total, vecs), np.arange(vecs - 1, total, vecs), total - 1]).astype(np.uint64)
             assert np.array_equal((k * np.uint64(magic)) >> np.uint64(32), k // np.uint64(vecs))
     assert taken > 2000 and narrow > 20
+    assert not _takes((23, 1896, 16, 31, "f32", 1), "bwdm")          # (87 MB, 64 registers a lane: measured 1.12 times slower)
 
 
 @pytest.mark.gpu
