@@ -454,7 +454,7 @@ void make_flat_plan(int N, int C, long long HW, int eb, FlatPlan* f)
     int waves = (channel <= 1024 || (channel <= 5000 && C >= 1024)) && total <= 32 * kWave ? 1 : kThreads / kWave, S = fits(waves);
     if (S == 0 || (flat_words(LB, S) > 32 && C <= kFlatUnits)) {
         S = fits(waves = 16);
-        if (S == 0 || C > kFlatUnits && !(C <= 2 * kFlatUnits ? LB == 16 || LB == 2 : LB == 2 && S == 16)) return;
+        if (S == 0 || (C > kFlatUnits && !(C <= 2 * kFlatUnits ? LB == 16 || LB == 2 : LB == 2 && S == 16))) return;
     }
     f->waves = waves;
     f->LB = LB;
@@ -911,8 +911,9 @@ Plan grouped(const Plan& p)
 //     too little of a unit (74 x 19 of 109 x 195 bf16 forward 44.5 / 50.5, 20 x 148 of 109 x 103 backward 61.6 / 71.7); few units, which leave the chip idle, and
 //     a few more than are resident at once (58 x 416 of 29 x 45 bf16 forward 45 / 51); many of next to nothing (1 x 3200 of 19 x 31 fp32 masked 20.5 / 23.0); with a shortcut, whose write-out waits for it batch by batch, all but
 //     large tensors of well filled units (5 x 80 of 211 x 315 fp32 76 / 95; 15 x 312 of 43 x 69 bf16 28 / 38).
-//   - 4-byte loads: forward 1.20, with a shortcut 1.09, backward 1.07, masked 1.12 for planes of float from 9 KB and of bfloat16 from 8 KB on; few units of several a
-//     channel 0.96, backward from 12.7 KB on 0.99.  Shorter planes of float where their slots are filled: up to 8 KB forward 1.15 from 150 MB on and 1.1 to 1.5
+//   - 4-byte loads, planes of float from 8 KB and of bfloat16 from 8000 bytes on: forward 1.25; with a shortcut 1.13 from 85 and 100 MB on and bfloat16 channels of one unit,
+//     else 0.95; backward 1.08 and masked 1.12, but 0.98 from 12 KB on (masked 1.08 from 60 MB on); few units of several a channel 0.96.  Shorter planes
+//     of float where their slots are filled: up to 8 KB forward 1.15 from 150 MB on and 1.1 to 1.5
 //     where a channel becomes one unit, else 0.9 to 1.0; with a shortcut 1.2 from 100 MB on, else 0.9; backward 1.08 from 150 MB on, else 0.8 to 1.1; masked 1.05 to 1.25
 //     from 70 MB on without further planes in LDS, else 0.77 to 1.1.
 //   - 8-byte loads, which large planes take without further data in LDS: forward beyond 16 KB 1.15, but 0.62 where a plane a wavefront became a plane a workgroup, 0.95
@@ -926,19 +927,20 @@ bool edges_pay(const FusedPlan& e, const FusedPlan& f, bool built, int C, long l
         if (plane_bytes <= 2048 && (second || e.U > 1 || e.total_units < 128)) return false;
         if (e.U > 1 && C < 16) return false;
         if (unit_bytes < 4096 && e.total_units > 1600) return false;
-        const long long thin = forward ? (C < 32 ? 70000 : 52000) : second ? 0 : 33000;
+        const long long thin = forward ? (C < 32 ? 70000 : 52000) : second ? (tensor_bytes < 60000000 ? 18000 : 0) : 33000;
         if (e.U > 1 && e.LPPC == 0 && unit_bytes < thin && (!forward || tensor_bytes < 200000000)) return false;
         if (forward && second) return !(e.LPPC > 0 && e.LPPC < 8) && (e.U == 1 ? tensor_bytes >= 100000000 : tensor_bytes >= 160000000 && unit_bytes >= 65000);
         if (forward && tensor_bytes < 100000000 && e.total_units > 768 && e.total_units < 900) return false;
         return e.total_units >= (e.U == 1 ? 48 : !forward ? 96 : tensor_bytes >= 60000000 ? 256 : 400);
     }
     if (f.LB == 4) {
-        if (e.U > 1 && e.total_units < (forward && second ? 400 : 256)) return false;
-        if (!forward && !second && plane_bytes > 12700) return false;
-        if (eb == 2) return plane_bytes >= 8000;
-        if (plane_bytes >= 9000) return true;
+        if (e.U > 1 && e.total_units < 256) return false;
+        if (!forward && plane_bytes > 12288 && (!second || tensor_bytes < 60000000)) return false;
+        const bool shortcut_pays = !(forward && second) || tensor_bytes >= (eb == 2 ? 100000000 : 85000000) || (eb == 2 && e.U == 1);
+        if (eb == 2) return plane_bytes >= 8000 && shortcut_pays;
+        if (plane_bytes >= 9000) return shortcut_pays;
         if (plane_bytes < 4096 || e.LPPC <= 0 || plane_bytes * 100 < (long long)e.LPPC * 1024 * 85) return false;
-        if (plane_bytes > 8192) return true;
+        if (plane_bytes > 8192) return shortcut_pays;
         if (forward && e.U == 1 && (f.U > 1 || (second && e.total_units <= 500))) return true;
         return !second ? tensor_bytes >= 150000000 : forward ? tensor_bytes >= 100000000 : tensor_bytes >= 70000000 && e.big == 0;
     }
@@ -969,8 +971,9 @@ constexpr bool fused_built(bool f32, bool forward, int act, int LB, int LPPC)
 //   for (see fused_built: separate sweeps).  Those whose plain backward they do not take either (planes of more than 4096 values, tiny ones in many
 //   images) and those they are built for (24 slots) are flat;
 // - backwards with 16-byte vectors of tensors that just outgrow the last-level cache (256 MB, of which a backward's three tensors take three tensors' bytes,
-//   a masked one's five): there the single-launch kernels, whose loads are non-temporal and go ahead of the stores, keep more of their inputs
-//   cached between calls.  Old / flat in us, 8 images of 23x24 fp32: backward of 44 MB 27.6 / 23.0, 62 MB 35.9 / 39.0, 88 MB 49.1 / 54.2, 141 MB 88.1 / 87.9,
+//   a masked one's five): there the single-launch kernels, whose loads are non-temporal and go ahead of the stores, are faster, also when
+//   nothing of a call's tensors is cached before it (8 of 3500 of 23x24 fp32, 62 MB, 35.2 / 38.3; with one wavefront a channel they are not: 2 of 12000 of 24x24 fp32
+//   48 / 34, which this does not look at yet).  Old / flat in us, 8 images of 23x24 fp32: backward of 44 MB 27.6 / 23.0, 62 MB 35.9 / 39.0, 88 MB 49.1 / 54.2, 141 MB 88.1 / 87.9,
 //   212 MB 144 / 131 (16 of 24x30: 147 MB 87.8 / 93.9, 230 MB 145 / 141); masked 26 MB 28.7 / 23.9, 35 MB 35.3 / 37.5, 62 MB 56.6 / 64.2, 88 MB 98.2 / 89.8 (2 of 60x64 bf16 77 MB 78.5 / 85.9; 64 registers a lane: 23 x 1896 of 16x31 fp32,
 //   87 MB, 81.0 / 90.8, 16 x 2000 of 24x30 92 MB 98.2 / 96.3); 16 of 24x30 masked 29 MB 32.5 / 30.5, 37 MB
 //   36.5 / 43.6, backward 46 MB 27.9 / 25.0, 60 MB 38.1 / 40.4.  (Non-temporal loads here: 18 MB backward 10.6 -> 12.8, masked 15.6 -> 20.0.)

@@ -5,7 +5,7 @@
 // large ones run at 4.5 ... 5.5 TB/s.  The single-launch kernels of cgbn_fused.h move a plane per wavefront at a time and leave a row per plane; where a
 // channel is a few short planes most of their lanes idle, and rows, shards and barriers cost more than the data.  Here a channel costs one sum over
 // its lanes (two in the forward).  Before / now in us, forward and backward: 4 images of 16 channels of 32x32 fp32 5.6 / 3.7 and 4.8 / 3.8; 2 of 1848 of
-// 27x40 bf16 14.6 / 5.9 and 12.9 / 7.5; 2 of 12000 of 24x24 fp32 59.8 / 18.0 and 47.4 / 35.0; 16 of 1720 of 14x22 bf16 22.5 / 9.8 and 18.4 / 11.0.
+// 27x40 bf16 14.6 / 5.9 and 12.9 / 7.5; 2 of 12000 of 24x24 fp32 forward 59.8 / 18.0; 16 of 1720 of 14x22 bf16 22.5 / 9.8 and 18.4 / 11.0.
 //
 // With one or four wavefronts a channel, 64 registers a lane are the most that leaves the masked backward its three tensors; sixteen have 32.  Vectors are the widest that a plane's bytes allow, so
 // that every plane of a channel starts on one; which plane a vector lies in is a quotient by the plane's vectors, formed as a product's high half.

@@ -33,7 +33,8 @@ CASES = [
     (2, 256, 1, 45061, "f32", 1), (8, 72, 201, 219, "f32", 8),
     # slot counts that calls of those shapes leave to other kernels
     (16, 64, 53, 47, "bf16", 4), (20, 64, 63, 33, "bf16", 5), (34, 104, 25, 41, "bf16", 2), (33, 16, 25, 41, "f32", 3), (4, 16, 25, 41, "f32", 2),
-    (10, 16, 29, 53, "f32", 5), (6, 24, 49, 37, "f32", 3),
+    (10, 16, 29, 53, "f32", 5), (6, 24, 49, 37, "f32", 3), (3, 16, 61, 70, "bf16", 1), (2, 16, 66, 79, "bf16", 2), (3, 16, 98, 63, "bf16", 3), (2, 16, 74, 111, "bf16", 1),
+    (2, 20, 143, 86, "bf16", 2),
 ]
 # forwards with a shortcut that take these kernels only from 100 MB on: planes that share a workgroup, tiles, a plane a wavefront with its last slots in LDS
 LARGE = [(3, 728, 93, 129, "f32", 1), (2, 1040, 83, 145, "f32", 1), (1, 557, 171, 263, "f32", 1), (3, 1336, 75, 113, "f32", 1)]
