@@ -532,9 +532,9 @@ bool cut_slabs(SlabPlan* s, int C, int cols, int nch, long long U, long long row
 // boundaries they share those lines: fp32 22400 x 264, 31 units 23.8 / 28.7, 32 units 21.5 / 24.5; 70200 x 112, 63 units 27.7 / 36.3, 64
 // units 24.3 / 29.7 (rows of whole lines: no difference).  Such slabs must also all be in flight together (measured, fp32
 // 268800 x 136 in four rounds 170 us, the sweeps 101).
-//   Such slabs in several rounds (`shared`: at least so many in flight, the rounds `full` per cent full): those in flight are then neighbours, in whole eights of units, so that the
+//   Such slabs in several rounds (`shared`: at least so many in flight): those in flight are then neighbours, in whole eights of units, so that the
 // lines two of them share are fetched by one XCD at about the same time and only those at the ends of the group twice.  See make_shared_plan.
-bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_words, int cus, bool forward, bool second, int shared = 0, int full = 0)
+bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_words, int cus, bool forward, bool second, int shared = 0)
 {
     const int rpp = kSlabThreads / cols;
     const long long cap = (long long)rpp * slab_most(forward, false);
@@ -555,7 +555,7 @@ bool cut_slabs_in_units(SlabPlan* s, int C, int cols, int nch, long long row_wor
         if (slabs * U > cus / U * U) {
             if (shared) {
                 U = (U + 7) / 8 * 8;
-                if (U > most || 100 * slabs < (cus / U < 8 && full < 84 ? 84 : full) * ((slabs + cus / U - 1) / (cus / U)) * (cus / U)) continue;
+                if (U > most || 10 * slabs < 7 * ((slabs + cus / U - 1) / (cus / U)) * (cus / U)) continue;
             } else if (!lines) {
                 continue;
             }
@@ -674,19 +674,41 @@ void make_slab_plan(int N, int C, long long HW, int layout, int eb, long long ro
 }
 
 // Channels-last calls that no plan above takes, rows of at least 24 vectors that are no whole lines: in several rounds of 128-byte slabs that share
-// lines, where enough of them are in flight and the rounds are well filled.  Measured over 200 random shapes, time of the sweeps over this one's, geometric mean of the
-// calls taken: forward 1.14, backward 1.14, masked 1.24: fp32 63104 x 1264 (eight and four in flight) 234 / 334 / 645 -> 187 / 281 / 498 us, 23936 x 1168 (16, ten)
-// 89 / 134 / 243 -> 64 / 90 / 145, bf16 43008 x 936 (ten, five) 69 / 100 / 149 -> 57 / 74 / 120.  Where the line lies:
-//   - fewer in flight: 97244 x 880 (two) backward 321 -> 345, 238080 x 408 (two, one) 235 / 364 -> 321 / 520, bf16 62424 x 1064 (four) masked 223 -> 249, backward with
-//     four 0.84 to 0.96, and with five to seven of less than 16 slabs (46898 x 840 bf16 0.89); masked float of rows of one tile, whose sweeps are faster:
-//     37392 x 904 (six) 225 -> 260;
-//   - rounds: bf16 forward and backward 84 and 87 % full (16872 x 1656 bf16, 26 slabs by ten, backward 46 -> 54; 19352 x 2032, 32 by ten, 50 -> 62), float with eight and
-//     more in flight 70 % (14280 x 1136, 36 slabs by 16, backward 1.33), with fewer 84 %;
-//   - rows of more than 512 vectors, but for masked calls, and those within a line of 8 KiB, of which the same columns of every row crowd few memory channels:
-//     50400 x 2072 fp32 241 / 362 -> 291 / 380, 26325 x 2040 masked 337 -> 388;
-//   - where the backward is sweeps, only forwards of 150 MB and more in at most 3.5 rounds: 1.16 to 1.37 times as fast (90321 x 568 fp32), a step that calls one directly
-//     after the other 0.95 to 1.04; of the others 1.03, the step 0.91, since the backward's sweeps find nothing of what the forward read in the last-level cache.
-// Nine columns a slab: 17920 x 1768 65 / 107, so 89 / 114.
+// lines, where enough of them are in flight and the rounds are at least 70 % full, and where that pays.  Measured over 454 random shapes of 5 to 420 MB, time of the
+// sweeps over this one's, geometric mean of the calls taken and, in brackets, of those left, bf16 and fp32: forward 1.14 (0.95) and 1.17 (1.01), backward 1.13
+// (0.91) and 1.18 (1.02), masked 1.18 (0.97) and 1.33 (1.02).  fp32 63104 x 1264 (eight and four in flight) 234 / 334 / 645 -> 187 / 281 / 498 us, 23936 x 1168 (16, ten)
+// 89 / 134 / 243 -> 64 / 90 / 145.
+//   - Rows of more than one tile of the sweeps (256 vectors), which are slower for them: 1.2 to 1.35 whatever the rounds; float beyond 60 slabs in rounds that are
+//     not full 0.9 to 1.05, as in more than ten rounds (forward five).
+//   - Rows within a line of 8 KiB (shorter ones of 4), of which the same columns of every row crowd few memory channels: 0.8 to 1.05 (26325 x 2040 fp32 masked
+//     337 -> 388, 44928 x 1016 backward 160 -> 184).
+//   - Shorter rows by how full the rounds are: bf16 forward 1.09 from 71 % with eight and more in flight, from 91 % with fewer, else 0.95 (46898 x 840, 14 slabs
+//     by ten, 0.90); backward 1.05 from 81 % (16872 x 1656, 26 by ten, 46 -> 54 us), but for rows of up to 120 vectors (0.97); masked 1.13 from 78 % in at most
+//     four rounds, else 0.97.  Float forward 1.14 from 80 % in at most four rounds, else 1.0; backward 1.12 from 84 %, but for rows of up to 107 vectors
+//     (four and five in flight: 0.84 to 1.05) and four in flight in six rounds and more (0.84 to 1.04); masked 1.32 always.
+//   - A forward before a backward of sweeps, which finds nothing of what this read in the last-level cache: one called directly after the other takes 0.87 to 1.04 of the
+//     speed, 0.95 in the mean.  Taken so only where it gains most itself, 1.17 to 1.37 times: rows of several tiles, and from 150 MB on in at most three rounds, 90 % full.
+// Fewer in flight: 97244 x 880 (two) backward 321 -> 345, 238080 x 408 (two, one) 235 / 364 -> 321 / 520, bf16 62424 x 1064 (four) masked 223 -> 249; masked float of
+// rows of one tile, whose sweeps are faster: 37392 x 904 (six) 225 -> 260.  Rounds two thirds full: bf16 79872 x 496 forward 58 -> 62.  Nine columns a slab: 17920 x 1768
+// 65 / 107, so 89 / 114.
+bool shared_full(const SlabPlan& x, int cus, int percent)
+{
+    const int flight = cus / x.U;
+    return 100 * x.slabs > percent * ((x.slabs + flight - 1) / flight) * flight;
+}
+bool shared_pays(const SlabPlan& x, int eb, int cus, bool forward, bool second)
+{
+    const int flight = cus / x.U, rounds = (x.slabs + flight - 1) / flight;
+    auto full = [&](int percent) { return shared_full(x, cus, percent); };
+    const bool bf16 = eb == 2, tiles = x.vecs > kThreads;
+    if ((x.row_bytes + 128) % (tiles ? 8192 : 4096) < 256) return false;
+    if (tiles && (bf16 || second)) return true;
+    if (tiles && forward) return x.slabs > 62 ? x.slabs <= 5 * flight && full(85) : 20 * x.slabs <= 101 * flight || full(84);
+    if (tiles) return 10 * x.slabs <= 101 * flight && (x.slabs <= 60 || full(78));
+    if (forward) return bf16 ? full(flight >= 8 ? 71 : 91) : 100 * x.slabs <= 415 * flight && full(80);
+    if (!second) return bf16 ? x.vecs > 120 && full(81) : x.vecs > 107 && full(84) && (flight > 4 || 2 * x.slabs <= 11 * flight);
+    return !bf16 || (full(78) && rounds <= 4);
+}
 void make_shared_plan(int N, int C, long long HW, int eb, long long row_words, int cus, bool forward, bool second, const SlabPlan& s, SlabPlan* x)
 {
     std::memset(x, 0, sizeof(*x));
@@ -698,10 +720,8 @@ void make_shared_plan(int N, int C, long long HW, int eb, long long row_words, i
     x->cpc = 1;
     const int cols = 8;
     if (x->row_bytes % 128 == 0) return;       // (whole lines)
-    if ((x->vecs > 512 && (forward || !second)) || (x->row_bytes + 128) % 8192 < 256) return;
-    const int flight = forward ? 6 : eb == 2 || !second ? 5 : x->vecs <= kThreads ? 8 : 4;
-    cut_slabs_in_units(x, C, cols, ceil_pow2(cols * vec), row_words, cus, forward, second, flight, forward ? 84 : eb == 2 ? 87 : 70);
-    if (x->ok && !forward && !second && x->slabs < 16 && cus / x->U < 8) x->ok = 0;
+    const int flight = forward ? 6 : eb == 2 ? 5 : second && x->vecs <= kThreads ? 8 : 4;
+    if (cut_slabs_in_units(x, C, cols, ceil_pow2(cols * vec), row_words, cus, forward, second, flight) && !shared_pays(*x, eb, cus, forward, second)) x->ok = 0;
 }
 
 // NCHW calls whose plan `s` has 16-byte vectors: one of 8-byte vectors in its place (see SlabVector), where that leaves at least half the compute
@@ -909,13 +929,14 @@ Plan grouped(const Plan& p)
 //   - the sweeps: forward 1.25 (0.93), with a shortcut 1.15 (0.95), backward 1.30 (0.83), masked 1.38 (0.91).  Left to them: fewer than 16 channels of several
 //     units, all of whose units read, wait and write together (77 x 8 of 329 x 399 fp32 backward 316 / 497 us, 71 x 8 of 289 x 223 forward 0.67); tiles that fill
 //     too little of a unit (74 x 19 of 109 x 195 bf16 forward 44.5 / 50.5, 20 x 148 of 109 x 103 backward 61.6 / 71.7); few units, which leave the chip idle, and
-//     a few more than are resident at once (58 x 416 of 29 x 45 bf16 forward 45 / 51); many of next to nothing (1 x 3200 of 19 x 31 fp32 masked 20.5 / 23.0); with a shortcut, whose write-out waits for it batch by batch, all but
-//     large tensors of well filled units (5 x 80 of 211 x 315 fp32 76 / 95; 15 x 312 of 43 x 69 bf16 28 / 38).
-//   - 4-byte loads, planes of float from 8 KB and of bfloat16 from 8000 bytes on: forward 1.25; with a shortcut 1.13 from 85 and 100 MB on and bfloat16 channels of one unit,
-//     else 0.95; backward 1.08 and masked 1.12, but 0.98 from 12 KB on (masked 1.08 from 60 MB on); few units of several a channel 0.96.  Shorter planes
-//     of float where their slots are filled: up to 8 KB forward 1.15 from 150 MB on and 1.1 to 1.5
-//     where a channel becomes one unit, else 0.9 to 1.0; with a shortcut 1.2 from 100 MB on, else 0.9; backward 1.08 from 150 MB on, else 0.8 to 1.1; masked 1.05 to 1.25
-//     from 70 MB on without further planes in LDS, else 0.77 to 1.1.
+//     a few more than are resident at once, three a compute unit (58 x 416 of 29 x 45 bf16 forward 45 / 51); many of next to nothing (1 x 3200 of 19 x 31 fp32
+//     masked 20.5 / 23.0); with a shortcut, whose write-out waits for it batch by batch, all but large tensors of well filled units (5 x 80 of 211 x 315 fp32
+//     76 / 95; 15 x 312 of 43 x 69 bf16 28 / 38).
+//   - 4-byte loads, planes of float from 8 KB and of bfloat16 from 8000 bytes on: forward 1.25; with a shortcut 1.13 from 85 and 100 MB on and bfloat16 channels
+//     of one unit, else 0.95; backward 1.08 and masked 1.12, but 0.98 from 12 KB on (masked 1.08 from 60 MB on); few units of several a channel 0.96.  Shorter
+//     planes of float where their slots are filled: forward 1.15 from 150 MB on and 1.1 to 1.5 where a channel becomes one unit, else 0.9 to 1.0; with a
+//     shortcut 1.2 from 100 MB on, else 0.9; backward 1.08 from 150 MB on, else 0.8 to 1.1; masked 1.05 to 1.25 from 70 MB on without further planes in LDS,
+//     else 0.77 to 1.1.
 //   - 8-byte loads, which large planes take without further data in LDS: forward beyond 16 KB 1.15, but 0.62 where a plane a wavefront became a plane a workgroup, 0.95
 //     where few planes that share one leave the chip idle, and 1.04 from 80 to 160 MB, where a backward that follows then takes longer (a step 0.97); backward 1.14
 //     and masked 1.11 where two or three planes share a workgroup, 0.99 and 1.00 for tiles.
@@ -1124,7 +1145,8 @@ cgbn_status make_plan(const Tuning& T, int N, int C, int H, int W, int layout, i
     if (layout == CGBN_NHWC) {
         make_shared_plan(N, C, HW, p->eb, row_words, cus, false, false, p->sb, &p->xb);
         make_shared_plan(N, C, HW, p->eb, row_words, cus, true, false, p->sf, &p->xf);
-        if (p->xf.ok && !p->xb.ok && !p->sb.ok && (S * p->eb < 150000000 || 2 * p->xf.slabs > 7 * (cus / p->xf.U))) p->xf.ok = 0;       // (see make_shared_plan)
+        if (p->xf.ok && !p->xb.ok && !p->sb.ok && p->xf.vecs <= kThreads && (S * p->eb < 150000000 || p->xf.slabs > 3 * (cus / p->xf.U) || !shared_full(p->xf, cus, 90)))
+            p->xf.ok = 0;                                 // (see shared_pays)
         make_shared_plan(N, C, HW, p->eb, row_words, cus, false, true, p->sbm, &p->xbm);
     }
     for (const SlabPlan* s : {&p->sf, &p->sfs, &p->sb, &p->sbm, &p->xf, &p->xb, &p->xbm})
