@@ -927,12 +927,12 @@ Plan grouped(const Plan& p)
 // sweeps).  Measured over 1000 random shapes of 0.4 to 400 MB, that time over this one's, geometric means of the calls taken and, in brackets, of those
 // left; single calls lie up to 9 % beside that, the same code in another process does where tensors about fill the 256 MB last-level cache:
 //   - the sweeps: forward 1.25 (0.93), with a shortcut 1.15 (0.95), backward 1.30 (0.83), masked 1.38 (0.91).  Left to them: fewer than 16 channels of several
-//     units, all of whose units read, wait and write together (77 x 8 of 329 x 399 fp32 backward 316 / 497 us, 71 x 8 of 289 x 223 forward 0.67); tiles that fill
+//     units, all of whose units read, wait and write together (77 x 8 of 329 x 399 fp32 backward 316 / 497 us, 71 x 8 of 289 x 223 forward 0.67; backwards of up to 13 MB 1.15); tiles that fill
 //     too little of a unit (74 x 19 of 109 x 195 bf16 forward 44.5 / 50.5, 20 x 148 of 109 x 103 backward 61.6 / 71.7); few units, which leave the chip idle, and
 //     a few more than are resident at once, three a compute unit (58 x 416 of 29 x 45 bf16 forward 45 / 51); many of next to nothing (1 x 3200 of 19 x 31 fp32
 //     masked 20.5 / 23.0); with a shortcut, whose write-out waits for it batch by batch, all but large tensors of well filled units (5 x 80 of 211 x 315 fp32
-//     76 / 95; 15 x 312 of 43 x 69 bf16 28 / 38).
-//   - 4-byte loads, planes of float from 8 KB and of bfloat16 from 8000 bytes on: forward 1.25; with a shortcut 1.13 from 85 and 100 MB on and bfloat16 channels
+//     76 / 95; 15 x 312 of 43 x 69 bf16 28 / 38; from 100 to 160 MB 0.92 where the units are more than are resident, else 1.1).
+//   - 4-byte loads, planes beyond 8 KB (bfloat16 of 8000 bytes 0.78 to 0.95 but for large tensors): forward 1.25; with a shortcut 1.13 from 85 and 100 MB on and bfloat16 channels
 //     of one unit, else 0.95; backward 1.08 and masked 1.12, but 0.98 from 12 KB on (masked 1.08 from 60 MB on); few units of several a channel 0.96.  Shorter
 //     planes of float where their slots are filled: forward 1.15 from 150 MB on and 1.1 to 1.5 where a channel becomes one unit, else 0.9 to 1.0; with a
 //     shortcut 1.2 from 100 MB on, else 0.9; backward 1.08 from 150 MB on, else 0.8 to 1.1; masked 1.05 to 1.25 from 70 MB on without further planes in LDS,
@@ -946,19 +946,19 @@ bool edges_pay(const FusedPlan& e, const FusedPlan& f, bool built, int C, long l
     const long long unit_bytes = tensor_bytes / e.total_units;
     if (!f.ok || !built) {
         if (plane_bytes <= 2048 && (second || e.U > 1 || e.total_units < 128)) return false;
-        if (e.U > 1 && C < 16) return false;
+        if (e.U > 1 && C < 16 && (forward || tensor_bytes > 13000000)) return false;
         if (unit_bytes < 4096 && e.total_units > 1600) return false;
         const long long thin = forward ? (C < 32 ? 70000 : 52000) : second ? (tensor_bytes < 60000000 ? 18000 : 0) : 33000;
         if (e.U > 1 && e.LPPC == 0 && unit_bytes < thin && (!forward || tensor_bytes < 200000000)) return false;
-        if (forward && second) return !(e.LPPC > 0 && e.LPPC < 8) && (e.U == 1 ? tensor_bytes >= 100000000 : tensor_bytes >= 160000000 && unit_bytes >= 65000);
+        if (forward && second) return !(e.LPPC > 0 && e.LPPC < 8) && (e.U == 1 || e.total_units <= 768 ? tensor_bytes >= 100000000 : tensor_bytes >= 160000000 && unit_bytes >= 65000);
         if (forward && tensor_bytes < 100000000 && e.total_units > 768 && e.total_units < 900) return false;
-        return e.total_units >= (e.U == 1 ? 48 : !forward ? 96 : tensor_bytes >= 60000000 ? 256 : 400);
+        return e.total_units >= (e.U == 1 ? 48 : !forward ? 96 : tensor_bytes >= 45000000 ? 256 : 400);
     }
     if (f.LB == 4) {
         if (e.U > 1 && e.total_units < 256) return false;
         if (!forward && plane_bytes > 12288 && (!second || tensor_bytes < 60000000)) return false;
         const bool shortcut_pays = !(forward && second) || tensor_bytes >= (eb == 2 ? 100000000 : 85000000) || (eb == 2 && e.U == 1);
-        if (eb == 2) return plane_bytes >= 8000 && shortcut_pays;
+        if (eb == 2) return plane_bytes > 8192 && shortcut_pays;
         if (plane_bytes >= 9000) return shortcut_pays;
         if (plane_bytes < 4096 || e.LPPC <= 0 || plane_bytes * 100 < (long long)e.LPPC * 1024 * 85) return false;
         if (plane_bytes > 8192) return shortcut_pays;

@@ -73,7 +73,7 @@ SLOWER = [((77, 8, 329, 399, "f32", 1), "fwd fwds bwd bwdm"), ((74, 19, 109, 195
           ((70, 201, 85, 139, "bf16", 1), "bwd"), ((58, 416, 29, 45, "bf16", 1), "fwd"), ((5, 80, 211, 315, "f32", 1), "fwds"), ((42, 66, 166, 163, "bf16", 1), "fwds"),
           ((15, 312, 43, 69, "bf16", 1), "fwds"), ((87, 48, 27, 45, "f32", 1), "bwd bwdm"), ((79, 172, 53, 21, "f32", 1), "fwd fwds bwd"), ((115, 9, 67, 126, "f32", 1), "fwd"),
           ((101, 8, 150, 213, "f32", 1), "fwd"), ((2, 51, 202, 214, "bf16", 1), "bwd bwdm"), ((8, 121, 122, 86, "bf16", 1), "bwd bwdm"), ((68, 8, 68, 131, "bf16", 1), "bwd bwdm"),
-          ((1, 3200, 19, 31, "f32", 1), "bwdm")]
+          ((1, 3200, 19, 31, "f32", 1), "bwdm"), ((5, 1556, 61, 66, "bf16", 1), "fwd fwds bwd"), ((57, 160, 54, 75, "bf16", 1), "fwd fwds bwd")]
 
 
 def test_calls_that_other_kernels_are_faster_at_are_left_to_them():
